@@ -123,6 +123,7 @@ int resolve_path(const ukst::Geom& g, int dtype, int path)
     if (ukst::mfma_supported(g, dtype) &&
         ((g.Cin >= 16 && g.Cout >= 16) || ukst::thin_mfma_supported(g, dtype)))
         return UKST_PATH_MFMA;
+    if (ukst::mfma_auto_extra(g, dtype)) return UKST_PATH_MFMA;
     return UKST_PATH_DIRECT;
 }
 
@@ -204,7 +205,7 @@ static int forward_checked(const void* x, const void* w, const float* bias, int 
     g = ukst::make_geom(B, Cin, Cout, H, W, n, P);
     g.ep.bias = bias;
     g.ep.act = act;
-    // element alignment is required of every buffer; the matrix-core kernels move the weights
+    // element alignment is required of every buffer; most matrix-core kernels move the weights
     // (and bf16 activations) in 16-byte pieces and need those buffers aligned to that
     const uintptr_t esz = dtype == UKST_F32 ? 4 : 2, osz = dtype == UKST_BF16_BF16 ? 2 : 4;
     if (((uintptr_t)x | (uintptr_t)w) & (esz - 1) || ((uintptr_t)y & (osz - 1)) || ((uintptr_t)bias & 3))
@@ -212,7 +213,8 @@ static int forward_checked(const void* x, const void* w, const float* bias, int 
     chosen = resolve_path(g, dtype, path);
     const bool x16 = chosen == UKST_PATH_MFMA && ukst::mfma_needs_aligned_x(g, dtype);
     const bool wide_ok = (((uintptr_t)w | (x16 ? (uintptr_t)x : 0)) & 15) == 0;
-    if (chosen == UKST_PATH_MFMA && !wide_ok) chosen = (path == UKST_PATH_AUTO) ? UKST_PATH_DIRECT : -1;
+    if (chosen == UKST_PATH_MFMA && !wide_ok && !(path == UKST_PATH_AUTO && ukst::mfma_any_alignment(g, dtype)))
+        chosen = (path == UKST_PATH_AUTO) ? UKST_PATH_DIRECT : -1;
     return chosen < 0 ? UKST_ERR_UNSUPPORTED : UKST_OK;
 }
 

@@ -141,6 +141,10 @@ bool thin_supported(const Geom& g, int dtype);
 hipError_t launch_thin(const Geom& g, const void* x, const void* w, float* y, hipStream_t stream);
 
 bool mfma_supported(const Geom& g, int dtype);
+// layers beyond mfma_supported that automatic selection takes to the matrix cores all the same
+bool mfma_auto_extra(const Geom& g, int dtype);
+// true if the kernel that launch_mfma runs needs no more than element alignment
+bool mfma_any_alignment(const Geom& g, int dtype);
 hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, int dtype,
                        Workspace& ws, hipStream_t stream);
 const char* mfma_kernel_name(const Geom& g, int dtype);
@@ -158,6 +162,12 @@ bool mfma_needs_aligned_x(const Geom& g, int dtype);
 bool mfma_f32_supported(const Geom& g, int dtype);
 hipError_t launch_mfma_f32(const Geom& g, const void* x, const void* w, float* y, int dtype, Workspace& ws,
                            hipStream_t stream);
+// bf16 matrix pipe from bf16 parts of the operands (three of an fp32 value, one of a bf16 value): any row
+// length and channel counts, n = 2..5, every dtype
+// (mfma_parts_tiles: the work in tiles of 64 channels x 256 quads, 0 if the kernel cannot run the layer)
+double mfma_parts_tiles(const Geom& g, int dtype);
+hipError_t launch_mfma_parts(const Geom& g, const void* x, const void* w, void* y, int dtype, Workspace& ws,
+                             hipStream_t stream);
 bool thin_mfma_supported(const Geom& g, int dtype);
 hipError_t launch_thin_mfma(const Geom& g, const void* x, const void* w, float* y, hipStream_t stream);
 

@@ -538,6 +538,32 @@ static bool bf16_pipe(const Geom& g, int dtype)
     return dtype != 0 && (mfma_aligned_supported(g, dtype) || make_args(g, dtype, a));
 }
 
+// Where the kernel on bf16 parts (ukst_mfma_parts_kernel.h) runs instead of the fp32 pipe or the vector
+// ALUs, in tiles of 64 channels x 256 quads.  Large layers gain whatever they are: fp32 128 -> 128 channels
+// on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 235, 601 -> 355, 872 -> 526 us; bf16 operands with
+// n = 5 861 -> 191 us.  Small ones do not, because a tile is one block's serial work: fp32 at 64 tiles (64
+// images of 128 -> 64 channels, 16 x 16, n = 4) 49.4 against 49.2 us, at 132 tiles 97.6 against 57.1; n = 5 at
+// 66 and 132 tiles 72 against 121 and 141 against 132; bf16 operands at 5 and 17 tiles 31 against 65 and 45
+// against 38.
+static bool prefer_parts(const Geom& g, int dtype)
+{
+    if (g.Cin < 16 || bf16_pipe(g, dtype) || (dtype == 0 && g.Cout <= 4)) return false;
+    const double tiles = mfma_parts_tiles(g, dtype);
+    if (tiles == 0.) return false;
+    if (mfma_f32_supported(g, dtype)) return tiles >= (dtype != 0 ? 16. : g.n <= 4 ? 72. : 160.);
+    // otherwise the vector ALUs, which win against one tile's serial work only with few channels or 5 x 5 fp32 kernels (77 -> 40 channels, 33 tiles: 67 against 91 us; 19 -> 21
+    // channels, 8 tiles: 12 against 15 us; 591 -> 96 channels bf16, 95 tiles: 7.7 ms against 103 us)
+    if (dtype != 0) return true;
+    return g.n == 5 ? tiles >= 64. : g.Cin >= 32 || tiles >= 24.;
+}
+
+bool mfma_auto_extra(const Geom& g, int dtype)
+{
+    return !mfma_supported(g, dtype) && prefer_parts(g, dtype);
+}
+
+bool mfma_any_alignment(const Geom& g, int dtype) { return prefer_parts(g, dtype); }
+
 bool mfma_supported(const Geom& g, int dtype)
 {
     if (dtype == 0) return mfma_f32_supported(g, dtype) || thin_mfma_supported(g, dtype);
@@ -554,6 +580,7 @@ bool mfma_needs_aligned_x(const Geom& g, int dtype)
 hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, int dtype,
                        Workspace& ws, hipStream_t stream)
 {
+    if (prefer_parts(g, dtype)) return launch_mfma_parts(g, x, w, y, dtype, ws, stream);
     if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)))
         return launch_mfma_f32(g, x, w, y, dtype, ws, stream);
     if (ws.query) return hipSuccess;  // the kernels below use no scratch
@@ -599,6 +626,7 @@ const char* mfma_kernel_name(const Geom& g, int dtype)
 {
     if (bf16_pipe(g, dtype))  // bf16 in; fp32 or bf16 out
         return prefer_aligned(g, dtype) ? "ukst_mfma_bf16_aligned_kernel" : "ukst_mfma_bf16_kernel";
+    if (prefer_parts(g, dtype)) return mfma_supported(g, dtype) ? "ukst_mfma_f32_kernel" : "ukst_mfma_f32_kernel_parts";
     return mfma_f32_supported(g, dtype) ? "ukst_mfma_f32_kernel" : "ukst_thin_mfma_kernel";
 }
 

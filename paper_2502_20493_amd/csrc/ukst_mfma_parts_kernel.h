@@ -1,0 +1,609 @@
+// Stride-2 forward layers on the bf16 matrix pipe from bf16 parts: fp32 operands as three exact parts
+// (ukst_parts.h), bf16 operands as one.  Any row length, any channel counts, n = 2..5.
+//
+// The product is the one of ukst_mfma_f32.hip: per quad the four parity classes of Algorithm 2 share a
+// window of the input (quads aligned to the output for even n and P, shifted quads otherwise); class
+// (r, s) multiplies window position p by its tap w[r+2u][s+2v] (Eqs. 1-4).  M = output channels, N =
+// quads flattened over (image, quad row, quad column), K = input channels, 16 per MFMA.
+//
+// What bounds it and why it is laid out like this.  With three parts a pair of fragment triples feeds
+// six MFMAs, so the LDS reads of a tap (3 KiB of weights, 6 KiB of activations that two taps share) come
+// with 12 MFMAs = 384 clocks and the matrix pipe is the bound; what has to be kept off its back is
+// staging.  Splitting costs about 7 vector instructions per element, hence a wide tile (64 channels x
+// 256 quads x 4 classes on 8 waves, two per SIMD, so that one wave's splitting runs beside the other's
+// MFMAs); a load costs the address unit about 16 clocks whatever its width, hence weights in pieces of
+// four taps x 2 (or 8) input channels, transposed in registers.  Weights are staged a run of 4 or 5
+// taps at a time into the other of two buffers while the current one is multiplied, activations of 16
+// channels once per n*n taps.  Only element alignment is needed anywhere.
+#pragma once
+#include "ukst_parts.h"
+
+namespace ukst {
+namespace parts {
+
+constexpr int KC = 16;  // input channels per stage (one MFMA K step)
+constexpr int LDS_LIMIT = 160 * 1024;
+
+struct PartsArgs {
+    GeomBase g;
+    int KHq, KWq;  // quad rows / columns
+    int cb_major;  // tile order: 1 = consecutive blocks share the channel block (big weights)
+    int Q;         // total quads
+    int EH;        // input rows one image's quad rows touch
+    int ROWS;      // input rows an activation stage holds
+    int LWX;       // 16-byte slots per staged row
+    int XPL;       // bytes of one part's activation stage (both channel halves)
+    int SH;        // slot of input column 0 = floor(P/2)
+    int CPR;       // activation units per row
+    int nco, nqt;
+    int ksplit, kstages;
+    size_t copy_bytes;  // distance of the slices' copies of y
+    FastDiv dKHW, dKW, dEH, dRW, dW;
+};
+
+// tap of class c = 2r + s at window position (pa, pb) lies at tap row a = r + 2u, pa = u (+ r if aligned)
+template <bool AL>
+constexpr int pos_of(int a) { return AL ? (a >> 1) + (a & 1) : a >> 1; }
+
+// Weights are staged in pieces of four consecutive taps (one 16- or 8-byte load per channel); a weight
+// stage is a run of taps, its pieces start where piece_at says (the last piece of a run that is no
+// multiple of four taps repeats some of its neighbour's).  Three parts: runs of 4 (or 5) taps, so that
+// two weight stages fit LDS beside the activations; one part: all taps at once.
+constexpr int sub_count(int n, int parts) { return parts == 1 ? 1 : n * n / 4; }
+constexpr int sub_first(int n, int parts, int sub)  // first tap of a stage; sub == sub_count: n*n
+{
+    return sub == 0 ? 0 : sub == sub_count(n, parts) ? n * n : 4 * sub;
+}
+constexpr int sub_taps(int n, int parts, int sub) { return sub_first(n, parts, sub + 1) - sub_first(n, parts, sub); }
+constexpr int sub_pieces(int n, int parts, int sub) { return (sub_taps(n, parts, sub) + 3) / 4; }
+constexpr int piece_at(int taps, int piece) { return 4 * piece + 4 <= taps ? 4 * piece : taps - 4; }  // within the stage
+constexpr int max_taps(int n, int parts) { return parts == 1 ? n * n : 4 + n * n % 4; }
+constexpr int max_pieces(int n, int parts) { return (max_taps(n, parts) + 3) / 4; }
+// LDS image of one part of a weight stage: 16-byte slots [channel half][tap][output channel], with strides
+// that spread the staging lanes over the banks: three parts, a wave writes 8 channels x 8 dwords of one
+// tap (halves 8 slots apart modulo 16); one part, 16-byte slots of pieces, halves and output channels
+// (pieces 4, halves 2 apart modulo 16).  The slots between the halves take what has no place.
+constexpr int w_tap_slots(int parts, int tm) { return parts == 3 ? tm : tm + 1; }
+constexpr int w_half_slots(int n, int parts, int tm)
+{
+    const int used = max_taps(n, parts) * w_tap_slots(parts, tm), want = parts == 3 ? 8 : 2;
+    return used + 1 + (want + 31 - used % 16) % 16;
+}
+
+// CW x QW waves: block tile = 32*CW channels x 64*QW quads; a wave owns 32 channels x 64 quads x 4 classes.
+// XU: staging units of activations per thread.  EPI / OUT16 as in the other kernels.
+template <int N, int CW, int QW, int XU, bool AL, bool EPI, typename TIn, bool OUT16>
+__global__ __launch_bounds__(64 * CW * QW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict__ w, void* __restrict__ y,
+                                PartsArgs a, Epilogue ep)
+{
+    constexpr int PARTS = sizeof(TIn) == 4 ? 3 : 1;
+    constexpr int ES = (int)sizeof(TIn);
+    constexpr int T = 64 * CW * QW;      // threads
+    constexpr int TM = 32 * CW, TN = 64 * QW;
+    constexpr int NN = N * N;
+    constexpr int NSUB = sub_count(N, PARTS);   // weight stages per 16 channels
+    constexpr int WTS = w_tap_slots(PARTS, TM) * 16, WHS = w_half_slots(N, PARTS, TM) * 16;
+    constexpr int WPL = 2 * WHS;                // bytes of one part's weight stage
+    constexpr int WBUF = PARTS * WPL;
+    constexpr int UK = PARTS == 3 ? 2 : 8;      // input channels of a weight unit
+    constexpr int UPC = KC / UK;                // weight units per (output channel, piece)
+    constexpr int WCG = PARTS == 3 ? (TM * UPC + T - 1) / T : 1;  // (groups of output channels per thread)
+    constexpr int WU = PARTS == 3 ? WCG * max_pieces(N, PARTS) : (TM * UPC * max_pieces(N, PARTS) + T - 1) / T;
+    // (WU: weight units per thread)
+    constexpr int PX = PARTS == 3 ? 1 : 4;      // pixels of an activation unit
+    constexpr int XS_OFF = 2 * WBUF;
+    typedef PartProducts<PARTS> PP;
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    const GeomBase& g = a.g;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cw = wave % CW, qw = wave / CW;
+    const int l32 = lane & 31, gk = lane >> 5;
+    const int KHW = a.KHq * a.KWq;
+
+    const int bid_all = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ks = bid_all % a.ksplit, bid = bid_all / a.ksplit;
+    const int cb = a.cb_major ? bid / a.nqt : bid % a.nco;
+    const int qt = a.cb_major ? bid % a.nqt : bid / a.nco;
+    const int co0 = cb * TM, q0 = qt * TN;
+    const int q_last = (q0 + TN - 1 < a.Q ? q0 + TN - 1 : a.Q - 1);
+    // quad row rho = b*KHq + kk uses input rows e = b*EH + kk + pa
+    const int bf0 = fdiv(q0, a.dKHW), kf0 = fdiv(q0 - bf0 * KHW, a.dKW);
+    const int e_first = bf0 * a.EH + kf0;
+
+    // ---- zero the activation stage once: halo columns are never written again
+    for (int i = tid; i < PARTS * a.XPL / 16; i += T)
+        *reinterpret_cast<u4v_t*>(lds + XS_OFF + i * 16) = u4v_t{0u, 0u, 0u, 0u};
+
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)x, 0, (int)((size_t)g.B * g.Cin * g.H * g.W * ES), kRawBuffer);
+    const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)w, 0, (int)((size_t)g.Cout * g.Cin * NN * ES), kRawBuffer);
+    const unsigned x_cstride = (unsigned)(g.H * g.W * ES);
+
+    // ---- staging units.  Activations: (channel half, row, PX columns), columns fastest; the last unit of a
+    // row whose length is no multiple of PX starts inside its neighbour
+    unsigned x_goff[XU];
+    int x_loff[XU], x_ci[XU];
+#pragma unroll
+    for (int j = 0; j < XU; ++j) {
+        const int e = tid + T * j;
+        const int h = fdiv(e, a.dRW);
+        const int rem = e - h * (a.ROWS * a.CPR);
+        const int row = fdiv(rem, a.dW), c = rem - row * a.CPR;
+        const int col = PX * c + PX <= g.W ? PX * c : g.W - PX;
+        x_goff[j] = kNoByte;
+        x_ci[j] = 8 * h;
+        x_loff[j] = -1;
+        if (h < 2) {
+            const int er = e_first + row;
+            const int b = fdiv(er, a.dEH), i = er - b * a.EH - (g.P >> 1);
+            if (b < g.B && i >= 0 && i < g.H)
+                x_goff[j] = (unsigned)((((b * g.Cin + 8 * h) * g.H + i) * g.W + col) * ES);
+            x_loff[j] = XS_OFF + ((h * a.ROWS + row) * a.LWX + a.SH + col) * 16;
+        }
+    }
+    // weights.  Three parts: the thread's unit j is (output channel tid/8 + (j % WCG)*T/8, two input channels,
+    // piece j / WCG), every unit exists; channels past the last output channel lie past the end of w and
+    // arrive as zeros.  One part: unit tid + T*j = (output channel, eight input channels, piece), piece
+    // fastest; units that do not exist read nothing and write to a pad slot.
+    int w_goff[PARTS == 3 ? 1 : WU], w_loff[PARTS == 3 ? 1 : WU], w_ci[PARTS == 3 ? 1 : WU];
+    if constexpr (PARTS == 3) {
+        const int cg = tid % UPC, co = tid / UPC;
+        w_ci[0] = UK * cg;
+        w_goff[0] = (((co0 + co) * g.Cin + UK * cg) * NN) * ES;
+        w_loff[0] = (UK * cg >> 3) * WHS + co * 16 + (UK * cg & 7) * 2;
+        if (TM * UPC < T && co >= TM) w_goff[0] = (int)kNoByte;  // (TM = 32 on 8 waves)
+    } else {
+#pragma unroll
+        for (int j = 0; j < WU; ++j) {
+            constexpr int pieces = sub_pieces(N, 1, 0);
+            const int e = tid + T * j;
+            const int t = e / pieces, tap = piece_at(NN, e - t * pieces);
+            const int cg = t % UPC, co = t / UPC;
+            w_ci[j] = UK * cg;
+            w_goff[j] = co < TM && co0 + co < g.Cout ? (((co0 + co) * g.Cin + UK * cg) * NN + tap) * ES : (int)kNoByte;
+            w_loff[j] = co < TM ? cg * WHS + tap * WTS + co * 16 : -1;
+        }
+    }
+    const int w_gstep = T / UPC * g.Cin * NN * ES;
+    // raw registers of the stage being fetched: UK (8) values of four taps (PX pixels) per unit
+    constexpr int WD = PARTS == 3 ? 4 : 2, XD = PARTS == 3 ? 1 : 2;  // dwords per load
+    unsigned xr[XU][8][XD], wr[WU][UK][WD];
+    PartRange seen;
+    auto load_x = [&](int s) {
+#pragma unroll
+        for (int j = 0; j < XU; ++j)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const unsigned soff = (unsigned)(s * KC + k) * x_cstride;
+                if constexpr (XD == 1) {
+                    xr[j][k][0] = __builtin_amdgcn_raw_buffer_load_b32(rs_x, x_goff[j], soff, 0);
+                } else {
+                    const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_x, x_goff[j], soff, 0);
+                    xr[j][k][0] = v.x;
+                    xr[j][k][1] = v.y;
+                }
+            }
+    };
+    auto w_units = [&](int sub) { return PARTS == 3 ? WCG * sub_pieces(N, PARTS, sub) : WU; };
+    auto load_w = [&](int s, int sub) {
+#pragma unroll
+        for (int j = 0; j < w_units(sub); ++j) {
+            const int tap0 = PARTS == 3 ? sub_first(N, PARTS, sub) + piece_at(sub_taps(N, PARTS, sub), j / WCG) : 0;
+            const unsigned voff = (unsigned)(PARTS == 3 ? w_goff[0] + (j % WCG) * w_gstep : w_goff[j]);
+#pragma unroll
+            for (int k = 0; k < UK; ++k) {
+                const unsigned soff = (unsigned)(((s * KC + k) * NN + tap0) * ES);
+                if constexpr (WD == 4) {
+                    const u4v_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_w, voff, soff, 0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) wr[j][k][i] = v[i];
+                } else {
+                    const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_w, voff, soff, 0);
+                    wr[j][k][0] = v.x;
+                    wr[j][k][1] = v.y;
+                }
+            }
+        }
+    };
+    // registers -> LDS.  A stage that reaches past the last input channel holds zeros there (what was
+    // loaded for them belongs to another image or output channel)
+    auto trim_w = [&](int s, int sub) {
+        if (s * KC + KC <= g.Cin) return;
+#pragma unroll
+        for (int j = 0; j < w_units(sub); ++j)
+#pragma unroll
+            for (int k = 0; k < UK; ++k) {
+                const bool in = s * KC + w_ci[PARTS == 3 ? 0 : j] + k < g.Cin;
+#pragma unroll
+                for (int i = 0; i < WD; ++i) wr[j][k][i] = in ? wr[j][k][i] : 0u;
+            }
+    };
+    auto store_w_tap = [&](int sub, int buf, int t) {  // tap t of every unit's piece
+#pragma unroll
+        for (int j = 0; j < w_units(sub); ++j) {
+            if constexpr (PARTS == 3) {
+                unsigned char* const dst = lds + buf * WBUF + w_loff[0] + (j % WCG) * (T / UPC * 16) +
+                                           (piece_at(sub_taps(N, PARTS, sub), j / WCG) + t) * WTS;
+                if (TM * UPC < T && wave >= TM * UPC / 64) continue;  // uniform
+                unsigned p[3];
+                split_pair(__uint_as_float(wr[j][0][t]), __uint_as_float(wr[j][1][t]), p[0], p[1], p[2], seen);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<unsigned*>(dst + i * WPL) = p[i];
+            } else {
+                u4v_t v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    v[i] = __builtin_amdgcn_perm(wr[j][2 * i + 1][t >> 1], wr[j][2 * i][t >> 1],
+                                                 (t & 1) ? 0x07060302u : 0x05040100u);
+                *reinterpret_cast<u4v_t*>(lds + buf * WBUF + (w_loff[j] < 0 ? WHS - 16 : w_loff[j] + t * WTS)) = v;
+            }
+        }
+    };
+    u4v_t xp[XU][PARTS * PX];
+    auto trim_x = [&](int s) {
+        if (s * KC + KC <= g.Cin) return;
+#pragma unroll
+        for (int j = 0; j < XU; ++j)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool in = s * KC + x_ci[j] + k < g.Cin;
+#pragma unroll
+                for (int i = 0; i < XD; ++i) xr[j][k][i] = in ? xr[j][k][i] : 0u;
+            }
+    };
+    auto pack_x = [&](int i) {  // items 0 .. 4*XU - 1
+        const int j = i >> 2, q = i & 3;
+        if constexpr (PARTS == 3) {
+            unsigned p0, p1, p2;
+            split_pair(__uint_as_float(xr[j][2 * q][0]), __uint_as_float(xr[j][2 * q + 1][0]), p0, p1, p2, seen);
+            xp[j][0][q] = p0;
+            xp[j][1][q] = p1;
+            xp[j][2][q] = p2;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                xp[j][q][k] = __builtin_amdgcn_perm(xr[j][2 * k + 1][q >> 1], xr[j][2 * k][q >> 1],
+                                                    (q & 1) ? 0x07060302u : 0x05040100u);
+        }
+    };
+    auto store_x = [&]() {
+#pragma unroll
+        for (int j = 0; j < XU; ++j)
+            if (x_loff[j] >= 0) {
+#pragma unroll
+                for (int i = 0; i < PARTS * PX; ++i)
+                    *reinterpret_cast<u4v_t*>(lds + (PARTS == 3 ? i * a.XPL : i * 16) + x_loff[j]) = xp[j][i];
+            }
+    };
+
+    // ---- operand positions of this lane
+    const int a_lds = gk * WHS + (cw * 32 + l32) * 16;
+    int b_lds[2];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        int q = q0 + (qw * 2 + nt) * 32 + l32;
+        if (q > q_last) q = q_last;
+        const int b = fdiv(q, a.dKHW);
+        const int rem = q - b * KHW;
+        const int kk = fdiv(rem, a.dKW), mm = rem - kk * a.KWq;
+        b_lds[nt] = XS_OFF + ((gk * a.ROWS + b * a.EH + kk - e_first) * a.LWX + mm) * 16;
+    }
+
+    f32x16_t acc[2][2][2];  // [quad group][row class][column class]
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[nt][c >> 1][c & 1][i] = 0.f;
+
+    // One weight stage (sub is a constant once unrolled), with the staging of the next ones dealt out
+    // between its MFMAs: two waves that share a SIMD get through their MFMAs side by side, so whatever is
+    // left for the end is left for both and finds the matrix pipe idle.
+    //   weights: three parts: the next stage's registers go to the other buffer under taps 1 and 2 and are
+    //     refilled at once for the stage after it; one part: fetched before the first tap, written under
+    //     the second half of them
+    //   activations of the next 16 channels: fetched before, split under the last tap of their last stage
+    const int s0 = ks * a.kstages;
+    const int nstages = (g.Cin + KC - 1) / KC;
+    const int s1 = s0 + a.kstages < nstages ? s0 + a.kstages : nstages;
+    auto stage_after = [&](int s, int sub, int d) {  // (the last stages fetch the last one again: unused)
+        const int r = s + (sub + d) / NSUB;
+        return r < s1 ? r : s1 - 1;
+    };
+    constexpr int AHEAD = PARTS == 3 ? 2 : 1;
+    auto compute = [&](int buf, int s, int sub) {
+        const unsigned char* const wb = lds + buf * WBUF + a_lds;
+        constexpr bool W3 = PARTS == 3;
+        const int taps = sub_taps(N, PARTS, sub);
+        const int s_w = stage_after(s, sub, 1), sub_w = (sub + 1) % NSUB;
+        bf16x8_t bf[2][PARTS];
+        int have = -1;
+        if (sub + 1 == NSUB) load_x(stage_after(s, sub, 1));
+        if (!W3) load_w(s_w, sub_w);
+#pragma unroll
+        for (int t = 0; t < taps; ++t) {
+            const int tap = sub_first(N, PARTS, sub) + t, tr = tap / N, tc = tap % N;
+            const int pa = pos_of<AL>(tr), pb = pos_of<AL>(tc);
+            __builtin_amdgcn_sched_barrier(0);
+            bf16x8_t af[PARTS];
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i) af[i] = *reinterpret_cast<const bf16x8_t*>(wb + i * WPL + t * WTS);
+            if (pa * 8 + pb != have) {
+                have = pa * 8 + pb;
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                    for (int i = 0; i < PARTS; ++i)
+                        bf[nt][i] = *reinterpret_cast<const bf16x8_t*>(lds + b_lds[nt] + i * a.XPL + pa * a.LWX * 16 +
+                                                                       pb * 16);
+            }
+            if (t == (W3 ? 1 : taps / 2)) trim_w(s_w, sub_w);
+            if (t + 1 == taps && sub + 1 == NSUB) trim_x(stage_after(s, sub, 1));
+#pragma unroll
+            for (int m = 0; m < PP::count; ++m) {
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    acc[nt][tr & 1][tc & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        af[PP::a[m]], bf[nt][PP::b[m]], acc[nt][tr & 1][tc & 1], 0, 0, 0);
+                if constexpr (W3) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if ((t == 1 || t == 2) && (m == 1 || m == 3)) store_w_tap(sub_w, buf ^ 1, 2 * (t - 1) + m / 2);
+                    if (t == 2 && m == 4) load_w(stage_after(s, sub, 2), (sub + 2) % NSUB);
+                    if (t + 1 == taps && sub + 1 == NSUB) {
+#pragma unroll
+                        for (int i = m * 4 * XU / 6; i < (m + 1) * 4 * XU / 6; ++i) pack_x(i);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                } else {
+                    // tap i of the pieces under tap taps/2 + i*(taps - taps/2)/4
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (t == taps / 2 + i * (taps - taps / 2) / 4) store_w_tap(sub_w, buf ^ 1, i);
+                    if (t + 1 == taps && sub + 1 == NSUB) {
+#pragma unroll
+                        for (int i = 0; i < 4 * XU; ++i) pack_x(i);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    load_w(s0, 0);
+    load_x(s0);
+    __syncthreads();  // zero fill done before the first activation writes
+    trim_w(s0, 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) store_w_tap(0, 0, t);
+    trim_x(s0);
+#pragma unroll
+    for (int i = 0; i < 4 * XU; ++i) pack_x(i);
+    store_x();
+    if constexpr (AHEAD == 2) load_w(stage_after(s0, 0, 1), 1 % NSUB);
+    __syncthreads();
+    int buf = 0;
+    for (int s = s0; s < s1; ++s) {
+#pragma unroll
+        for (int sub = 0; sub < NSUB; ++sub) {
+            // addresses are worked out again in every weight stage: hoisted out of the loop, one per (part,
+            // window row, tap run), they would push the accumulators out of the register file
+            asm("" : "+v"(b_lds[0]), "+v"(b_lds[1]));
+            compute(buf, s, sub);
+            __syncthreads();
+            buf ^= 1;
+        }
+        store_x();
+        __syncthreads();
+    }
+
+    // ---- results
+    constexpr int OS = OUT16 ? 2 : 4;
+    const size_t ybytes = (size_t)g.B * g.Cout * g.OH * g.OW * OS;
+    unsigned char* const yb = (unsigned char*)y + (size_t)ks * a.copy_bytes;
+
+    if constexpr (PARTS == 3) {
+        if (__syncthreads_or(seen.bad() ? 1 : 0)) {
+            // an operand whose parts do not hold it: this block's outputs again, in fp32 throughout
+            const int ci1 = s1 * KC < g.Cin ? s1 * KC : g.Cin;
+            for (int e = tid; e < TN * 4 * (TM / 8); e += T) {
+                const int q = q0 + e % TN, cls = (e / TN) & 3, cbase = co0 + e / (4 * TN) * 8;
+                if (q > q_last) continue;
+                const int r = cls >> 1, sc = cls & 1;
+                const int b = fdiv(q, a.dKHW);
+                const int rem = q - b * KHW;
+                const int kk = fdiv(rem, a.dKW), mm = rem - kk * a.KWq;
+                const int oy = AL ? 2 * kk + r : 2 * (g.k_min + kk) - r - g.P;
+                const int ox = AL ? 2 * mm + sc : 2 * (g.m_min + mm) - sc - g.P;
+                if (oy < 0 || oy >= g.OH || ox < 0 || ox >= g.OW) continue;
+                float sum[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sum[k] = 0.f;
+                for (int ci = s0 * KC; ci < ci1; ++ci)
+                    for (int ta = r; ta < N; ta += 2) {
+                        const int i = kk + pos_of<AL>(ta) - (g.P >> 1);
+                        if (i < 0 || i >= g.H) continue;
+                        for (int tc = sc; tc < N; tc += 2) {
+                            const int j = mm + pos_of<AL>(tc) - (g.P >> 1);
+                            if (j < 0 || j >= g.W) continue;
+                            const float xv = element_f32(x[(((size_t)b * g.Cin + ci) * g.H + i) * g.W + j]);
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) {
+                                const int ch = cbase + k < g.Cout ? cbase + k : g.Cout - 1;
+                                sum[k] = fmaf(xv, element_f32(w[((size_t)ch * g.Cin + ci) * NN + ta * N + tc]), sum[k]);
+                            }
+                        }
+                    }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (cbase + k >= g.Cout) continue;
+                    float v = sum[k];
+                    if constexpr (EPI) v = epilogue(v, ep.bias ? ep.bias[cbase + k] : 0.f, ep.act);
+                    const size_t o = (((size_t)b * g.Cout + cbase + k) * g.OH + oy) * g.OW + ox;
+                    if constexpr (OUT16) ((uint16_t*)yb)[o] = __builtin_bit_cast(uint16_t, (__bf16)v);
+                    else ((float*)yb)[o] = v;
+                }
+            }
+            return;
+        }
+    }
+
+    // accumulator register i of a tile holds channel 8*(i/4) + 4*gk + (i%4) of the wave's 32, for the
+    // lane's quad; the two column classes of a quad are neighbours in memory
+    const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc((void*)yb, 0, (int)ybytes, kRawBuffer);
+    const unsigned plane = (unsigned)(g.OH * g.OW * OS);
+    const int co_w = co0 + cw * 32 + 4 * gk;  // channel of register 0
+    auto drain = [&](auto act_tag) {
+        constexpr int ACT = decltype(act_tag)::value;  // -1: no epilogue at all
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const int q = q0 + (qw * 2 + nt) * 32 + l32;
+            const bool qv = q <= q_last;
+            const int qq = qv ? q : q_last;
+            const int b = fdiv(qq, a.dKHW);
+            const int rem = qq - b * KHW;
+            const int kk = fdiv(rem, a.dKW), mm = rem - kk * a.KWq;
+            // first row / column of the quad in the output (-1 where only the second one exists)
+            const int oy = AL ? 2 * kk : 2 * (g.k_min + kk) - 1 - g.P;
+            const int ox = AL ? 2 * mm : 2 * (g.m_min + mm) - 1 - g.P;
+            const bool c0v = ox >= 0, c1v = ox + 1 < g.OW;
+            const unsigned y_off = (unsigned)(((b * g.Cout + co_w) * g.OH + oy) * g.OW + ox) * (unsigned)OS;
+#pragma unroll
+            for (int rr = 0; rr < 2; ++rr) {
+                const bool vrow = qv && oy + rr >= 0 && oy + rr < g.OH;
+                const unsigned base = y_off + (unsigned)(rr * g.OW * OS);
+                const unsigned off_pair = vrow && c0v && c1v ? base : kNoByte;
+                const bool only0 = vrow && c0v && !c1v, only1 = vrow && !c0v && c1v;
+                const unsigned off_edge = only0 ? base : only1 ? base + (unsigned)OS : kNoByte;
+                const bool any_edge = !AL && __builtin_amdgcn_ballot_w64(only0 || only1) != 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int ch = 8 * (i / 4) + (i % 4);
+                    if (co0 + cw * 32 + ch >= g.Cout) continue;  // uniform
+                    const bool chv = co_w + ch < g.Cout;         // (the upper four of a partial group of 8)
+                    const unsigned soff = (unsigned)ch * plane;
+                    // shifted quads hold class 1 in their first row / column
+                    float v0 = AL ? acc[nt][rr][0][i] : acc[nt][1 - rr][1][i];
+                    float v1 = AL ? acc[nt][rr][1][i] : acc[nt][1 - rr][0][i];
+                    if constexpr (ACT >= 0) {
+                        const float bv = ep.bias ? ep.bias[chv ? co_w + ch : 0] : 0.f;
+                        v0 = epilogue_t<ACT>(v0, bv);
+                        v1 = epilogue_t<ACT>(v1, bv);
+                    }
+                    const unsigned op = chv ? off_pair : kNoByte, oe = chv ? off_edge : kNoByte;
+                    if constexpr (OUT16) {
+                        const unsigned bits = pack_bf16(v0, v1);
+                        __builtin_amdgcn_raw_buffer_store_b32(bits, rs_y, op, soff, 0);
+                        if (any_edge)
+                            __builtin_amdgcn_raw_buffer_store_b16((short)(only0 ? bits & 0xFFFFu : bits >> 16), rs_y, oe,
+                                                                  soff, 0);
+                    } else {
+                        u2v_t d;
+                        d.x = __float_as_uint(v0);
+                        d.y = __float_as_uint(v1);
+                        __builtin_amdgcn_raw_buffer_store_b64(d, rs_y, op, soff, 0);
+                        if (any_edge)
+                            __builtin_amdgcn_raw_buffer_store_b32(only0 ? d.x : d.y, rs_y, oe, soff, 0);
+                    }
+                }
+            }
+        }
+    };
+    if constexpr (EPI) with_activation(ep.act, drain);
+    else drain(std::integral_constant<int, -1>{});
+}
+
+// tile configuration: 32*cw channels x 64*qw quads per block, xu activation units per thread
+struct Config { int cw, qw, xu; };
+
+inline int weight_stage_bytes(int n, int parts, int cw) { return parts * 2 * w_half_slots(n, parts, 32 * cw) * 16; }
+
+template <int N, int CW, int QW, int XU, bool AL, typename TIn, bool OUT16>
+hipError_t launch_c(const PartsArgs& a, const Epilogue& ep, const void* x, const void* w, void* y, hipStream_t stream)
+{
+    const size_t lds = 2 * (size_t)weight_stage_bytes(N, sizeof(TIn) == 4 ? 3 : 1, CW) +
+                       (size_t)(sizeof(TIn) == 4 ? 3 : 1) * a.XPL;
+    typedef void (*kernel_t)(const TIn*, const TIn*, void*, PartsArgs, Epilogue);
+    const kernel_t kfn = has_epilogue(ep) ? ukst_mfma_f32_kernel_parts<N, CW, QW, XU, AL, true, TIn, OUT16>
+                                          : ukst_mfma_f32_kernel_parts<N, CW, QW, XU, AL, false, TIn, OUT16>;
+    const hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)(a.nco * a.nqt * a.ksplit)), dim3(64 * CW * QW), lds, stream,
+                       (const TIn*)x, (const TIn*)w, y, a, ep);
+    return hipGetLastError();
+}
+
+template <int N, bool AL, typename TIn, bool OUT16>
+hipError_t launch_n(const PartsArgs& a, const Config& c, const Epilogue& ep, const void* x, const void* w, void* y,
+                    hipStream_t st)
+{
+#define UKST_PARTS_CASE(CW, QW, XU) \
+    if (c.cw == CW && c.qw == QW && c.xu == XU) return launch_c<N, CW, QW, XU, AL, TIn, OUT16>(a, ep, x, w, y, st);
+    if constexpr (sizeof(TIn) == 4) {
+        UKST_PARTS_CASE(2, 4, 2) UKST_PARTS_CASE(2, 4, 3) UKST_PARTS_CASE(2, 4, 4)
+        UKST_PARTS_CASE(2, 2, 2) UKST_PARTS_CASE(2, 2, 4)
+        UKST_PARTS_CASE(1, 4, 2) UKST_PARTS_CASE(1, 4, 4) UKST_PARTS_CASE(1, 8, 2) UKST_PARTS_CASE(1, 8, 4)
+    } else {
+        UKST_PARTS_CASE(2, 4, 1) UKST_PARTS_CASE(2, 4, 2)
+        UKST_PARTS_CASE(2, 2, 1) UKST_PARTS_CASE(2, 2, 2)
+        UKST_PARTS_CASE(1, 4, 1) UKST_PARTS_CASE(1, 4, 2)
+    }
+#undef UKST_PARTS_CASE
+    return hipErrorInvalidValue;
+}
+
+// every instance of one kernel side and operand type (one translation unit each: ukst_mfma_parts_*.hip)
+template <int N, typename TIn>
+hipError_t launch_side(const PartsArgs& a, const Config& c, const Epilogue& ep, const void* x, const void* w, void* y,
+                       bool out16, hipStream_t st);
+
+template <>
+hipError_t launch_side<2, float>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<2, uint16_t>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<3, float>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<3, uint16_t>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<4, float>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<4, uint16_t>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<5, float>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+template <>
+hipError_t launch_side<5, uint16_t>(const PartsArgs&, const Config&, const Epilogue&, const void*, const void*, void*,
+                           bool, hipStream_t);
+
+template <int N, typename TIn>
+hipError_t launch_side_impl(const PartsArgs& a, const Config& c, const Epilogue& ep, const void* x, const void* w,
+                            void* y, bool out16, hipStream_t st)
+{
+    if constexpr (sizeof(TIn) == 2) {
+        if (out16) {
+            if constexpr (N % 2 == 0) {
+                if (a.g.P % 2 == 0) return launch_n<N, true, TIn, true>(a, c, ep, x, w, y, st);
+            }
+            return launch_n<N, false, TIn, true>(a, c, ep, x, w, y, st);
+        }
+    }
+    if constexpr (N % 2 == 0) {
+        if (a.g.P % 2 == 0) return launch_n<N, true, TIn, false>(a, c, ep, x, w, y, st);
+    }
+    return launch_n<N, false, TIn, false>(a, c, ep, x, w, y, st);
+}
+
+}  // namespace parts
+}  // namespace ukst

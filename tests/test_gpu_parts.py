@@ -1,0 +1,107 @@
+"""The matrix-core kernel on bf16 parts: edges of its tiles (channel tails, ragged columns, several images
+per tile), and operands whose three bf16 parts do not hold them (infinite, NaN, huge, tiny)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_20493_amd import binding as ukst
+from paper_2502_20493_amd import workloads as wl
+from gpu_util import TOL, check_against_oracle, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# B, Cin, Cout, H, W, n, P, dtype
+SHAPES = [
+    (2, 33, 21, 9, 11, 3, 0, "f32"),     # channel tail of 1, one partial 32-channel block
+    (1, 47, 70, 5, 13, 4, 2, "f32"),     # aligned quads, two channel blocks, the second with 6 channels
+    (3, 40, 37, 3, 4, 4, 1, "f32"),      # shifted quads, many images per tile
+    (2, 35, 5, 7, 19, 2, 0, "f32"),      # n = 2 aligned
+    (2, 35, 9, 7, 19, 2, 3, "f32"),      # n = 2 shifted, P beyond the kernel
+    (1, 50, 33, 2, 129, 3, 2, "f32"),    # rows longer than a tile's quads
+    (1, 36, 30, 40, 117, 3, 1, "f32"),   # 512-quad tiles of 32 channels
+    (4, 17, 41, 64, 63, 5, 3, "f32"),    # n = 5: 26 stages of taps, 17 channels
+    (9, 18, 35, 33, 61, 5, 0, "f32"),
+    (2, 17, 21, 9, 11, 3, 0, "bf16"),
+    (1, 47, 70, 5, 13, 4, 2, "bf16"),    # rows of no multiple of 4: the last piece starts inside its neighbour
+    (3, 24, 37, 3, 4, 4, 1, "bf16"),
+    (2, 31, 2, 7, 5, 5, 2, "bf16"),      # thin output
+    (2, 35, 9, 7, 19, 2, 3, "bf16"),
+    (1, 16, 33, 2, 130, 5, 4, "bf16"),
+    (2, 64, 100, 16, 127, 3, 1, "bf16"),
+]
+
+
+def _mk(shape):
+    B, Cin, Cout, H, W, n, P, dtype = shape
+    return wl.Workload("parts", 9800 + sum(shape[:7]), B, Cin, Cout, H, W, n, P, dtype, "normal", "normal:0.5")
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_tile_edges_every_element(shape):
+    w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    assert ukst.ukst_kernel_name(w.B, w.Cin, w.Cout, w.H, w.W, w.n, w.P, dt) == "ukst_mfma_f32_kernel_parts"
+    for integer in (True, False):
+        print(f"case {shape} integer={integer}", flush=True)
+        data = wl.generate(w, integer=integer)
+        y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+        y = run_gpu(data, w.dtype, w.P, guard=4096)
+        check_against_oracle(y, y_ref, S, TOL["f32"], exact=integer)  # (bf16 products are exact in fp32)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[10], SHAPES[13], (2, 33, 21, 9, 11, 3, 0, "bf16")])
+def test_bf16_output_and_epilogue(shape):
+    import torch
+    from gpu_util import to_device
+    w = _mk(shape)
+    data = wl.generate(w)
+    x, k = to_device(data, w.dtype)
+    bias = np.linspace(-1.0, 1.0, w.Cout).astype(np.float32)
+    y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+    z = np.maximum(y_ref + bias.astype(np.float64)[None, :, None, None], 0.0)
+    y = ukst.ukst_conv_transpose2d_bias_act(x, k, w.P, bias=torch.from_numpy(bias).cuda(), act=ukst.UKST_ACT_RELU,
+                                            out_bf16=True)
+    got = y.float().cpu().numpy().astype(np.float64)
+    # the fp32 sum's tolerance and half a bf16 ulp (2^-9 of the value)
+    assert (np.abs(got - z) <= TOL["f32"] * S + 2.0 ** -8 * np.abs(z) + 1e-30).all()
+
+
+@pytest.mark.parametrize("shape", [(2, 41, 24, 9, 12, 4, 2, "f32"), (2, 33, 35, 10, 9, 3, 1, "f32")])
+@pytest.mark.parametrize("what", ["inf", "nan", "huge", "tiny", "weight_inf", "all_tiny", "zero"])
+def test_operands_that_three_parts_do_not_hold(shape, what):
+    """Values a bf16 part cannot carry reach the outputs they reach in fp32 arithmetic, and no others."""
+    import torch
+    w = _mk(shape)
+    data = wl.generate(w)
+    x, k = data["x"].copy(), data["w"].copy()
+    if what == "inf":
+        x[0, 3, 2, 4], x[1, 7, 0, 0] = np.inf, -np.inf
+    elif what == "nan":
+        x[1, 5, 3, 3] = np.nan
+    elif what == "huge":
+        x[0, 1, 4, 4], k[2, 1, 1, 1] = 3.4e38, 1e-3  # rounds up to infinity as a bf16
+    elif what == "tiny":
+        x[0, :, 4:6, :] *= np.float32(1e-36)
+    elif what == "weight_inf":
+        k[3, 2, 1, 1] = np.inf
+    elif what == "all_tiny":
+        x *= np.float32(1e-34)
+    elif what == "zero":
+        x[0] = 0.0
+    assert ukst.ukst_kernel_name(w.B, w.Cin, w.Cout, w.H, w.W, w.n, w.P, ukst.UKST_F32) == "ukst_mfma_f32_kernel_parts"
+    y = ukst.ukst_conv_transpose2d(torch.from_numpy(x).cuda(), torch.from_numpy(k).cuda(), w.P).cpu().numpy()
+    fin = lambda a: np.where(np.isfinite(a), a, 0.0).astype(np.float32)
+    ref, S = oracle.naive(fin(x), fin(k), w.P)
+    # which outputs an infinite or NaN operand reaches, and with what
+    x64, k64 = torch.from_numpy(x).double(), torch.from_numpy(k).double()
+    full = torch.nn.functional.conv_transpose2d(x64, k64.flip(2, 3).transpose(0, 1), stride=2, padding=0).numpy()
+    lo = w.n - 1 - w.P
+    full = full[:, :, lo:full.shape[2] - lo, lo:full.shape[3] - lo]
+    with np.errstate(over="ignore"):
+        full = full.astype(np.float32).astype(np.float64)  # (sums beyond fp32 are infinite)
+    assert np.array_equal(np.isnan(full), np.isnan(y))
+    inf = np.isinf(full)
+    assert np.array_equal(inf, np.isinf(y)) and np.array_equal(full[inf], y[inf])
+    ok = np.isfinite(full)
+    # (1e-44: a few units of the smallest fp32 number)
+    assert (np.abs(y[ok].astype(np.float64) - ref[ok]) <= 1e-5 * S[ok] + 1e-44).all()
