@@ -1,4 +1,5 @@
-// The two generalisations Sec. 5 of the paper points to, on the vector ALUs, one kernel for both:
+// The two generalisations Sec. 5 of the paper points to, on the vector ALUs, one kernel for both (layers of at
+// least 16 input and 8 output channels run on the matrix cores where they fit: ukst_general_mfma.hip):
 //
 //  * transpose convolution with a general stride s: s-1 zeros are inserted between neighbouring
 //    pixels (Algorithm 1 with s in place of 2), so tap a of output row oy meets a pixel only where
@@ -116,6 +117,8 @@ hipError_t launch_general(int dilated, int B, int Cin, int Cout, int H, int W, i
                           int OH, int OW, const void* x, const void* w, float* y, int dtype,
                           hipStream_t stream)
 {
+    hipError_t err = hipSuccess;
+    if (launch_general_mfma(dilated, B, Cin, Cout, H, W, n, P, k, OH, OW, x, w, y, dtype, stream, &err)) return err;
     GenArgs a;
     a.B = B; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.n = n; a.P = P; a.k = k;
     a.OH = OH; a.OW = OW; a.dilated = dilated;

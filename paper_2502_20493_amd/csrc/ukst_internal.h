@@ -176,6 +176,10 @@ hipError_t launch_general(int dilated, int B, int Cin, int Cout, int H, int W, i
                           int OH, int OW, const void* x, const void* w, float* y, int dtype,
                           hipStream_t stream);
 
+// The same on the matrix cores: false if the layer is not for it (nothing launched), else *err is the launch
+bool launch_general_mfma(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW,
+                         const void* x, const void* w, float* y, int dtype, hipStream_t stream, hipError_t* err);
+
 // Backward pass (vector-ALU kernels, any shape; dtype 0: fp32, 1: bf16 operands, fp32 result)
 hipError_t launch_grad_input(const Geom& g, const void* dy, const void* w, float* dx, int dtype,
                              Workspace& ws, hipStream_t stream);

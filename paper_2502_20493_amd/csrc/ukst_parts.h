@@ -40,6 +40,8 @@ struct PartRange {
         constexpr unsigned short top = (127 + 62) << 7, bottom = (127 - 100) << 7;
         return hi.x >= top || hi.y >= top || lo.x + 1 < bottom || lo.y + 1 < bottom;
     }
+    // an infinity or NaN alone (operands that are bf16 already)
+    __device__ __forceinline__ bool not_finite() const { return hi.x >= 0x7F80 || hi.y >= 0x7F80; }
 };
 
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)

@@ -105,3 +105,61 @@ def test_operands_that_three_parts_do_not_hold(shape, what):
     ok = np.isfinite(full)
     # (1e-44: a few units of the smallest fp32 number)
     assert (np.abs(y[ok].astype(np.float64) - ref[ok]) <= 1e-5 * S[ok] + 1e-44).all()
+
+
+# op, k, (B, Cin, Cout, H, W, n, P)
+GENERAL_SHAPES = [
+    ("strided", 3, (2, 16, 8, 9, 11, 5, 2)),     # classes of 4, 2 and 1 taps
+    ("strided", 3, (2, 33, 70, 7, 13, 4, 0)),    # channel tails, input columns that start at 1
+    ("strided", 4, (3, 21, 33, 5, 6, 3, 1)),     # classes without taps: zeros
+    ("strided", 5, (1, 18, 9, 6, 37, 7, 8)),     # P beyond the kernel
+    ("strided", 1, (2, 17, 40, 12, 20, 4, 3)),   # one class
+    ("strided", 3, (1, 16, 33, 2, 130, 3, 2)),   # rows longer than half a tile
+    ("dilated", 2, (2, 33, 37, 15, 19, 3, 2)),
+    ("dilated", 4, (3, 20, 8, 11, 11, 5, 8)),    # several images per tile, mostly halo
+    ("dilated", 3, (1, 17, 65, 21, 13, 4, 13)),  # windows that meet no input
+    ("dilated", 1, (2, 16, 9, 8, 70, 1, 0)),     # a single tap
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", GENERAL_SHAPES)
+def test_general_operations_on_the_matrix_cores(case, dtype):
+    from test_gpu_general import _run
+    op, k, shape = case
+    w = wl.Workload("general_parts", 9900 + sum(shape) + k, *shape, dtype, "normal", "normal:0.5")
+    _run(op, w, k, integer=True)
+    _run(op, w, k, integer=False)
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "all_tiny", "bf16_weight_inf"])
+def test_general_operations_with_operands_that_three_parts_do_not_hold(what):
+    import torch
+    rng = np.random.default_rng(31)
+    x = rng.normal(size=(2, 17, 9, 10)).astype(np.float32)
+    w = rng.normal(size=(9, 17, 3, 3)).astype(np.float32)
+    if what == "bf16_weight_inf":  # the padding is left out, not multiplied
+        x, w = (wl.bf16_bits_to_f32(wl.round_to_bf16_bits(a)) for a in (x, w))
+        w[4, 3, 0, 1] = np.inf
+        put = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+        y = ukst.ukst_dilated_conv2d(put(x), put(w), 2, 2).cpu().numpy()
+        assert np.isfinite(y[:, [0, 1, 2, 3, 5, 6, 7, 8]]).all() and not np.isnan(y).any()
+        assert np.isfinite(y[:, 4, :2]).all() and np.isinf(y[:, 4, 2:]).all()
+        return
+    if what == "all_tiny":
+        x *= np.float32(1e-34)
+    else:
+        x[1, 4, 3, 5] = np.inf if what == "inf" else np.nan
+    x64, w64 = torch.from_numpy(x).double(), torch.from_numpy(w).double()
+    for got, ref in (
+            (ukst.ukst_conv_transpose2d_strided(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 2, 3),
+             torch.nn.functional.conv_transpose2d(x64, w64.flip(2, 3).transpose(0, 1), stride=3)),
+            (ukst.ukst_dilated_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 0, 2),
+             torch.nn.functional.conv2d(x64, w64, dilation=2))):
+        got, ref = got.cpu().numpy(), ref.numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(np.isinf(got), np.isinf(ref))
+        ok = np.isfinite(ref)
+        # 153 products of at most |x| |w| < 25 units of x's scale: 1e-5 of their sum
+        scale = 1e-34 if what == "all_tiny" else 1.0
+        assert (np.abs(got[ok] - ref[ok]) <= 1e-5 * 153 * 25 * scale + 1e-44).all()
