@@ -160,6 +160,7 @@ bool mfma_needs_aligned_x(const Geom& g, int dtype);
 // fp32-operand MFMA kernels (used by the functions above for dtype 0): the general one, and the
 // one for layers with at most 4 output channels, where the parity classes fill the MFMA columns
 bool mfma_f32_supported(const Geom& g, int dtype);
+long long mfma_f32_blocks(const Geom& g, int dtype);  // its grid with a workspace, 0 if unsupported
 hipError_t launch_mfma_f32(const Geom& g, const void* x, const void* w, float* y, int dtype, Workspace& ws,
                            hipStream_t stream);
 // bf16 matrix pipe from bf16 parts of the operands (three of an fp32 value, one of a bf16 value): any row
@@ -168,6 +169,10 @@ hipError_t launch_mfma_f32(const Geom& g, const void* x, const void* w, float* y
 double mfma_parts_tiles(const Geom& g, int dtype);
 hipError_t launch_mfma_parts(const Geom& g, const void* x, const void* w, void* y, int dtype, Workspace& ws,
                              hipStream_t stream);
+// fp32 layers of few tiles, given a workspace: slices of the input channels and a sum over them
+bool mfma_parts_split_supported(const Geom& g, int dtype);
+hipError_t launch_mfma_parts_split(const Geom& g, const void* x, const void* w, float* y, Workspace& ws,
+                                   hipStream_t stream);
 bool thin_mfma_supported(const Geom& g, int dtype);
 hipError_t launch_thin_mfma(const Geom& g, const void* x, const void* w, float* y, hipStream_t stream);
 

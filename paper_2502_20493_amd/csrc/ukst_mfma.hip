@@ -550,11 +550,23 @@ static bool prefer_parts(const Geom& g, int dtype)
     if (g.Cin < 16 || bf16_pipe(g, dtype) || (dtype == 0 && g.Cout <= 4)) return false;
     const double tiles = mfma_parts_tiles(g, dtype);
     if (tiles == 0.) return false;
-    if (mfma_f32_supported(g, dtype)) return tiles >= (dtype != 0 ? 16. : g.n <= 4 ? 72. : 160.);
+    if (mfma_f32_supported(g, dtype)) return tiles >= (dtype != 0 ? 16. : g.n <= 4 ? 72. : 120.);
     // otherwise the vector ALUs, which win against one tile's serial work only with few channels or 5 x 5 fp32 kernels (77 -> 40 channels, 33 tiles: 67 against 91 us; 19 -> 21
     // channels, 8 tiles: 12 against 15 us; 591 -> 96 channels bf16, 95 tiles: 7.7 ms against 103 us)
     if (dtype != 0) return true;
     return g.n == 5 ? tiles >= 64. : g.Cin >= 32 || tiles >= 24.;
+}
+
+// ... and, given a workspace, with slices of the input channels: layers of few tiles that are long on the
+// fp32 pipe (from 3e9 multiply-adds on: 128 images of 512 -> 256 channels, 4 x 4, n = 4: 81 against 62 us; half of
+// it, which fills that kernel's grid once, 47 against 43 us and not worth a workspace), or leave most of the chip
+// idle there (2 images of 376 -> 488 channels, 8 x 35, 88 blocks: 125 against 34 us)
+static bool prefer_parts_split(const Geom& g, int dtype)
+{
+    if (dtype != 0 || g.Cin < 16 || g.Cout <= 4 || !mfma_f32_supported(g, dtype) || prefer_parts(g, dtype)) return false;
+    const double macs = (double)g.B * g.Cin * g.Cout * g.H * g.W * g.n * g.n;
+    return (macs >= 3e9 || mfma_f32_blocks(g, dtype) < 192) && mfma_parts_tiles(g, dtype) >= 12. &&
+           mfma_parts_split_supported(g, dtype);
 }
 
 bool mfma_auto_extra(const Geom& g, int dtype)
@@ -581,6 +593,13 @@ hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, in
                        Workspace& ws, hipStream_t stream)
 {
     if (prefer_parts(g, dtype)) return launch_mfma_parts(g, x, w, y, dtype, ws, stream);
+    if (prefer_parts_split(g, dtype)) {
+        Workspace need;
+        need.query = true;
+        const hipError_t e = launch_mfma_parts_split(g, nullptr, nullptr, nullptr, need, stream);
+        if (e == hipSuccess && (ws.query || (ws.ptr != nullptr && ws.bytes >= need.need)))
+            return launch_mfma_parts_split(g, x, w, y, ws, stream);
+    }
     if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)))
         return launch_mfma_f32(g, x, w, y, dtype, ws, stream);
     if (ws.query) return hipSuccess;  // the kernels below use no scratch

@@ -97,7 +97,8 @@ constexpr int tap_at(int pa, int pb, int c)
 // TIn = float, or uint16_t for bf16 operands: they are widened to fp32 on their way into LDS
 // (exact) and multiplied on the fp32 matrix pipe -- the path of bf16 layers whose kernel side the
 // bf16 kernels do not take (n = 2, 3, 5).
-template <int N, int NW, int KC, bool EPI, bool AL, typename TIn>
+// SLICE (NW = 0): the block takes a slice of the stages, one of them or an even number.
+template <int N, int NW, int KC, bool EPI, bool AL, bool SLICE, typename TIn>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NW == 4 ? 1 : 2)))
 void ukst_mfma_f32_kernel(const TIn* __restrict__ x, const TIn* __restrict__ w,
                           float* __restrict__ y, F32Args a, Epilogue ep)
@@ -375,22 +376,25 @@ void ukst_mfma_f32_kernel(const TIn* __restrict__ x, const TIn* __restrict__ w,
             }
             __syncthreads();
         };
+        const int sk0 = SLICE ? s0 : 0;
+        const int sk1 = SLICE ? (s0 + 1 < stages ? s0 + 1 : s0) : 1;  // (unsliced: the stage count is even)
         const std::integral_constant<int, 0> i0;
         const std::integral_constant<int, 1> i1;
 #pragma unroll
-        for (int jj = 0; jj < PPS; ++jj) load_pair(i0, jj, 0);
+        for (int jj = 0; jj < PPS; ++jj) load_pair(i0, jj, sk0);
 #pragma unroll
-        for (int j = 0; j < NXS_SMALL; ++j) load_x(j, 0);
+        for (int j = 0; j < NXS_SMALL; ++j) load_x(j, sk0);
         __syncthreads();  // zero fill done before the first activation writes
 #pragma unroll
         for (int j = 0; j < NXS_SMALL; ++j) store_x(j, 0);
 #pragma unroll
-        for (int j = 0; j < NXS_SMALL; ++j) load_x(j, 1);  // (the stage count is even: stage 1 exists)
+        for (int j = 0; j < NXS_SMALL; ++j) load_x(j, sk1);
 #pragma unroll
-        for (int jj = 0; jj < PPS; ++jj) load_pair(i1, jj, 1);
+        for (int jj = 0; jj < PPS; ++jj) load_pair(i1, jj, sk1);
         __syncthreads();
-        for (int s = 0; s < stages; s += 2) {
+        for (int s = sk0; s < stages; s += 2) {
             stage_sk(0, i0, s);
+            if (SLICE && a.kstages == 1) break;
             stage_sk(1, i1, s + 1);
         }
     }
@@ -653,6 +657,14 @@ bool make_args(const Geom& g, F32Args& a, int es = 4)
             if (distance(ks) < distance(a.ksplit)) a.ksplit = ks;
         }
     }
+    // the small tiles: few blocks and many stages leave a layer to the latency of a serial chain (one image,
+    // 512 -> 256 channels, 4 x 4 maps: 8 blocks of 16 stages, 46 us): slices of one stage or an even number
+    // of them, as many as keep the block count at that of the compute units
+    if (NW == 0 && ybytes % 16 == 0) {
+        for (int ks = 2; ks <= stages && tiles * ks <= 256; ++ks)
+            if (stages % ks == 0 && (stages == ks || stages / ks % 2 == 0) && (size_t)ks * ybytes <= ((size_t)1 << 26))
+                a.ksplit = ks;
+    }
     a.kstages = stages / a.ksplit;
     return true;
 }
@@ -670,8 +682,9 @@ hipError_t launch_a(const F32Args& a, const Epilogue& ep, const TIn* x, const TI
     // the epilogue belongs to whole sums: with a split K loop the slice sum applies it
     const bool epi = a.ksplit == 1 && has_epilogue(ep);
     typedef void (*kernel_t)(const TIn*, const TIn*, float*, F32Args, Epilogue);
-    const kernel_t kfn = epi ? ukst_mfma_f32_kernel<N, NW, KC, true, AL, TIn>
-                             : ukst_mfma_f32_kernel<N, NW, KC, false, AL, TIn>;
+    const kernel_t whole = epi ? ukst_mfma_f32_kernel<N, NW, KC, true, AL, false, TIn>
+                               : ukst_mfma_f32_kernel<N, NW, KC, false, AL, false, TIn>;
+    const kernel_t kfn = NW == 0 && a.ksplit > 1 ? ukst_mfma_f32_kernel<N, NW, KC, false, AL, NW == 0, TIn> : whole;
     hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const unsigned nblocks = (unsigned)(a.nco * a.nqt * a.ksplit);
@@ -745,6 +758,13 @@ bool mfma_f32_supported(const Geom& g, int dtype)
     return (dtype == 0 || dtype == 1) && pick_nw(g, a, dtype == 0 ? 4 : 2) != 0;  // (-1: the split-K-in-block tile)
 }
 
+long long mfma_f32_blocks(const Geom& g, int dtype)
+{
+    F32Args a;
+    if (dtype > 1 || pick_nw(g, a, dtype == 0 ? 4 : 2) == 0) return 0;
+    return (long long)a.nco * a.nqt * a.ksplit;
+}
+
 hipError_t launch_mfma_f32(const Geom& g, const void* x, const void* w, float* y, int dtype, Workspace& ws,
                            hipStream_t stream)
 {
@@ -758,7 +778,8 @@ hipError_t launch_mfma_f32(const Geom& g, const void* x, const void* w, float* y
     }
     // without a workspace, and for outputs the slice sum cannot move in 16-byte pieces, the K loop
     // stays in one block per tile
-    if (a.ksplit > 1 && (ws.ptr == nullptr || ((uintptr_t)y & 15) != 0)) {
+    // (the small tiles, which work well enough without, do so with too small a workspace as well)
+    if (a.ksplit > 1 && (ws.ptr == nullptr || ((uintptr_t)y & 15) != 0 || (nw == -1 && ws.bytes < need))) {
         a.kstages *= a.ksplit;
         a.ksplit = 1;
     }

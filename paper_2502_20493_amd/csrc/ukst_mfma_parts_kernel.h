@@ -70,9 +70,9 @@ constexpr int w_half_slots(int n, int parts, int tm)
     return used + 1 + (want + 31 - used % 16) % 16;
 }
 
-// CW x QW waves: block tile = 32*CW channels x 64*QW quads; a wave owns 32 channels x 64 quads x 4 classes.
+// CW x QW waves: block tile = 32*CW channels x 32*NT*QW quads; a wave owns 32 channels x 32*NT quads x 4 classes.
 // XU: staging units of activations per thread.  EPI / OUT16 as in the other kernels.
-template <int N, int CW, int QW, int XU, bool AL, bool EPI, typename TIn, bool OUT16>
+template <int N, int CW, int QW, int NT, int XU, bool AL, bool EPI, typename TIn, bool OUT16>
 __global__ __launch_bounds__(64 * CW * QW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict__ w, void* __restrict__ y,
                                 PartsArgs a, Epilogue ep)
@@ -80,7 +80,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     constexpr int PARTS = sizeof(TIn) == 4 ? 3 : 1;
     constexpr int ES = (int)sizeof(TIn);
     constexpr int T = 64 * CW * QW;      // threads
-    constexpr int TM = 32 * CW, TN = 64 * QW;
+    constexpr int TM = 32 * CW, TN = 32 * NT * QW;
     constexpr int NN = N * N;
     constexpr int NSUB = sub_count(N, PARTS);   // weight stages per 16 channels
     constexpr int WTS = w_tap_slots(PARTS, TM) * 16, WHS = w_half_slots(N, PARTS, TM) * 16;
@@ -283,10 +283,10 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
 
     // ---- operand positions of this lane
     const int a_lds = gk * WHS + (cw * 32 + l32) * 16;
-    int b_lds[2];
+    int b_lds[NT];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        int q = q0 + (qw * 2 + nt) * 32 + l32;
+    for (int nt = 0; nt < NT; ++nt) {
+        int q = q0 + (qw * NT + nt) * 32 + l32;
         if (q > q_last) q = q_last;
         const int b = fdiv(q, a.dKHW);
         const int rem = q - b * KHW;
@@ -294,9 +294,9 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         b_lds[nt] = XS_OFF + ((gk * a.ROWS + b * a.EH + kk - e_first) * a.LWX + mm) * 16;
     }
 
-    f32x16_t acc[2][2][2];  // [quad group][row class][column class]
+    f32x16_t acc[NT][2][2];  // [quad group][row class][column class]
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -316,13 +316,12 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         const int r = s + (sub + d) / NSUB;
         return r < s1 ? r : s1 - 1;
     };
-    constexpr int AHEAD = PARTS == 3 ? 2 : 1;
     auto compute = [&](int buf, int s, int sub) {
         const unsigned char* const wb = lds + buf * WBUF + a_lds;
         constexpr bool W3 = PARTS == 3;
         const int taps = sub_taps(N, PARTS, sub);
         const int s_w = stage_after(s, sub, 1), sub_w = (sub + 1) % NSUB;
-        bf16x8_t bf[2][PARTS];
+        bf16x8_t bf[NT][PARTS];
         int have = -1;
         if (sub + 1 == NSUB) load_x(stage_after(s, sub, 1));
         if (!W3) load_w(s_w, sub_w);
@@ -337,7 +336,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             if (pa * 8 + pb != have) {
                 have = pa * 8 + pb;
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int i = 0; i < PARTS; ++i)
                         bf[nt][i] = *reinterpret_cast<const bf16x8_t*>(lds + b_lds[nt] + i * a.XPL + pa * a.LWX * 16 +
@@ -348,7 +347,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
 #pragma unroll
             for (int m = 0; m < PP::count; ++m) {
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
                     acc[nt][tr & 1][tc & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         af[PP::a[m]], bf[nt][PP::b[m]], acc[nt][tr & 1][tc & 1], 0, 0, 0);
                 if constexpr (W3) {
@@ -385,7 +384,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
 #pragma unroll
     for (int i = 0; i < 4 * XU; ++i) pack_x(i);
     store_x();
-    if constexpr (AHEAD == 2) load_w(stage_after(s0, 0, 1), 1 % NSUB);
+    if constexpr (PARTS == 3) load_w(stage_after(s0, 0, 1), 1 % NSUB);
     __syncthreads();
     int buf = 0;
     for (int s = s0; s < s1; ++s) {
@@ -393,7 +392,8 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         for (int sub = 0; sub < NSUB; ++sub) {
             // addresses are worked out again in every weight stage: hoisted out of the loop, one per (part,
             // window row, tap run), they would push the accumulators out of the register file
-            asm("" : "+v"(b_lds[0]), "+v"(b_lds[1]));
+            #pragma unroll
+            for (int nt = 0; nt < NT; ++nt) asm("" : "+v"(b_lds[nt]));
             compute(buf, s, sub);
             __syncthreads();
             buf ^= 1;
@@ -461,8 +461,8 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     auto drain = [&](auto act_tag) {
         constexpr int ACT = decltype(act_tag)::value;  // -1: no epilogue at all
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int q = q0 + (qw * 2 + nt) * 32 + l32;
+        for (int nt = 0; nt < NT; ++nt) {
+            const int q = q0 + (qw * NT + nt) * 32 + l32;
             const bool qv = q <= q_last;
             const int qq = qv ? q : q_last;
             const int b = fdiv(qq, a.dKHW);
@@ -518,19 +518,19 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     else drain(std::integral_constant<int, -1>{});
 }
 
-// tile configuration: 32*cw channels x 64*qw quads per block, xu activation units per thread
-struct Config { int cw, qw, xu; };
+// tile configuration: cw x qw waves of 32 channels x 32*nt quads, xu activation units per thread
+struct Config { int cw, qw, nt, xu; };
 
 inline int weight_stage_bytes(int n, int parts, int cw) { return parts * 2 * w_half_slots(n, parts, 32 * cw) * 16; }
 
-template <int N, int CW, int QW, int XU, bool AL, typename TIn, bool OUT16>
+template <int N, int CW, int QW, int NT, int XU, bool AL, typename TIn, bool OUT16>
 hipError_t launch_c(const PartsArgs& a, const Epilogue& ep, const void* x, const void* w, void* y, hipStream_t stream)
 {
     const size_t lds = 2 * (size_t)weight_stage_bytes(N, sizeof(TIn) == 4 ? 3 : 1, CW) +
                        (size_t)(sizeof(TIn) == 4 ? 3 : 1) * a.XPL;
     typedef void (*kernel_t)(const TIn*, const TIn*, void*, PartsArgs, Epilogue);
-    const kernel_t kfn = has_epilogue(ep) ? ukst_mfma_f32_kernel_parts<N, CW, QW, XU, AL, true, TIn, OUT16>
-                                          : ukst_mfma_f32_kernel_parts<N, CW, QW, XU, AL, false, TIn, OUT16>;
+    const kernel_t kfn = has_epilogue(ep) ? ukst_mfma_f32_kernel_parts<N, CW, QW, NT, XU, AL, true, TIn, OUT16>
+                                          : ukst_mfma_f32_kernel_parts<N, CW, QW, NT, XU, AL, false, TIn, OUT16>;
     const hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kfn, dim3((unsigned)(a.nco * a.nqt * a.ksplit)), dim3(64 * CW * QW), lds, stream,
@@ -542,16 +542,17 @@ template <int N, bool AL, typename TIn, bool OUT16>
 hipError_t launch_n(const PartsArgs& a, const Config& c, const Epilogue& ep, const void* x, const void* w, void* y,
                     hipStream_t st)
 {
-#define UKST_PARTS_CASE(CW, QW, XU) \
-    if (c.cw == CW && c.qw == QW && c.xu == XU) return launch_c<N, CW, QW, XU, AL, TIn, OUT16>(a, ep, x, w, y, st);
+#define UKST_PARTS_CASE(CW, QW, NT, XU)                          \
+    if (c.cw == CW && c.qw == QW && c.nt == NT && c.xu == XU)    \
+        return launch_c<N, CW, QW, NT, XU, AL, TIn, OUT16>(a, ep, x, w, y, st);
     if constexpr (sizeof(TIn) == 4) {
-        UKST_PARTS_CASE(2, 4, 2) UKST_PARTS_CASE(2, 4, 3) UKST_PARTS_CASE(2, 4, 4)
-        UKST_PARTS_CASE(2, 2, 2) UKST_PARTS_CASE(2, 2, 4)
-        UKST_PARTS_CASE(1, 4, 2) UKST_PARTS_CASE(1, 4, 4) UKST_PARTS_CASE(1, 8, 2) UKST_PARTS_CASE(1, 8, 4)
+        UKST_PARTS_CASE(2, 4, 2, 2) UKST_PARTS_CASE(2, 4, 2, 3) UKST_PARTS_CASE(2, 4, 2, 4)
+        UKST_PARTS_CASE(2, 4, 1, 2) UKST_PARTS_CASE(2, 4, 1, 4)
+        UKST_PARTS_CASE(1, 4, 2, 2) UKST_PARTS_CASE(1, 4, 2, 4) UKST_PARTS_CASE(1, 8, 2, 2) UKST_PARTS_CASE(1, 8, 2, 4)
     } else {
-        UKST_PARTS_CASE(2, 4, 1) UKST_PARTS_CASE(2, 4, 2)
-        UKST_PARTS_CASE(2, 2, 1) UKST_PARTS_CASE(2, 2, 2)
-        UKST_PARTS_CASE(1, 4, 1) UKST_PARTS_CASE(1, 4, 2)
+        UKST_PARTS_CASE(2, 4, 2, 1) UKST_PARTS_CASE(2, 4, 2, 2)
+        UKST_PARTS_CASE(2, 4, 1, 1) UKST_PARTS_CASE(2, 4, 1, 2)
+        UKST_PARTS_CASE(1, 4, 2, 1) UKST_PARTS_CASE(1, 4, 2, 2)
     }
 #undef UKST_PARTS_CASE
     return hipErrorInvalidValue;

@@ -163,3 +163,30 @@ def test_general_operations_with_operands_that_three_parts_do_not_hold(what):
         # 153 products of at most |x| |w| < 25 units of x's scale: 1e-5 of their sum
         scale = 1e-34 if what == "all_tiny" else 1.0
         assert (np.abs(got[ok] - ref[ok]) <= 1e-5 * 153 * 25 * scale + 1e-44).all()
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 512, 40, 3, 4, 4, 2),    # small tiles of the fp32 pipe in slices of one stage, ragged channel block
+    (60, 512, 24, 4, 4, 4, 2),   # slices of two stages
+    (60, 376, 72, 8, 8, 4, 2),   # bf16 parts, slices of 16 channels, a half stage at the end
+])
+def test_slices_of_the_input_channels(shape):
+    """Layers of few tiles with a workspace: partial sums per slice of the input channels, with the epilogue on
+    their sum; without one, or with one that is too small for the slices, the unsliced kernel."""
+    import torch
+    B, Cin, Cout, H, W, n, P = shape
+    w = wl.Workload("slices", 9700 + sum(shape), *shape, "f32", "normal", "normal:0.5")
+    need = ukst.ukst_workspace_bytes(ukst.UKST_OP_FORWARD, *shape, ukst.UKST_F32)
+    assert need > 0
+    data = wl.generate(w)
+    y_ref, S = oracle.naive(data["x"], data["w"], P)
+    bias = np.linspace(-1.0, 1.0, Cout).astype(np.float32)
+    z = np.maximum(y_ref + bias.astype(np.float64)[None, :, None, None], 0.0)
+    x, k, b = (torch.from_numpy(a).cuda() for a in (data["x"], data["w"], bias))
+    for space in (None, False, torch.empty(256, dtype=torch.uint8, device="cuda")):
+        y = ukst.ukst_conv_transpose2d_ws(x, k, P, bias=b, act=ukst.UKST_ACT_RELU, workspace=space)
+        print(shape, space is None, flush=True)
+        err = np.abs(y.cpu().numpy().astype(np.float64) - z)
+        assert (err <= 1e-5 * S + 1.2e-7 * np.abs(y_ref)).all()
+    one, two = (ukst.ukst_conv_transpose2d_ws(x, k, P) for _ in range(2))
+    assert torch.equal(one, two)
