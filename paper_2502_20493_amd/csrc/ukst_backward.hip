@@ -1086,7 +1086,6 @@ __global__ __launch_bounds__(256) void ukst_grad_weight_kernel(const TIn* __rest
 // the tiles and write partial results as [slice][co][tap][ci] (lanes along ci);
 // ukst_sum_taps_kernel adds the slices in a fixed order and stores dw[co][ci][tap].
 typedef __bf16 gw_bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 gw_bf16x8u __attribute__((ext_vector_type(8), aligned(2)));
 typedef unsigned gw_u4 __attribute__((ext_vector_type(4)));
 typedef unsigned gw_u4u __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned gw_u2 __attribute__((ext_vector_type(2)));
@@ -1400,6 +1399,54 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restr
     dw[((size_t)co * Cin + ci) * NN + tap] = v;
 }
 
+// The same for kernels of many channel pairs, bit for bit: a block takes 64 input channels of one output channel, reads
+// along the input channels, turns the (tap, channel) square in LDS and writes one contiguous run of dw, where
+// the kernel above stores 4 bytes every n*n floats.  From 2048 blocks on: with fewer, many copies and a thread
+// for every fourth tap only, it is the slower one (64 x 64 channels, n = 5: 63 against 119 us with the gradient).
+__global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __restrict__ part,
+                                                           float* __restrict__ dw, int n, int copies,
+                                                           int NN, int Cin)
+{
+    extern __shared__ __align__(16) float lds_t[];  // [64][NN + 1]
+    const int tilesI = (Cin + 63) / 64;
+    const int co = blockIdx.x / tilesI, ci0 = (blockIdx.x - co * tilesI) * 64;
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (ci0 + l < Cin)
+        for (int tap = wv; tap < NN; tap += 4) {
+            const float* p = part + ((size_t)co * NN + tap) * Cin + ci0 + l;
+            // four running sums (copies k, k+1, k+2, k+3 in turn): four loads in flight
+            float v4[4] = {0.f, 0.f, 0.f, 0.f};
+            int k = 0;
+            for (; k + 3 < copies; k += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v4[u] += p[(size_t)(k + u) * n];
+            }
+            for (int u = 0; k < copies; ++k, ++u) v4[u] += p[(size_t)k * n];
+            lds_t[l * (NN + 1) + tap] = (v4[0] + v4[1]) + (v4[2] + v4[3]);
+        }
+    __syncthreads();
+    const int cis = Cin - ci0 < 64 ? Cin - ci0 : 64;
+    float* out = dw + ((size_t)co * Cin + ci0) * NN;
+    for (int e = threadIdx.x; e < cis * NN; e += 256) {
+        const int ci = e / NN;
+        out[e] = lds_t[ci * (NN + 1) + e - ci * NN];
+    }
+}
+
+// dw from the copies of a kernel gradient
+hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size_t elems, int copies, hipStream_t stream)
+{
+    const int NN = g.n * g.n;
+    const long long blocks = (long long)g.Cout * ((g.Cin + 63) / 64);
+    if (blocks >= 2048 && blocks <= 0x7fffffffLL)
+        hipLaunchKernelGGL(ukst_sum_taps_wide_kernel, dim3((unsigned)blocks), dim3(256), 64 * (NN + 1) * sizeof(float),
+                           stream, part, dw, (int)elems, copies, NN, g.Cin);
+    else
+        hipLaunchKernelGGL(ukst_sum_taps_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, stream, part, dw,
+                           (int)elems, copies, NN, g.Cin);
+    return hipGetLastError();
+}
+
 template <int NC>
 bool gw_mfma_args(const Geom& g, GwMfmaArgs& a)
 {
@@ -1475,9 +1522,7 @@ hipError_t launch_gw_mfma(const GwMfmaArgs& a, const void* x, const void* dy, fl
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(ukst_sum_taps_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, stream,
-                           (const float*)part, dw, (int)elems, a.nSlices, N * N, g.Cin);
-        e = hipGetLastError();
+        e = launch_sum_taps(g, (const float*)part, dw, elems, a.nSlices, stream);
     }
     return e;
 }
@@ -1490,10 +1535,9 @@ hipError_t launch_gw_mfma(const GwMfmaArgs& a, const void* x, const void* dy, fl
 // pixel axis as the K axis of v_mfma_f32_32x32x16_bf16: a lane's operand is 8 consecutive pixels of
 // one channel, which is how NCHW rows lie in memory, so x goes to LDS as it is (16-byte pieces) and
 // dy rows are split by column parity on the way (one v_perm pair per piece), which makes the 8
-// pixels of any tap consecutive too.  A tap's lattice starts 0 or 1 elements into its half row:
-// half of the dy fragments are 16-byte LDS reads at a 2-byte-aligned address (the hardware's
-// unaligned DS access; no second, shifted copy of the tile is kept).  Tiles, slices, the dealing
-// of taps to waves and the partial-sum layout are those of the fp32 kernel above.
+// pixels of any tap consecutive too.  A tap's lattice starts 0 or 1 elements into its half row; the
+// one-element shift is made in registers (see the kernel).  Tiles, slices and the partial-sum layout are
+// those of the fp32 kernel above.
 struct GwB16Args {
     GeomBase g;
     int TJ, logTJ, TI, logTI, TB, TR, logPix;  // logPix = log2(TR * TJ)
@@ -1527,7 +1571,13 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
                                                                            const uint16_t* __restrict__ dy,
                                                                            float* __restrict__ part, GwB16Args a)
 {
-    constexpr int NN = N * N, TS = (NN + 3) / 4, CI_T = 32 * NC;
+    // n = 3, 4: a wave owns the taps of one tap row (its MFMA count is that of taps dealt one by one: 3 or 4 at
+    // most), because the taps of a row whose columns are of one parity read the same half row of dy, one element
+    // apart: one aligned 16-byte LDS read and the dword behind it give both, the second shifted in registers.
+    // (Read as they lie, half of the fragments were 16-byte reads at 2-byte alignment, twice the LDS time, and
+    // the LDS rate bounded the multiplication.)  n = 2: one tap per wave.
+    constexpr bool ROWS = N >= 3;
+    constexpr int NN = N * N, TS = ROWS ? N : 1, CI_T = 32 * NC;
     extern __shared__ __align__(16) unsigned char lds_b[];
     const GeomBase& g = a.g;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1546,14 +1596,10 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
     const int slice = bid;
     const int co0 = cot * 32, ci0 = cit * CI_T;
 
-    const int nts = (NN - wave + 3) / 4;   // taps of this wave: wave, wave + 4, ...
-    int tapoff[TS];
-#pragma unroll
-    for (int ts = 0; ts < TS; ++ts) {
-        const int t = wave + 4 * ts < NN ? wave + 4 * ts : 0;
-        const int ta = t / N, tc = t % N;
-        tapoff[ts] = (N - 1 - ta) * a.cols + ((N - 1 - tc) & 1) * a.HC + ((N - 1 - tc) >> 1);
-    }
+    // first element of the wave's tap row (n = 2: of its tap) in a channel's tile; tap column tc of the row is
+    // (N - 1 - tc) >> 1 elements into the half row of parity (N - 1 - tc) & 1
+    const int trow = ROWS ? wave : wave / N;
+    const int tapoff = (N - 1 - trow) * a.cols + (ROWS ? 0 : ((N - 1 - wave % N) & 1) * a.HC);
     f32x16 acc[TS][NC];
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts)
@@ -1668,41 +1714,56 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
         // K steps of 16 pixels along a row; pixels past the end of the row are zeros in x
         const int wj = g.W - j0 < a.TJ ? g.W - j0 : a.TJ;
         const int steps = (wj + 15) >> 4;
-        // the tap count of a wave is TS or TS - 1: one branch per stage picks a loop body whose
-        // taps are unrolled, so that all fragment reads of a step are in flight before its MFMAs
-        auto rows = [&](auto nts_tag) {
-            constexpr int NTS = decltype(nts_tag)::value;
-            for (int tr = 0; tr < a.TR; ++tr) {
-                const int bl = tr >> a.logTI, li = tr & (a.TI - 1);
-                if (b0 + bl >= g.B || i0 + li >= g.H) continue;  // uniform
-                const uint16_t* ap = dys + a_lane + (bl * a.LR + 2 * li) * a.cols;
-                const uint16_t* bp = xs + b_lane + tr * a.TJ;
-                for (int sp = 0; sp < steps; ++sp) {
-                    gw_bf16x8 bv[NC], av[NTS > 0 ? NTS : 1];
+        if (ROWS && wave >= N) continue;  // (n = 3: three tap rows)
+        for (int tr = 0; tr < a.TR; ++tr) {
+            const int bl = tr >> a.logTI, li = tr & (a.TI - 1);
+            if (b0 + bl >= g.B || i0 + li >= g.H) continue;  // uniform
+            const uint16_t* ap = dys + a_lane + (bl * a.LR + 2 * li) * a.cols + tapoff;
+            const uint16_t* bp = xs + b_lane + tr * a.TJ;
+            for (int sp = 0; sp < steps; ++sp) {
+                gw_bf16x8 bv[NC], av[TS];
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc)
+                    bv[nc] = *reinterpret_cast<const gw_bf16x8*>(bp + nc * 32 * a.XP + 16 * sp);
+                if constexpr (ROWS) {
+                    gw_u4 h[2];
+                    unsigned next[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        h[p] = *reinterpret_cast<const gw_u4*>(ap + p * a.HC + 16 * sp);
+                        if (p < N - 2) next[p] = *reinterpret_cast<const unsigned*>(ap + p * a.HC + 16 * sp + 8);
+                    }
+#pragma unroll
+                    for (int ts = 0; ts < TS; ++ts) {  // tap column ts
+                        const int p = (N - 1 - ts) & 1;
+                        if ((N - 1 - ts) >> 1) {
+                            const gw_u4 v = {__builtin_amdgcn_alignbit(h[p].y, h[p].x, 16),
+                                             __builtin_amdgcn_alignbit(h[p].z, h[p].y, 16),
+                                             __builtin_amdgcn_alignbit(h[p].w, h[p].z, 16),
+                                             __builtin_amdgcn_alignbit(next[p], h[p].w, 16)};
+                            av[ts] = __builtin_bit_cast(gw_bf16x8, v);
+                        } else {
+                            av[ts] = __builtin_bit_cast(gw_bf16x8, h[p]);
+                        }
+                    }
+                } else {
+                    av[0] = *reinterpret_cast<const gw_bf16x8*>(ap + 16 * sp);
+                }
+#pragma unroll
+                for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
                     for (int nc = 0; nc < NC; ++nc)
-                        bv[nc] = *reinterpret_cast<const gw_bf16x8*>(bp + nc * 32 * a.XP + 16 * sp);
-#pragma unroll
-                    for (int ts = 0; ts < NTS; ++ts)
-                        av[ts] = *reinterpret_cast<const gw_bf16x8u*>(ap + 16 * sp + tapoff[ts]);
-#pragma unroll
-                    for (int ts = 0; ts < NTS; ++ts)
-#pragma unroll
-                        for (int nc = 0; nc < NC; ++nc)
-                            acc[ts][nc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ts], bv[nc], acc[ts][nc], 0, 0, 0);
-                }
+                        acc[ts][nc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ts], bv[nc], acc[ts][nc], 0, 0, 0);
             }
-        };
-        if (nts == TS) rows(std::integral_constant<int, TS>{});
-        else rows(std::integral_constant<int, TS - 1>{});
+        }
     }
 
     // accumulator register i: output channel 8*(i/4) + 4*kk + (i%4) of the 32, input channel l32
     float* out = part + (size_t)slice * g.Cout * g.Cin * NN;
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {
-        if (ts >= nts) continue;
-        const int t = wave + 4 * ts;
+        if (ROWS && wave >= N) continue;
+        const int t = ROWS ? wave * N + ts : wave;
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
             const int ci = ci0 + nc * 32 + l32;
@@ -1791,9 +1852,7 @@ hipError_t launch_gw_b16(const GwB16Args& a, const void* x, const void* dy, floa
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(ukst_sum_taps_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, stream,
-                           (const float*)part, dw, (int)elems, a.nSlices, N * N, g.Cin);
-        e = hipGetLastError();
+        e = launch_sum_taps(g, (const float*)part, dw, elems, a.nSlices, stream);
     }
     return e;
 }
