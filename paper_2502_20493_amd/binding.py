@@ -175,18 +175,51 @@ def ukst_workspace_bytes(op: int, B, Cin, Cout, H, W, n, P, dtype) -> int:
     return int(lib().ukst_workspace_bytes(int(op), B, Cin, Cout, H, W, n, P, dtype))
 
 
+_raw_stream = None  # device index -> handle of torch's current stream there
+
+
+def _stream_handle(stream, device):
+    """Handle of the stream a call goes to.  None: torch's current stream on the device, read without
+    building a Stream object where torch offers that (a small call's launch takes 2 us, the object 1 us)."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+    if _raw_stream is None:
+        import torch
+
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _raw_stream(device.index)
+
+
+def _call(device, fn, *args):
+    """fn(*args) with `device` current (switched to only if it is not); raises on a status that is not ok."""
+    import torch
+
+    if torch.cuda.current_device() == device.index:
+        status = fn(*args)
+    else:
+        with torch.cuda.device(device):
+            status = fn(*args)
+    if status != UKST_OK:
+        _check(int(status))
+
+
 def _workspace(workspace, need: int, device, stream):
     """The (pointer, size) pair of a call.  workspace: None = allocate `need` bytes with torch for
     this call (torch supplies device memory; the library itself never allocates), False = pass
-    none, or a caller-provided uint8 device tensor."""
+    none, or a caller-provided uint8 device tensor.  stream: the caller's, None for the current one."""
     import torch
 
     if workspace is False or (workspace is None and need == 0):
         return None, 0, None
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=device)
+        # the block must outlive the work enqueued on `stream`; on the current stream, which it was
+        # allocated for, it is only handed on to later work of that stream anyway
         if hasattr(stream, "cuda_stream"):
-            workspace.record_stream(stream)  # the block must outlive the work enqueued on `stream`
+            workspace.record_stream(stream)
+        return workspace.data_ptr(), need, workspace
     if not (workspace.is_cuda and workspace.dtype == torch.uint8 and workspace.is_contiguous()):
         raise ValueError("workspace must be a contiguous uint8 device tensor")
     return workspace.data_ptr(), workspace.numel(), workspace
@@ -253,31 +286,30 @@ def ukst_conv_transpose2d(x, w, P: int, y=None, path: int = UKST_PATH_AUTO, stre
         raise ValueError("a bfloat16 output needs bfloat16 inputs")
     dtype = UKST_F32 if x.dtype == torch.float32 else (UKST_BF16_BF16 if out_bf16 else UKST_BF16_F32)
     ydt = torch.bfloat16 if out_bf16 else torch.float32
-    OH, OW = ukst_output_shape(H, W, n, P)
+    OH, OW = 2 * H + 2 * P - n, 2 * W + 2 * P - n
+    if OH < 1 or OW < 1:
+        ukst_output_shape(H, W, n, P)  # raises
+    device = x.device
     if y is None:
-        y = torch.empty((B, Cout, OH, OW), dtype=ydt, device=x.device)
+        y = torch.empty((B, Cout, OH, OW), dtype=ydt, device=device)
     elif (tuple(y.shape) != (B, Cout, OH, OW) or y.dtype != ydt
           or not y.is_contiguous() or not y.is_cuda):
         raise ValueError("y must be a contiguous device tensor [B,Cout,OH,OW], float32 or, for a "
                          "bfloat16 output, bfloat16")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
-    sp = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
-    with torch.cuda.device(x.device):
-        if workspace is not False:
-            need = ukst_workspace_bytes(UKST_OP_FORWARD, B, Cin, Cout, H, W, n, P, dtype)
-            wp, wb, _keep = _workspace(workspace, need, x.device, stream)
-            _check(int(lib().ukst_conv_transpose2d_ws(
-                x.data_ptr(), w.data_ptr(), None if _bias is None else _bias.data_ptr(),
-                y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype,
-                UKST_ACT_NONE if _act is None else int(_act), path, wp, wb, sp)))
-        elif _act is None:
-            _check(ukst_conv_transpose2d_raw(x.data_ptr(), w.data_ptr(), y.data_ptr(), B, Cin, Cout,
-                                             H, W, n, P, dtype, path, sp))
-        else:
-            _check(int(lib().ukst_conv_transpose2d_bias_act(
-                x.data_ptr(), w.data_ptr(), None if _bias is None else _bias.data_ptr(),
-                y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype, int(_act), path, sp)))
+    sp = _stream_handle(stream, device)
+    if workspace is not False:
+        need = ukst_workspace_bytes(UKST_OP_FORWARD, B, Cin, Cout, H, W, n, P, dtype)
+        wp, wb, _keep = _workspace(workspace, need, device, stream)
+        _call(device, lib().ukst_conv_transpose2d_ws, x.data_ptr(), w.data_ptr(),
+              None if _bias is None else _bias.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype,
+              UKST_ACT_NONE if _act is None else int(_act), path, wp, wb, sp)
+    elif _act is None:
+        _call(device, lib().ukst_conv_transpose2d_path, x.data_ptr(), w.data_ptr(), y.data_ptr(), B, Cin, Cout,
+              H, W, n, P, dtype, path, sp)
+    else:
+        _call(device, lib().ukst_conv_transpose2d_bias_act, x.data_ptr(), w.data_ptr(),
+              None if _bias is None else _bias.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype,
+              int(_act), path, sp)
     return y
 
 
@@ -295,6 +327,14 @@ def _backward_operands(p0, p1):
     if p0.dim() != 4 or p1.dim() != 4:
         raise ValueError("operands must be 4-D")
     return UKST_F32 if p0.dtype == torch.float32 else UKST_BF16_F32
+
+
+def _is_output(dy, H, W, n, P) -> bool:
+    """dy has the output's rows and columns; raises where the layer has no output."""
+    OH, OW = 2 * H + 2 * P - n, 2 * W + 2 * P - n
+    if H < 1 or W < 1 or n < 1 or P < 0 or OH < 1 or OW < 1:
+        ukst_output_shape(H, W, n, P)  # raises
+    return dy.shape[2] == OH and dy.shape[3] == OW
 
 
 def _out(t, shape, device):
@@ -318,17 +358,15 @@ def ukst_conv_transpose2d_grad_input(dy, w, H: int, W: int, P: int, dx=None, str
     dtype = _backward_operands(dy, w)
     B, Cout = dy.shape[:2]
     Cout2, Cin, n, n2 = w.shape
-    if Cout2 != Cout or n != n2 or tuple(dy.shape[2:]) != ukst_output_shape(H, W, n, P):
+    if Cout2 != Cout or n != n2 or not _is_output(dy, H, W, n, P):
         raise ValueError("expected dy[B,Cout,2H+2P-n,2W+2P-n] and w[Cout,Cin,n,n]")
-    dx = _out(dx, (B, Cin, H, W), dy.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(dy.device)
-    sp = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
-    with torch.cuda.device(dy.device):
-        need = ukst_workspace_bytes(UKST_OP_GRAD_INPUT, B, Cin, Cout, H, W, n, P, dtype)
-        wp, wb, _keep = _workspace(workspace, need, dy.device, stream)
-        _check(int(lib().ukst_conv_transpose2d_grad_input(dy.data_ptr(), w.data_ptr(), dx.data_ptr(),
-                                                          B, Cin, Cout, H, W, n, P, dtype, wp, wb, sp)))
+    device = dy.device
+    dx = _out(dx, (B, Cin, H, W), device)
+    sp = _stream_handle(stream, device)
+    need = ukst_workspace_bytes(UKST_OP_GRAD_INPUT, B, Cin, Cout, H, W, n, P, dtype)
+    wp, wb, _keep = _workspace(workspace, need, device, stream)
+    _call(device, lib().ukst_conv_transpose2d_grad_input, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), B, Cin, Cout,
+          H, W, n, P, dtype, wp, wb, sp)
     return dx
 
 
@@ -344,15 +382,12 @@ def ukst_conv_transpose2d_grad_weight_static(x, dy, n: int, P: int, dw, stream=N
     dtype = _backward_operands(x, dy)
     B, Cin, H, W = x.shape
     B2, Cout = dy.shape[:2]
-    if B2 != B or tuple(dy.shape[2:]) != ukst_output_shape(H, W, n, P):
+    if B2 != B or not _is_output(dy, H, W, n, P):
         raise ValueError("expected x[B,Cin,H,W] and dy[B,Cout,2H+2P-n,2W+2P-n]")
-    dw = _out(dw, (Cout, Cin, n, n), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
-    sp = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
-    with torch.cuda.device(x.device):
-        _check(int(lib().ukst_conv_transpose2d_grad_weight_static(
-            x.data_ptr(), dy.data_ptr(), dw.data_ptr(), B, Cin, Cout, H, W, n, P, dtype, sp)))
+    device = x.device
+    dw = _out(dw, (Cout, Cin, n, n), device)
+    _call(device, lib().ukst_conv_transpose2d_grad_weight_static, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), B, Cin,
+          Cout, H, W, n, P, dtype, _stream_handle(stream, device))
     return dw
 
 
@@ -366,17 +401,15 @@ def ukst_conv_transpose2d_grad_weight(x, dy, n: int, P: int, dw=None, stream=Non
     dtype = _backward_operands(x, dy)
     B, Cin, H, W = x.shape
     B2, Cout = dy.shape[:2]
-    if B2 != B or tuple(dy.shape[2:]) != ukst_output_shape(H, W, n, P):
+    if B2 != B or not _is_output(dy, H, W, n, P):
         raise ValueError("expected x[B,Cin,H,W] and dy[B,Cout,2H+2P-n,2W+2P-n]")
-    dw = _out(dw, (Cout, Cin, n, n), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
-    sp = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
-    with torch.cuda.device(x.device):
-        need = ukst_workspace_bytes(UKST_OP_GRAD_WEIGHT, B, Cin, Cout, H, W, n, P, dtype)
-        wp, wb, _keep = _workspace(workspace, need, x.device, stream)
-        _check(int(lib().ukst_conv_transpose2d_grad_weight(x.data_ptr(), dy.data_ptr(), dw.data_ptr(),
-                                                           B, Cin, Cout, H, W, n, P, dtype, wp, wb, sp)))
+    device = x.device
+    dw = _out(dw, (Cout, Cin, n, n), device)
+    sp = _stream_handle(stream, device)
+    need = ukst_workspace_bytes(UKST_OP_GRAD_WEIGHT, B, Cin, Cout, H, W, n, P, dtype)
+    wp, wb, _keep = _workspace(workspace, need, device, stream)
+    _call(device, lib().ukst_conv_transpose2d_grad_weight, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), B, Cin, Cout,
+          H, W, n, P, dtype, wp, wb, sp)
     return dw
 
 
@@ -412,13 +445,11 @@ def _general(fn, shape_fn, x, w, P, k, y, stream):
     B, Cin, H, W = x.shape
     Cout, _, n, _ = w.shape
     OH, OW = shape_fn(H, W, n, P, k)
-    y = _out(y, (B, Cout, OH, OW), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
-    sp = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+    device = x.device
+    y = _out(y, (B, Cout, OH, OW), device)
     dtype = UKST_F32 if x.dtype == torch.float32 else UKST_BF16_F32
-    with torch.cuda.device(x.device):
-        _check(int(fn(x.data_ptr(), w.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, k, dtype, sp)))
+    _call(device, fn, x.data_ptr(), w.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, k, dtype,
+          _stream_handle(stream, device))
     return y
 
 
