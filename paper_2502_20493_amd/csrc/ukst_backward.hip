@@ -1507,11 +1507,18 @@ hipError_t launch_gw_mfma(const GwMfmaArgs& a, const void* x, const void* dy, fl
     constexpr int NC = gw_nc(N);
     const GeomBase& g = a.g;
     const size_t elems = (size_t)g.Cout * g.Cin * N * N;
-    const size_t need = elems * a.nSlices * sizeof(float);  // one copy of dw per slice
+    // n = 3, 4 and rows of at least 16 pixels: on the bf16 pipe from bf16 parts, in no more copies of dw
+    const int parts = N <= 4 ? grad_weight_parts_slices(g, (int)sizeof(TIn), a.nSlices) : 0;
+    const int copies = parts ? parts : a.nSlices;
+    const size_t need = elems * copies * sizeof(float);  // one copy of dw per slice
     if (ws.query) { ws.need = need; return hipSuccess; }
     if (ws.bytes < need) return kWorkspaceTooSmall;
     float* part = (float*)ws.ptr;
     hipError_t e;
+    if (parts) {
+        e = launch_grad_weight_parts(g, x, dy, part, (int)sizeof(TIn), a.nSlices, stream);
+        return e != hipSuccess ? e : launch_sum_taps(g, (const float*)part, dw, elems, copies, stream);
+    }
     const size_t lds = (size_t)4 * (32 * NC * a.XP + 32 * a.DP);
     const void* kfn = (const void*)ukst_grad_weight_mfma_kernel<N, NC, TIn>;
     e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -201,6 +201,12 @@ hipError_t launch_grad_input_window(const Geom& g, const void* dy, const void* w
 bool grad_narrow_supported(const Geom& g, int dtype);
 hipError_t launch_grad_narrow(int which, const Geom& g, const void* p0, const void* p1, float* out, Workspace& ws,
                               hipStream_t stream);
+// Kernel gradient of wide layers from bf16 parts (n = 3, 4, rows of at least 16 pixels): the number of copies of dw,
+// laid out [co][tap][ci], that it writes to `part` (at most max_slices; 0: the layer is not for it).  es: 4 or 2,
+// bytes of an operand element
+int grad_weight_parts_slices(const GeomBase& g, int es, int max_slices);
+hipError_t launch_grad_weight_parts(const GeomBase& g, const void* x, const void* dy, float* part, int es,
+                                    int max_slices, hipStream_t stream);
 // which: 0 gradient w.r.t. the input, 1 w.r.t. the kernel
 const char* grad_kernel_name(const Geom& g, int which, int dtype);
 

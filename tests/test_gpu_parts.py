@@ -190,3 +190,64 @@ def test_slices_of_the_input_channels(shape):
         assert (err <= 1e-5 * S + 1.2e-7 * np.abs(y_ref)).all()
     one, two = (ukst.ukst_conv_transpose2d_ws(x, k, P) for _ in range(2))
     assert torch.equal(one, two)
+
+
+# B, Cin, Cout, H, W, n, P, dtype
+GRAD_WEIGHT_SHAPES = [
+    (2, 33, 34, 65, 63, 3, 0, "f32"),     # channel tails, odd rows, a second column tile of 31
+    (1, 40, 70, 96, 90, 4, 1, "f32"),     # tap rows in two halves, third column tile of 26
+    (40, 32, 33, 13, 17, 3, 2, "f32"),    # 17 of 32 columns, several images per slice
+    (33, 65, 32, 16, 16, 4, 2, "f32"),    # 16-column tiles, two rows per stage
+    (2, 33, 34, 65, 63, 4, 2, "bf16"),
+    (3, 40, 36, 64, 49, 3, 1, "bf16"),
+]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("shape", GRAD_WEIGHT_SHAPES)
+def test_kernel_gradient_from_parts(shape, integer):
+    from gpu_util import check_elements, run_gpu_grad_weight
+    w = _mk(shape)
+    print(f"case {shape} integer={integer}", flush=True)
+    data = wl.generate(w, integer=integer)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
+    ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
+    got = run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096)
+    check_elements(got, ref, S, TOL["f32"], exact=integer)
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "tiny"])
+def test_gradients_with_operands_that_three_parts_do_not_hold(what):
+    """An infinite or NaN gradient reaches the elements whose sums hold it, and no others; tiny ones keep their bits."""
+    import torch
+    import torch.nn.functional as F
+    B, Cin, Cout, H, W, n, P = 7, 33, 34, 61, 61, 3, 1
+    rng = np.random.default_rng(77)
+    x = rng.normal(size=(B, Cin, H, W)).astype(np.float32)
+    w = rng.normal(size=(Cout, Cin, n, n)).astype(np.float32)
+    OH, OW = oracle.out_shape(H, W, n, P)
+    dy = rng.normal(size=(B, Cout, OH, OW)).astype(np.float32)
+    scale = 1.0
+    if what == "tiny":
+        scale = 1e-33
+        dy *= np.float32(scale)
+    else:
+        dy[2, 5, 40, 7] = np.inf if what == "inf" else np.nan
+    xg, wg, dg = (torch.from_numpy(a).cuda() for a in (x, w, dy))
+    dx = ukst.ukst_conv_transpose2d_grad_input(dg, wg, H, W, P).cpu().double()
+    dw = ukst.ukst_conv_transpose2d_grad_weight(xg, dg, n, P).cpu().double()
+    x64, w64, d64 = (torch.from_numpy(a).double() for a in (x, w, dy))
+    rx = F.conv2d(d64, w64.flip(2, 3).transpose(0, 1).contiguous(), stride=2, padding=n - 1 - P)
+    padded = F.pad(d64, (n - 1, n - 1, n - 1, n - 1))
+    rw = torch.zeros(Cout, Cin, n, n, dtype=torch.float64)
+    for a in range(n):
+        for c in range(n):
+            d = padded[:, :, n - 1 + P - a:, n - 1 + P - c:][:, :, :2 * H:2, :2 * W:2][:, :, :H, :W]
+            # (finite factors first: an infinite one meets every input channel of its output channel)
+            rw[:, :, a, c] = d.transpose(0, 1).reshape(Cout, -1) @ x64.transpose(0, 1).reshape(Cin, -1).t()
+    # sums of up to 26047 products of factors below 6 (and dy's scale): 1e-5 of the sum of their magnitudes
+    for got, ref, terms in ((dx, rx, Cout * n * n), (dw, rw, B * H * W)):
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+        ok = torch.isfinite(ref)
+        assert (~ok).any() == (what != "tiny")
+        assert ((got - ref).abs()[ok] <= 1e-5 * terms * scale).all()
