@@ -777,6 +777,10 @@ hipError_t launch_gi_mfma(const GiMfmaArgs& a, const void* dy, const void* w, fl
     const size_t need = (pelems + (a.KS > 1 ? xelems * a.KS : 0)) * sizeof(float);
     if (ws.query) { ws.need = need; return hipSuccess; }
     if (ws.bytes < need) return kWorkspaceTooSmall;
+    if constexpr (sizeof(TIn) == 4) {
+        // on the bf16 pipe from bf16 parts (the workspace is asked for all the same and not used)
+        if (grad_input_parts_supported(g)) return launch_grad_input_parts(g, (const float*)dy, (const float*)w, dx, stream);
+    }
     float* wp = (float*)ws.ptr;
     hipError_t e;
     float* part = wp + pelems;

@@ -207,6 +207,9 @@ hipError_t launch_grad_narrow(int which, const Geom& g, const void* p0, const vo
 int grad_weight_parts_slices(const GeomBase& g, int es, int max_slices);
 hipError_t launch_grad_weight_parts(const GeomBase& g, const void* x, const void* dy, float* part, int es,
                                     int max_slices, hipStream_t stream);
+// Input gradient of wide fp32 layers with enough pixels from bf16 parts; no scratch
+bool grad_input_parts_supported(const GeomBase& g);
+hipError_t launch_grad_input_parts(const GeomBase& g, const float* dy, const float* w, float* dx, hipStream_t stream);
 // which: 0 gradient w.r.t. the input, 1 w.r.t. the kernel
 const char* grad_kernel_name(const Geom& g, int which, int dtype);
 

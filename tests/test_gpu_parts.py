@@ -201,6 +201,15 @@ GRAD_WEIGHT_SHAPES = [
     (2, 33, 34, 65, 63, 4, 2, "bf16"),
     (3, 40, 36, 64, 49, 3, 1, "bf16"),
 ]
+# from 100 tiles of 256 pixels on
+GRAD_INPUT_SHAPES = [
+    (3, 66, 17, 100, 90, 3, 1),           # eight waves, two channels of the second group, one channel past a stage
+    (7, 33, 20, 61, 61, 4, 0),            # four waves
+    (2, 40, 16, 128, 101, 5, 2),          # classes of 9, 6, 6 and 4 taps
+    (2, 35, 18, 120, 110, 2, 1),          # one tap per class
+    (2, 33, 16, 120, 110, 7, 9),          # P beyond the kernel
+    (420, 34, 16, 8, 8, 3, 0),            # four images per tile
+]
 
 
 @pytest.mark.parametrize("integer", [True, False])
@@ -213,6 +222,19 @@ def test_kernel_gradient_from_parts(shape, integer):
     dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
     ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
     got = run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096)
+    check_elements(got, ref, S, TOL["f32"], exact=integer)
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("shape", GRAD_INPUT_SHAPES)
+def test_input_gradient_from_parts(shape, integer):
+    from gpu_util import check_elements, run_gpu_grad_input
+    w = _mk(shape + ("f32",))
+    print(f"case {shape} integer={integer}", flush=True)
+    data = wl.generate(w, integer=integer)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
+    ref, S = oracle.grad_input(dyd["dy"], data["w"], w.H, w.W, w.P)
+    got = run_gpu_grad_input(data, dyd, w.dtype, w.H, w.W, w.P, guard=4096)
     check_elements(got, ref, S, TOL["f32"], exact=integer)
 
 
