@@ -36,7 +36,10 @@ extern "C" {
 
 /* Element types.  Accumulation is always fp32. */
 typedef enum {
-    UKST_F32 = 0,      /* x, w, y are IEEE fp32 */
+    UKST_F32 = 0,      /* x, w, y are IEEE fp32.  Wide layers multiply three exact bf16 parts of every value
+                          (six products, fp32 sums) on the bf16 matrix pipe: errors are no larger than on
+                          the fp32 pipe, and infinities, NaN, huge and tiny operands behave as in fp32
+                          arithmetic (a tile that meets one is computed again with fp32 multiply-adds) */
     UKST_BF16_F32 = 1, /* x, w are bfloat16 (upper half of an fp32), y is fp32, stored unrounded */
     UKST_BF16_BF16 = 2 /* x, w, y are bfloat16: the fp32 sum (after the fused epilogue, if any) is
                           rounded once, to nearest even, at the store; halves the output traffic */
@@ -112,8 +115,8 @@ int ukst_select_path(int B, int Cin, int Cout, int H, int W, int n, int P, int d
  *
  * Only element alignment is required (4 bytes fp32, 2 bytes bf16, for y too; UKST_ERR_UNSUPPORTED
  * otherwise).
- * The matrix-core kernels additionally want w (and x, for bf16 and for fp32 layers with at most 4
- * output channels) aligned to 16 bytes: when they are not, ukst_conv_transpose2d uses the vector-ALU kernels instead.  The caller owns all buffers;
+ * Most matrix-core kernels additionally want w (and x, for bf16 and for fp32 layers with at most 4
+ * output channels) aligned to 16 bytes: when they are not, ukst_conv_transpose2d uses another kernel instead.  The caller owns all buffers;
  * the call enqueues work on `stream` and returns without synchronising.  Arguments are validated
  * on the host before anything touches the GPU; on a validation error nothing is launched.  A
  * failing launch is reported as UKST_ERR_LAUNCH.  This entry point (like the two below it) takes
@@ -157,13 +160,14 @@ typedef enum { UKST_OP_FORWARD = 0, UKST_OP_GRAD_INPUT = 1, UKST_OP_GRAD_WEIGHT 
 /*
  * Bytes of scratch memory the given operation uses on this problem (host arithmetic only, a
  * function of the arguments alone; 0 if the operation needs none, or on invalid arguments).
- *   UKST_OP_FORWARD      layers with fewer output tiles than compute units on the fp32
- *                        matrix-core path divide the input channels of a tile among 2, 4 or 8
- *                        blocks; each slice writes its partial sums to its own copy of y in the
- *                        workspace and a second kernel adds the copies in slice order.
+ *   UKST_OP_FORWARD      fp32 matrix-core layers with fewer output tiles than compute units divide
+ *                        the input channels of a tile among several blocks; each slice writes its
+ *                        partial sums to its own copy of y in the workspace and a second kernel
+ *                        adds the copies in slice order.
  *   UKST_OP_GRAD_INPUT   matrix-core kernels (Cin >= 32, Cout >= 16): the weights re-packed once
  *                        per call, plus, for layers with few pixels, one copy of dx per slice of
- *                        the sum over output channels (added in slice order).
+ *                        the sum over output channels (added in slice order).  Asked for also where
+ *                        the layer runs on a kernel that leaves it untouched.
  *   UKST_OP_GRAD_WEIGHT  one copy of dw per slice of the sum over batch and space (added in a
  *                        fixed order); every kernel of this operation needs it.
  * The workspace is caller-owned DEVICE memory, 256-byte aligned, needs no initialisation, holds
@@ -181,7 +185,8 @@ size_t ukst_workspace_bytes(int op, int B, int Cin, int Cout, int H, int W, int 
  * ukst_conv_transpose2d_bias_act: layers that would split their input channels keep the whole sum
  * in one block per tile instead (same result up to fp32 summation order, fewer blocks).  With a
  * workspace smaller than ukst_workspace_bytes(UKST_OP_FORWARD, ...) for a layer that uses one the
- * call returns UKST_ERR_WORKSPACE and launches nothing.  Results are bit-reproducible either way.
+ * call keeps the whole sum in one block per tile or, for layers whose fp32 tiles are 64 channels
+ * wide, returns UKST_ERR_WORKSPACE and launches nothing.  Results are bit-reproducible either way.
  */
 int ukst_conv_transpose2d_ws(const void* x, const void* w, const float* bias, void* y, int B, int Cin,
                              int Cout, int H, int W, int n, int P, int dtype, int act, int path,
@@ -246,12 +251,16 @@ size_t ukst_static_workspace_bytes(void);
  * Cout a multiple of 8, W >= 16 -- bf16 MFMA with an output channel's 16 taps as the contraction;
  * "ukst_grad_input_mfma_bf16_kernel": bf16 MFMA for other bf16 operands where its LDS tile fits,
  * i.e. kernel sides up to about 5;
- * "ukst_grad_input_mfma_kernel": fp32 MFMA otherwise; weights packed once per call into the
- * workspace, which also holds the copies of dx when the sum over output channels is split),
+ * "ukst_grad_input_mfma_kernel": otherwise; fp32 layers with enough pixels run the instance
+ * ukst_grad_input_mfma_kernel_parts, bf16 MFMA on three exact bf16 parts of every operand, the rest
+ * fp32 MFMA: weights packed once per call into the workspace, which also holds the copies of dx
+ * when the sum over output channels is split),
  * layers with Cin, Cout >= 32 run the kernel gradient there too
  * ("ukst_grad_weight_mfma_bf16_kernel": bf16 MFMA with the pixel axis as the contraction, for bf16
  * operands with kernel sides 2 to 4, W a multiple of 8 and at least 16;
- * "ukst_grad_weight_mfma_kernel": fp32 MFMA for everything else of that width, either dtype).
+ * "ukst_grad_weight_mfma_kernel": everything else of that width, either dtype;
+ * ukst_grad_weight_mfma_kernel_parts, bf16 MFMA on bf16 parts, for n = 3, 4 and rows of at least 16
+ * pixels on layers with enough of them, fp32 MFMA for the rest).
  * Layers with at most 4 output channels, Cout * n * n <= 64 and Cin >= 16 run the kernel gradient
  * as "ukst_grad_weight_thin_mfma_kernel" (fp32 MFMA whose rows are (channel, tap) pairs).
  * Narrow fp32 layers (Cin, Cout <= 4, 2 <= n <= 5, W >= 32) run both gradients as
@@ -264,7 +273,8 @@ const char* ukst_grad_kernel_name(int which, int B, int Cin, int Cout, int H, in
 /*
  * The two generalisations the paper's discussion (Sec. 5) points to.  Both use the computation
  * pattern of Algorithm 2 -- every output pixel selects, from its own coordinates, the taps that
- * can meet data, and no inserted zero is ever multiplied -- in one general vector-ALU kernel.
+ * can meet data, and no inserted zero is ever multiplied -- in one general vector-ALU kernel, and on
+ * the matrix cores ("ukst_general_mfma_kernel") for layers of at least 16 input and 8 output channels.
  *
  * ukst_conv_transpose2d_strided: transpose convolution with stride s (Algorithm 1 with s-1 zeros
  * between neighbouring pixels; s = 2 is ukst_conv_transpose2d).  s*s parity classes: output row oy

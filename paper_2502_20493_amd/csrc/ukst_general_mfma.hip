@@ -23,7 +23,7 @@ namespace ukst {
 namespace {
 
 constexpr int KC = 16, TN = 256, T = 256;
-constexpr int LDS_LIMIT = 160 * 1024;
+constexpr int LDS_LIMIT = 160 * 1024 - 256;  // (256 bytes belong to __syncthreads_or)
 
 struct ConvArgs {
     int B, Cin, Cout, H, W, n, P, k, OH, OW;
@@ -239,7 +239,7 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
         to_parts<PARTS>(wr, p, seen);
         if constexpr (PARTS == 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) seen.see(p[0][i]);
+            for (int i = 0; i < 4; ++i) seen.see_parts(p[0][i]);
         }
 #pragma unroll
         for (int i = 0; i < PARTS; ++i) *reinterpret_cast<u4v_t*>(lds + buf * WBUF + i * WPL + w_loff) = p[i];

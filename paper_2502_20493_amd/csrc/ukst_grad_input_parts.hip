@@ -21,7 +21,7 @@ namespace ukst {
 namespace {
 
 constexpr int KC = 16, TN = 256;
-constexpr int LDS_LIMIT = 160 * 1024;
+constexpr int LDS_LIMIT = 160 * 1024 - 256;  // (256 bytes belong to __syncthreads_or)
 
 struct GiPartsArgs {
     int B, Cin, Cout, H, W, n, P, OH, OW;

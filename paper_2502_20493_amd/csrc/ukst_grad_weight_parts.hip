@@ -62,7 +62,10 @@ template <int PARTS>
 __device__ __forceinline__ void pair_parts(unsigned a, unsigned b, unsigned (&p)[PARTS], PartRange& seen)
 {
     if constexpr (PARTS == 3) split_pair(__uint_as_float(a), __uint_as_float(b), p[0], p[1], p[2], seen);
-    else p[0] = a | (b << 16);
+    else {
+        p[0] = a | (b << 16);
+        seen.see_parts(p[0]);
+    }
 }
 
 template <int N, typename TIn>
@@ -261,9 +264,10 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
     }
 
     float* out = part + (size_t)slice * g.Cout * g.Cin * NN;
-    const bool bad = PARTS == 3 && __syncthreads_or(seen.bad() ? 1 : 0);  // (also: every wave is done with the tiles)
-    if (bad) {
-        // an operand whose parts do not hold it: this block's sums again, in fp32 throughout
+    // (also: every wave is done with the tiles)
+    if (__syncthreads_or((PARTS == 3 ? seen.bad() : seen.not_finite()) ? 1 : 0)) {
+        // an operand whose parts do not hold it, or that must not meet the zeros past a row's end: this block's
+        // sums again, in fp32 throughout
         for (int e = tid; e < 32 * CI_T * NN; e += 256) {
             const int ci = ci0 + e % CI_T, r = e / CI_T, tap = r % NN, co = co0 + r / NN;
             if (ci >= g.Cin || co >= g.Cout) continue;
@@ -290,7 +294,6 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
         return;
     }
     if constexpr (KHALF) {
-        if constexpr (PARTS == 1) __syncthreads();
         float* const lf = reinterpret_cast<float*>(lds);  // [wc][tap][register][lane]
         if (wh == 1) {
 #pragma unroll

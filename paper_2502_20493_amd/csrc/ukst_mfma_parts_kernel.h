@@ -22,7 +22,7 @@ namespace ukst {
 namespace parts {
 
 constexpr int KC = 16;  // input channels per stage (one MFMA K step)
-constexpr int LDS_LIMIT = 160 * 1024;
+constexpr int LDS_LIMIT = 160 * 1024 - 256;  // (256 bytes belong to __syncthreads_or)
 
 struct PartsArgs {
     GeomBase g;
@@ -127,7 +127,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     // ---- staging units.  Activations: (channel half, row, PX columns), columns fastest; the last unit of a
     // row whose length is no multiple of PX starts inside its neighbour
     unsigned x_goff[XU];
-    int x_loff[XU], x_ci[XU];
+    int x_loff[XU];
 #pragma unroll
     for (int j = 0; j < XU; ++j) {
         const int e = tid + T * j;
@@ -136,7 +136,6 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         const int row = fdiv(rem, a.dW), c = rem - row * a.CPR;
         const int col = PX * c + PX <= g.W ? PX * c : g.W - PX;
         x_goff[j] = kNoByte;
-        x_ci[j] = 8 * h;
         x_loff[j] = -1;
         if (h < 2) {
             const int er = e_first + row;
@@ -150,10 +149,9 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     // piece j / WCG), every unit exists; channels past the last output channel lie past the end of w and
     // arrive as zeros.  One part: unit tid + T*j = (output channel, eight input channels, piece), piece
     // fastest; units that do not exist read nothing and write to a pad slot.
-    int w_goff[PARTS == 3 ? 1 : WU], w_loff[PARTS == 3 ? 1 : WU], w_ci[PARTS == 3 ? 1 : WU];
+    int w_goff[PARTS == 3 ? 1 : WU], w_loff[PARTS == 3 ? 1 : WU];
     if constexpr (PARTS == 3) {
         const int cg = tid % UPC, co = tid / UPC;
-        w_ci[0] = UK * cg;
         w_goff[0] = (((co0 + co) * g.Cin + UK * cg) * NN) * ES;
         w_loff[0] = (UK * cg >> 3) * WHS + co * 16 + (UK * cg & 7) * 2;
         if (TM * UPC < T && co >= TM) w_goff[0] = (int)kNoByte;  // (TM = 32 on 8 waves)
@@ -164,7 +162,6 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             const int e = tid + T * j;
             const int t = e / pieces, tap = piece_at(NN, e - t * pieces);
             const int cg = t % UPC, co = t / UPC;
-            w_ci[j] = UK * cg;
             w_goff[j] = co < TM && co0 + co < g.Cout ? (((co0 + co) * g.Cin + UK * cg) * NN + tap) * ES : (int)kNoByte;
             w_loff[j] = co < TM ? cg * WHS + tap * WTS + co * 16 : -1;
         }
@@ -218,7 +215,10 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         for (int j = 0; j < w_units(sub); ++j)
 #pragma unroll
             for (int k = 0; k < UK; ++k) {
-                const bool in = s * KC + w_ci[PARTS == 3 ? 0 : j] + k < g.Cin;
+                int e = tid + (PARTS == 3 ? 0 : T * j);
+                asm("" : "+v"(e));
+                const int cg = PARTS == 3 ? e % UPC : e / sub_pieces(N, 1, 0) % UPC;
+                const bool in = s * KC + UK * cg + k < g.Cin;
 #pragma unroll
                 for (int i = 0; i < WD; ++i) wr[j][k][i] = in ? wr[j][k][i] : 0u;
             }
@@ -248,13 +248,17 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     auto trim_x = [&](int s) {
         if (s * KC + KC <= g.Cin) return;
 #pragma unroll
-        for (int j = 0; j < XU; ++j)
+        for (int j = 0; j < XU; ++j) {
+            int e = tid + T * j;
+            asm("" : "+v"(e));  // (worked out here, once per call, and not kept across the loop: registers are short)
+            const int h = fdiv(e, a.dRW);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const bool in = s * KC + x_ci[j] + k < g.Cin;
+                const bool in = s * KC + 8 * h + k < g.Cin;
 #pragma unroll
                 for (int i = 0; i < XD; ++i) xr[j][k][i] = in ? xr[j][k][i] : 0u;
             }
+        }
     };
     auto pack_x = [&](int i) {  // items 0 .. 4*XU - 1
         const int j = i >> 2, q = i & 3;

@@ -10,6 +10,8 @@
 // The parts hold what the value holds only while no part under- or overflows: operands that are
 // infinite, NaN, at least 2^62 or below 2^-100 (but not 0) are noticed while they are staged, and the
 // block that met one computes its tile again with fp32 multiply-adds.
+// (128 -> 128 channels, 64 x 64, n = 5: 574 us; 530 with the minimum of the leading parts, which counts
+// values below 2^-134 as 0 and is not used for that; 580 with a class test per value.)
 #pragma once
 #include "ukst_internal.h"
 
@@ -25,20 +27,27 @@ typedef unsigned short us2_t __attribute__((ext_vector_type(2)));
 constexpr int kRawBuffer = 0x00020000;        // raw 32-bit buffer, gfx9 family
 constexpr unsigned kNoByte = 0xFFFFFF00u;     // byte offset that is out of range for any buffer
 
-// Largest and smallest non-zero leading part seen by a thread, as bf16 magnitudes (two lanes of 16 bits).
+// What a thread has staged: the largest leading part (two lanes of 16 bits) and the smallest fp32 magnitude but 0 (its
+// bits without the sign, less 1, so that zeros wrap around to the top).  The smallest is taken from the values and
+// not from the leading parts: a value below 2^-134 has leading part 0 and would be lost among the zeros.
 struct PartRange {
     us2_t hi = {0, 0};
-    us2_t lo = {0xFFFF, 0xFFFF};  // of magnitude - 1: zeros wrap around to the top
-    __device__ __forceinline__ void see(unsigned p0)
+    unsigned lo = 0xFFFFFFFFu;
+    __device__ __forceinline__ void see_parts(unsigned p0)
     {
-        const us2_t m = __builtin_bit_cast(us2_t, p0 & 0x7FFF7FFFu);
-        hi = __builtin_elementwise_max(hi, m);
-        lo = __builtin_elementwise_min(lo, (us2_t)(m - (us2_t){1, 1}));
+        hi = __builtin_elementwise_max(hi, __builtin_bit_cast(us2_t, p0 & 0x7FFF7FFFu));
+    }
+    __device__ __forceinline__ void see_values(float a, float b)
+    {
+        const unsigned ua = (__float_as_uint(a) << 1) - 1u, ub = (__float_as_uint(b) << 1) - 1u;
+        const unsigned m = ua < ub ? ua : ub;
+        lo = lo < m ? lo : m;
     }
     __device__ __forceinline__ bool bad() const
     {
-        constexpr unsigned short top = (127 + 62) << 7, bottom = (127 - 100) << 7;
-        return hi.x >= top || hi.y >= top || lo.x + 1 < bottom || lo.y + 1 < bottom;
+        constexpr unsigned short top = (127 + 62) << 7;
+        constexpr unsigned bottom = ((unsigned)(127 - 100) << 24) - 1u;
+        return hi.x >= top || hi.y >= top || lo < bottom;
     }
     // an infinity or NaN alone (operands that are bf16 already)
     __device__ __forceinline__ bool not_finite() const { return hi.x >= 0x7F80 || hi.y >= 0x7F80; }
@@ -54,8 +63,9 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2,
                                            PartRange& seen)
 {
+    seen.see_values(a, b);
     p0 = pack_bf16(a, b);
-    seen.see(p0);
+    seen.see_parts(p0);
     a -= __uint_as_float(p0 << 16);
     b -= __uint_as_float(p0 & 0xFFFF0000u);
     p1 = pack_bf16(a, b);
