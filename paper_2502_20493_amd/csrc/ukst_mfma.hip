@@ -540,7 +540,7 @@ static bool bf16_pipe(const Geom& g, int dtype)
 
 // Where the kernel on bf16 parts (ukst_mfma_parts_kernel.h) runs instead of the fp32 pipe or the vector
 // ALUs, in tiles of 64 channels x 256 quads.  Large layers gain whatever they are: fp32 128 -> 128 channels
-// on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 235, 601 -> 355, 872 -> 526 us; bf16 operands with
+// on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 231, 601 -> 346, 872 -> 580 us; bf16 operands with
 // n = 5 861 -> 191 us.  Small ones do not, because a tile is one block's serial work: fp32 at 64 tiles (64
 // images of 128 -> 64 channels, 16 x 16, n = 4) 49.4 against 49.2 us, at 132 tiles 97.6 against 57.1; n = 5 at
 // 66 and 132 tiles 72 against 121 and 141 against 132; bf16 operands at 5 and 17 tiles 31 against 65 and 45
