@@ -344,6 +344,12 @@ bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
     // slices a stage or two: 2 images of 16 x 16 19 against 23 us, 4 of 20 x 33 36 against 39, 64 of 16 x 16 with
     // n = 4 77 against 49
     if ((long long)g.B * g.H * g.W < 8192) return false;
+    // fp32: rows that fill less than 5/8 of their column tiles multiply too many zeros (64 images of 17 x 17,
+    // 128 -> 128 channels, n = 3 / 4: 111 / 157 us on the fp32 pipe against 112 / 163; 32 of 33 x 33, 64 -> 64, n = 3
+    // 82 against 85; 64 of 18 x 18 115 / 162 against 117 / 171; 40 of 31 x 31, n = 3 167 against 128;
+    // 64 of 20 x 20 130 / 186 against 124 / 184)
+    const int tiled_cols = g.W > 16 ? (g.W + 31) / 32 * 32 : 16;
+    if (es == 4 && g.W * 8 < tiled_cols * 5) return false;
     // single buffer descriptors, 32-bit byte offsets
     if ((size_t)g.B * g.Cin * g.H * g.W * es > 0x7FFFFFF0u || (size_t)g.B * g.Cout * g.OH * g.OW * es > 0x7FFFFFF0u)
         return false;
