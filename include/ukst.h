@@ -39,7 +39,8 @@ typedef enum {
     UKST_F32 = 0,      /* x, w, y are IEEE fp32.  Wide layers multiply three exact bf16 parts of every value
                           (six products, fp32 sums) on the bf16 matrix pipe: errors are no larger than on
                           the fp32 pipe, and infinities, NaN, huge and tiny operands behave as in fp32
-                          arithmetic (a tile that meets one is computed again with fp32 multiply-adds) */
+                          arithmetic (sums that hold an infinity, a NaN or partial sums beyond 1e24 are
+                          taken again in fp32: the same results, in a few times the time) */
     UKST_BF16_F32 = 1, /* x, w are bfloat16 (upper half of an fp32), y is fp32, stored unrounded */
     UKST_BF16_BF16 = 2 /* x, w, y are bfloat16: the fp32 sum (after the fused epilogue, if any) is
                           rounded once, to nearest even, at the store; halves the output traffic */

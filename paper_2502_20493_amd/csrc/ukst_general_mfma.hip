@@ -167,7 +167,6 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
     const int w_loff = w_h * WHS + w_t * WTS + w_co * 16;
 
     unsigned xr[XU][8][PARTS == 3 ? 1 : 2], wr[8];
-    PartRange seen;
     auto load_x = [&](int s) {
 #pragma unroll
         for (int j = 0; j < XU; ++j)
@@ -200,7 +199,7 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = xr[j][k][0];
                 u4v_t p[3];
-                to_parts<3>(v, p, seen);
+                to_parts<3>(v, p);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) *reinterpret_cast<u4v_t*>(lds + i * XPL + x_loff[j]) = p[i];
             } else {
@@ -236,11 +235,7 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
             for (int k = 0; k < 8; ++k) wr[k] = s * KC + 8 * w_h + k < a.Cin ? wr[k] : 0u;
         }
         u4v_t p[PARTS];
-        to_parts<PARTS>(wr, p, seen);
-        if constexpr (PARTS == 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) seen.see_parts(p[0][i]);
-        }
+        to_parts<PARTS>(wr, p);
 #pragma unroll
         for (int i = 0; i < PARTS; ++i) *reinterpret_cast<u4v_t*>(lds + buf * WBUF + i * WPL + w_loff) = p[i];
     };
@@ -320,41 +315,6 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
         }
     }
 
-    if (__syncthreads_or((PARTS == 3 ? seen.bad() : seen.not_finite()) ? 1 : 0)) {
-        // an operand whose parts do not hold it, or a weight that must not meet the zeros of the halo: this
-        // block's outputs again, in fp32 throughout
-        for (int e = tid; e < TN * (TM / 8); e += T) {
-            const int q = q0 + e % TN, cbase = co0 + e / TN * 8;
-            if (q > q_last) continue;
-            const int b = small_div(q, IJ, rIJ), rem = q - b * IJ;
-            const int i0 = small_div(rem, g.NJ, rNJ), j0 = rem - i0 * g.NJ;
-            float sum[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sum[k] = 0.f;
-            for (int ci = 0; ci < a.Cin; ++ci)
-                for (int u = 0; u < g.Tr; ++u) {
-                    const int i = i0 + g.rb + u * g.xs;
-                    if (i < 0 || i >= a.H) continue;
-                    for (int v = 0; v < g.Tc; ++v) {
-                        const int j = j0 + g.cb + v * g.xs;
-                        if (j < 0 || j >= a.W) continue;
-                        const float xv = element_f32(x[(((size_t)b * a.Cin + ci) * a.H + i) * a.W + j]);
-                        const int t = (g.r + u * g.ws) * a.n + g.c + v * g.ws;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const int ch = cbase + k < a.Cout ? cbase + k : a.Cout - 1;
-                            sum[k] = fmaf(xv, element_f32(w[((size_t)ch * a.Cin + ci) * NN + t]), sum[k]);
-                        }
-                    }
-                }
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (cbase + k < a.Cout)
-                    y[(((size_t)b * a.Cout + cbase + k) * a.OH + g.oy0 + i0 * g.os) * a.OW + g.ox0 + j0 * g.os] = sum[k];
-        }
-        return;
-    }
-
     // accumulator register i of a tile holds channel 8*(i/4) + 4*gk + (i%4), for the lane's pixel
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
         (void*)y, 0, (int)((size_t)a.B * a.Cout * a.OH * a.OW * 4), kRawBuffer);
@@ -372,10 +332,101 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int ch = 32 * m + 8 * (e / 4) + (e % 4);
-                const float val = acc[m][nt][e];  // by value, then bits
+                const float val = PARTS == 3 ? acc[m][nt][e] * kPartsDown : acc[m][nt][e];
                 const bool on = q <= q_last && co0 + 4 * gk + ch < a.Cout;
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), rs_y, on ? off : kNoByte, (unsigned)ch * plane, 0);
             }
+    }
+
+    // tiles that hold a sum that is not finite (ukst_parts.h)
+    unsigned tiles = 0u;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            if (!wave_finite(acc[m][nt])) tiles |= 1u << (2 * m + nt);
+    if (!__syncthreads_or(tiles != 0u ? 1 : 0)) return;
+    if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
+    __syncthreads();
+    const unsigned w_cstride = (unsigned)(NN * ES);
+    const size_t pixels = (size_t)a.OH * a.OW;
+    // group: (four channels, pixel) of the block's outputs
+#pragma unroll 1
+    for (int m = 0; m < MT; ++m) {
+        if ((tiles >> (2 * m) & 3) == 0u) continue;
+        const int ch = co0 + 32 * m + l32 < a.Cout ? co0 + 32 * m + l32 : a.Cout - 1;
+        bool on[2], halo[2];
+        int b[2], i0[2], j0[2];
+        f32x16_t sum[2];
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const int ql = q0 + (wave * 2 + nt) * 32 + l32;
+            on[nt] = ql <= q_last;
+            halo[nt] = false;
+            const int q = on[nt] ? ql : q_last;
+            b[nt] = small_div(q, IJ, rIJ);
+            const int rem = q - b[nt] * IJ;
+            i0[nt] = small_div(rem, g.NJ, rNJ);
+            j0[nt] = rem - i0[nt] * g.NJ;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[nt][i] = 0.f;
+        }
+        for (int u = 0; u < g.Tr; ++u)
+            for (int v = 0; v < g.Tc; ++v) {
+                unsigned xo[2];
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    const int i = i0[nt] + g.rb + u * g.xs, j = j0[nt] + g.cb + v * g.xs;
+                    const bool in = on[nt] && i >= 0 && i < a.H && j >= 0 && j < a.W;
+                    halo[nt] = halo[nt] || !in;
+                    xo[nt] = in ? (unsigned)(((b[nt] * a.Cin * a.H + i) * a.W + j) * ES) : kNoByte;
+                }
+                sum_tiles<TIn>(sum, rs_w, (unsigned)((ch * a.Cin * NN + (g.r + u * g.ws) * a.n + g.c + v * g.ws) * ES),
+                               w_cstride, rs_x, xo, x_cstride, 0, a.Cin);
+            }
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            if (!(tiles >> (2 * m + nt) & 1) || !on[nt]) continue;
+            float* const out =
+                y + ((size_t)b[nt] * a.Cout * a.OH + g.oy0 + i0[nt] * g.os) * a.OW + g.ox0 + j0[nt] * g.os;
+            put_tile(
+                lds, sum[nt], halo[nt],
+                [&](int i, float v) {
+                    const int c = co0 + 32 * m + 8 * (i / 4) + 4 * gk + i % 4;
+                    if (c < a.Cout) out[c * pixels] = v;
+                },
+                [&](int i) { return (8 * m + 2 * i + gk) * TN + (wave * 2 + nt) * 32 + l32; });
+        }
+    }
+    __threadfence();  // what was stored lies in memory before it is stored again
+    __syncthreads();
+    const int listed = *reinterpret_cast<const int*>(lds);
+    for (int e = tid; e < listed; e += T) {
+        const int group = reinterpret_cast<const unsigned short*>(lds + 16)[e];
+        const int q = q0 + group % TN, cbase = co0 + group / TN * 4;
+        if (cbase >= a.Cout) continue;
+        const int b = small_div(q, IJ, rIJ), rem = q - b * IJ;
+        const int i0 = small_div(rem, g.NJ, rNJ), j0 = rem - i0 * g.NJ;
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < g.Tr; ++u) {
+            const int i = i0 + g.rb + u * g.xs;
+            if (i < 0 || i >= a.H) continue;
+            for (int v = 0; v < g.Tc; ++v) {
+                const int j = j0 + g.cb + v * g.xs;
+                if (j < 0 || j >= a.W) continue;
+                unsigned wo[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    wo[k] = (unsigned)(((cbase + k < a.Cout ? cbase + k : a.Cout - 1) * a.Cin * NN +
+                                        (g.r + u * g.ws) * a.n + g.c + v * g.ws) * ES);
+                sum_products<TIn>(sum, rs_x, (unsigned)(((b * a.Cin * a.H + i) * a.W + j) * ES), x_cstride, rs_w, wo,
+                                  w_cstride, 0, a.Cin);
+            }
+        }
+        float* const out = y + ((size_t)b * a.Cout * a.OH + g.oy0 + i0 * g.os) * a.OW + g.ox0 + j0 * g.os;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (cbase + k < a.Cout) out[(cbase + k) * pixels] = sum[k];
     }
 }
 
@@ -415,6 +466,7 @@ bool make_plan(ConvArgs a, int es, ConvPlan& p)
     else p.xu = per <= 1 ? 1 : per <= 2 ? 2 : 4;
     if (per > p.xu) return false;
     p.lds = 2 * (size_t)parts * 4 * (32 * p.mt + 4) * 16 + (size_t)parts * a.XPL;
+    if (p.lds < redo_bytes(TN * 8 * p.mt)) p.lds = redo_bytes(TN * 8 * p.mt);
     if (p.lds > LDS_LIMIT) return false;
     a.nqt = (int)((qmax + TN - 1) / TN);
     const long long nb = (long long)a.nqt * a.nco * a.classes;

@@ -101,7 +101,6 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
 
     const int stages = (a.Cout + KC - 1) / KC;
     unsigned xr[XU][8], wr[8];
-    PartRange seen;
     // a group of two taps: stage of 16 channels, class, group of the class
     struct At { int s, cls, grp; };
     auto next = [&](At t) {
@@ -134,7 +133,7 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
                     xr[j][k] = t.s * KC + (x_ij[j] < 0 ? 8 : 0) + k < a.Cout ? xr[j][k] : 0u;
             }
             u4v_t p[3];
-            to_parts<3>(xr[j], p, seen);
+            to_parts<3>(xr[j], p);
             if (x_loff[j] < 0) continue;
 #pragma unroll
             for (int i = 0; i < 3; ++i) *reinterpret_cast<u4v_t*>(lds + i * XPL + x_loff[j]) = p[i];
@@ -158,7 +157,7 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
             for (int k = 0; k < 8; ++k) wr[k] = t.s * KC + 8 * w_h + k < a.Cout ? wr[k] : 0u;
         }
         u4v_t p[3];
-        to_parts<3>(wr, p, seen);
+        to_parts<3>(wr, p);
 #pragma unroll
         for (int i = 0; i < 3; ++i) *reinterpret_cast<u4v_t*>(lds + buf * WBUF + i * WPL + w_loff) = p[i];
     };
@@ -238,29 +237,6 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
         n1 = n2;
     }
 
-    if (__syncthreads_or(seen.bad() ? 1 : 0)) {
-        // an operand whose parts do not hold it: this block's outputs again, in fp32 throughout
-        for (int e = tid; e < TN * TM; e += T) {
-            const int q = q0 + e % TN, ci = ci0 + e / TN;
-            if (q > q_last || ci >= a.Cin) continue;
-            const int b = fdiv(q, a.dHW), rem = q - b * HW;
-            const int i = fdiv(rem, a.dW), j = rem - i * a.W;
-            float sum = 0.f;
-            for (int co = 0; co < a.Cout; ++co)
-                for (int ta = 0; ta < a.n; ++ta) {
-                    const int oy = 2 * i + a.P - ta;
-                    if (oy < 0 || oy >= a.OH) continue;
-                    for (int tc = 0; tc < a.n; ++tc) {
-                        const int ox = 2 * j + a.P - tc;
-                        if (ox < 0 || ox >= a.OW) continue;
-                        sum = fmaf(dy[(((size_t)b * a.Cout + co) * a.OH + oy) * a.OW + ox],
-                                   w[((size_t)co * a.Cin + ci) * NN + ta * a.n + tc], sum);
-                    }
-                }
-            dx[((size_t)b * a.Cin + ci) * HW + rem] = sum;
-        }
-        return;
-    }
     // accumulator register e of a tile holds channel 8*(e/4) + 4*gk + (e%4), for the lane's pixel
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
@@ -273,9 +249,80 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int ci = ci0 + cw * 64 + 32 * m + 8 * (e / 4) + 4 * gk + (e % 4);
-                const float val = acc[m][nt][e];
+                const float val = acc[m][nt][e] * kPartsDown;
                 if (ci < a.Cin) out[(size_t)ci * HW] = val;
             }
+    }
+
+    // tiles that hold a sum that is not finite (ukst_parts.h)
+    unsigned tiles = 0u;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            if (!wave_finite(acc[m][nt])) tiles |= 1u << (2 * m + nt);
+    if (!__syncthreads_or(tiles != 0u ? 1 : 0)) return;
+    if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
+    __syncthreads();
+    const unsigned w_cstride = (unsigned)(a.Cin * NN) * 4u;
+    // group: (four channels, pixel) of the block's outputs
+    for (; tiles != 0u; tiles &= tiles - 1) {
+        const int t = __builtin_ctz(tiles), m = t >> 1, ql = (qw * 2 + (t & 1)) * 32 + l32;
+        const bool on = q0 + ql <= q_last;
+        const int q = on ? q0 + ql : q_last;
+        const int b = fdiv(q, a.dHW), rem = q - b * HW;
+        const int i = fdiv(rem, a.dW), j = rem - i * a.W;
+        const int cl = 64 * cw + 32 * m, ch = ci0 + cl + l32 < a.Cin ? ci0 + cl + l32 : a.Cin - 1;
+        bool halo = false;
+        f32x16_t sum[1];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) sum[0][k] = 0.f;
+        for (int ta = 0; ta < a.n; ++ta)
+            for (int tc = 0; tc < a.n; ++tc) {
+                const int oy = 2 * i + a.P - ta, ox = 2 * j + a.P - tc;
+                const bool in = on && oy >= 0 && oy < a.OH && ox >= 0 && ox < a.OW;
+                halo = halo || !in;
+                const unsigned dyo[1] = {in ? (unsigned)((b * a.Cout * a.OH + oy) * a.OW + ox) * 4u : kNoByte};
+                sum_tiles<float>(sum, rs_w, (unsigned)(ch * NN + ta * a.n + tc) * 4u, w_cstride, rs_dy, dyo, y_cstride, 0,
+                                 a.Cout);
+            }
+        float* const out = dx + (size_t)b * a.Cin * HW + rem;
+        if (on)
+            put_tile(
+                lds, sum[0], halo,
+                [&](int k, float v) {
+                    const int c = ci0 + cl + 8 * (k / 4) + 4 * gk + k % 4;
+                    if (c < a.Cin) out[(size_t)c * HW] = v;
+                },
+                [&](int k) { return (cl / 4 + 2 * k + gk) * TN + ql; });
+    }
+    __threadfence();  // what was stored lies in memory before it is stored again
+    __syncthreads();
+    const int listed = *reinterpret_cast<const int*>(lds);
+    for (int e = tid; e < listed; e += T) {
+        const int group = reinterpret_cast<const unsigned short*>(lds + 16)[e];
+        const int q = q0 + group % TN, cbase = ci0 + group / TN * 4;
+        if (cbase >= a.Cin) continue;
+        const int b = fdiv(q, a.dHW), rem = q - b * HW;
+        const int i = fdiv(rem, a.dW), j = rem - i * a.W;
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int ta = 0; ta < a.n; ++ta) {
+            const int oy = 2 * i + a.P - ta;
+            if (oy < 0 || oy >= a.OH) continue;
+            for (int tc = 0; tc < a.n; ++tc) {
+                const int ox = 2 * j + a.P - tc;
+                if (ox < 0 || ox >= a.OW) continue;
+                unsigned wo[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    wo[k] = (unsigned)((cbase + k < a.Cin ? cbase + k : a.Cin - 1) * NN + ta * a.n + tc) * 4u;
+                sum_products<float>(sum, rs_dy, (unsigned)((b * a.Cout * a.OH + oy) * a.OW + ox) * 4u, y_cstride, rs_w,
+                                    wo, w_cstride, 0, a.Cout);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (cbase + k < a.Cin) dx[((size_t)b * a.Cin + cbase + k) * HW + rem] = sum[k];
     }
 }
 
@@ -306,6 +353,7 @@ bool make_plan(const GeomBase& g, GiPlan& p)
     p.xu = p.cw == 2 ? (per <= 2 ? 2 : per <= 3 ? 3 : 4) : (per <= 4 ? 4 : 6);
     if (per > p.xu) return false;
     p.lds = 2 * (size_t)3 * 4 * (64 * p.cw + 4) * 16 + (size_t)3 * a.XPL;
+    if (p.lds < redo_bytes(TN * 16 * p.cw)) p.lds = redo_bytes(TN * 16 * p.cw);
     if (p.lds > LDS_LIMIT) return false;
     a.nci = (g.Cin + 64 * p.cw - 1) / (64 * p.cw);
     a.nqt = (int)((Q + TN - 1) / TN);

@@ -59,13 +59,10 @@ __device__ __forceinline__ Piece load_piece(const __amdgpu_buffer_rsrc_t& rs, un
 }
 // two elements -> PARTS packed dwords
 template <int PARTS>
-__device__ __forceinline__ void pair_parts(unsigned a, unsigned b, unsigned (&p)[PARTS], PartRange& seen)
+__device__ __forceinline__ void pair_parts(unsigned a, unsigned b, unsigned (&p)[PARTS])
 {
-    if constexpr (PARTS == 3) split_pair(__uint_as_float(a), __uint_as_float(b), p[0], p[1], p[2], seen);
-    else {
-        p[0] = a | (b << 16);
-        seen.see_parts(p[0]);
-    }
+    if constexpr (PARTS == 3) split_pair(__uint_as_float(a), __uint_as_float(b), p[0], p[1], p[2]);
+    else p[0] = a | (b << 16);
 }
 
 template <int N, typename TIn>
@@ -105,7 +102,6 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
         for (int c = 0; c < N; ++c)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][c][i] = 0.f;
-    PartRange seen;
 
     const int a_lane = (l32 * a.DP + 8 * kk) * 2, b_lane = ((wc * 32 + l32) * a.XP + 8 * kk) * 2;
     const int st0 = slice * a.stagesPerSlice;
@@ -153,8 +149,8 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
                 unsigned char* const base = dys + (wave * 8 + h * GRP + c) * a.DP * 2 + dst;
                 const Piece v = sh != 0 ? shifted(q[c], sh) : q[c];
                 unsigned ev[PARTS], od[PARTS];
-                pair_parts<PARTS>(v.v[0], v.v[2], ev, seen);
-                pair_parts<PARTS>(v.v[1], v.v[3], od, seen);
+                pair_parts<PARTS>(v.v[0], v.v[2], ev);
+                pair_parts<PARTS>(v.v[1], v.v[3], od);
 #pragma unroll
                 for (int i = 0; i < PARTS; ++i) {
                     *reinterpret_cast<unsigned*>(base + i * DPB) = ev[i];
@@ -193,8 +189,8 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
                     if (dst[u] >= 0) {
                         const Piece v = sh[u] <= -4 ? Piece{{0u, 0u, 0u, 0u}} : sh[u] != 0 ? shifted(q[u], sh[u]) : q[u];
                         unsigned lo[PARTS], hi[PARTS];
-                        pair_parts<PARTS>(v.v[0], v.v[1], lo, seen);
-                        pair_parts<PARTS>(v.v[2], v.v[3], hi, seen);
+                        pair_parts<PARTS>(v.v[0], v.v[1], lo);
+                        pair_parts<PARTS>(v.v[2], v.v[3], hi);
 #pragma unroll
                         for (int i = 0; i < PARTS; ++i)
                             *reinterpret_cast<u2v_t*>(xs + i * XPB + dst[u]) = u2v_t{lo[i], hi[i]};
@@ -264,36 +260,8 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
     }
 
     float* out = part + (size_t)slice * g.Cout * g.Cin * NN;
-    // (also: every wave is done with the tiles)
-    if (__syncthreads_or((PARTS == 3 ? seen.bad() : seen.not_finite()) ? 1 : 0)) {
-        // an operand whose parts do not hold it, or that must not meet the zeros past a row's end: this block's
-        // sums again, in fp32 throughout
-        for (int e = tid; e < 32 * CI_T * NN; e += 256) {
-            const int ci = ci0 + e % CI_T, r = e / CI_T, tap = r % NN, co = co0 + r / NN;
-            if (ci >= g.Cin || co >= g.Cout) continue;
-            const int ta = tap / N, tc = tap % N;
-            float sum = 0.f;
-            for (int st = st0; st < st_end; ++st) {
-                int t = st;
-                const int tx = t % a.tilesX; t /= a.tilesX;
-                const int ty = t % a.tilesY, b0 = t / a.tilesY * a.TB;
-                for (int tr = 0; tr < a.TR; ++tr) {
-                    const int b = b0 + (tr >> a.logTI), i = ty * a.TI + (tr & (a.TI - 1));
-                    const int oy = 2 * i + g.P - ta;
-                    if (b >= g.B || i >= g.H || oy < 0 || oy >= g.OH) continue;
-                    const TIn* xr = x + (((size_t)b * g.Cin + ci) * g.H + i) * g.W;
-                    const TIn* dr = dy + (((size_t)b * g.Cout + co) * g.OH + oy) * g.OW;
-                    for (int j = tx * a.TJ; j < g.W && j < (tx + 1) * a.TJ; ++j) {
-                        const int ox = 2 * j + g.P - tc;
-                        if (ox >= 0 && ox < g.OW) sum = fmaf(element_f32(xr[j]), element_f32(dr[ox]), sum);
-                    }
-                }
-            }
-            out[((size_t)co * NN + tap) * g.Cin + ci] = sum;
-        }
-        return;
-    }
     if constexpr (KHALF) {
+        __syncthreads();  // every wave is done with the tiles
         float* const lf = reinterpret_cast<float*>(lds);  // [wc][tap][register][lane]
         if (wh == 1) {
 #pragma unroll
@@ -304,28 +272,72 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel_parts(con
                     for (int i = 0; i < 16; ++i) lf[((wc * NN + r * N + c) * 16 + i) * 64 + lane] = acc[r][c][i];
         }
         __syncthreads();
-        if (wh == 1) return;
+        if (wh == 0) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int c = 0; c < N; ++c)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[r][c][i] += lf[((wc * NN + r * N + c) * 16 + i) * 64 + lane];
+        }
+    }
+    const bool owner = !KHALF || wh == 0;  // uniform
+    // tiles that hold a sum that is not finite (ukst_parts.h)
+    unsigned tiles = 0u;
+    if (owner) {
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
             for (int c = 0; c < N; ++c)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[r][c][i] += lf[((wc * NN + r * N + c) * 16 + i) * 64 + lane];
+                if (!wave_finite(acc[r][c])) tiles |= 1u << (r * N + c);
     }
     // accumulator register i: output channel 8*(i/4) + 4*kk + (i%4) of the 32, input channel l32
-    const int ci = ci0 + wc * 32 + l32;
+    if (owner) {
+        const int ci = ci0 + wc * 32 + l32;
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+        for (int r = 0; r < RW; ++r)
 #pragma unroll
-        for (int c = 0; c < N; ++c) {
-            const int tap = (KHALF ? r : wh * RW + r) * N + c;
+            for (int c = 0; c < N; ++c) {
+                const int tap = (KHALF ? r : wh * RW + r) * N + c;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int co = co0 + 8 * (i / 4) + 4 * kk + (i % 4);
-                const float v = acc[r][c][i];
-                if (co < g.Cout && ci < g.Cin) out[((size_t)co * NN + tap) * g.Cin + ci] = v;
+                for (int i = 0; i < 16; ++i) {
+                    const int co = co0 + 8 * (i / 4) + 4 * kk + (i % 4);
+                    const float v = PARTS == 3 ? acc[r][c][i] * kPartsDown : acc[r][c][i];
+                    if (co < g.Cout && ci < g.Cin) out[((size_t)co * NN + tap) * g.Cin + ci] = v;
+                }
+            }
+    }
+
+    for (; tiles != 0u; tiles &= tiles - 1) {
+        const int t = __builtin_ctz(tiles), tap = (KHALF ? 0 : wh * RW * N) + t, ta = tap / N, tc = tap % N;
+        const int co = co0 + l32 < g.Cout ? co0 + l32 : g.Cout - 1, cil = ci0 + wc * 32 + l32;
+        const int j_lo = (tc - g.P + 1) >> 1, j_hi = ((g.OW - 1 - g.P + tc) >> 1) + 1;  // 0 <= 2j + P - tc < OW
+        f32x16_t sum[1];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[0][i] = 0.f;
+        for (int st = st0; st < st_end; ++st) {
+            int t = st;
+            const int tx = t % a.tilesX; t /= a.tilesX;
+            const int ty = t % a.tilesY, b0 = t / a.tilesY * a.TB;
+            int j0 = tx * a.TJ, j1 = j0 + a.TJ < g.W ? j0 + a.TJ : g.W;
+            if (j0 < j_lo) j0 = j_lo;
+            if (j1 > j_hi) j1 = j_hi;
+            if (j0 >= j1) continue;
+            for (int tr = 0; tr < a.TR; ++tr) {
+                const int b = b0 + (tr >> a.logTI), i = ty * a.TI + (tr & (a.TI - 1));
+                const int oy = 2 * i + g.P - ta, ci = cil < g.Cin ? cil : g.Cin - 1;
+                if (b >= g.B || i >= g.H || oy < 0 || oy >= g.OH) continue;
+                const unsigned xo[1] = {(unsigned)((((b * g.Cin + ci) * g.H + i) * g.W + j0) * ES)};
+                sum_tiles<TIn>(sum, rs_dy, (unsigned)((((b * g.Cout + co) * g.OH + oy) * g.OW + 2 * j0 + g.P - tc) * ES),
+                               2 * ES, rs_x, xo, ES, 0, j1 - j0);
             }
         }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int c = co0 + 8 * (i / 4) + 4 * kk + i % 4;
+            if (c < g.Cout && cil < g.Cin) out[((size_t)c * NN + tap) * g.Cin + cil] = sum[0][i];
+        }
+    }
 }
 
 int log2_of(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }

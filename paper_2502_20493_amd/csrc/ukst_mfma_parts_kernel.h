@@ -170,7 +170,6 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     // raw registers of the stage being fetched: UK (8) values of four taps (PX pixels) per unit
     constexpr int WD = PARTS == 3 ? 4 : 2, XD = PARTS == 3 ? 1 : 2;  // dwords per load
     unsigned xr[XU][8][XD], wr[WU][UK][WD];
-    PartRange seen;
     auto load_x = [&](int s) {
 #pragma unroll
         for (int j = 0; j < XU; ++j)
@@ -231,7 +230,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
                                            (piece_at(sub_taps(N, PARTS, sub), j / WCG) + t) * WTS;
                 if (TM * UPC < T && wave >= TM * UPC / 64) continue;  // uniform
                 unsigned p[3];
-                split_pair(__uint_as_float(wr[j][0][t]), __uint_as_float(wr[j][1][t]), p[0], p[1], p[2], seen);
+                split_pair(__uint_as_float(wr[j][0][t]), __uint_as_float(wr[j][1][t]), p[0], p[1], p[2]);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) *reinterpret_cast<unsigned*>(dst + i * WPL) = p[i];
             } else {
@@ -264,7 +263,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         const int j = i >> 2, q = i & 3;
         if constexpr (PARTS == 3) {
             unsigned p0, p1, p2;
-            split_pair(__uint_as_float(xr[j][2 * q][0]), __uint_as_float(xr[j][2 * q + 1][0]), p0, p1, p2, seen);
+            split_pair(__uint_as_float(xr[j][2 * q][0]), __uint_as_float(xr[j][2 * q + 1][0]), p0, p1, p2);
             xp[j][0][q] = p0;
             xp[j][1][q] = p1;
             xp[j][2][q] = p2;
@@ -411,52 +410,6 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     const size_t ybytes = (size_t)g.B * g.Cout * g.OH * g.OW * OS;
     unsigned char* const yb = (unsigned char*)y + (size_t)ks * a.copy_bytes;
 
-    if constexpr (PARTS == 3) {
-        if (__syncthreads_or(seen.bad() ? 1 : 0)) {
-            // an operand whose parts do not hold it: this block's outputs again, in fp32 throughout
-            const int ci1 = s1 * KC < g.Cin ? s1 * KC : g.Cin;
-            for (int e = tid; e < TN * 4 * (TM / 8); e += T) {
-                const int q = q0 + e % TN, cls = (e / TN) & 3, cbase = co0 + e / (4 * TN) * 8;
-                if (q > q_last) continue;
-                const int r = cls >> 1, sc = cls & 1;
-                const int b = fdiv(q, a.dKHW);
-                const int rem = q - b * KHW;
-                const int kk = fdiv(rem, a.dKW), mm = rem - kk * a.KWq;
-                const int oy = AL ? 2 * kk + r : 2 * (g.k_min + kk) - r - g.P;
-                const int ox = AL ? 2 * mm + sc : 2 * (g.m_min + mm) - sc - g.P;
-                if (oy < 0 || oy >= g.OH || ox < 0 || ox >= g.OW) continue;
-                float sum[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) sum[k] = 0.f;
-                for (int ci = s0 * KC; ci < ci1; ++ci)
-                    for (int ta = r; ta < N; ta += 2) {
-                        const int i = kk + pos_of<AL>(ta) - (g.P >> 1);
-                        if (i < 0 || i >= g.H) continue;
-                        for (int tc = sc; tc < N; tc += 2) {
-                            const int j = mm + pos_of<AL>(tc) - (g.P >> 1);
-                            if (j < 0 || j >= g.W) continue;
-                            const float xv = element_f32(x[(((size_t)b * g.Cin + ci) * g.H + i) * g.W + j]);
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const int ch = cbase + k < g.Cout ? cbase + k : g.Cout - 1;
-                                sum[k] = fmaf(xv, element_f32(w[((size_t)ch * g.Cin + ci) * NN + ta * N + tc]), sum[k]);
-                            }
-                        }
-                    }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (cbase + k >= g.Cout) continue;
-                    float v = sum[k];
-                    if constexpr (EPI) v = epilogue(v, ep.bias ? ep.bias[cbase + k] : 0.f, ep.act);
-                    const size_t o = (((size_t)b * g.Cout + cbase + k) * g.OH + oy) * g.OW + ox;
-                    if constexpr (OUT16) ((uint16_t*)yb)[o] = __builtin_bit_cast(uint16_t, (__bf16)v);
-                    else ((float*)yb)[o] = v;
-                }
-            }
-            return;
-        }
-    }
-
     // accumulator register i of a tile holds channel 8*(i/4) + 4*gk + (i%4) of the wave's 32, for the
     // lane's quad; the two column classes of a quad are neighbours in memory
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc((void*)yb, 0, (int)ybytes, kRawBuffer);
@@ -494,6 +447,10 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
                     // shifted quads hold class 1 in their first row / column
                     float v0 = AL ? acc[nt][rr][0][i] : acc[nt][1 - rr][1][i];
                     float v1 = AL ? acc[nt][rr][1][i] : acc[nt][1 - rr][0][i];
+                    if constexpr (PARTS == 3) {
+                        v0 *= kPartsDown;
+                        v1 *= kPartsDown;
+                    }
                     if constexpr (ACT >= 0) {
                         const float bv = ep.bias ? ep.bias[chv ? co_w + ch : 0] : 0.f;
                         v0 = epilogue_t<ACT>(v0, bv);
@@ -520,6 +477,135 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     };
     if constexpr (EPI) with_activation(ep.act, drain);
     else drain(std::integral_constant<int, -1>{});
+    if constexpr (PARTS == 3) {
+        // tiles that hold a sum that is not finite (ukst_parts.h)
+        unsigned tiles[NT];
+        bool redo = false;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            tiles[nt] = 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (!wave_finite(acc[nt][c >> 1][c & 1])) tiles[nt] |= 1u << c;
+            redo = redo || tiles[nt] != 0u;
+        }
+        if (!__syncthreads_or(redo ? 1 : 0)) return;
+        if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
+        __syncthreads();
+        const int ci0 = s0 * KC, ci1 = s1 * KC < g.Cin ? s1 * KC : g.Cin;
+        const unsigned w_cstride = NN * ES;
+        const size_t planes = (size_t)g.OH * g.OW;
+        // the class's place of quad q in channel 0 of y (and image, row, column of the quad); false if there is none
+        auto place = [&](int q, int cls, size_t& o, int& b, int& kk, int& mm) {
+            b = fdiv(q, a.dKHW);
+            const int rem = q - b * KHW;
+            kk = fdiv(rem, a.dKW);
+            mm = rem - kk * a.KWq;
+            const int oy = AL ? 2 * kk + (cls >> 1) : 2 * (g.k_min + kk) - (cls >> 1) - g.P;
+            const int ox = AL ? 2 * mm + (cls & 1) : 2 * (g.m_min + mm) - (cls & 1) - g.P;
+            o = ((size_t)b * g.Cout * g.OH + oy) * g.OW + ox;
+            return oy >= 0 && oy < g.OH && ox >= 0 && ox < g.OW;
+        };
+        auto put = [&](size_t o, int ch, float v) {
+            if (ch >= g.Cout) return;
+            if constexpr (EPI) v = epilogue(v, ep.bias ? ep.bias[ch] : 0.f, ep.act);
+            if constexpr (OUT16) ((uint16_t*)yb)[o + ch * planes] = __builtin_bit_cast(uint16_t, (__bf16)v);
+            else ((float*)yb)[o + ch * planes] = v;
+        };
+        // Group: (class, four channels, quad) of the block's outputs.  The four classes of 32 quads together: a lane's
+        // weights, which lie in as many cache lines as there are lanes, come four taps to a load
+#pragma unroll 1
+        for (int nt = 0; nt < NT; ++nt) {
+            const unsigned todo = NT > 1 && nt == 1 ? tiles[NT - 1] : tiles[0];
+            if (todo == 0u) continue;
+            const int ql = (qw * NT + nt) * 32 + l32;
+            const bool on = q0 + ql <= q_last;
+            size_t o;
+            int b, kk, mm;
+            place(on ? q0 + ql : q_last, 0, o, b, kk, mm);
+            const int ch = co0 + cw * 32 + l32 < g.Cout ? co0 + cw * 32 + l32 : g.Cout - 1;
+            const unsigned wo = (unsigned)((ch * g.Cin + gk) * NN * ES);
+            constexpr int W = pos_of<AL>(N - 1) + 1;  // window side
+            unsigned xo[W][W];
+            bool halo = false;
+#pragma unroll
+            for (int pa = 0; pa < W; ++pa)
+#pragma unroll
+                for (int pb = 0; pb < W; ++pb) {
+                    const int i = kk + pa - (g.P >> 1), j = mm + pb - (g.P >> 1);
+                    const bool in = on && i >= 0 && i < g.H && j >= 0 && j < g.W;
+                    halo = halo || !in;
+                    xo[pa][pb] = in ? (unsigned)((((b * g.Cin + gk) * g.H + i) * g.W + j) * ES) : kNoByte;
+                }
+            f32x16_t sum[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum[c][i] = 0.f;
+#pragma unroll 1
+            for (int ci = ci0; ci < ci1; ci += 2) {
+                if (wave_nan(sum[0]) && wave_nan(sum[1]) && wave_nan(sum[2]) && wave_nan(sum[3])) break;
+                const bool in = ci + gk < ci1;
+                float wv[NN], xv[W][W];
+#pragma unroll
+                for (int p = 0; p < (NN + 3) / 4; ++p) {
+                    const unsigned soff = (unsigned)((ci * NN + piece_at(NN, p)) * ES);
+                    if constexpr (ES == 4) {
+                        const u4v_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_w, in ? wo : kNoByte, soff, 0);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) wv[piece_at(NN, p) + t] = __uint_as_float(v[t]);
+                    } else {
+                        const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_w, in ? wo : kNoByte, soff, 0);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            wv[piece_at(NN, p) + t] = __uint_as_float(t & 1 ? v[t >> 1] & 0xFFFF0000u : v[t >> 1] << 16);
+                    }
+                }
+#pragma unroll
+                for (int pa = 0; pa < W; ++pa)
+#pragma unroll
+                    for (int pb = 0; pb < W; ++pb) xv[pa][pb] = load_f32<TIn>(rs_x, in ? xo[pa][pb] : kNoByte, ci * x_cstride);
+#pragma unroll
+                for (int tap = 0; tap < NN; ++tap) {
+                    const int ta = tap / N, tc = tap % N, c = 2 * (ta & 1) + (tc & 1);
+                    sum[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[tap], xv[pos_of<AL>(ta)][pos_of<AL>(tc)], sum[c], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((todo >> c & 1) && place(on ? q0 + ql : q_last, c, o, b, kk, mm) && on)
+                    put_tile(lds, sum[c], halo, [&](int i, float v) { put(o, co0 + cw * 32 + 8 * (i / 4) + 4 * gk + i % 4, v); },
+                             [&](int i) { return (c * (TM / 4) + cw * 8 + 2 * i + gk) * TN + ql; });
+        }
+        __threadfence();  // what was stored lies in memory before it is stored again
+        __syncthreads();
+        const int listed = *reinterpret_cast<const int*>(lds);
+        for (int e = tid; e < listed; e += T) {
+            const int group = reinterpret_cast<const unsigned short*>(lds + 16)[e];
+            const int cbase = co0 + group / TN % (TM / 4) * 4, cls = group / (TN * (TM / 4));
+            if (cbase >= g.Cout) continue;
+            size_t o;
+            int b, kk, mm;
+            place(q0 + group % TN, cls, o, b, kk, mm);
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int ta = cls >> 1; ta < N; ta += 2) {
+                const int i = kk + pos_of<AL>(ta) - (g.P >> 1);
+                if (i < 0 || i >= g.H) continue;
+                for (int tc = cls & 1; tc < N; tc += 2) {
+                    const int j = mm + pos_of<AL>(tc) - (g.P >> 1);
+                    if (j < 0 || j >= g.W) continue;
+                    unsigned wo[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        wo[k] = (unsigned)(((cbase + k < g.Cout ? cbase + k : g.Cout - 1) * g.Cin * NN + ta * N + tc) * ES);
+                    sum_products<TIn>(sum, rs_x, (unsigned)(((b * g.Cin * g.H + i) * g.W + j) * ES), x_cstride, rs_w, wo,
+                                      w_cstride, ci0, ci1);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put(o, cbase + k, sum[k]);
+        }
+    }
 }
 
 // tile configuration: cw x qw waves of 32 channels x 32*nt quads, xu activation units per thread
@@ -530,8 +616,10 @@ inline int weight_stage_bytes(int n, int parts, int cw) { return parts * 2 * w_h
 template <int N, int CW, int QW, int NT, int XU, bool AL, typename TIn, bool OUT16>
 hipError_t launch_c(const PartsArgs& a, const Epilogue& ep, const void* x, const void* w, void* y, hipStream_t stream)
 {
-    const size_t lds = 2 * (size_t)weight_stage_bytes(N, sizeof(TIn) == 4 ? 3 : 1, CW) +
-                       (size_t)(sizeof(TIn) == 4 ? 3 : 1) * a.XPL;
+    constexpr size_t list = redo_bytes(32 * CW * 32 * NT * QW);
+    size_t lds = 2 * (size_t)weight_stage_bytes(N, sizeof(TIn) == 4 ? 3 : 1, CW) +
+                 (size_t)(sizeof(TIn) == 4 ? 3 : 1) * a.XPL;
+    if (lds < list) lds = list;
     typedef void (*kernel_t)(const TIn*, const TIn*, void*, PartsArgs, Epilogue);
     const kernel_t kfn = has_epilogue(ep) ? ukst_mfma_f32_kernel_parts<N, CW, QW, NT, XU, AL, true, TIn, OUT16>
                                           : ukst_mfma_f32_kernel_parts<N, CW, QW, NT, XU, AL, false, TIn, OUT16>;

@@ -1,5 +1,5 @@
-"""The matrix-core kernel on bf16 parts: edges of its tiles (channel tails, ragged columns, several images
-per tile), and operands whose three bf16 parts do not hold them (infinite, NaN, huge, tiny)."""
+"""The matrix-core kernels on bf16 parts: edges of their tiles (channel tails, ragged columns, several images
+per tile), and operands and sums at and beyond the ends of what scaled bf16 parts hold (infinite, NaN, huge, tiny)."""
 import numpy as np
 import pytest
 
@@ -109,6 +109,60 @@ def test_operands_that_three_parts_do_not_hold(shape, what):
     assert (np.abs(y[ok].astype(np.float64) - ref[ok]) <= 1e-5 * S[ok] + 5e-43).all()
 
 
+# scales of x and w.  Products of 2e-38 and less are denormal; 1e25 and 1e30 are beyond the range that the scaled
+# parts hold; sums of 1e26 fit fp32 but not a sum that is 2^48 times as large
+@pytest.mark.parametrize("sx,sw", [(1e-19, 1e-19), (1e-22, 1e-17), (1e-28, 1e-12), (1e25, 1e-20), (1e30, 1e-36),
+                                   (1e13, 1e13)])
+@pytest.mark.parametrize("shape", [(2, 41, 24, 9, 12, 4, 2, "f32"), (2, 33, 35, 10, 9, 3, 1, "f32")])
+def test_products_at_the_ends_of_the_range(shape, sx, sw):
+    import torch
+    w = _mk(shape)
+    data = wl.generate(w)
+    x, k = data["x"] * np.float32(sx), data["w"] * np.float32(sw)
+    y = ukst.ukst_conv_transpose2d(torch.from_numpy(x).cuda(), torch.from_numpy(k).cuda(), w.P).cpu().numpy()
+    ref, S = oracle.naive(x, k, w.P)
+    # (1.4e-45 for each of up to 41 x 16 / 4 products, were each rounded to a denormal)
+    assert (np.abs(y.astype(np.float64) - ref) <= 1e-5 * S + 164 * 1.4e-45).all()
+
+
+def _time(call):
+    import torch
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(5):
+            call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("op", ["forward", "strided", "grad_input", "grad_weight"])
+def test_tiny_operands_cost_no_time(op):
+    """One weight (or gradient element) in 64 channels far below the smallest bf16 product, or all of them: the same
+    kernel in the same time (2 times: the clock; a tile summed again costs ten times and more)."""
+    import torch
+    B, C, H, n, P = 16, 128, 40, 3, 1
+    g = torch.Generator(device="cuda").manual_seed(5)
+    OH, OW = ukst.ukst_output_shape(H, H, n, P)
+    x, w, dy = (torch.randn(s, generator=g, device="cuda") for s in ((B, C, H, H), (C, C, n, n), (B, C, OH, OW)))
+    calls = {"forward": lambda: ukst.ukst_conv_transpose2d(x, w, P),
+             "strided": lambda: ukst.ukst_conv_transpose2d_strided(x, w, P, 3),
+             "grad_input": lambda: ukst.ukst_conv_transpose2d_grad_input(dy, w, H, H, P),
+             "grad_weight": lambda: ukst.ukst_conv_transpose2d_grad_weight(x, dy, n, P)}
+    plain = _time(calls[op])
+    w[::64, 3, 1, 1] = 1e-35
+    dy[:, ::32, 3, 1] = 1e-41
+    some = _time(calls[op])
+    w *= 1e-33
+    dy *= 1e-33
+    every = _time(calls[op])
+    print(op, plain, some, every, flush=True)
+    assert some < 2 * plain and every < 2 * plain
+
+
 # op, k, (B, Cin, Cout, H, W, n, P)
 GENERAL_SHAPES = [
     ("strided", 3, (2, 16, 8, 9, 11, 5, 2)),     # classes of 4, 2 and 1 taps
@@ -134,7 +188,7 @@ def test_general_operations_on_the_matrix_cores(case, dtype):
     _run(op, w, k, integer=False)
 
 
-@pytest.mark.parametrize("what", ["inf", "nan", "all_tiny", "bf16_weight_inf"])
+@pytest.mark.parametrize("what", ["inf", "nan", "all_tiny", "large", "bf16_weight_inf"])
 def test_general_operations_with_operands_that_three_parts_do_not_hold(what):
     import torch
     rng = np.random.default_rng(31)
@@ -150,6 +204,9 @@ def test_general_operations_with_operands_that_three_parts_do_not_hold(what):
         return
     if what == "all_tiny":
         x *= np.float32(1e-34)
+    elif what == "large":  # sums beyond 2^80
+        x *= np.float32(1e15)
+        w *= np.float32(1e15)
     else:
         x[1, 4, 3, 5] = np.inf if what == "inf" else np.nan
     x64, w64 = torch.from_numpy(x).double(), torch.from_numpy(w).double()
@@ -163,7 +220,7 @@ def test_general_operations_with_operands_that_three_parts_do_not_hold(what):
         assert np.array_equal(np.isinf(got), np.isinf(ref))
         ok = np.isfinite(ref)
         # 153 products of at most |x| |w| < 25 units of x's scale: 1e-5 of their sum
-        scale = 1e-34 if what == "all_tiny" else 1.0
+        scale = {"all_tiny": 1e-34, "large": 1e30}.get(what, 1.0)
         assert (np.abs(got[ok] - ref[ok]) <= 1e-5 * 153 * 25 * scale + 1e-44).all()
 
 
@@ -240,7 +297,7 @@ def test_input_gradient_from_parts(shape, integer):
     check_elements(got, ref, S, TOL["f32"], exact=integer)
 
 
-@pytest.mark.parametrize("what", ["inf", "nan", "tiny"])
+@pytest.mark.parametrize("what", ["inf", "nan", "tiny", "large"])
 def test_gradients_with_operands_that_three_parts_do_not_hold(what):
     """An infinite or NaN gradient reaches the elements whose sums hold it, and no others; tiny ones keep their bits."""
     import torch
@@ -255,6 +312,10 @@ def test_gradients_with_operands_that_three_parts_do_not_hold(what):
     if what == "tiny":
         scale = 1e-33
         dy *= np.float32(scale)
+    elif what == "large":  # sums beyond 2^80
+        scale = 1e30
+        for t in (x, w, dy):
+            t *= np.float32(1e15)
     else:
         dy[2, 5, 40, 7] = np.inf if what == "inf" else np.nan
     xg, wg, dg = (torch.from_numpy(a).cuda() for a in (x, w, dy))
@@ -273,5 +334,5 @@ def test_gradients_with_operands_that_three_parts_do_not_hold(what):
     for got, ref, terms in ((dx, rx, Cout * n * n), (dw, rw, B * H * W)):
         assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
         ok = torch.isfinite(ref)
-        assert (~ok).any() == (what != "tiny")
+        assert (~ok).any() == (what in ("inf", "nan"))
         assert ((got - ref).abs()[ok] <= 1e-5 * terms * scale).all()
