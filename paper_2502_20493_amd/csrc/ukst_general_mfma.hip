@@ -338,6 +338,12 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
             }
     }
 
+    float most = 0.f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) most = peak(acc[m][nt], most);
+    if (!__syncthreads_or(most < __builtin_inff() ? 0 : 1)) return;
     // tiles that hold a sum that is not finite (ukst_parts.h)
     unsigned tiles = 0u;
 #pragma unroll
@@ -345,7 +351,6 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
             if (!wave_finite(acc[m][nt])) tiles |= 1u << (2 * m + nt);
-    if (!__syncthreads_or(tiles != 0u ? 1 : 0)) return;
     if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
     __syncthreads();
     const unsigned w_cstride = (unsigned)(NN * ES);

@@ -254,6 +254,12 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
             }
     }
 
+    float most = 0.f;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) most = peak(acc[m][nt], most);
+    if (!__syncthreads_or(most < __builtin_inff() ? 0 : 1)) return;
     // tiles that hold a sum that is not finite (ukst_parts.h)
     unsigned tiles = 0u;
 #pragma unroll
@@ -261,7 +267,6 @@ void ukst_grad_input_mfma_kernel_parts(const float* __restrict__ dy, const float
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
             if (!wave_finite(acc[m][nt])) tiles |= 1u << (2 * m + nt);
-    if (!__syncthreads_or(tiles != 0u ? 1 : 0)) return;
     if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
     __syncthreads();
     const unsigned w_cstride = (unsigned)(a.Cin * NN) * 4u;

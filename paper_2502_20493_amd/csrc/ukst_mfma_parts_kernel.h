@@ -477,134 +477,136 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     };
     if constexpr (EPI) with_activation(ep.act, drain);
     else drain(std::integral_constant<int, -1>{});
-    if constexpr (PARTS == 3) {
-        // tiles that hold a sum that is not finite (ukst_parts.h)
-        unsigned tiles[NT];
-        bool redo = false;
+
+    float most = 0.f;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            tiles[nt] = 0u;
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (!wave_finite(acc[nt][c >> 1][c & 1])) tiles[nt] |= 1u << c;
-            redo = redo || tiles[nt] != 0u;
-        }
-        if (!__syncthreads_or(redo ? 1 : 0)) return;
-        if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
-        __syncthreads();
-        const int ci0 = s0 * KC, ci1 = s1 * KC < g.Cin ? s1 * KC : g.Cin;
-        const unsigned w_cstride = NN * ES;
-        const size_t planes = (size_t)g.OH * g.OW;
-        // the class's place of quad q in channel 0 of y (and image, row, column of the quad); false if there is none
-        auto place = [&](int q, int cls, size_t& o, int& b, int& kk, int& mm) {
-            b = fdiv(q, a.dKHW);
-            const int rem = q - b * KHW;
-            kk = fdiv(rem, a.dKW);
-            mm = rem - kk * a.KWq;
-            const int oy = AL ? 2 * kk + (cls >> 1) : 2 * (g.k_min + kk) - (cls >> 1) - g.P;
-            const int ox = AL ? 2 * mm + (cls & 1) : 2 * (g.m_min + mm) - (cls & 1) - g.P;
-            o = ((size_t)b * g.Cout * g.OH + oy) * g.OW + ox;
-            return oy >= 0 && oy < g.OH && ox >= 0 && ox < g.OW;
-        };
-        auto put = [&](size_t o, int ch, float v) {
-            if (ch >= g.Cout) return;
-            if constexpr (EPI) v = epilogue(v, ep.bias ? ep.bias[ch] : 0.f, ep.act);
-            if constexpr (OUT16) ((uint16_t*)yb)[o + ch * planes] = __builtin_bit_cast(uint16_t, (__bf16)v);
-            else ((float*)yb)[o + ch * planes] = v;
-        };
-        // Group: (class, four channels, quad) of the block's outputs.  The four classes of 32 quads together: a lane's
-        // weights, which lie in as many cache lines as there are lanes, come four taps to a load
+        for (int c = 0; c < 4; ++c) most = peak(acc[nt][c >> 1][c & 1], most);
+    if (!__syncthreads_or(most < __builtin_inff() ? 0 : 1)) return;
+    // tiles that hold a sum that is not finite (ukst_parts.h)
+    unsigned tiles[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        tiles[nt] = 0u;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (!wave_finite(acc[nt][c >> 1][c & 1])) tiles[nt] |= 1u << c;
+    }
+    if (tid == 0) *reinterpret_cast<unsigned*>(lds) = 0u;
+    __syncthreads();
+    const int ci0 = s0 * KC, ci1 = s1 * KC < g.Cin ? s1 * KC : g.Cin;
+    const unsigned w_cstride = NN * ES;
+    const size_t planes = (size_t)g.OH * g.OW;
+    // the class's place of quad q in channel 0 of y (and image, row, column of the quad); false if there is none
+    auto place = [&](int q, int cls, size_t& o, int& b, int& kk, int& mm) {
+        b = fdiv(q, a.dKHW);
+        const int rem = q - b * KHW;
+        kk = fdiv(rem, a.dKW);
+        mm = rem - kk * a.KWq;
+        const int oy = AL ? 2 * kk + (cls >> 1) : 2 * (g.k_min + kk) - (cls >> 1) - g.P;
+        const int ox = AL ? 2 * mm + (cls & 1) : 2 * (g.m_min + mm) - (cls & 1) - g.P;
+        o = ((size_t)b * g.Cout * g.OH + oy) * g.OW + ox;
+        return oy >= 0 && oy < g.OH && ox >= 0 && ox < g.OW;
+    };
+    auto put = [&](size_t o, int ch, float v) {
+        if (ch >= g.Cout) return;
+        if constexpr (EPI) v = epilogue(v, ep.bias ? ep.bias[ch] : 0.f, ep.act);
+        if constexpr (OUT16) ((uint16_t*)yb)[o + ch * planes] = __builtin_bit_cast(uint16_t, (__bf16)v);
+        else ((float*)yb)[o + ch * planes] = v;
+    };
+    // Group: (class, four channels, quad) of the block's outputs.  The four classes of 32 quads together: a lane's
+    // weights, which lie in as many cache lines as there are lanes, come four taps to a load
 #pragma unroll 1
-        for (int nt = 0; nt < NT; ++nt) {
-            const unsigned todo = NT > 1 && nt == 1 ? tiles[NT - 1] : tiles[0];
-            if (todo == 0u) continue;
-            const int ql = (qw * NT + nt) * 32 + l32;
-            const bool on = q0 + ql <= q_last;
-            size_t o;
-            int b, kk, mm;
-            place(on ? q0 + ql : q_last, 0, o, b, kk, mm);
-            const int ch = co0 + cw * 32 + l32 < g.Cout ? co0 + cw * 32 + l32 : g.Cout - 1;
-            const unsigned wo = (unsigned)((ch * g.Cin + gk) * NN * ES);
-            constexpr int W = pos_of<AL>(N - 1) + 1;  // window side
-            unsigned xo[W][W];
-            bool halo = false;
+    for (int nt = 0; nt < NT; ++nt) {
+        const unsigned todo = NT > 1 && nt == 1 ? tiles[NT - 1] : tiles[0];
+        if (todo == 0u) continue;
+        const int ql = (qw * NT + nt) * 32 + l32;
+        const bool on = q0 + ql <= q_last;
+        size_t o;
+        int b, kk, mm;
+        place(on ? q0 + ql : q_last, 0, o, b, kk, mm);
+        const int ch = co0 + cw * 32 + l32 < g.Cout ? co0 + cw * 32 + l32 : g.Cout - 1;
+        const unsigned wo = (unsigned)((ch * g.Cin + gk) * NN * ES);
+        constexpr int W = pos_of<AL>(N - 1) + 1;  // window side
+        unsigned xo[W][W];
+        bool halo = false;
+#pragma unroll
+        for (int pa = 0; pa < W; ++pa)
+#pragma unroll
+            for (int pb = 0; pb < W; ++pb) {
+                const int i = kk + pa - (g.P >> 1), j = mm + pb - (g.P >> 1);
+                const bool in = on && i >= 0 && i < g.H && j >= 0 && j < g.W;
+                halo = halo || !in;
+                xo[pa][pb] = in ? (unsigned)((((b * g.Cin + gk) * g.H + i) * g.W + j) * ES) : kNoByte;
+            }
+        f32x16_t sum[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[c][i] = 0.f;
+#pragma unroll 1
+        for (int ci = ci0; ci < ci1; ci += 2) {
+            if (wave_nan(sum[0]) && wave_nan(sum[1]) && wave_nan(sum[2]) && wave_nan(sum[3])) break;
+            const bool in = ci + gk < ci1;
+            float wv[NN], xv[W][W];
+#pragma unroll
+            for (int p = 0; p < (NN + 3) / 4; ++p) {
+                const unsigned soff = (unsigned)((ci * NN + piece_at(NN, p)) * ES);
+                if constexpr (ES == 4) {
+                    const u4v_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_w, in ? wo : kNoByte, soff, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) wv[piece_at(NN, p) + t] = __uint_as_float(v[t]);
+                } else {
+                    const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_w, in ? wo : kNoByte, soff, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        wv[piece_at(NN, p) + t] = __uint_as_float(t & 1 ? v[t >> 1] & 0xFFFF0000u : v[t >> 1] << 16);
+                }
+            }
 #pragma unroll
             for (int pa = 0; pa < W; ++pa)
 #pragma unroll
-                for (int pb = 0; pb < W; ++pb) {
-                    const int i = kk + pa - (g.P >> 1), j = mm + pb - (g.P >> 1);
-                    const bool in = on && i >= 0 && i < g.H && j >= 0 && j < g.W;
-                    halo = halo || !in;
-                    xo[pa][pb] = in ? (unsigned)((((b * g.Cin + gk) * g.H + i) * g.W + j) * ES) : kNoByte;
-                }
-            f32x16_t sum[4];
+                for (int pb = 0; pb < W; ++pb) xv[pa][pb] = load_f32<TIn>(rs_x, in ? xo[pa][pb] : kNoByte, ci * x_cstride);
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum[c][i] = 0.f;
-#pragma unroll 1
-            for (int ci = ci0; ci < ci1; ci += 2) {
-                if (wave_nan(sum[0]) && wave_nan(sum[1]) && wave_nan(sum[2]) && wave_nan(sum[3])) break;
-                const bool in = ci + gk < ci1;
-                float wv[NN], xv[W][W];
-#pragma unroll
-                for (int p = 0; p < (NN + 3) / 4; ++p) {
-                    const unsigned soff = (unsigned)((ci * NN + piece_at(NN, p)) * ES);
-                    if constexpr (ES == 4) {
-                        const u4v_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_w, in ? wo : kNoByte, soff, 0);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) wv[piece_at(NN, p) + t] = __uint_as_float(v[t]);
-                    } else {
-                        const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_w, in ? wo : kNoByte, soff, 0);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            wv[piece_at(NN, p) + t] = __uint_as_float(t & 1 ? v[t >> 1] & 0xFFFF0000u : v[t >> 1] << 16);
-                    }
-                }
-#pragma unroll
-                for (int pa = 0; pa < W; ++pa)
-#pragma unroll
-                    for (int pb = 0; pb < W; ++pb) xv[pa][pb] = load_f32<TIn>(rs_x, in ? xo[pa][pb] : kNoByte, ci * x_cstride);
-#pragma unroll
-                for (int tap = 0; tap < NN; ++tap) {
-                    const int ta = tap / N, tc = tap % N, c = 2 * (ta & 1) + (tc & 1);
-                    sum[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[tap], xv[pos_of<AL>(ta)][pos_of<AL>(tc)], sum[c], 0, 0, 0);
-                }
+            for (int tap = 0; tap < NN; ++tap) {
+                const int ta = tap / N, tc = tap % N, c = 2 * (ta & 1) + (tc & 1);
+                sum[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[tap], xv[pos_of<AL>(ta)][pos_of<AL>(tc)], sum[c], 0, 0, 0);
             }
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if ((todo >> c & 1) && place(on ? q0 + ql : q_last, c, o, b, kk, mm) && on)
-                    put_tile(lds, sum[c], halo, [&](int i, float v) { put(o, co0 + cw * 32 + 8 * (i / 4) + 4 * gk + i % 4, v); },
-                             [&](int i) { return (c * (TM / 4) + cw * 8 + 2 * i + gk) * TN + ql; });
         }
-        __threadfence();  // what was stored lies in memory before it is stored again
-        __syncthreads();
-        const int listed = *reinterpret_cast<const int*>(lds);
-        for (int e = tid; e < listed; e += T) {
-            const int group = reinterpret_cast<const unsigned short*>(lds + 16)[e];
-            const int cbase = co0 + group / TN % (TM / 4) * 4, cls = group / (TN * (TM / 4));
-            if (cbase >= g.Cout) continue;
-            size_t o;
-            int b, kk, mm;
-            place(q0 + group % TN, cls, o, b, kk, mm);
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int ta = cls >> 1; ta < N; ta += 2) {
-                const int i = kk + pos_of<AL>(ta) - (g.P >> 1);
-                if (i < 0 || i >= g.H) continue;
-                for (int tc = cls & 1; tc < N; tc += 2) {
-                    const int j = mm + pos_of<AL>(tc) - (g.P >> 1);
-                    if (j < 0 || j >= g.W) continue;
-                    unsigned wo[4];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        wo[k] = (unsigned)(((cbase + k < g.Cout ? cbase + k : g.Cout - 1) * g.Cin * NN + ta * N + tc) * ES);
-                    sum_products<TIn>(sum, rs_x, (unsigned)(((b * g.Cin * g.H + i) * g.W + j) * ES), x_cstride, rs_w, wo,
-                                      w_cstride, ci0, ci1);
-                }
+        for (int c = 0; c < 4; ++c)
+            if ((todo >> c & 1) && place(on ? q0 + ql : q_last, c, o, b, kk, mm) && on)
+                put_tile(lds, sum[c], halo, [&](int i, float v) { put(o, co0 + cw * 32 + 8 * (i / 4) + 4 * gk + i % 4, v); },
+                         [&](int i) { return (c * (TM / 4) + cw * 8 + 2 * i + gk) * TN + ql; });
+    }
+    __threadfence();  // what was stored lies in memory before it is stored again
+    __syncthreads();
+    const int listed = *reinterpret_cast<const int*>(lds);
+    for (int e = tid; e < listed; e += T) {
+        const int group = reinterpret_cast<const unsigned short*>(lds + 16)[e];
+        const int cbase = co0 + group / TN % (TM / 4) * 4, cls = group / (TN * (TM / 4));
+        if (cbase >= g.Cout) continue;
+        size_t o;
+        int b, kk, mm;
+        place(q0 + group % TN, cls, o, b, kk, mm);
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int ta = cls >> 1; ta < N; ta += 2) {
+            const int i = kk + pos_of<AL>(ta) - (g.P >> 1);
+            if (i < 0 || i >= g.H) continue;
+            for (int tc = cls & 1; tc < N; tc += 2) {
+                const int j = mm + pos_of<AL>(tc) - (g.P >> 1);
+                if (j < 0 || j >= g.W) continue;
+                unsigned wo[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    wo[k] = (unsigned)(((cbase + k < g.Cout ? cbase + k : g.Cout - 1) * g.Cin * NN + ta * N + tc) * ES);
+                sum_products<TIn>(sum, rs_x, (unsigned)(((b * g.Cin * g.H + i) * g.W + j) * ES), x_cstride, rs_w, wo,
+                                  w_cstride, ci0, ci1);
             }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) put(o, cbase + k, sum[k]);
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) put(o, cbase + k, sum[k]);
     }
 }
 

@@ -109,6 +109,35 @@ def test_operands_that_three_parts_do_not_hold(shape, what):
     assert (np.abs(y[ok].astype(np.float64) - ref[ok]) <= 1e-5 * S[ok] + 5e-43).all()
 
 
+@pytest.mark.parametrize("out_bf16", [False, True])
+@pytest.mark.parametrize("what", ["weight_inf", "inf", "nan"])
+@pytest.mark.parametrize("shape", [(2, 17, 21, 9, 11, 3, 0, "bf16"), (2, 31, 34, 7, 10, 5, 3, "bf16"),
+                                   (1, 47, 70, 5, 13, 4, 2, "bf16")])
+def test_bf16_operands_that_are_not_finite(shape, what, out_bf16):
+    """They reach the outputs whose sums hold them: the halo is left out, not multiplied by zero."""
+    import torch
+    w = _mk(shape)
+    data = wl.generate(w)
+    x, k = data["x"].copy(), data["w"].copy()
+    if what == "weight_inf":
+        k[3, 2, 0, 1], k[4, 16, w.n - 1, w.n - 1] = np.inf, -np.inf
+    else:
+        x[0, 3, 2, 4], x[w.B - 1, 7, 0, 0] = (np.inf, -np.inf) if what == "inf" else (np.nan, np.nan)
+    assert ukst.ukst_kernel_name(w.B, w.Cin, w.Cout, w.H, w.W, w.n, w.P, ukst.UKST_BF16_F32) == "ukst_mfma_f32_kernel_parts"
+    put = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    y = ukst.ukst_conv_transpose2d(put(x), put(k), w.P, out_bf16=out_bf16).float().cpu().numpy()
+    ref = torch.nn.functional.conv_transpose2d(torch.from_numpy(x).double(),
+                                               torch.from_numpy(k).double().flip(2, 3).transpose(0, 1), stride=2)
+    pad = w.P - (w.n - 1)
+    ref = torch.nn.functional.pad(ref, (pad, pad, pad, pad)).numpy()
+    assert np.array_equal(np.isnan(ref), np.isnan(y))
+    inf = np.isinf(ref)
+    assert np.array_equal(inf, np.isinf(y)) and np.array_equal(ref[inf], y[inf])
+    ok = np.isfinite(ref)
+    # (one bf16 rounding; up to 47 x 9 products of a few units in fp32)
+    assert (np.abs(y[ok] - ref[ok]) <= 2.0 ** -8 * np.abs(ref[ok]) + 1e-3).all()
+
+
 # scales of x and w.  Products of 2e-38 and less are denormal; 1e25 and 1e30 are beyond the range that the scaled
 # parts hold; sums of 1e26 fit fp32 but not a sum that is 2^48 times as large
 @pytest.mark.parametrize("sx,sw", [(1e-19, 1e-19), (1e-22, 1e-17), (1e-28, 1e-12), (1e25, 1e-20), (1e30, 1e-36),
