@@ -94,8 +94,12 @@ int ukst_output_shape(int H, int W, int n, int P, int* OH, int* OW);
 unsigned long long ukst_mac_count(int B, int Cin, int Cout, int H, int W, int n, int P, int kind);
 
 /*
- * The path UKST_PATH_AUTO resolves to for this problem (UKST_PATH_DIRECT or UKST_PATH_MFMA),
- * or a negative ukst_status on invalid arguments.  Host arithmetic only.
+ * The path (UKST_PATH_DIRECT or UKST_PATH_MFMA) that a program passes on to get the kernel family
+ * UKST_PATH_AUTO takes for this problem, or a negative ukst_status on invalid arguments.  A call
+ * with the path that is returned is accepted for buffers aligned to 16 bytes.  Layers that only
+ * UKST_PATH_AUTO takes to the matrix cores (channel counts that UKST_PATH_MFMA refuses, on
+ * "ukst_mfma_f32_kernel_parts") answer UKST_PATH_DIRECT, the one path they can be forced to.
+ * Host arithmetic only.
  */
 int ukst_select_path(int B, int Cin, int Cout, int H, int W, int n, int P, int dtype);
 

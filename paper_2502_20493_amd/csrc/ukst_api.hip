@@ -184,7 +184,11 @@ int ukst_select_path(int B, int Cin, int Cout, int H, int W, int n, int P, int d
     if (st != UKST_OK) return -st;
     if (dtype != UKST_F32 && dtype != UKST_BF16_F32 && dtype != UKST_BF16_BF16) return -UKST_ERR_DTYPE;
     if (n > UKST_MAX_N) return -UKST_ERR_UNSUPPORTED;
-    return resolve_path(ukst::make_geom(B, Cin, Cout, H, W, n, P), dtype, UKST_PATH_AUTO);
+    // layers that only automatic selection takes to the matrix cores have no path of their own: the answer is one
+    // that a call accepts
+    const ukst::Geom g = ukst::make_geom(B, Cin, Cout, H, W, n, P);
+    const int chosen = resolve_path(g, dtype, UKST_PATH_AUTO);
+    return resolve_path(g, dtype, chosen) == chosen ? chosen : UKST_PATH_DIRECT;
 }
 
 // Validation shared by the forward entry points and the workspace query; on UKST_OK `g` holds the

@@ -194,6 +194,20 @@ def test_select_path():
     assert ukst.ukst_kernel_name(16, 3, 3, 1, 224, 3, 0, 0) == ""
 
 
+@pytest.mark.parametrize("dtype", [ukst.UKST_F32, ukst.UKST_BF16_F32, ukst.UKST_BF16_BF16])
+def test_a_selected_path_can_be_forced(dtype):
+    """The path that ukst_select_path names is one that a call accepts (a kernel name for it), also for the layers
+    that only automatic selection takes to the matrix cores (odd channel counts, any row length)."""
+    rng = np.random.default_rng(11)
+    for _ in range(1500):
+        B, Cin, Cout, H, W, n = (int(v) for v in rng.integers([1, 1, 1, 4, 4, 1], [40, 200, 150, 90, 90, 8]))
+        shape = (B, Cin, Cout, H, W, n, int(rng.integers(0, n)))
+        path = ukst.ukst_select_path(*shape, dtype)
+        assert ukst.ukst_kernel_name(*shape, dtype, path) != "", (shape, path)
+    assert ukst.ukst_kernel_name(8, 77, 40, 33, 35, 3, 0, ukst.UKST_F32) == "ukst_mfma_f32_kernel_parts"
+    assert ukst.ukst_select_path(8, 77, 40, 33, 35, 3, 0, ukst.UKST_F32) == ukst.UKST_PATH_DIRECT
+
+
 def test_workloads_are_seeded_and_shaped():
     from paper_2502_20493_amd import workloads as wl
     a = wl.generate(wl.WORKLOADS["cfg1"])
