@@ -256,16 +256,16 @@ size_t ukst_static_workspace_bytes(void);
  * Cout a multiple of 8, W >= 16 -- bf16 MFMA with an output channel's 16 taps as the contraction;
  * "ukst_grad_input_mfma_bf16_kernel": bf16 MFMA for other bf16 operands where its LDS tile fits,
  * i.e. kernel sides up to about 5;
- * "ukst_grad_input_mfma_kernel": otherwise; fp32 layers with enough pixels run the instance
- * ukst_grad_input_mfma_kernel_parts, bf16 MFMA on three exact bf16 parts of every operand, the rest
- * fp32 MFMA: weights packed once per call into the workspace, which also holds the copies of dx
- * when the sum over output channels is split),
+ * "ukst_grad_input_mfma_kernel_parts": other fp32 layers with enough pixels, bf16 MFMA on three exact
+ * bf16 parts of every operand;
+ * "ukst_grad_input_mfma_kernel": fp32 MFMA for the rest, weights packed once per call into the
+ * workspace, which also holds the copies of dx when the sum over output channels is split),
  * layers with Cin, Cout >= 32 run the kernel gradient there too
  * ("ukst_grad_weight_mfma_bf16_kernel": bf16 MFMA with the pixel axis as the contraction, for bf16
  * operands with kernel sides 2 to 4, W a multiple of 8 and at least 16;
- * "ukst_grad_weight_mfma_kernel": everything else of that width, either dtype;
- * ukst_grad_weight_mfma_kernel_parts, bf16 MFMA on bf16 parts, for n = 3, 4 and rows of at least 16
- * pixels on layers with enough of them, fp32 MFMA for the rest).
+ * "ukst_grad_weight_mfma_kernel_parts": bf16 MFMA on bf16 parts (three of an fp32 value, one of a
+ * bf16 value), for n = 3, 4 and rows of at least 16 pixels on layers with enough of them;
+ * "ukst_grad_weight_mfma_kernel": fp32 MFMA for everything else of that width, either dtype).
  * Layers with at most 4 output channels, Cout * n * n <= 64 and Cin >= 16 run the kernel gradient
  * as "ukst_grad_weight_thin_mfma_kernel" (fp32 MFMA whose rows are (channel, tap) pairs).
  * Narrow fp32 layers (Cin, Cout <= 4, 2 <= n <= 5, W >= 32) run both gradients as
@@ -316,6 +316,8 @@ unsigned long long ukst_mac_count_dilated(int B, int Cin, int Cout, int H, int W
 /*
  * Name of the device kernel the given path launches for this problem, as it appears in a
  * profiler's kernel trace (substring match), or "" on invalid arguments.  Static storage.
+ * Without a workspace, that is: of the layers for which ukst_workspace_bytes(UKST_OP_FORWARD, ...)
+ * asks for one, the long ones run on "ukst_mfma_f32_kernel_parts" if they are given it.
  */
 const char* ukst_kernel_name(int B, int Cin, int Cout, int H, int W, int n, int P, int dtype,
                              int path);

@@ -2339,7 +2339,9 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
         if (dtype == 1 && gw_b16_args(g, ba)) return "ukst_grad_weight_mfma_bf16_kernel";
         GwMfmaArgs wa;
         const bool m = g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa) : gw_mfma_args<gw_nc(5)>(g, wa);
-        if (m) return "ukst_grad_weight_mfma_kernel";
+        if (m)
+            return g.n <= 4 && grad_weight_parts_slices(g, dtype == 0 ? 4 : 2, wa.nSlices) != 0
+                       ? "ukst_grad_weight_mfma_kernel_parts" : "ukst_grad_weight_mfma_kernel";
         GwThinArgs ta;
         int MT = 1, CT = 1;
         const bool th = g.n == 2 ? gw_thin_pick<2>(g, ta, MT, CT) : g.n == 3 ? gw_thin_pick<3>(g, ta, MT, CT)
@@ -2350,7 +2352,8 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
     if (grad_narrow_supported(g, dtype)) return "ukst_grad_input_narrow_kernel";
     GiMfmaArgs ma;
     if (dtype == 1 && gi_mfma_args(g, ma, true)) return "ukst_grad_input_mfma_bf16_kernel";
-    return gi_mfma_args(g, ma) ? "ukst_grad_input_mfma_kernel" : "ukst_grad_input_kernel";
+    if (!gi_mfma_args(g, ma)) return "ukst_grad_input_kernel";
+    return dtype == 0 && grad_input_parts_supported(g) ? "ukst_grad_input_mfma_kernel_parts" : "ukst_grad_input_mfma_kernel";
 }
 
 hipError_t launch_grad_input(const Geom& g, const void* dy, const void* w, float* dx, int dtype,

@@ -645,7 +645,7 @@ const char* mfma_kernel_name(const Geom& g, int dtype)
 {
     if (bf16_pipe(g, dtype))  // bf16 in; fp32 or bf16 out
         return prefer_aligned(g, dtype) ? "ukst_mfma_bf16_aligned_kernel" : "ukst_mfma_bf16_kernel";
-    if (prefer_parts(g, dtype)) return mfma_supported(g, dtype) ? "ukst_mfma_f32_kernel" : "ukst_mfma_f32_kernel_parts";
+    if (prefer_parts(g, dtype)) return "ukst_mfma_f32_kernel_parts";
     return mfma_f32_supported(g, dtype) ? "ukst_mfma_f32_kernel" : "ukst_thin_mfma_kernel";
 }
 

@@ -246,9 +246,13 @@ def test_backward_kernel_selection_is_host_arithmetic():
     assert name(1, 2, 16, 5, 16, 16, 4, 2, ukst.UKST_F32) == "ukst_grad_weight_kernel"   # 5 x 16 rows: too many
     assert name(1, 2, 16, 3, 16, 2, 3, 0, ukst.UKST_F32) == "ukst_grad_weight_kernel"    # rows of two pixels
     assert name(1, 2, 16, 3, 16, 16, 3, 0, ukst.UKST_F32) == "ukst_grad_weight_thin_mfma_kernel"
-    for k in ("cfg3_L1", "cfg3_L2", "cfg3_L3", "cfg4a", "cfg4b"):
-        assert name(0, *shape(k), ukst.UKST_F32) == "ukst_grad_input_mfma_kernel", k
-        assert name(1, *shape(k), ukst.UKST_F32) == "ukst_grad_weight_mfma_kernel", k
+    # wide fp32 layers: the fp32 pipe, or bf16 parts from 100 tiles of 256 pixels (input gradient) and from 8192 pixels
+    # in rows of at least 16 on, n = 3, 4 (kernel gradient)
+    for k, dx, dw in (("cfg3_L1", "", ""), ("cfg3_L2", "", ""), ("cfg3_L3", "", "_parts"), ("cfg4a", "_parts", ""),
+                      ("cfg4b", "_parts", "_parts")):
+        assert name(0, *shape(k), ukst.UKST_F32) == "ukst_grad_input_mfma_kernel" + dx, k
+        assert name(1, *shape(k), ukst.UKST_F32) == "ukst_grad_weight_mfma_kernel" + dw, k
+    assert name(1, 9, 64, 64, 31, 30, 4, 2, ukst.UKST_BF16_F32) == "ukst_grad_weight_mfma_kernel_parts"
     for k in ("cfg5a", "cfg5b"):
         assert name(0, *shape(k), ukst.UKST_BF16_F32) == "ukst_grad_input_window_mfma_bf16_kernel", k
         assert name(1, *shape(k), ukst.UKST_BF16_F32) == "ukst_grad_weight_mfma_bf16_kernel", k

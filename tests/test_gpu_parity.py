@@ -281,14 +281,16 @@ def test_mfma_f32_small_shapes_every_element(shape):
 def test_bf16_layers_with_other_kernel_sides_run_on_the_fp32_matrix_pipe(shape):
     """bf16 layers whose kernel side the bf16 MFMA kernels do not take (n = 2, 3, 5: the dataset
     kernels of Tables 2-3) are widened on their way into LDS and multiplied by the fp32 MFMA
-    kernel instead of falling to the vector ALUs."""
+    kernel instead of falling to the vector ALUs; from 16 tiles of 64 channels x 256 quads on they
+    run on the bf16 pipe as one part."""
     B, Cin, Cout, H, W, n, P = shape
     w = _mk("mfma_f32_bf16in", 8300 + sum(shape), B, Cin, Cout, H, W, n, P, dtype="bf16")
     name = ukst.ukst_kernel_name(B, Cin, Cout, H, W, n, P, ukst.UKST_BF16_F32, PATHS["mfma"])
     if n == 3 and Cin % 16 == 0 and Cout % 8 == 0 and W % 8 == 0:
         assert name == "ukst_mfma_bf16_kernel"   # 9 taps: the bf16 pipe takes them
     elif n != 4:
-        assert name == "ukst_mfma_f32_kernel"
+        quads = B * ((2 * H + 2 * P - n) // 2 + 1) * ((2 * W + 2 * P - n) // 2 + 1)
+        assert name == ("ukst_mfma_f32_kernel_parts" if -(-Cout // 64) * quads > 15 * 256 else "ukst_mfma_f32_kernel")
     assert name
     _parity(w, PATHS["mfma"], integer=True)
     _parity(w, PATHS["mfma"], integer=False)
@@ -405,7 +407,7 @@ def test_repeat_runs_are_bit_identical():
 @pytest.mark.parametrize("name,kernel", [("cfg2a", "ukst_narrow_kernel"), ("cfg2b", "ukst_narrow_kernel"),
                                          ("cfg3_L1", "ukst_mfma_f32_kernel"),
                                          ("cfg3_L4", "ukst_thin_mfma_kernel"),
-                                         ("cfg4a", "ukst_mfma_f32_kernel"),
+                                         ("cfg4a", "ukst_mfma_f32_kernel_parts"),
                                          ("cfg5a", "ukst_mfma_bf16_aligned_kernel"),
                                          ("cfg5a_P1", "ukst_mfma_bf16_kernel"),
                                          ("cfg5b", "ukst_mfma_bf16_aligned_kernel"),
