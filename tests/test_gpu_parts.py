@@ -28,6 +28,11 @@ SHAPES = [
     (2, 35, 9, 7, 19, 2, 3, "bf16"),
     (1, 16, 33, 2, 130, 5, 4, "bf16"),
     (2, 64, 100, 16, 127, 3, 1, "bf16"),
+    # 256-quad tiles on eight waves: from 129 of them on
+    (2, 17, 70, 95, 97, 5, 0, "f32"),
+    (3, 33, 70, 79, 93, 3, 1, "f32"),
+    (2, 17, 100, 95, 97, 5, 2, "bf16"),
+    (2, 19, 100, 95, 97, 2, 1, "bf16"),
 ]
 
 
@@ -49,7 +54,7 @@ def test_tile_edges_every_element(shape):
         check_against_oracle(y, y_ref, S, TOL["f32"], exact=integer)  # (bf16 products are exact in fp32)
 
 
-@pytest.mark.parametrize("shape", [SHAPES[10], SHAPES[13], (2, 33, 21, 9, 11, 3, 0, "bf16")])
+@pytest.mark.parametrize("shape", [SHAPES[10], SHAPES[13], (2, 33, 21, 9, 11, 3, 0, "bf16"), SHAPES[18], SHAPES[19]])
 def test_bf16_output_and_epilogue(shape):
     import torch
     from gpu_util import to_device
@@ -107,6 +112,27 @@ def test_operands_that_three_parts_do_not_hold(shape, what):
     ok = np.isfinite(full)
     # (5e-43: half a unit of the smallest fp32 number for each of 41 x 16 products)
     assert (np.abs(y[ok].astype(np.float64) - ref[ok]) <= 1e-5 * S[ok] + 5e-43).all()
+
+
+@pytest.mark.parametrize("dx,dw,dy", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (3, 3, 3)])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[8], SHAPES[10], SHAPES[11], SHAPES[14]])
+def test_operands_at_element_alignment(shape, dx, dw, dy):
+    """x, w and y that start dx, dw and dy elements past 16 bytes: 16- and 8-byte loads at 4 and 2 bytes."""
+    import torch
+    from gpu_util import to_device
+    w = _mk(shape)
+    data = wl.generate(w, integer=True)
+    x, k = to_device(data, w.dtype)
+
+    def off(t, n):
+        buf = torch.empty(t.numel() + 64, dtype=t.dtype, device="cuda")
+        assert buf.data_ptr() % 16 == 0
+        return buf[n:n + t.numel()].view(t.shape).copy_(t)
+    OH, OW = oracle.out_shape(w.H, w.W, w.n, w.P)
+    y = off(torch.full((w.B, w.Cout, OH, OW), -777.0, device="cuda"), dy)
+    ukst.ukst_conv_transpose2d(off(x, dx), off(k, dw), w.P, y=y)
+    y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+    check_against_oracle(y.cpu().numpy(), y_ref, S, TOL["f32"], exact=True)
 
 
 @pytest.mark.parametrize("out_bf16", [False, True])
@@ -282,20 +308,21 @@ def test_slices_of_the_input_channels(shape):
 
 # B, Cin, Cout, H, W, n, P, dtype
 GRAD_WEIGHT_SHAPES = [
-    (2, 33, 34, 65, 63, 3, 0, "f32"),     # channel tails, odd rows, a second column tile of 31
+    (3, 33, 34, 65, 63, 3, 0, "f32"),     # channel tails, odd rows, a second column tile of 31
     (1, 40, 70, 96, 90, 4, 1, "f32"),     # tap rows in two halves, third column tile of 26
     (40, 32, 33, 13, 20, 3, 2, "f32"),    # 20 of 32 columns, several images per slice
     (33, 65, 32, 16, 16, 4, 2, "f32"),    # 16-column tiles, two rows per stage
-    (2, 33, 34, 65, 63, 4, 2, "bf16"),
+    (3, 33, 34, 65, 63, 4, 2, "bf16"),
     (3, 40, 36, 64, 49, 3, 1, "bf16"),
 ]
 # from 100 tiles of 256 pixels on
 GRAD_INPUT_SHAPES = [
     (3, 66, 17, 100, 90, 3, 1),           # eight waves, two channels of the second group, one channel past a stage
     (7, 33, 20, 61, 61, 4, 0),            # four waves
-    (2, 40, 16, 128, 101, 5, 2),          # classes of 9, 6, 6 and 4 taps
+    (2, 72, 16, 128, 101, 5, 2),          # classes of 9, 6, 6 and 4 taps
+    (26, 40, 16, 32, 32, 5, 2),           # the same on four waves
     (2, 35, 18, 120, 110, 2, 1),          # one tap per class
-    (2, 33, 16, 120, 110, 7, 9),          # P beyond the kernel
+    (26, 33, 16, 31, 33, 7, 9),           # P beyond the kernel
     (420, 34, 16, 8, 8, 3, 0),            # four images per tile
 ]
 
@@ -305,6 +332,8 @@ GRAD_INPUT_SHAPES = [
 def test_kernel_gradient_from_parts(shape, integer):
     from gpu_util import check_elements, run_gpu_grad_weight
     w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    assert ukst.ukst_grad_kernel_name(1, *shape[:7], dt) == "ukst_grad_weight_mfma_kernel_parts"
     print(f"case {shape} integer={integer}", flush=True)
     data = wl.generate(w, integer=integer)
     dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
@@ -313,11 +342,23 @@ def test_kernel_gradient_from_parts(shape, integer):
     check_elements(got, ref, S, TOL["f32"], exact=integer)
 
 
+@pytest.mark.parametrize("shape", [(2, 530, 256, 4, 16, 4, 2, "bf16"), (2, 530, 256, 5, 7, 3, 1, "f32")])
+def test_sum_of_the_copies_of_many_channel_pairs(shape):
+    """From 2048 runs of 64 input channels on the copies are turned through LDS; the last run here has 18."""
+    from gpu_util import check_elements, run_gpu_grad_weight
+    w = _mk(shape)
+    data = wl.generate(w, integer=True)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=True)
+    ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
+    check_elements(run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096), ref, S, TOL["f32"], exact=True)
+
+
 @pytest.mark.parametrize("integer", [True, False])
 @pytest.mark.parametrize("shape", GRAD_INPUT_SHAPES)
 def test_input_gradient_from_parts(shape, integer):
     from gpu_util import check_elements, run_gpu_grad_input
     w = _mk(shape + ("f32",))
+    assert ukst.ukst_grad_kernel_name(0, *shape, ukst.UKST_F32) == "ukst_grad_input_mfma_kernel_parts"
     print(f"case {shape} integer={integer}", flush=True)
     data = wl.generate(w, integer=integer)
     dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
@@ -326,8 +367,9 @@ def test_input_gradient_from_parts(shape, integer):
     check_elements(got, ref, S, TOL["f32"], exact=integer)
 
 
-@pytest.mark.parametrize("what", ["inf", "nan", "tiny", "large"])
-def test_gradients_with_operands_that_three_parts_do_not_hold(what):
+@pytest.mark.parametrize("what,dtype", [("inf", "f32"), ("nan", "f32"), ("tiny", "f32"), ("large", "f32"),
+                                        ("inf", "bf16"), ("nan", "bf16"), ("x_inf", "bf16")])
+def test_gradients_with_operands_that_three_parts_do_not_hold(what, dtype):
     """An infinite or NaN gradient reaches the elements whose sums hold it, and no others; tiny ones keep their bits."""
     import torch
     import torch.nn.functional as F
@@ -345,9 +387,19 @@ def test_gradients_with_operands_that_three_parts_do_not_hold(what):
         scale = 1e30
         for t in (x, w, dy):
             t *= np.float32(1e15)
+    elif what == "x_inf":
+        x[4, 9, 30, 20] = np.inf
     else:
         dy[2, 5, 40, 7] = np.inf if what == "inf" else np.nan
-    xg, wg, dg = (torch.from_numpy(a).cuda() for a in (x, w, dy))
+    if dtype == "bf16":
+        x, w, dy = (np.where(np.isfinite(a), wl.bf16_bits_to_f32(wl.round_to_bf16_bits(a)), a) for a in (x, w, dy))
+    code = ukst.UKST_F32 if dtype == "f32" else ukst.UKST_BF16_F32
+    shape = (B, Cin, Cout, H, W, n, P)
+    assert ukst.ukst_grad_kernel_name(1, *shape, code) == "ukst_grad_weight_mfma_kernel_parts"
+    if dtype == "f32":
+        assert ukst.ukst_grad_kernel_name(0, *shape, code) == "ukst_grad_input_mfma_kernel_parts"
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    xg, wg, dg = (torch.from_numpy(a).to(tt).cuda() for a in (x, w, dy))
     dx = ukst.ukst_conv_transpose2d_grad_input(dg, wg, H, W, P).cpu().double()
     dw = ukst.ukst_conv_transpose2d_grad_weight(xg, dg, n, P).cpu().double()
     x64, w64, d64 = (torch.from_numpy(a).double() for a in (x, w, dy))
@@ -360,8 +412,9 @@ def test_gradients_with_operands_that_three_parts_do_not_hold(what):
             # (finite factors first: an infinite one meets every input channel of its output channel)
             rw[:, :, a, c] = d.transpose(0, 1).reshape(Cout, -1) @ x64.transpose(0, 1).reshape(Cin, -1).t()
     # sums of up to 26047 products of factors below 6 (and dy's scale): 1e-5 of the sum of their magnitudes
-    for got, ref, terms in ((dx, rx, Cout * n * n), (dw, rw, B * H * W)):
+    # (the bf16 input gradient is another kernel)
+    for got, ref, terms in ((dx, rx, Cout * n * n), (dw, rw, B * H * W))[0 if dtype == "f32" else 1:]:
         assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
         ok = torch.isfinite(ref)
-        assert (~ok).any() == (what in ("inf", "nan"))
+        assert (~ok).any() == (what in ("inf", "nan", "x_inf"))
         assert ((got - ref).abs()[ok] <= 1e-5 * terms * scale).all()
