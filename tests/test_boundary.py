@@ -179,6 +179,22 @@ def test_mac_counts():
     assert abs(2 * ukst.ukst_mac_count(32, 128, 128, 64, 64, 5, 0, 0) / 1e9 - 99.47) < 0.01
 
 
+def test_output_size_in_place_is_ukst_output_shape():
+    """The binding works the output size out by itself for sizes in range; what the library refuses it refuses with
+    the same error, whatever the sign of the result."""
+    for H in (-1, 0, 1, 2, 7, 1 << 28, (1 << 28) + 1):
+        for W in (0, 1, 5):
+            for n in (0, 1, 3, 7):
+                for P in (-1, 0, 2, 40, 1 << 28, (1 << 28) + 1):
+                    want, got = [], []
+                    for f, out in ((ukst.ukst_output_shape, want), (ukst._output_size, got)):
+                        try:
+                            out.append(f(H, W, n, P))
+                        except ukst.UkstError as e:
+                            out.append(e.status)
+                    assert want == got, (H, W, n, P)
+
+
 def test_select_path():
     assert ukst.ukst_select_path(16, 3, 3, 224, 224, 3, 0, ukst.UKST_F32) == ukst.UKST_PATH_DIRECT
     # few output channels: the parity classes fill the MFMA columns when Cin % 16 == 0, W % 4 == 0

@@ -651,3 +651,13 @@ def test_unaligned_buffers_take_the_vector_alu_kernels(dtype, cout):
     with pytest.raises(ukst.UkstError):
         ukst.ukst_conv_transpose2d(x, k, w.P, path=PATHS["mfma"])
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("shape,P", [((1, 1, 0, 5), 2), ((1, 1, 4, 4), -1), ((1, 1, 2, 2), (1 << 28) + 1)])
+def test_refused_shapes_raise_before_anything_is_allocated(shape, P):
+    """No rows, negative padding and padding beyond the library's limit, where 2H + 2P - n alone would look valid."""
+    import torch
+    x, w = torch.zeros(shape, device="cuda"), torch.zeros((1, 1, 3, 3), device="cuda")
+    with pytest.raises(ukst.UkstError) as e:
+        ukst.ukst_conv_transpose2d(x, w, P)
+    assert e.value.status == ukst.UKST_ERR_SHAPE
