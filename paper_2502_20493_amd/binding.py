@@ -35,6 +35,7 @@ BENCH_EXPORTS = ["ukst_bench_mfma_ceiling", "ukst_bench_stream_ceiling"]
 
 _lib = None
 _bench_lib = None
+_torch = None  # the module, from the time the library is loaded on
 
 
 class UkstError(RuntimeError):
@@ -46,7 +47,7 @@ class UkstError(RuntimeError):
 def lib():
     """Load libukst.so (once).  Raises if it is missing: build it with
     ``python -m paper_2502_20493_amd.build`` (or ``__graft_entry__.build()``)."""
-    global _lib
+    global _lib, _torch
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -55,7 +56,8 @@ def lib():
         # PyTorch bundles its own HIP runtime.  It has to be in the process before this library
         # is loaded, otherwise the two ends see different runtimes and the first HIP call made
         # from here reports that there is no device.
-        import torch  # noqa: F401
+        import torch
+        _torch = torch
         L = ctypes.CDLL(LIB_PATH)
         i, vp = ctypes.c_int, ctypes.c_void_p
         ip = ctypes.POINTER(ctypes.c_int)
@@ -205,12 +207,10 @@ def _stream_handle(stream, device):
 
 def _call(device, fn, *args):
     """fn(*args) with `device` current (switched to only if it is not); raises on a status that is not ok."""
-    import torch
-
-    if torch.cuda.current_device() == device.index:
+    if _torch.cuda.current_device() == device.index:
         status = fn(*args)
     else:
-        with torch.cuda.device(device):
+        with _torch.cuda.device(device):
             status = fn(*args)
     if status != UKST_OK:
         _check(int(status))
@@ -297,7 +297,9 @@ def ukst_conv_transpose2d(x, w, P: int, y=None, path: int = UKST_PATH_AUTO, stre
         raise ValueError("a bfloat16 output needs bfloat16 inputs")
     dtype = UKST_F32 if x.dtype == torch.float32 else (UKST_BF16_BF16 if out_bf16 else UKST_BF16_F32)
     ydt = torch.bfloat16 if out_bf16 else torch.float32
-    OH, OW = _output_size(H, W, n, P)
+    OH, OW = 2 * H + 2 * P - n, 2 * W + 2 * P - n  # (_output_size without its call)
+    if OH < 1 or OW < 1 or P < 0 or P > _MAX_SIDE or H < 1 or W < 1 or n < 1:
+        ukst_output_shape(H, W, n, P)  # raises
     device = x.device
     if y is None:
         y = torch.empty((B, Cout, OH, OW), dtype=ydt, device=device)
