@@ -540,21 +540,24 @@ static bool bf16_pipe(const Geom& g, int dtype)
 
 // Where the kernel on bf16 parts (ukst_mfma_parts_kernel.h) runs instead of the fp32 pipe or the vector
 // ALUs, in tiles of 64 channels x 256 quads.  Large layers gain whatever they are: fp32 128 -> 128 channels
-// on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 231, 601 -> 346, 872 -> 580 us; bf16 operands with
-// n = 5 861 -> 191 us.  Small ones do not, because a tile is one block's serial work: fp32 at 64 tiles (64
-// images of 128 -> 64 channels, 16 x 16, n = 4) 49.4 against 49.2 us, at 132 tiles 97.6 against 57.1; n = 5 at
-// 66 and 132 tiles 72 against 121 and 141 against 132; bf16 operands at 5 and 17 tiles 31 against 65 and 45
-// against 38.
+// on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 220, 601 -> 330, 872 -> 531 us; bf16 operands with
+// n = 5 861 -> 191 us.
+// fp32, from more than 64 tiles on, where the fp32 pipe's 256 tiles of 64 x 64 quads begin a second round: 128 -> 64
+// channels, 32 x 32 maps, 68 tiles n = 4 76.7 against 42.8 us, n = 5 137 against 70, n = 3 at 72 tiles 68.4 against 33.2;
+// at 64 tiles 49.7 against 42.4 (n = 4), 71.2 against 68.7 (n = 5, 60.3 with a workspace).
+// bf16 operands: at 9 tiles (64 -> 64 channels, n = 5) 39.9 against 21.5 us, but 23.0 with a workspace; 13 tiles of
+// 256 -> 64 channels 134 (57) against 58, 16 tiles with n = 3 58.3 (43.8) against 39.2.
 static bool prefer_parts(const Geom& g, int dtype)
 {
     if (g.Cin < 16 || bf16_pipe(g, dtype) || (dtype == 0 && g.Cout <= 4)) return false;
     const double tiles = mfma_parts_tiles(g, dtype);
     if (tiles == 0.) return false;
-    if (mfma_f32_supported(g, dtype)) return tiles >= (dtype != 0 ? 16. : g.n <= 4 ? 72. : 120.);
-    // otherwise the vector ALUs, which win against one tile's serial work only with few channels or 5 x 5 fp32 kernels (77 -> 40 channels, 33 tiles: 67 against 91 us; 19 -> 21
-    // channels, 8 tiles: 12 against 15 us; 591 -> 96 channels bf16, 95 tiles: 7.7 ms against 103 us)
-    if (dtype != 0) return true;
-    return g.n == 5 ? tiles >= 64. : g.Cin >= 32 || tiles >= 24.;
+    if (mfma_f32_supported(g, dtype)) return dtype != 0 ? tiles >= 16. : tiles > 64.;
+    // otherwise the vector ALUs, which win against one tile's serial work only with few channels (fp32, n = 5: 19 -> 21
+    // channels, 4 to 35 tiles: 17.0 to 20.0 against 24.4 to 25.4 us, 33 -> 5 27.0 against 31.3, 40 -> 20 the same, 45 ->
+    // 70 39.6 against 31.0, 77 -> 40 at 4 and 26 tiles 59 against 42 and 81 against 44; n = 3, 17 -> 21 channels, 8 tiles:
+    // 11.4 against 15.7; 591 -> 96 channels bf16, 95 tiles: 7.7 ms against 103 us)
+    return dtype != 0 || (g.n == 5 ? g.Cin >= 45 || tiles >= 64. : g.Cin >= 32 || tiles >= 24.);
 }
 
 // ... and, given a workspace, with slices of the input channels: layers of few tiles that are long on the

@@ -21,6 +21,9 @@ SHAPES = [
     (1, 36, 30, 40, 117, 3, 1, "f32"),   # 512-quad tiles of 32 channels
     (4, 17, 41, 64, 63, 5, 3, "f32"),    # n = 5: 26 stages of taps, 17 channels
     (9, 18, 35, 33, 61, 5, 0, "f32"),
+    (17, 16, 64, 32, 32, 5, 2, "f32"),   # 68 tiles: just beyond one round of the fp32 pipe
+    (17, 16, 64, 32, 32, 4, 2, "f32"),
+    (2, 45, 33, 9, 11, 5, 3, "f32"),     # the fewest channels that leave the vector ALUs with a single tile
     (2, 17, 21, 9, 11, 3, 0, "bf16"),
     (1, 47, 70, 5, 13, 4, 2, "bf16"),    # rows of no multiple of 4: the last piece starts inside its neighbour
     (3, 24, 37, 3, 4, 4, 1, "bf16"),
@@ -54,7 +57,7 @@ def test_tile_edges_every_element(shape):
         check_against_oracle(y, y_ref, S, TOL["f32"], exact=integer)  # (bf16 products are exact in fp32)
 
 
-@pytest.mark.parametrize("shape", [SHAPES[10], SHAPES[13], (2, 33, 21, 9, 11, 3, 0, "bf16"), SHAPES[18], SHAPES[19]])
+@pytest.mark.parametrize("shape", [SHAPES[13], SHAPES[16], (2, 33, 21, 9, 11, 3, 0, "bf16"), SHAPES[21], SHAPES[22]])
 def test_bf16_output_and_epilogue(shape):
     import torch
     from gpu_util import to_device
@@ -115,7 +118,7 @@ def test_operands_that_three_parts_do_not_hold(shape, what):
 
 
 @pytest.mark.parametrize("dx,dw,dy", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (3, 3, 3)])
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[8], SHAPES[10], SHAPES[11], SHAPES[14]])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[8], SHAPES[13], SHAPES[14], SHAPES[17]])
 def test_operands_at_element_alignment(shape, dx, dw, dy):
     """x, w and y that start dx, dw and dy elements past 16 bytes: 16- and 8-byte loads at 4 and 2 bytes."""
     import torch
