@@ -364,9 +364,14 @@ bool make_plan(const GeomBase& g, GiPlan& p)
     a.nqt = (int)((Q + TN - 1) / TN);
     const long long nb = (long long)a.nci * a.nqt;
     // a tile is one block's serial work: few of them lose to the fp32 pipe, which splits the sum over channels (64
-    // tiles, 64 images of 128 -> 64 channels, 16 x 16, n = 4: 68 against 84 us; 82 tiles of 40 -> 189, n = 5: 318 against
-    // 343; 233 of 64 -> 64, n = 3: 97 against 65)
-    if (nb < 100 || nb > 0x3FFFFFFF) return false;
+    // tiles, 64 images of 128 -> 64 channels, 16 x 16, n = 4: 68 against 84 us; 102 tiles of 128 -> 128, 51 x 51, n = 2 /
+    // 3 / 4 / 5 / 7: 131 / 193 / 276 / 383 / 667 against 90 / 118 / 168 / 257 / 478).  Blocks of four waves, up to 64
+    // input channels, take as long for half the channels; with many output channels, which that pipe splits further,
+    // they gain from there on only at n = 3 and 4 (33 -> 160 channels, 102 tiles, n = 4: 202 against 197; n = 5 / 7 at
+    // 122 tiles 265 / 445 against 298 / 502; 33 -> 96, n = 2, 102 tiles: 59 against 70; 64 -> 16, n = 5: 56 against 34;
+    // 33 -> 256 at 133 tiles, n = 2 / 5 / 7: 186 / 511 / 894 against 177 / 472 / 801)
+    const bool late = p.cw == 1 && (g.n >= 5 ? g.Cout > 32 : g.n == 2 && g.Cout > 64);
+    if (nb < (late ? 130 : 100) || nb > 0x3FFFFFFF) return false;
     p.blocks = (unsigned)nb;
     a.dHW = make_fastdiv((unsigned)hw);
     a.dW = make_fastdiv((unsigned)g.W);

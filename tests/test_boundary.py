@@ -269,6 +269,11 @@ def test_backward_kernel_selection_is_host_arithmetic():
         assert name(0, *shape(k), ukst.UKST_F32) == "ukst_grad_input_mfma_kernel" + dx, k
         assert name(1, *shape(k), ukst.UKST_F32) == "ukst_grad_weight_mfma_kernel" + dw, k
     assert name(1, 9, 64, 64, 31, 30, 4, 2, ukst.UKST_BF16_F32) == "ukst_grad_weight_mfma_kernel_parts"
+    # four-wave blocks (up to 64 input channels) gain later for n = 2 and n >= 5, unless there are few output channels
+    for images, co, n, tail in ((10, 160, 5, ""), (13, 160, 5, "_parts"), (10, 160, 7, ""), (10, 16, 7, "_parts"),
+                                (10, 160, 3, "_parts"), (10, 96, 2, ""), (13, 96, 2, "_parts"), (10, 64, 2, "_parts")):
+        assert name(0, images, 33, co, 51, 51, n, n // 2, ukst.UKST_F32) == "ukst_grad_input_mfma_kernel" + tail, (co, n)
+    assert name(0, 10, 72, 160, 51, 51, 5, 2, ukst.UKST_F32) == "ukst_grad_input_mfma_kernel_parts"
     for k in ("cfg5a", "cfg5b"):
         assert name(0, *shape(k), ukst.UKST_BF16_F32) == "ukst_grad_input_window_mfma_bf16_kernel", k
         assert name(1, *shape(k), ukst.UKST_BF16_F32) == "ukst_grad_weight_mfma_bf16_kernel", k
