@@ -538,6 +538,26 @@ static bool bf16_pipe(const Geom& g, int dtype)
     return dtype != 0 && (mfma_aligned_supported(g, dtype) || make_args(g, dtype, a));
 }
 
+// Layers that the fp32 pipe does not take, of few channels and little work, where the vector ALUs are the faster ones:
+// an input channel costs them a step of a serial chain, the kernel on parts takes sixteen at once whether they are there
+// or not, and 32 output channels.  v: pixels times output channels.  (40 x 41 maps, us, vector ALUs against parts.
+// fp32, n = 2: 17 -> 31 channels, v = 8.1e5 12.8 / 14.4, 17 -> 63, 4.1e5 9.4 / 10.4, 12.4e5 (47) 14.5 / 10.2;
+// 35 -> 31, 4.1e5 15.2 / 15.6; 40 -> 17 11.9 / 13.5.  n = 3: 17 -> 17, 4.5e5 15.8 / 16.5; 17 -> 31, 8.1e5 18.7 / 17.5;
+// 21 -> 31, 4.1e5 16.4 / 17.3.  n = 4: 17 -> 31, 4.1e5 17.1 / 19.8.  n = 5: 17 -> 7 28.0 / 31.9.  21 -> 5, 128 images,
+// n = 2 / 3 / 4 / 5: 22 / 34 / 43 / 58 against 27 / 36 / 46 / 61; 25 -> 7, 64 images, n = 3 27 / 20.  bf16, n = 2: 17 -> 80
+// 8.2 / 9.3, 23 -> 17 9.6 / 8.9)
+static bool alus_win(const Geom& g, int dtype)
+{
+    const double v = (double)g.B * g.H * g.W * g.Cout;
+    if (dtype != 0) return g.n == 2 && g.Cin < 20 && v < 2.1e5;
+    if (g.Cin >= 48) return false;
+    if (g.Cout <= 8 && g.Cin < 24) return true;
+    const bool half = g.Cout <= 32;  // blocks of 32 channels
+    if (g.n == 2) return v < (g.Cin < 24 ? (half ? 8.2e5 : 5e5) : half ? 4.5e5 : 0.);
+    if (g.n == 5) return false;  // (from 64 tiles on, below)
+    return g.Cin < 20 ? v < (half ? 7.5e5 : 4.2e5) : g.Cin < 24 && half && v < 4.1e5;
+}
+
 // Where the kernel on bf16 parts (ukst_mfma_parts_kernel.h) runs instead of the fp32 pipe or the vector
 // ALUs, in tiles of 64 channels x 256 quads.  Large layers gain whatever they are: fp32 128 -> 128 channels
 // on 64 x 64 maps, 16 to 32 images, n = 3 / 4 / 5: 396 -> 220, 601 -> 330, 872 -> 531 us; bf16 operands with
@@ -553,10 +573,11 @@ static bool prefer_parts(const Geom& g, int dtype)
     const double tiles = mfma_parts_tiles(g, dtype);
     if (tiles == 0.) return false;
     if (mfma_f32_supported(g, dtype)) return dtype != 0 ? tiles >= 16. : tiles > 64.;
-    // otherwise the vector ALUs, which win against one tile's serial work only with few channels (fp32, n = 5: 19 -> 21
-    // channels, 4 to 35 tiles: 17.0 to 20.0 against 24.4 to 25.4 us, 33 -> 5 27.0 against 31.3, 40 -> 20 the same, 45 ->
-    // 70 39.6 against 31.0, 77 -> 40 at 4 and 26 tiles 59 against 42 and 81 against 44; n = 3, 17 -> 21 channels, 8 tiles:
-    // 11.4 against 15.7; 591 -> 96 channels bf16, 95 tiles: 7.7 ms against 103 us)
+    // otherwise the vector ALUs, which win against one tile's serial work with few channels (fp32, n = 5: 19 -> 21, 4 to 35
+    // tiles 17.0 to 20.0 against 24.4 to 25.4 us, 40 -> 20 the same, 45 -> 70 39.6 against 31.0, 77 -> 40 at 4 and 26
+    // tiles 59 against 42 and 81 against 44; n = 3, 17 -> 21, 8 tiles: 11.4 against 15.7; 591 -> 96 channels bf16, 95
+    // tiles: 7.7 ms against 103 us)
+    if (alus_win(g, dtype)) return false;
     return dtype != 0 || (g.n == 5 ? g.Cin >= 45 || tiles >= 64. : g.Cin >= 32 || tiles >= 24.);
 }
 

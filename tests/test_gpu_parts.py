@@ -15,8 +15,8 @@ SHAPES = [
     (2, 33, 21, 9, 11, 3, 0, "f32"),     # channel tail of 1, one partial 32-channel block
     (1, 47, 70, 5, 13, 4, 2, "f32"),     # aligned quads, two channel blocks, the second with 6 channels
     (3, 40, 37, 3, 4, 4, 1, "f32"),      # shifted quads, many images per tile
-    (2, 35, 5, 7, 19, 2, 0, "f32"),      # n = 2 aligned
-    (2, 35, 9, 7, 19, 2, 3, "f32"),      # n = 2 shifted, P beyond the kernel
+    (2, 51, 5, 7, 19, 2, 0, "f32"),      # n = 2 aligned
+    (2, 51, 9, 7, 19, 2, 3, "f32"),      # n = 2 shifted, P beyond the kernel
     (1, 50, 33, 2, 129, 3, 2, "f32"),    # rows longer than a tile's quads
     (1, 36, 30, 40, 117, 3, 1, "f32"),   # 512-quad tiles of 32 channels
     (4, 17, 41, 64, 63, 5, 3, "f32"),    # n = 5: 26 stages of taps, 17 channels
