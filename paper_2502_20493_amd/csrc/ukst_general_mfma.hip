@@ -504,6 +504,19 @@ bool launch_general_mfma(int dilated, int B, int Cin, int Cout, int H, int W, in
     // one stage of channels and many lattice pixels: writing y with a stride is all there is (16 -> 16 channels,
     // 8 x 48 x 48, stride 3, fp32: 17.2 against 17.7 us)
     if (!dilated && dtype == 0 && Cin * Cout < 512 && (long long)B * H * W > 4096) return false;
+    // one or two stages of channels and no class with more than one tap: little to multiply, and the vector ALUs neither
+    // pad the channels nor write y a class at a time.  fp32, 24 x 25 maps, 4 images, vector ALUs against this kernel, us:
+    // 17 -> 64 channels, n = 1, stride 1 9.2 / 11.2, n = 2, stride 2 10.2 / 12.4, 17 -> 8, n = 1, stride 5 9.0 / 10.6 (16
+    // images of 40 x 41, 17 -> 64, n = 1, stride 1 14.7 / 12.5; 17 -> 200, n = 1, stride 5 39 / 33); stride 8 16 -> 32,
+    // n = 1 19.1 / 22.1, 16 -> 200, n = 2 71 / 86, 17 -> 8, n = 3 12.2 / 15.9 (17 -> 32, n = 3 25.8 / 24.8); bf16
+    // 16 -> 64, n = 2, stride 8 28.0 / 32.2, and 16 images of 40 x 41, 17 -> 8, n = 4, stride 4 23.1 / 27.4, 16 -> 8, n = 5,
+    // stride 8 62.6 / 71.2 (stride 5 29.7 / 27.6)
+    if (!dilated && Cin < 20 && n <= k) {
+        const bool few = (long long)B * H * W < 4096;
+        if (dtype != 0 && !few && Cout <= 8 && k % 4 == 0) return false;
+        if (dtype == 0 && few && n <= 3 && Cin > 16 && Cout <= 64 && k < 8) return false;
+        if (k >= 8 && n <= 3 && ((n == 2 && few) || (dtype == 0 && (n == 1 || Cout <= 8)))) return false;
+    }
     ConvArgs a;
     a.B = B; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.n = n; a.P = P; a.k = k; a.OH = OH; a.OW = OW;
     a.dilated = dilated;

@@ -228,11 +228,16 @@ GENERAL_SHAPES = [
     ("strided", 4, (3, 21, 33, 5, 6, 3, 1)),     # classes without taps: zeros
     ("strided", 5, (1, 18, 9, 6, 37, 7, 8)),     # P beyond the kernel
     ("strided", 1, (2, 17, 40, 12, 20, 4, 3)),   # one class
-    ("strided", 3, (1, 16, 33, 2, 130, 3, 2)),   # rows longer than half a tile
+    ("strided", 3, (1, 32, 33, 2, 130, 3, 2)),   # rows longer than half a tile
     ("dilated", 2, (2, 33, 37, 15, 19, 3, 2)),
     ("dilated", 4, (3, 20, 8, 11, 11, 5, 8)),    # several images per tile, mostly halo
     ("dilated", 3, (1, 17, 65, 21, 13, 4, 13)),  # windows that meet no input
-    ("dilated", 1, (2, 16, 9, 8, 70, 1, 0)),     # a single tap
+    ("dilated", 1, (2, 32, 9, 8, 70, 1, 0)),     # a single tap
+    # few channels and at most a tap per class: the vector ALUs, beside the first layers that leave them
+    ("strided", 8, (2, 17, 8, 9, 11, 3, 1)),
+    ("strided", 8, (2, 20, 8, 9, 11, 3, 1)),
+    ("strided", 2, (2, 19, 40, 12, 13, 2, 0)),
+    ("dilated", 3, (2, 19, 9, 8, 70, 1, 0)),
 ]
 
 
