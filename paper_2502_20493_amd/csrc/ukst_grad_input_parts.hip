@@ -366,12 +366,17 @@ bool make_plan(const GeomBase& g, GiPlan& p)
     // a tile is one block's serial work: few of them lose to the fp32 pipe, which splits the sum over channels (64
     // tiles, 64 images of 128 -> 64 channels, 16 x 16, n = 4: 68 against 84 us; 102 tiles of 128 -> 128, 51 x 51, n = 2 /
     // 3 / 4 / 5 / 7: 131 / 193 / 276 / 383 / 667 against 90 / 118 / 168 / 257 / 478).  Blocks of four waves, up to 64
-    // input channels, take as long for half the channels; with many output channels, which that pipe splits further,
-    // they gain from there on only at n = 3 and 4 (33 -> 160 channels, 102 tiles, n = 4: 202 against 197; n = 5 / 7 at
-    // 122 tiles 265 / 445 against 298 / 502; 33 -> 96, n = 2, 102 tiles: 59 against 70; 64 -> 16, n = 5: 56 against 34;
-    // 33 -> 256 at 133 tiles, n = 2 / 5 / 7: 186 / 511 / 894 against 177 / 472 / 801)
-    const bool late = p.cw == 1 && (g.n >= 5 ? g.Cout > 32 : g.n == 2 && g.Cout > 64);
-    if (nb < (late ? 130 : 100) || nb > 0x3FFFFFFF) return false;
+    // input channels, take as long for half the channels, and that pipe splits further with many output channels: from
+    // there on they gain at n = 3 and 4 only (33 -> 160 channels, n = 4, 102 tiles: 202 against 197).  n = 5 and 7, 33 ->
+    // 160: 102 tiles 263 / 441 against 297 / 502, 122 tiles 265 / 445 against 298 / 502, 133 tiles 330 / 559 against
+    // 297 / 504; n = 6 355 against 399 at 102, 428 against 400 at 122; 33 -> 256, n = 5, 122 tiles 484 against 472; n = 2 only
+    // 33 -> 96, 59 against 70 (-> 64 and -> 128 gain); with few output channels all of them, 64 -> 64 as 64 -> 16 (n = 5,
+    // 102 tiles: 129 against 118, 56 against 34; 33 -> 64, n = 7: 191 against 204); 64 -> 160, n = 7, 122 tiles 525 against 480
+    int line = 100;
+    if (p.cw == 1 && g.n >= 5 && (g.Cout > 64 || (g.Cout > 32 && g.Cin < 40)))
+        line = (g.n == 7 && g.Cin < 56) || (g.n == 5 && g.Cout <= 160) ? 130 : 115;
+    if (p.cw == 1 && g.n == 2 && g.Cout > 64 && g.Cout <= 96) line = 115;
+    if (nb < line || nb > 0x3FFFFFFF) return false;
     p.blocks = (unsigned)nb;
     a.dHW = make_fastdiv((unsigned)hw);
     a.dW = make_fastdiv((unsigned)g.W);

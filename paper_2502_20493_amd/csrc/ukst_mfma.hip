@@ -541,21 +541,26 @@ static bool bf16_pipe(const Geom& g, int dtype)
 // Layers that the fp32 pipe does not take, of few channels and little work, where the vector ALUs are the faster ones:
 // an input channel costs them a step of a serial chain, the kernel on parts takes sixteen at once whether they are there
 // or not, and 32 output channels.  v: pixels times output channels.  (40 x 41 maps, us, vector ALUs against parts.
-// fp32, n = 2: 17 -> 31 channels, v = 8.1e5 12.8 / 14.4, 17 -> 63, 4.1e5 9.4 / 10.4, 12.4e5 (47) 14.5 / 10.2;
-// 35 -> 31, 4.1e5 15.2 / 15.6; 40 -> 17 11.9 / 13.5.  n = 3: 17 -> 17, 4.5e5 15.8 / 16.5; 17 -> 31, 8.1e5 18.7 / 17.5;
-// 21 -> 31, 4.1e5 16.4 / 17.3.  n = 4: 17 -> 31, 4.1e5 17.1 / 19.8.  n = 5: 17 -> 7 28.0 / 31.9.  21 -> 5, 128 images,
-// n = 2 / 3 / 4 / 5: 22 / 34 / 43 / 58 against 27 / 36 / 46 / 61; 25 -> 7, 64 images, n = 3 27 / 20.  bf16, n = 2: 17 -> 80
-// 8.2 / 9.3, 23 -> 17 9.6 / 8.9)
+// fp32, n = 2: 17 -> 31 channels, v = 8.1e5 12.8 / 14.4, 17 -> 63, 4.1e5 9.4 / 10.4, 17 -> 47, 12.4e5 14.5 / 10.2; 25 -> 31,
+// 4.1e5 12.0 / 13.6; 35 -> 17, 2.2e5 13.5 / 14.4, 35 -> 17, 4.5e5 15.9 / 14.8; 43 -> 7 14.3 / 13.2; 16 -> 22 8.6 / 10.5.
+// n = 3: 17 -> 17, 4.5e5 15.8 / 16.5; 17 -> 31, 8.1e5 18.7 / 17.5; 21 -> 31, 4.1e5 16.4 / 17.3; 16 -> 33 11.7 / 9.9.  n = 4:
+// 17 -> 31, 4.1e5 17.1 / 19.8.  n = 5: 17 -> 7 28.0 / 31.9.  19 -> 5, 128 images, n = 2 / 3 / 4 / 5: 21 / 32 / 39 / 53 against
+// 27 / 36 / 46 / 61; 21 -> 7, 64 images, n = 3 21.4 / 19.8.  bf16, n = 2: 17 -> 80, 1.5e5 8.2 / 9.3, 17 -> 31, 2.0e5
+// 9.8 / 9.4, 19 -> 7 8.4 / 7.9)
 static bool alus_win(const Geom& g, int dtype)
 {
     const double v = (double)g.B * g.H * g.W * g.Cout;
-    if (dtype != 0) return g.n == 2 && g.Cin < 20 && v < 2.1e5;
-    if (g.Cin >= 48) return false;
-    if (g.Cout <= 8 && g.Cin < 24) return true;
+    if (dtype != 0) return g.n == 2 && g.Cin == 17 && v < 1.55e5;
     const bool half = g.Cout <= 32;  // blocks of 32 channels
-    if (g.n == 2) return v < (g.Cin < 24 ? (half ? 8.2e5 : 5e5) : half ? 4.5e5 : 0.);
+    if (g.n == 2) {
+        if (g.Cin < 22 && g.Cout <= 8) return true;
+        if (half) return g.Cin <= 40 && v < (g.Cin < 22 ? 8.2e5 : g.Cin < 26 ? 4.2e5 : 3.3e5);
+        return g.Cin < 22 && v < (g.Cin >= 17 && g.Cin < 20 ? 5e5 : 3.3e5);
+    }
+    if (g.Cin == 16 || g.Cin >= 24) return false;
+    if (g.Cin < 20 && g.Cout <= 8) return true;
     if (g.n == 5) return false;  // (from 64 tiles on, below)
-    return g.Cin < 20 ? v < (half ? 7.5e5 : 4.2e5) : g.Cin < 24 && half && v < 4.1e5;
+    return g.Cin < 20 ? v < (half ? 7.5e5 : 3.9e5) : half && v < 4.1e5;
 }
 
 // Where the kernel on bf16 parts (ukst_mfma_parts_kernel.h) runs instead of the fp32 pipe or the vector

@@ -181,14 +181,14 @@ def test_mac_counts():
 
 def test_layers_of_few_channels_stay_on_the_vector_alus():
     """Where the kernel on bf16 parts is the slower one: a few channels and little work (fp32, n = 2 to 4, bf16, n = 2),
-    at most 8 output channels of fewer than 24 input channels whatever the work."""
+    at most 8 output channels of 17 to 19 (n = 2: up to 21) input channels whatever the work."""
     direct, parts = "ukst_direct_kernel", "ukst_mfma_f32_kernel_parts"
     for B, ci, co, n, dtype, kernel in (
             (8, 17, 31, 2, 0, direct), (64, 17, 31, 2, 0, parts), (4, 17, 63, 2, 0, direct), (16, 17, 63, 2, 0, parts),
-            (8, 35, 31, 2, 0, direct), (16, 35, 31, 2, 0, parts), (4, 35, 63, 2, 0, parts), (4, 51, 9, 2, 0, parts),
+            (8, 35, 17, 2, 0, direct), (8, 35, 31, 2, 0, parts), (4, 35, 63, 2, 0, parts), (4, 51, 9, 2, 0, parts),
             (8, 17, 31, 3, 0, direct), (64, 17, 31, 4, 0, parts), (8, 21, 31, 4, 0, direct), (8, 25, 31, 4, 0, parts),
-            (256, 21, 7, 3, 0, direct), (256, 21, 7, 5, 0, direct), (64, 25, 7, 3, 0, parts), (32, 17, 31, 5, 0, parts),
-            (1, 17, 80, 2, 1, direct), (2, 17, 80, 2, 1, parts), (1, 23, 17, 2, 1, parts), (1, 17, 17, 3, 1, parts)):
+            (256, 19, 7, 3, 0, direct), (256, 19, 7, 5, 0, direct), (256, 21, 7, 2, 0, direct), (64, 21, 7, 3, 0, parts), (64, 25, 7, 3, 0, parts), (32, 17, 31, 5, 0, parts),
+            (1, 17, 80, 2, 1, direct), (2, 17, 80, 2, 1, parts), (1, 19, 80, 2, 1, parts), (1, 23, 17, 2, 1, parts), (1, 17, 17, 3, 1, parts)):
         assert ukst.ukst_kernel_name(B, ci, co, 40, 41, n, 1, dtype) == kernel, (B, ci, co, n, dtype)
 
 
