@@ -14,7 +14,7 @@
 // than 64 input channels eight waves share one (128 channels x 256 pixels, two waves per SIMD), else four waves take 64
 // channels and two blocks share a compute unit.  A wave owns 64 channels x 64 pixels and reads 12 KiB of fragments per
 // tap for 24 MFMAs.  Weights go through LDS two taps at a time, the group after next on its way in registers.
-// fp32 pipe -> this kernel, 32 x 128 -> 128 channels: 63 x 63, n = 3 443 -> 257 us; 64 x 64, n = 4 674 -> 386, n = 5 960 -> 588.
+// fp32 pipe -> this kernel, 32 x 128 -> 128 channels: 63 x 63, n = 3 444 -> 259 us; 64 x 64, n = 4 671 -> 388, n = 5 953 -> 610.
 #include "ukst_parts.h"
 
 namespace ukst {

@@ -13,8 +13,8 @@
 // matrix pipes idle.)  Of a 16-pixel step at n = 3 a wave reads 23 KiB of fragments for 54 MFMAs of three parts,
 // about 0.4 of the LDS rate; staging a piece of four elements costs about 30 vector instructions and is what keeps
 // the pipes from more.  No more copies of dw than the fp32-pipe kernel writes, in the same layout.  fp32 pipe -> this
-// kernel, with the sum of the copies: fp32 32 x 128 -> 128 channels, 63 x 63, n = 3 509 -> 356 us, 64 x 64, n = 4 723 -> 557;
-// bf16 16 x 64 -> 64, 61 x 61, n = 3 / 4 96 -> 64 / 122 -> 58.
+// kernel, with the sum of the copies: fp32 32 x 128 -> 128 channels, 63 x 63, n = 3 509 -> 343 us, 64 x 64, n = 4 724 -> 544;
+// bf16 16 x 64 -> 64, 61 x 61, n = 3 / 4 96 -> 59 / 122 -> 55.
 #include "ukst_parts.h"
 
 namespace ukst {
@@ -353,13 +353,13 @@ bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
 {
     if (g.Cin < 32 || g.Cout < 32 || g.n < 3 || g.n > 4 || g.W < 16 || g.OW < 4) return false;
     // (n = 2, 64 x 64 maps: 290 against 289 us, four taps do not pay for their staging)  Few pixels leave the
-    // slices a stage or two: 2 images of 16 x 16 19 against 23 us, 4 of 20 x 33 36 against 39, 64 of 16 x 16 with
-    // n = 4 77 against 49
+    // slices a stage or two and gain nothing: 64 -> 64 channels, 2 images of 16 x 16, n = 3 18.8 against 19.2 us, 4 of
+    // 20 x 33 28.2 against 28.0, 64 of 16 x 16 with n = 4 58 against 46
     if ((long long)g.B * g.H * g.W < 8192) return false;
-    // fp32: rows that fill less than 5/8 of their column tiles multiply too many zeros (64 images of 17 x 17,
-    // 128 -> 128 channels, n = 3 / 4: 111 / 157 us on the fp32 pipe against 112 / 163; 32 of 33 x 33, 64 -> 64, n = 3
-    // 82 against 85; 64 of 18 x 18 115 / 162 against 117 / 171; 40 of 31 x 31, n = 3 167 against 128;
-    // 64 of 20 x 20 130 / 186 against 124 / 184)
+    // fp32: rows that fill less than 5/8 of their column tiles multiply too many zeros for n = 4 (64 images of 17 x 17,
+    // 128 -> 128 channels, n = 3 / 4: 111 / 157 us on the fp32 pipe against 101 / 156; 64 of 18 x 18 115 / 162 against
+    // 107 / 163; 32 of 33 x 33, 64 -> 64, n = 3 83 against 75; 64 of 20 x 20, 128 -> 128, 129 / 186 against 115 / 178; 40
+    // of 31 x 31, n = 3 167 against 118)
     const int tiled_cols = g.W > 16 ? (g.W + 31) / 32 * 32 : 16;
     if (es == 4 && g.W * 8 < tiled_cols * 5) return false;
     // single buffer descriptors, 32-bit byte offsets

@@ -2,7 +2,8 @@
 // (24 significant bits = 3 x 8; each part is the remainder rounded to nearest even), so
 //     x*w = x0*w0 + (x0*w1 + x1*w0) + (x1*w1 + x0*w2 + x2*w0) + [x1*w2 + x2*w1 + x2*w2]
 // and the six products outside the bracket, each exact in fp32 and summed in fp32 by the MFMA, leave
-// out less than 2^-25 of a product.  v_mfma_f32_32x32x16_bf16 multiplies 16 times as fast as
+// out at most about 2^-24 of a product, half a unit in its last place (|x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|:
+// x = w = 1 + 2^-8 - 2^-17 comes to 1.98 * 2^-25).  v_mfma_f32_32x32x16_bf16 multiplies 16 times as fast as
 // v_mfma_f32_32x32x2_f32, so six of them per 16 channels take 6/16 of the time of the fp32 pipe, and
 // the sum is rounded 6 times per 16 channels instead of 8.  Measured against 64-bit sums the error is
 // below that of the fp32 pipe (128 channels x 25 taps: see the kernels that use this).
