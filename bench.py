@@ -11,8 +11,8 @@ ramps for the first ~100 ms after idle), 5 windows of `steps` launches each are 
 events on the launch stream; the MEDIAN window is reported (the spread is in `roofline.windows_us`).
 
 Prints ONE compact JSON line on stdout (detail rows go to stderr).  Besides the contract fields:
-  roofline      for the headline kernel (useful flops / launch duration against the fp32 MFMA
-                peak), with
+  roofline      for the headline kernel (useful flops / launch duration against the bf16 MFMA
+                peak / 6: six products of bf16 parts for one of fp32 values), with
     roofline.per_config   every benchmark configuration, forward and backward, each against the
                           roofline that bounds it: {us, frac, bound, peak, traffic_ratio}
     roofline.ceilings     what the chip sustains with nothing else going on (matrix pipes,
@@ -254,8 +254,8 @@ def measure_backward(w, which, steps, rotate_bytes=LLC_BYTES + (64 << 20)):
     med, best, per = time_windows(step, steps, 1, warm_seconds=0.2, windows=3, stream=stream)
     exact = 2 * ukst.ukst_mac_count(*shape, 0)
     bound = BOUND.get(w.name, "hbm")
-    if which == "grad_weight" and w.n == 5 and bound == "mfma_f32_parts":
-        bound = "mfma_f32"  # the kernel gradient of 5 x 5 kernels runs on the fp32 pipe
+    if bound in ("mfma_f32", "mfma_f32_parts"):  # the pipe the gradient runs on, whatever the forward layer does
+        bound = "mfma_f32_parts" if kernel.endswith("_parts") else "mfma_f32"
     roof = _roof(bound, exact, nbytes, med, kernel, measured_traffic(f"{w.name} {which}"))
     if bound != "hbm" and "mfma" not in kernel:
         roof["bound"] = "alu"  # fp32 vector peak = fp32 MFMA peak on this chip (157.3 TFLOP/s)
@@ -324,7 +324,7 @@ def measure_stack(steps, nsets=8):
 def measure_general(op, k, shape, steps):
     """Time one of the generalised operations of Sec. 5 (op = "strided": stride-k transpose
     convolution, "dilated": dilation-k convolution) on a synthetic fp32 layer; reported against the
-    fp32 vector peak (the kernel runs on the vector ALUs)."""
+    bf16 MFMA peak / 6 (the layers run on the matrix cores, from three bf16 parts per fp32 value)."""
     import torch
     from paper_2502_20493_amd import binding as ukst
     B, Cin, Cout, H, W, n, P = shape

@@ -279,7 +279,8 @@ const char* ukst_grad_kernel_name(int which, int B, int Cin, int Cout, int H, in
  * The two generalisations the paper's discussion (Sec. 5) points to.  Both use the computation
  * pattern of Algorithm 2 -- every output pixel selects, from its own coordinates, the taps that
  * can meet data, and no inserted zero is ever multiplied -- in one general vector-ALU kernel, and on
- * the matrix cores ("ukst_general_mfma_kernel") for layers of at least 16 input and 8 output channels.
+ * the matrix cores ("ukst_general_mfma_kernel") for layers of at least 16 input and 8 output channels
+ * (all but a few with hardly anything to multiply).
  *
  * ukst_conv_transpose2d_strided: transpose convolution with stride s (Algorithm 1 with s-1 zeros
  * between neighbouring pixels; s = 2 is ukst_conv_transpose2d).  s*s parity classes: output row oy
