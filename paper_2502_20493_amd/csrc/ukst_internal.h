@@ -77,8 +77,7 @@ inline FastDiv make_fastdiv(unsigned d)
     FastDiv f;
     f.d = d; f.M = 0; f.sh = 0;
     if (d <= 1) return f;
-    int l = 0;
-    while ((1ull << l) < d) ++l;
+    const int l = 32 - __builtin_clz(d - 1);  // 2^l >= d
     f.M = (unsigned)(((1ull << (31 + l)) / d) + 1);
     f.sh = l - 1;
     return f;
@@ -173,6 +172,23 @@ hipError_t launch_mfma_parts(const Geom& g, const void* x, const void* w, void* 
 bool mfma_parts_split_supported(const Geom& g, int dtype);
 hipError_t launch_mfma_parts_split(const Geom& g, const void* x, const void* w, float* y, Workspace& ws,
                                    hipStream_t stream);
+// Layers of few tiles: 32 x 32 or 16 x 16 output tiles on the fp32 matrix pipe, the sum dealt to the block's waves
+// (ukst_small_kernel.h).  X [B][K][XH][XW] -> Y [B][M][OH][OW]; op grad_input: X = dy, Y = dx, w [K][M][n][n],
+// else w [M][K][n][n].  step: of strided (2..4) and dilated.  dtype as in launch_mfma (2 only forward)
+enum class SmallOp { forward, grad_input, strided, dilated };
+struct SmallProblem {
+    SmallOp op;
+    int B, K, M, XH, XW, OH, OW, n, P, step, dtype;
+};
+long long small_blocks(const SmallProblem& q);  // the layer's size in 32 x 32 tiles, 0 if the kernels do not take it
+// bytes of workspace with which fp32 forward layers of very few blocks run in slices (without, or with less: unsliced)
+size_t small_workspace(const SmallProblem& q);
+hipError_t launch_small(const SmallProblem& q, const Epilogue& ep, const void* x, const void* w, void* y, Workspace& ws,
+                        hipStream_t stream);
+// y[i] = part[0][i] + part[1][i] + ... in this order, `ks` copies copy_bytes apart, then the epilogue
+hipError_t launch_sum_slices(const void* part, size_t copy_bytes, float* y, size_t total, int ks, const Epilogue& ep,
+                             unsigned plane, unsigned cout, hipStream_t stream);
+
 bool thin_mfma_supported(const Geom& g, int dtype);
 hipError_t launch_thin_mfma(const Geom& g, const void* x, const void* w, float* y, hipStream_t stream);
 

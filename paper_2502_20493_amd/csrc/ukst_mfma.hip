@@ -598,12 +598,38 @@ static bool prefer_parts_split(const Geom& g, int dtype)
            mfma_parts_split_supported(g, dtype);
 }
 
-bool mfma_auto_extra(const Geom& g, int dtype)
+// Layers of few tiles and a long sum: small tiles whose waves split the sum (ukst_small_kernel.h).  In 32 x 32 tiles: fp32
+// layers up to two rounds of the compute units (n = 2, 3) or a little more, where the other kernels, with tiles sixteen
+// times as large, are a serial chain on a few of them; bf16 layers, which multiply 16 times as fast on their own pipe, up to one.
+// Against the kernel on parts, the fp32 pipe's wider tiles, the vector ALUs, over 160 drawn layers (us): fp32 414 -> 217
+// channels, 5 images of 12 x 12, n = 3 82 -> 24; 733 -> 358, 5 of 5 x 5, n = 5 385 -> 62; 512 -> 256, 64 of 4 x 4, n = 4 46.9 ->
+// 37; 161 -> 158, 20 of 7 x 21, n = 3, 405 tiles 40.1 -> 23.5, but 83 -> 72, 3 of 54 x 54, 861 tiles
+// 26.5 -> 30.0 and n = 2, 672 -> 232, 800 tiles 71 -> 80; bf16 120 -> 176, n = 2, 348 tiles 18.5 -> 13.5 but 63 ->
+// 32, n = 4, 289 tiles 14.2 -> 15.4.  Below 52 channels there is little to split (2 images, 33 -> 21 channels, 9 x 11: 13 -> 10),
+// and layers of up to four output channels have kernels of their own up to 96 channels (104 -> 4 14.8 -> 10.1; 56 -> 4 9.5 ->
+// 9.8).
+static SmallProblem small_problem(const Geom& g, int dtype)
 {
-    return !mfma_supported(g, dtype) && prefer_parts(g, dtype);
+    return SmallProblem{SmallOp::forward, g.B, g.Cin, g.Cout, g.H, g.W, g.OH, g.OW, g.n, g.P, 2, dtype};
 }
 
-bool mfma_any_alignment(const Geom& g, int dtype) { return prefer_parts(g, dtype); }
+static bool prefer_small(const Geom& g, int dtype)
+{
+    if (g.Cin < (g.Cout <= 4 ? 96 : 52) || g.n > 5 || (double)g.B * g.KH * g.KW * g.Cout > 1024. * 1024. * 2.) return false;
+    const long long tiles = small_blocks(small_problem(g, dtype));
+    if (dtype != 0) return tiles > 0 && tiles <= 256 && !bf16_pipe(g, dtype);
+    if (g.Cout <= 4) return tiles > 0 && tiles <= 256;
+    // output-aligned quads: 64 images, 128 -> 64 channels, 16 x 16, n = 4, 1024 tiles, 49.5 -> 42.6 (parts 42.4)
+    const bool aligned = g.P % 2 == 0 && (g.n == 4 || (g.n == 2 && g.Cin % 128 == 0));
+    return tiles > 0 && tiles <= (aligned ? 1024 : g.n <= 3 ? 512 : 700);
+}
+
+bool mfma_auto_extra(const Geom& g, int dtype)
+{
+    return prefer_small(g, dtype) || (!mfma_supported(g, dtype) && prefer_parts(g, dtype));
+}
+
+bool mfma_any_alignment(const Geom& g, int dtype) { return prefer_small(g, dtype) || prefer_parts(g, dtype); }
 
 bool mfma_supported(const Geom& g, int dtype)
 {
@@ -621,15 +647,35 @@ bool mfma_needs_aligned_x(const Geom& g, int dtype)
 hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, int dtype,
                        Workspace& ws, hipStream_t stream)
 {
-    if (prefer_parts(g, dtype)) return launch_mfma_parts(g, x, w, y, dtype, ws, stream);
-    if (prefer_parts_split(g, dtype)) {
+    const bool small = prefer_small(g, dtype);
+    if (!small && prefer_parts(g, dtype)) return launch_mfma_parts(g, x, w, y, dtype, ws, stream);
+    // (of the layers for the small tiles only those that are long on them too)
+    if (prefer_parts_split(g, dtype) && (!small || small_blocks(small_problem(g, dtype)) > 256)) {
         Workspace need;
         need.query = true;
         const hipError_t e = launch_mfma_parts_split(g, nullptr, nullptr, nullptr, need, stream);
         if (e == hipSuccess && (ws.query || (ws.ptr != nullptr && ws.bytes >= need.need)))
             return launch_mfma_parts_split(g, x, w, y, ws, stream);
     }
-    if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)))
+    // even n and P, whole stages of 64 (n = 2: 128) channels: slices, if they are of use
+    const bool slices = g.n % 2 == 0 && g.P % 2 == 0 && g.Cin % (g.n == 2 ? 128 : 64) == 0;
+    if (small && (!ws.query || slices)) {
+        if (ws.query) {
+            ws.need = small_workspace(small_problem(g, dtype));
+            return hipSuccess;
+        }
+        // the others need no workspace; what is asked for, and refused if it is too small, is what the kernel asks for
+        // that runs such layers beyond the line
+        if (ws.ptr != nullptr && !slices && mfma_f32_supported(g, dtype) && !prefer_parts(g, dtype)) {
+            Workspace need;
+            need.query = true;
+            const hipError_t e = launch_mfma_f32(g, nullptr, nullptr, nullptr, dtype, need, stream);
+            if (e != hipSuccess) return e;
+            if (ws.bytes < need.need && ((uintptr_t)y & 15) == 0) return kWorkspaceTooSmall;
+        }
+        return launch_small(small_problem(g, dtype), g.ep, x, w, y, ws, stream);
+    }
+    if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)) && !(small && prefer_parts(g, dtype)))
         return launch_mfma_f32(g, x, w, y, dtype, ws, stream);
     if (ws.query) return hipSuccess;  // the kernels below use no scratch
     if (dtype == 0) return launch_thin_mfma(g, x, w, y, stream);
@@ -674,6 +720,7 @@ const char* mfma_kernel_name(const Geom& g, int dtype)
 {
     if (bf16_pipe(g, dtype))  // bf16 in; fp32 or bf16 out
         return prefer_aligned(g, dtype) ? "ukst_mfma_bf16_aligned_kernel" : "ukst_mfma_bf16_kernel";
+    if (prefer_small(g, dtype)) return "ukst_mfma_f32_kernel";
     if (prefer_parts(g, dtype)) return "ukst_mfma_f32_kernel_parts";
     return mfma_f32_supported(g, dtype) ? "ukst_mfma_f32_kernel" : "ukst_thin_mfma_kernel";
 }

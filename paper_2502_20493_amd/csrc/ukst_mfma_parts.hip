@@ -167,6 +167,14 @@ static hipError_t launch_sides(const PartsArgs& a, const Config& c, const Epilog
     }
 }
 
+hipError_t launch_sum_slices(const void* part, size_t copy_bytes, float* y, size_t total, int ks, const Epilogue& ep,
+                             unsigned plane, unsigned cout, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ukst_sum_part_slices_kernel, dim3((unsigned)((total + 1023) / 1024)), dim3(256), 0, stream,
+                       (const float4*)part, copy_bytes / 16, y, (int)total, ks, ep.bias, ep.act, plane, cout);
+    return hipGetLastError();
+}
+
 // fp32 layers with a workspace: partial sums of the slices, added in slice order
 hipError_t launch_mfma_parts_split(const Geom& g, const void* x, const void* w, float* y, Workspace& ws, hipStream_t stream)
 {
@@ -179,11 +187,8 @@ hipError_t launch_mfma_parts_split(const Geom& g, const void* x, const void* w, 
     const Epilogue none = {nullptr, 0};
     const hipError_t e = launch_sides(a, c, none, x, w, ws.ptr, 0, stream);
     if (e != hipSuccess) return e;
-    const size_t total = (size_t)g.B * g.Cout * g.OH * g.OW;
-    hipLaunchKernelGGL(ukst_sum_part_slices_kernel, dim3((unsigned)((total + 1023) / 1024)), dim3(256), 0, stream,
-                       (const float4*)ws.ptr, a.copy_bytes / 16, y, (int)total, a.ksplit, g.ep.bias, g.ep.act,
-                       (unsigned)(g.OH * g.OW), (unsigned)g.Cout);
-    return hipGetLastError();
+    return launch_sum_slices(ws.ptr, a.copy_bytes, y, (size_t)g.B * g.Cout * g.OH * g.OW, a.ksplit, g.ep,
+                             (unsigned)(g.OH * g.OW), (unsigned)g.Cout, stream);
 }
 
 hipError_t launch_mfma_parts(const Geom& g, const void* x, const void* w, void* y, int dtype, Workspace& ws,

@@ -1,0 +1,15 @@
+// Small tiles on the fp32 matrix pipe (ukst_small_kernel.h): instances of one kind and operand type.
+#include "ukst_small_kernel.h"
+
+namespace ukst {
+namespace small {
+
+template <>
+hipError_t launch_kind<kInputGrad, float>(const SmallArgs& a, int n, int s, int mt, int wv, const Epilogue& ep, const void* x,
+                                const void* w, void* y, hipStream_t st)
+{
+    return launch_kind_impl<kInputGrad, float>(a, n, s, mt, wv, ep, x, w, y, st);
+}
+
+}  // namespace small
+}  // namespace ukst

@@ -1,0 +1,114 @@
+"""The small tiles of the fp32 matrix pipe (layers of few tiles and a long sum): tails of the channels and of the tiles,
+several images per tile, every quad alignment, the last stage that repeats channels, and operands that are not finite."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_20493_amd import binding as ukst
+from paper_2502_20493_amd import workloads as wl
+from gpu_util import TOL, check_against_oracle, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# B, Cin, Cout, H, W, n, P, dtype
+FORWARD_SHAPES = [
+    (1, 52, 8, 4, 4, 4, 2, "f32"),       # one tile of 16 x 16, half of it empty
+    (3, 53, 33, 5, 7, 4, 2, "f32"),      # a last stage of one new channel, a second channel tile of one
+    (5, 61, 40, 5, 5, 3, 0, "f32"),      # several images per tile, odd output
+    (2, 70, 65, 9, 17, 2, 0, "f32"),     # columns in three tiles of six
+    (2, 66, 17, 6, 9, 2, 3, "f32"),      # P beyond the kernel
+    (1, 101, 35, 33, 11, 5, 4, "f32"),   # n = 5, seven and a half windows of P
+    (64, 128, 64, 6, 6, 4, 2, "f32"),    # blocks of four waves
+    (3, 97, 4, 8, 8, 5, 1, "f32"),       # a thin output
+    (3, 60, 33, 5, 7, 4, 1, "bf16"),
+    (2, 77, 35, 7, 5, 5, 3, "bf16"),
+    (9, 64, 40, 3, 3, 3, 2, "bf16"),
+]
+
+
+def _mk(shape):
+    B, Cin, Cout, H, W, n, P, dtype = shape
+    return wl.Workload("small", 9500 + sum(shape[:7]), B, Cin, Cout, H, W, n, P, dtype, "normal", "normal:0.5")
+
+
+@pytest.mark.parametrize("shape", FORWARD_SHAPES)
+def test_forward_every_element(shape):
+    w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    assert ukst.ukst_kernel_name(*shape[:7], dt) == "ukst_mfma_f32_kernel"
+    for integer in (True, False):
+        print(f"case {shape} integer={integer}", flush=True)
+        data = wl.generate(w, integer=integer)
+        y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+        y = run_gpu(data, w.dtype, w.P, guard=4096)
+        check_against_oracle(y, y_ref, S, TOL["f32"], exact=integer)  # (bf16 products are exact in fp32)
+
+
+@pytest.mark.parametrize("out_bf16", [False, True])
+@pytest.mark.parametrize("act", [ukst.UKST_ACT_RELU, ukst.UKST_ACT_TANH])
+def test_epilogue_and_bf16_output(act, out_bf16):
+    import torch
+    from gpu_util import to_device
+    w = _mk(FORWARD_SHAPES[8] if out_bf16 else FORWARD_SHAPES[2])
+    data = wl.generate(w)
+    x, k = to_device(data, w.dtype)
+    bias = np.linspace(-1.0, 1.0, w.Cout).astype(np.float32)
+    y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+    z = y_ref + bias.astype(np.float64)[None, :, None, None]
+    z = np.maximum(z, 0.0) if act == ukst.UKST_ACT_RELU else np.tanh(z)
+    y = ukst.ukst_conv_transpose2d_bias_act(x, k, w.P, bias=torch.from_numpy(bias).cuda(), act=act, out_bf16=out_bf16)
+    got = y.float().cpu().numpy().astype(np.float64)
+    # the fp32 sum, half an ulp of the biased value, the activation's own error, half a bf16 ulp
+    slack = TOL["f32"] * S + 1.2e-7 * np.abs(y_ref) + (2e-6 if act == ukst.UKST_ACT_TANH else 0.0)
+    assert (np.abs(got - z) <= slack + (2.0 ** -8 * np.abs(z) if out_bf16 else 0.0)).all()
+
+
+@pytest.mark.parametrize("what", ["weight_inf", "inf", "nan", "huge"])
+@pytest.mark.parametrize("shape", [FORWARD_SHAPES[1], FORWARD_SHAPES[2], FORWARD_SHAPES[9]])
+def test_forward_operands_that_are_not_finite(shape, what):
+    """They reach the outputs whose sums hold them: the halo is left out, not multiplied by zero, and neither are the
+    channels that a last stage repeats."""
+    import torch
+    w = _mk(shape)
+    data = wl.generate(w)
+    x, k = data["x"].copy(), data["w"].copy()
+    if what == "weight_inf":
+        k[3, 2, 0, 1], k[4, w.Cin - 3, w.n - 1, w.n - 1] = np.inf, -np.inf
+    elif what == "huge":
+        x[0, 5, 2, 3] = 3e38
+        k[:, 5] *= 100.0
+    else:
+        x[0, 3, 2, 4], x[w.B - 1, w.Cin - 4, 0, 0] = (np.inf, -np.inf) if what == "inf" else (np.nan, np.nan)
+    dt = torch.float32 if w.dtype == "f32" else torch.bfloat16
+    x, k = torch.from_numpy(x).to(dt), torch.from_numpy(k).to(dt)
+    y = ukst.ukst_conv_transpose2d(x.cuda(), k.cuda(), w.P).cpu().numpy()
+    # (products that overflow do so in any order of the sums: 3e38 against weights of 100 and more)
+    ref = torch.nn.functional.conv_transpose2d(x.double(), k.double().flip(2, 3).transpose(0, 1), stride=2)
+    pad = w.P - (w.n - 1)
+    ref = torch.nn.functional.pad(ref, (pad, pad, pad, pad)).numpy()
+    with np.errstate(over="ignore"):
+        ref32 = ref.astype(np.float32)
+    assert np.array_equal(np.isnan(ref32), np.isnan(y))
+    inf = np.isinf(ref32)
+    assert np.array_equal(inf, np.isinf(y)) and np.array_equal(ref32[inf], y[inf])
+    ok = np.isfinite(ref32)
+    scale = 3e38 * 1e2 * 1e-7 if what == "huge" else 1.0
+    assert (np.abs(y[ok] - ref32[ok]) <= 1e-5 * np.abs(ref32[ok]) + 1e-3 * scale).all()
+
+
+def test_element_alignment_and_repeat_runs():
+    import torch
+    from gpu_util import to_device
+    for shape in (FORWARD_SHAPES[2], FORWARD_SHAPES[9]):
+        w = _mk(shape)
+        data = wl.generate(w, integer=True)
+        x, k = to_device(data, w.dtype)
+
+        def off(t, n):
+            buf = torch.empty(t.numel() + 64, dtype=t.dtype, device="cuda")
+            return buf[n:n + t.numel()].view(t.shape).copy_(t)
+        y = ukst.ukst_conv_transpose2d(off(x, 1), off(k, 3), w.P)
+        y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+        check_against_oracle(y.cpu().numpy(), y_ref, S, TOL["f32"], exact=True)
+        a, b = (ukst.ukst_conv_transpose2d(x, k, w.P) for _ in range(2))
+        assert torch.equal(a, b)
