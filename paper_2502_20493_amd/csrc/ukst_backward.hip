@@ -2331,6 +2331,49 @@ hipError_t launch_gw_t(const Geom& g, const void* x, const void* dy, float* dw, 
 
 }  // namespace
 
+namespace {
+
+SmallProblem small_problem(const Geom& g, int dtype)
+{
+    return SmallProblem{SmallOp::grad_input, g.B, g.Cout, g.Cin, g.OH, g.OW, g.H, g.W, g.n, g.P, 2, dtype};
+}
+
+// Input gradients on the small tiles (ukst_small_kernel.h), in 32 x 32 tiles.  Where the fp32 pipe's own kernel would run,
+// always: its blocks of 64 channels x 256 pixels pack the weights first and add slices afterwards (us, its time against the
+// small tiles': 27 images, 144 <- 454 channels, 10 x 18, n = 4 601 / 118; 104 <- 368, 14 of 5 x 16, n = 2 35.6 / 18.4; over 124
+// drawn layers 1.27 to 6 times as fast).  Against the vector ALUs, which take layers of fewer than 32 input channels, up to the
+// tile counts where those catch up (24 <- 456, 4 of 11 x 5, n = 2 343 / 15; 24 <- 256 bf16, 56 of 20 x 20, n = 4 434 / 76; fp32 120 <- 13,
+// 1136 tiles 13.0 / 15.6).  Against the bf16 pipe, which multiplies 16 times as fast, only with a long sum and up to
+// about a round of blocks (72 <- 248, 11 of 10 x 22, n = 4 99 / 27; 216 <- 176, 12 of 9 x 9 33.0 / 20.7; 112 <- 112, 4 of 26 x 26, n = 5, 368
+// tiles 36.2 / 39.6).
+bool prefer_small(const Geom& g, int dtype)
+{
+    if (g.n < 2 || g.n > 5 || g.Cin < 16 || g.Cout < 8 || grad_narrow_supported(g, dtype)) return false;
+    GiMfmaArgs ma;
+    const bool b16 = dtype == 1 && (grad_input_window_supported(g, dtype) || gi_mfma_args(g, ma, true));
+    const bool wide = gi_mfma_args(g, ma);
+    if (!b16 && wide && dtype == 0 && grad_input_parts_supported(g)) return false;
+    if (b16 && g.Cout < 72) return false;
+    const long long tiles = small_blocks(small_problem(g, dtype));
+    return tiles > 0 && tiles <= (b16 ? 300 : !wide && dtype == 0 ? 1000 : 2500);
+}
+
+hipError_t launch_gi(const Geom& g, const void* dy, const void* w, float* dx, int dtype, Workspace& ws, hipStream_t stream)
+{
+    switch (g.n) {
+        case 1: return launch_gi_n<1>(g, dy, w, dx, dtype, ws, stream);
+        case 2: return launch_gi_n<2>(g, dy, w, dx, dtype, ws, stream);
+        case 3: return launch_gi_n<3>(g, dy, w, dx, dtype, ws, stream);
+        case 4: return launch_gi_n<4>(g, dy, w, dx, dtype, ws, stream);
+        case 5: return launch_gi_n<5>(g, dy, w, dx, dtype, ws, stream);
+        case 6: return launch_gi_n<6>(g, dy, w, dx, dtype, ws, stream);
+        case 7: return launch_gi_n<7>(g, dy, w, dx, dtype, ws, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
 const char* grad_kernel_name(const Geom& g, int which, int dtype)
 {
     if (which == 1) {
@@ -2348,6 +2391,7 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
                       : g.n == 4 ? gw_thin_pick<4>(g, ta, MT, CT) : g.n == 5 ? gw_thin_pick<5>(g, ta, MT, CT) : false;
         return th ? "ukst_grad_weight_thin_mfma_kernel" : "ukst_grad_weight_kernel";
     }
+    if (prefer_small(g, dtype)) return "ukst_grad_input_mfma_kernel";
     if (grad_input_window_supported(g, dtype)) return "ukst_grad_input_window_mfma_bf16_kernel";
     if (grad_narrow_supported(g, dtype)) return "ukst_grad_input_narrow_kernel";
     GiMfmaArgs ma;
@@ -2359,16 +2403,15 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
 hipError_t launch_grad_input(const Geom& g, const void* dy, const void* w, float* dx, int dtype,
                              Workspace& ws, hipStream_t stream)
 {
-    switch (g.n) {
-        case 1: return launch_gi_n<1>(g, dy, w, dx, dtype, ws, stream);
-        case 2: return launch_gi_n<2>(g, dy, w, dx, dtype, ws, stream);
-        case 3: return launch_gi_n<3>(g, dy, w, dx, dtype, ws, stream);
-        case 4: return launch_gi_n<4>(g, dy, w, dx, dtype, ws, stream);
-        case 5: return launch_gi_n<5>(g, dy, w, dx, dtype, ws, stream);
-        case 6: return launch_gi_n<6>(g, dy, w, dx, dtype, ws, stream);
-        case 7: return launch_gi_n<7>(g, dy, w, dx, dtype, ws, stream);
-        default: return hipErrorInvalidValue;
-    }
+    if (ws.query || !prefer_small(g, dtype)) return launch_gi(g, dy, w, dx, dtype, ws, stream);
+    // (the small tiles use no workspace; what is asked for and refused is what the kernel beyond the line asks for)
+    Workspace need;
+    need.query = true;
+    const hipError_t e = launch_gi(g, nullptr, nullptr, nullptr, dtype, need, stream);
+    if (e != hipSuccess) return e;
+    if (ws.bytes < need.need) return kWorkspaceTooSmall;
+    Workspace none;
+    return launch_small(small_problem(g, dtype), Epilogue{nullptr, 0}, dy, w, dx, none, stream);
 }
 
 hipError_t launch_grad_weight(const Geom& g, const void* x, const void* dy, float* dw, int dtype,

@@ -112,11 +112,30 @@ __global__ __launch_bounds__(256) void ukst_general_kernel(const TIn* __restrict
 
 }  // namespace
 
+// Layers of few tiles (ukst_small_kernel.h), in 32 x 32 tiles of a dilated layer, 16 x 16 tiles of every class of a strided
+// one.  Up to these the kernel on parts, whose blocks take 64 channels x 256 lattice pixels of one class, is a serial chain
+// on a part of the chip (us, its time against the small tiles': dilation 2, 192 -> 120 channels, 18 of 9 x 9, n = 5 251 / 28;
+// dilation 3, 72 -> 39, 2 of 16 x 85, n = 3 128 / 10; stride 4, 136 -> 96, 2 of 14 x 14, n = 3 29.3 / 9.5), beyond them it
+// catches up (fp32 dilation 2, 328 -> 23, n = 3, 2940 tiles 178 / 198; bf16 40 -> 136, n = 3, 912 tiles 41 / 38, 24 -> 272, n = 4, 1440
+// tiles 23.1 / 25.5; stride 3, 16 -> 40, n = 5, 756 tiles 13.1 / 17.9, bf16 96 -> 214, 1638 tiles 24.5 / 49)
+static bool prefer_small(const SmallProblem& q)
+{
+    if (q.K < 16 || q.M < 8 || q.n < 2 || q.n > 5) return false;
+    if (q.op == SmallOp::strided && q.step != 3 && q.step != 4) return false;
+    const long long tiles = small_blocks(q, q.op == SmallOp::strided ? 16 : 32);
+    return tiles > 0 && tiles <= (q.op == SmallOp::strided ? (q.dtype == 0 ? 512 : 256) : q.dtype == 0 ? 1200 : 512);
+}
+
 // k = stride (dilated == 0) or dilation (dilated == 1); shapes validated by the caller
 hipError_t launch_general(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k,
                           int OH, int OW, const void* x, const void* w, float* y, int dtype,
                           hipStream_t stream)
 {
+    const SmallProblem q{dilated ? SmallOp::dilated : SmallOp::strided, B, Cin, Cout, H, W, OH, OW, n, P, k, dtype};
+    if (prefer_small(q)) {
+        Workspace none;
+        return launch_small(q, Epilogue{nullptr, 0}, x, w, y, none, stream);
+    }
     hipError_t err = hipSuccess;
     if (launch_general_mfma(dilated, B, Cin, Cout, H, W, n, P, k, OH, OW, x, w, y, dtype, stream, &err)) return err;
     GenArgs a;

@@ -180,7 +180,7 @@ struct SmallProblem {
     SmallOp op;
     int B, K, M, XH, XW, OH, OW, n, P, step, dtype;
 };
-long long small_blocks(const SmallProblem& q);  // the layer's size in 32 x 32 tiles, 0 if the kernels do not take it
+long long small_blocks(const SmallProblem& q, int edge = 32);  // its edge x edge tiles, 0 if the kernels do not take it
 // bytes of workspace with which fp32 forward layers of very few blocks run in slices (without, or with less: unsliced)
 size_t small_workspace(const SmallProblem& q);
 hipError_t launch_small(const SmallProblem& q, const Epilogue& ep, const void* x, const void* w, void* y, Workspace& ws,

@@ -173,11 +173,11 @@ hipError_t launch_t(const SmallProblem& q, const SmallArgs& a, int mt, int wv, c
 
 }  // namespace
 
-long long small_blocks(const SmallProblem& q)
+long long small_blocks(const SmallProblem& q, int edge)
 {
     SmallArgs a;
     if (!make_args(q, 16, a) && !make_args(q, 32, a)) return 0;
-    const long long m = (q.M + 31) / 32, p = (a.Q + 31) / 32;
+    const long long m = (q.M + edge - 1) / edge, p = (a.Q + edge - 1) / edge;
     return m * p * a.nct * a.res * a.res;
 }
 

@@ -214,9 +214,11 @@ __device__ __forceinline__ void small_tile(const TIn* __restrict__ x, const TIn*
     };
     auto store_x = [&](int k, int j) __attribute__((always_inline)) { Xs[k * L::XPL + 64 * j + lane] = __uint_as_float(B16 ? xr[k][j] << 16 : xr[k][j]); };
 
-    acc_t acc[NC];
+    // (one class: its taps in turn on four accumulators, a quarter of the roundings in a chain)
+    constexpr int NA = NC == 1 ? 4 : NC;
+    acc_t acc[NA];
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NA; ++c)
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[c][i] = 0.f;
 
@@ -236,7 +238,7 @@ __device__ __forceinline__ void small_tile(const TIn* __restrict__ x, const TIn*
         }
     };
     auto multiply = [&](int kk, int t) __attribute__((always_inline)) {
-        const int ta = t / N, tb = t % N, c = NC == 1 ? 0 : ta % S * S + tb % S;
+        const int ta = t / N, tb = t % N, c = NC == 1 ? t % 4 : ta % S * S + tb % S;
         const float af = av[kk & 1][t], bf = bv[kk & 1][place_of(KIND, N, S, ta) * WIN + place_of(KIND, N, S, tb)];
         if constexpr (MT == 32) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(af, bf, acc[c], 0, 0, 0);
         else acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(af, bf, acc[c], 0, 0, 0);
@@ -297,6 +299,7 @@ __device__ __forceinline__ void small_tile(const TIn* __restrict__ x, const TIn*
         });
     }
 
+    if constexpr (NC == 1) acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     // ---- the waves' sums meet in LDS, four rows (output channels) at a time: [wave][class][row group][lane]
     __syncthreads();
     constexpr int RG = R / 4;

@@ -112,3 +112,98 @@ def test_element_alignment_and_repeat_runs():
         check_against_oracle(y.cpu().numpy(), y_ref, S, TOL["f32"], exact=True)
         a, b = (ukst.ukst_conv_transpose2d(x, k, w.P) for _ in range(2))
         assert torch.equal(a, b)
+
+
+# B, Cin, Cout, H, W, n, P, dtype
+GRAD_INPUT_SHAPES = [
+    (3, 17, 9, 5, 5, 4, 2, "f32"),       # several images per tile, two channel tiles of 16, a stage of nine channels
+    (2, 33, 40, 7, 19, 3, 0, "f32"),     # odd rows of dy
+    (1, 70, 53, 11, 6, 5, 4, "f32"),     # a last stage of one new channel
+    (5, 40, 24, 3, 4, 2, 1, "f32"),
+    (2, 16, 30, 9, 9, 4, 6, "f32"),      # P beyond the kernel
+    (9, 130, 72, 6, 7, 4, 1, "bf16"),
+    (2, 24, 37, 9, 10, 3, 2, "bf16"),
+    (2, 19, 16, 6, 5, 5, 0, "bf16"),     # an odd number of channels of 25 taps
+]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("shape", GRAD_INPUT_SHAPES)
+def test_input_gradient_every_element(shape, integer):
+    from gpu_util import check_elements, run_gpu_grad_input
+    w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    if shape[:2] != (2, 19):  # (the vector ALUs keep that one)
+        assert ukst.ukst_grad_kernel_name(0, *shape[:7], dt) == "ukst_grad_input_mfma_kernel"
+    print(f"case {shape} integer={integer}", flush=True)
+    data = wl.generate(w, integer=integer)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
+    ref, S = oracle.grad_input(dyd["dy"], data["w"], w.H, w.W, w.P)
+    got = run_gpu_grad_input(data, dyd, w.dtype, w.H, w.W, w.P, guard=4096)
+    check_elements(got, ref, S, TOL["f32"], exact=integer)
+
+
+# op, step, B, Cin, Cout, H, W, n, P; the last two of each beyond the line, on the kernel for larger layers
+GENERAL_SHAPES = [
+    ("strided", 3, (2, 17, 9, 7, 9, 4, 2)), ("strided", 4, (1, 53, 33, 6, 11, 5, 3)), ("strided", 4, (3, 20, 16, 5, 5, 3, 7)),
+    ("strided", 3, (1, 21, 35, 64, 70, 5, 2)), ("strided", 4, (2, 33, 40, 61, 63, 3, 1)),
+    ("dilated", 2, (3, 33, 17, 9, 9, 5, 4)), ("dilated", 3, (2, 61, 40, 10, 17, 3, 4)), ("dilated", 4, (7, 20, 9, 5, 6, 4, 6)),
+    ("dilated", 1, (2, 19, 33, 8, 9, 2, 1)), ("dilated", 8, (1, 16, 8, 20, 20, 3, 9)),
+    ("dilated", 2, (3, 17, 70, 90, 95, 3, 2)), ("dilated", 3, (2, 20, 100, 101, 97, 4, 5)),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", GENERAL_SHAPES)
+def test_strided_and_dilated_every_element(case, dtype):
+    from test_gpu_general import _run
+    op, k, shape = case
+    w = wl.Workload("small_general", 9600 + sum(shape) + k, *shape, dtype, "normal", "normal:0.5")
+    _run(op, w, k, integer=True)
+    _run(op, w, k, integer=False)
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "weight_inf"])
+@pytest.mark.parametrize("op", ["grad_input", "strided", "dilated"])
+def test_other_operations_with_operands_that_are_not_finite(op, what):
+    """As for the forward layers; against the definitions in 64 bits, products with the padding left out."""
+    import torch
+    B, K, M, H, W, n, P, k = 2, 53, 20, 6, 7, 3, 1, 3
+    rng = np.random.default_rng(7)
+    wshape = (K, M, n, n) if op == "grad_input" else (M, K, n, n)
+    OH, OW = ukst.ukst_output_shape(H, W, n, P) if op == "grad_input" else (0, 0)
+    x = rng.normal(size=(B, K, OH, OW) if op == "grad_input" else (B, K, H, W)).astype(np.float32)
+    w = rng.normal(size=wshape).astype(np.float32)
+    if what == "weight_inf":
+        w[1, 2, 0, 1], w[3, 9, 2, 2] = np.inf, -np.inf
+    else:
+        x[0, 5, 2, 3], x[1, K - 2, 0, 0] = (np.inf, -np.inf) if what == "inf" else (np.nan, np.nan)
+    xt, wt = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    call = {"grad_input": lambda: ukst.ukst_conv_transpose2d_grad_input(xt, wt, H, W, P),
+            "strided": lambda: ukst.ukst_conv_transpose2d_strided(xt, wt, P, k),
+            "dilated": lambda: ukst.ukst_dilated_conv2d(xt, wt, P, k)}[op]
+    y = call().cpu().numpy()
+    ref = np.zeros(y.shape)
+    with np.errstate(invalid="ignore"):
+        for a in range(n):
+            for c in range(n):
+                for i in range(y.shape[2]):
+                    for j in range(y.shape[3]):
+                        if op == "grad_input":
+                            r, q = 2 * i + P - a, 2 * j + P - c
+                        elif op == "dilated":
+                            r, q = i - P + k * a, j - P + k * c
+                        else:
+                            r, q = i - P + a, j - P + c
+                            if r % k or q % k:
+                                continue
+                            r, q = r // k, q // k
+                        if 0 <= r < x.shape[2] and 0 <= q < x.shape[3]:
+                            t = w[:, :, a, c].astype(np.float64)
+                            t = t.T if op == "grad_input" else t
+                            ref[:, :, i, j] += (x[:, None, :, r, q].astype(np.float64) * t[None]).sum(-1)
+    assert np.array_equal(np.isnan(ref), np.isnan(y))
+    inf = np.isinf(ref)
+    assert np.array_equal(inf, np.isinf(y)) and np.array_equal(ref[inf], y[inf])
+    ok = np.isfinite(ref)
+    assert ok.any() and (np.abs(y[ok] - ref[ok]) <= 1e-5 * K * n * n * 16).all()
