@@ -1105,10 +1105,12 @@ struct GwMfmaArgs {
     int coTiles, ciTiles;
     int cols4;                 // four-column pieces per staged dy row
     int fast, npass;           // piecewise staging (rows of at least four elements), its passes per channel
+    int flush;                 // every stage is added to the copy of dw in memory
     FastDiv dC4, dRows, dLR;
 };
 
-template <int N, int NC, typename TIn>
+// FLUSH: every stage is added to the block's copy of dw in memory (see gw_mfma_args)
+template <int N, int NC, typename TIn, bool FLUSH>
 __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn* __restrict__ x,
                                                                       const TIn* __restrict__ dy,
                                                                       float* __restrict__ part, GwMfmaArgs a)
@@ -1131,6 +1133,8 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
     const int cot = bid % a.coTiles; bid /= a.coTiles;
     const int slice = bid;
     const int co0 = cot * 32, ci0 = cit * CI_T;
+    const __amdgpu_buffer_rsrc_t rs_out = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(part + (size_t)slice * g.Cout * g.Cin * NN), 0, (int)((size_t)g.Cout * g.Cin * NN * 4), kGwRsrcFlags);
 
     const int nts = (NN - wave + 3) / 4;   // taps of this wave: wave, wave + 4, ...
     int tapoff[TS];
@@ -1361,7 +1365,30 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
         };
         if (nts == TS) rows(std::integral_constant<int, TS>{});
         else rows(std::integral_constant<int, TS - 1>{});
+        if constexpr (FLUSH) {
+            const bool add = st > slice * a.stagesPerSlice;  // uniform
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) {
+                if (ts >= nts) continue;
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) {
+                    const int ci = ci0 + nc * 32 + l32;
+                    int row = (co0 + 4 * kk) * NN + wave + 4 * ts;
+                    asm("" : "+v"(row));  // (worked out here and not kept across the loop)
+                    const unsigned voff = ci < g.Cin ? (unsigned)((row * g.Cin + ci) * 4) : kGwInvalid;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const unsigned soff = (unsigned)((8 * (i / 4) + (i % 4)) * NN * g.Cin * 4);
+                        float v = acc[ts][nc][i];
+                        if (add) v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_out, voff, soff, 0));
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs_out, voff, soff, 0);
+                        acc[ts][nc][i] = 0.f;
+                    }
+                }
+            }
+        }
     }
+    if constexpr (FLUSH) return;
 
     // accumulator register i: output channel 8*(i/4) + 4*kk + (i%4) of the 32, input channel l32
     float* out = part + (size_t)slice * g.Cout * g.Cin * NN;
@@ -1381,6 +1408,37 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
     }
 }
 
+// Sum of the copies p[0], p[n], p[2n], ...: running sums taken in turn, each with a load in flight, then pairs of them.  From
+// 64 copies on sixteen of them: a chain of copies / 16 roundings keeps the sum as exact as the copies are, and few kernel
+// elements leave a thread's loads a chain of round trips; with fewer copies the remainder costs more than it gives
+// (128 x 128 channels, n = 3, 63 copies: 194 -> 200 us with the gradient), so four.
+template <int SUMS>
+__device__ __forceinline__ float sum_copies_in(const float* __restrict__ p, int n, int copies)
+{
+    float v[SUMS];
+#pragma unroll
+    for (int u = 0; u < SUMS; ++u) v[u] = 0.f;
+    int k = 0;
+    for (; k + SUMS - 1 < copies; k += SUMS) {
+#pragma unroll
+        for (int u = 0; u < SUMS; ++u) v[u] += p[(size_t)(k + u) * n];
+    }
+    for (int u = 0; k < copies; ++k, ++u) {
+        const float t = p[(size_t)k * n];
+#pragma unroll
+        for (int w = 0; w < SUMS - 1; ++w) v[w] += w == u ? t : 0.f;
+    }
+#pragma unroll
+    for (int m = 1; m < SUMS; m *= 2)
+#pragma unroll
+        for (int u = 0; u < SUMS; u += 2 * m) v[u] += v[u + m];
+    return v[0];
+}
+__device__ __forceinline__ float sum_copies(const float* __restrict__ p, int n, int copies)
+{
+    return copies >= 64 ? sum_copies_in<16>(p, n, copies) : sum_copies_in<4>(p, n, copies);  // uniform
+}
+
 // dw[co][ci][tap] = sum over the copies of part[copy][co][tap][ci], copies added in a fixed order;
 // threads run along the copies' layout (coalesced reads), the single write pass is scattered
 __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restrict__ part,
@@ -1389,15 +1447,7 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restr
 {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
-    // four running sums (copies k, k+1, k+2, k+3 in turn): four loads in flight
-    float v4[4] = {0.f, 0.f, 0.f, 0.f};
-    int k = 0;
-    for (; k + 3 < copies; k += 4) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v4[u] += part[(size_t)(k + u) * n + s];
-    }
-    for (int u = 0; k < copies; ++k, ++u) v4[u] += part[(size_t)k * n + s];
-    const float v = (v4[0] + v4[1]) + (v4[2] + v4[3]);
+    const float v = sum_copies(part + s, n, copies);
     const int ci = s % Cin, r = s / Cin;
     const int tap = r % NN, co = r / NN;
     dw[((size_t)co * Cin + ci) * NN + tap] = v;
@@ -1418,15 +1468,7 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __
     if (ci0 + l < Cin)
         for (int tap = wv; tap < NN; tap += 4) {
             const float* p = part + ((size_t)co * NN + tap) * Cin + ci0 + l;
-            // four running sums (copies k, k+1, k+2, k+3 in turn): four loads in flight
-            float v4[4] = {0.f, 0.f, 0.f, 0.f};
-            int k = 0;
-            for (; k + 3 < copies; k += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v4[u] += p[(size_t)(k + u) * n];
-            }
-            for (int u = 0; k < copies; ++k, ++u) v4[u] += p[(size_t)k * n];
-            lds_t[l * (NN + 1) + tap] = (v4[0] + v4[1]) + (v4[2] + v4[3]);
+            lds_t[l * (NN + 1) + tap] = sum_copies(p, n, copies);
         }
     __syncthreads();
     const int cis = Cin - ci0 < 64 ? Cin - ci0 : 64;
@@ -1452,10 +1494,21 @@ hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size
 }
 
 template <int NC>
-bool gw_mfma_args(const Geom& g, GwMfmaArgs& a)
+bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
 {
     const int N = g.n, CI_T = 32 * NC;
-    if (g.Cin < 32 || g.Cout < 32 || N < 2) return false;
+    // Layers of 16 to 31 channels leave up to half of a tile empty and still beat the vector ALUs (us, bf16: 30 -> 234
+    // channels, 7 x 23 x 23, n = 5 222 -> 50; 17 -> 346, 17 x 12 x 43, n = 4 238 -> 43; 178 -> 31, 14 x 72 x 72, n = 3 548 -> 47).
+    // Those kernels sum a few pixels in a chain: with 490 pixels this one's error against 64
+    // bits is 6 % above theirs (5.26e-8), with 5365 it is below (7.9e-8 -> 7.7e-8).  fp32 operands are rounded 16 times
+    // as often as bf16 ones: n = 5 adds every stage of at most 256 pixels to its copy of dw in memory (38 -> 30, 29 x 88 x 88
+    // 1412 -> 700 us, error 2.4e-7 -> 1.5e-7; 17 -> 78, 4 x 90 x 90 420 -> 190, 1.9e-7 -> 1.4e-7), for smaller kernels that costs
+    // what it gives (n = 4, 21 -> 70, 15 x 32 x 32 88 -> 96 us).
+    const int least = g.Cin < g.Cout ? g.Cin : g.Cout;
+    const long long pixels = (long long)g.B * g.H * g.W;
+    if (least < 16 || N < 2 || (least < 32 && (N > 5 || (es == 4 ? N < 5 || pixels < 4096 : pixels < 2048)))) return false;
+    a.flush = least < 32 && es == 4 ? 1 : 0;
+    if (a.flush && (size_t)g.Cout * g.Cin * N * N * 4 > 0x7FFFFFF0u) return false;  // (one buffer descriptor)
     a.g = g;
     a.TJ = pow2_ceil(g.W < 32 ? g.W : 32);
     if (a.TJ < 2) a.TJ = 2;
@@ -1463,7 +1516,7 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a)
     a.HC = a.TJ + N / 2;
     a.cols = 2 * a.HC;
     const size_t budget = 78 * 1024;
-    int TR = 512 / a.TJ;  // at most 512 pixels per stage
+    int TR = (a.flush ? 256 : 512) / a.TJ;  // at most that many pixels per stage
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);
@@ -1524,11 +1577,15 @@ hipError_t launch_gw_mfma(const GwMfmaArgs& a, const void* x, const void* dy, fl
         return e != hipSuccess ? e : launch_sum_taps(g, (const float*)part, dw, elems, copies, stream);
     }
     const size_t lds = (size_t)4 * (32 * NC * a.XP + 32 * a.DP);
-    const void* kfn = (const void*)ukst_grad_weight_mfma_kernel<N, NC, TIn>;
+    typedef void (*kernel_t)(const TIn*, const TIn*, float*, GwMfmaArgs);
+    kernel_t kernel = ukst_grad_weight_mfma_kernel<N, NC, TIn, false>;
+    if constexpr (sizeof(TIn) == 4 && N == 5)
+        if (a.flush) kernel = ukst_grad_weight_mfma_kernel<N, NC, TIn, true>;
+    const void* kfn = (const void*)kernel;
     e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess) {
         const unsigned nb = (unsigned)((long long)a.nSlices * a.coTiles * a.ciTiles);
-        hipLaunchKernelGGL((ukst_grad_weight_mfma_kernel<N, NC, TIn>), dim3(nb), dim3(256), lds, stream,
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), lds, stream,
                            (const TIn*)x, (const TIn*)dy, part, a);
         e = hipGetLastError();
     }
@@ -1792,7 +1849,8 @@ constexpr int GW_B16_NC = 2;
 bool gw_b16_args(const Geom& g, GwB16Args& a)
 {
     const int N = g.n, CI_T = 32 * GW_B16_NC;
-    if (g.Cin < 32 || g.Cout < 32 || N < 2 || N > 4) return false;
+    if (g.Cin < 16 || g.Cout < 16 || N < 2 || N > 4) return false;
+    if ((g.Cin < 32 || g.Cout < 32) && (long long)g.B * g.H * g.W < 2048) return false;  // (see gw_mfma_args)
     if (g.W % 8 != 0 || g.W < 16) return false;
     a.g = g;
     a.TJ = g.W >= 32 ? 32 : 16;
@@ -2298,7 +2356,7 @@ hipError_t launch_gw_n(const Geom& g, const void* x, const void* dy, float* dw, 
     }
     if constexpr (N >= 2) {
         GwMfmaArgs ma;
-        if (gw_mfma_args<gw_nc(N)>(g, ma)) return launch_gw_mfma<N, TIn>(ma, x, dy, dw, ws, stream);
+        if (gw_mfma_args<gw_nc(N)>(g, ma, (int)sizeof(TIn))) return launch_gw_mfma<N, TIn>(ma, x, dy, dw, ws, stream);
     }
     if constexpr (N >= 2 && N <= 5) {
         GwThinArgs ta;  // few output channels: (channel, tap) pairs as MFMA rows
@@ -2381,7 +2439,8 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
         GwB16Args ba;
         if (dtype == 1 && gw_b16_args(g, ba)) return "ukst_grad_weight_mfma_bf16_kernel";
         GwMfmaArgs wa;
-        const bool m = g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa) : gw_mfma_args<gw_nc(5)>(g, wa);
+        const int es = dtype == 0 ? 4 : 2;
+        const bool m = g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa, es) : gw_mfma_args<gw_nc(5)>(g, wa, es);
         if (m)
             return g.n <= 4 && grad_weight_parts_slices(g, dtype == 0 ? 4 : 2, wa.nSlices) != 0
                        ? "ukst_grad_weight_mfma_kernel_parts" : "ukst_grad_weight_mfma_kernel";

@@ -351,7 +351,8 @@ size_t lds_bytes(const GwPartsArgs& a, int es)
 
 bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
 {
-    if (g.Cin < 32 || g.Cout < 32 || g.n < 3 || g.n > 4 || g.W < 16 || g.OW < 4) return false;
+    const int least = es == 2 ? 16 : 32;  // (fp32: see gw_mfma_args)
+    if (g.Cin < least || g.Cout < least || g.n < 3 || g.n > 4 || g.W < 16 || g.OW < 4) return false;
     // (n = 2, 64 x 64 maps: 290 against 289 us, four taps do not pay for their staging)  Few pixels leave the
     // slices a stage or two and gain nothing: 64 -> 64 channels, 2 images of 16 x 16, n = 3 18.8 against 19.2 us, 4 of
     // 20 x 33 28.2 against 28.0, 64 of 16 x 16 with n = 4 58 against 46

@@ -207,3 +207,25 @@ def test_other_operations_with_operands_that_are_not_finite(op, what):
     assert np.array_equal(inf, np.isinf(y)) and np.array_equal(ref[inf], y[inf])
     ok = np.isfinite(ref)
     assert ok.any() and (np.abs(y[ok] - ref[ok]) <= 1e-5 * K * n * n * 16).all()
+
+
+# B, Cin, Cout, H, W, n, P, dtype
+@pytest.mark.parametrize("shape", [
+    (2, 17, 40, 33, 35, 5, 2, "bf16"),   # fp32 pipe, widened
+    (3, 40, 19, 26, 32, 3, 1, "bf16"),   # bf16 pipe, a channel tile of 8
+    (2, 21, 18, 65, 63, 4, 0, "bf16"),   # one part
+    (5, 16, 33, 30, 31, 2, 1, "bf16"),
+    (4, 18, 37, 33, 35, 5, 2, "f32"),    # every stage added to the copy in memory
+    (9, 70, 16, 20, 25, 5, 4, "f32"),
+])
+@pytest.mark.parametrize("integer", [True, False])
+def test_kernel_gradient_of_16_to_31_channels(shape, integer):
+    from gpu_util import check_elements, run_gpu_grad_weight
+    w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    assert "mfma" in ukst.ukst_grad_kernel_name(1, *shape[:7], dt)
+    data = wl.generate(w, integer=integer)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
+    ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
+    got = run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096)
+    check_elements(got, ref, S, TOL["f32"], exact=integer)
