@@ -1,4 +1,7 @@
-"""Thin ctypes binding of libukst: same names as include/ukst.h, argument marshalling only.
+"""Thin binding of libukst: same names as include/ukst.h, argument marshalling only.
+
+Ordinary calls (tensors on the current device, the result and the workspace allocated for the call, torch's current stream)
+are marshalled natively by _ukst_marshal.so, everything else and every refusal here with ctypes.
 
 Every step of the computation runs in the HIP kernels behind the C ABI.  There is no CPU
 fallback: if the library has not been built, loading raises.
@@ -6,10 +9,12 @@ fallback: if the library has not been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libukst.so")
+MARSHAL_PATH = os.path.join(_HERE, "_ukst_marshal.so")
 BENCH_LIB_PATH = os.path.join(_HERE, "libukst_bench.so")
 
 UKST_F32, UKST_BF16_F32, UKST_BF16_BF16 = 0, 1, 2
@@ -35,6 +40,7 @@ BENCH_EXPORTS = ["ukst_bench_mfma_ceiling", "ukst_bench_stream_ceiling"]
 
 _lib = None
 _bench_lib = None
+_native = None  # the extension module, from the time the library is loaded on
 _torch = None  # the module, from the time the library is loaded on
 
 
@@ -47,12 +53,13 @@ class UkstError(RuntimeError):
 def lib():
     """Load libukst.so (once).  Raises if it is missing: build it with
     ``python -m paper_2502_20493_amd.build`` (or ``__graft_entry__.build()``)."""
-    global _lib, _torch
+    global _lib, _torch, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(
-                f"{LIB_PATH} is missing: the HIP library has not been built "
-                "(python -m paper_2502_20493_amd.build). There is no fallback path.")
+        for path in (LIB_PATH, MARSHAL_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError(
+                    f"{path} is missing: the HIP library has not been built "
+                    "(python -m paper_2502_20493_amd.build). There is no fallback path.")
         # PyTorch bundles its own HIP runtime.  It has to be in the process before this library
         # is loaded, otherwise the two ends see different runtimes and the first HIP call made
         # from here reports that there is no device.
@@ -91,8 +98,20 @@ def lib():
             f.argtypes, f.restype = [i] * 9, ctypes.c_ulonglong
         L.ukst_static_workspace_bytes.argtypes = []
         L.ukst_static_workspace_bytes.restype = ctypes.c_size_t
-        _lib = L
+        spec = importlib.util.spec_from_file_location("_ukst_marshal", MARSHAL_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        native.bind(*(ctypes.cast(f, vp).value for f in (
+            L.ukst_workspace_bytes, L.ukst_conv_transpose2d_path, L.ukst_conv_transpose2d_bias_act,
+            L.ukst_conv_transpose2d_ws, L.ukst_conv_transpose2d_grad_input, L.ukst_conv_transpose2d_grad_weight,
+            L.ukst_conv_transpose2d_strided, L.ukst_dilated_conv2d)))
+        _lib, _native = L, native
     return _lib
+
+
+def _load_native():
+    lib()
+    return _native
 
 
 def bench_lib():
@@ -248,6 +267,10 @@ def ukst_conv_transpose2d_bias_act(x, w, P: int, bias=None, act: int = UKST_ACT_
                                    workspace=False):
     """Marshal torch device tensors into ukst_conv_transpose2d_bias_act:
     y = act(conv_transpose(x, w) + bias[co]); bias: float32 device tensor [Cout] or None."""
+    if y is None and stream is None and path == UKST_PATH_AUTO and (workspace is None or workspace is False):
+        out = (_native or _load_native()).forward(x, w, P, bias, act, out_bf16, workspace is None)
+        if out is not None:
+            return out
     import torch
 
     if bias is not None:
@@ -279,6 +302,11 @@ def ukst_conv_transpose2d(x, w, P: int, y=None, path: int = UKST_PATH_AUTO, stre
     out_bf16 (bf16 inputs only), or a bfloat16 y: the output is bfloat16 (UKST_BF16_BF16).
     The call is asynchronous on ``stream`` (default: torch's current stream).
     """
+    if (y is None and stream is None and path == UKST_PATH_AUTO and _act is None
+            and (workspace is None or workspace is False)):
+        out = (_native or _load_native()).forward(x, w, P, None, None, out_bf16, workspace is None)
+        if out is not None:
+            return out
     import torch
 
     if not (x.is_cuda and w.is_cuda):
@@ -361,6 +389,10 @@ def ukst_conv_transpose2d_grad_input(dy, w, H: int, W: int, P: int, dx=None, str
     dy: [B,Cout,OH,OW], w: [Cout,Cin,n,n] (float32 or bfloat16) -> dx float32 [B,Cin,H,W].
     workspace: uint8 device tensor (>= ukst_workspace_bytes(UKST_OP_GRAD_INPUT, ...)), or None to
     have it allocated with torch for this call."""
+    if dx is None and stream is None and workspace is None:
+        out = (_native or _load_native()).input_gradient(dy, w, H, W, P)
+        if out is not None:
+            return out
     import torch
 
     dtype = _backward_operands(dy, w)
@@ -404,6 +436,10 @@ def ukst_conv_transpose2d_grad_weight(x, dy, n: int, P: int, dw=None, stream=Non
     x: [B,Cin,H,W], dy: [B,Cout,OH,OW] (float32 or bfloat16) -> dw float32 [Cout,Cin,n,n].
     workspace: uint8 device tensor (>= ukst_workspace_bytes(UKST_OP_GRAD_WEIGHT, ...)), or None to
     have it allocated with torch for this call."""
+    if dw is None and stream is None and workspace is None:
+        out = (_native or _load_native()).kernel_gradient(x, dy, n, P)
+        if out is not None:
+            return out
     import torch
 
     dtype = _backward_operands(x, dy)
@@ -441,8 +477,15 @@ def ukst_mac_count_dilated(B, Cin, Cout, H, W, n, P, d, kind: int) -> int:
     return int(lib().ukst_mac_count_dilated(B, Cin, Cout, H, W, n, P, d, kind))
 
 
-def _general(fn, shape_fn, x, w, P, k, y, stream):
+def _general(dilated, x, w, P, k, y, stream):
+    if y is None and stream is None:
+        out = (_native or _load_native()).general(x, w, P, k, dilated)
+        if out is not None:
+            return out
     import torch
+
+    fn, shape_fn = ((lib().ukst_dilated_conv2d, ukst_output_shape_dilated) if dilated
+                    else (lib().ukst_conv_transpose2d_strided, ukst_output_shape_strided))
 
     if not (x.is_cuda and w.is_cuda and x.is_contiguous() and w.is_contiguous()):
         raise ValueError("x and w must be contiguous device tensors")
@@ -464,10 +507,10 @@ def _general(fn, shape_fn, x, w, P, k, y, stream):
 def ukst_conv_transpose2d_strided(x, w, P: int, s: int, y=None, stream=None):
     """Marshal torch device tensors into ukst_conv_transpose2d_strided (stride-s transpose
     convolution; float32 output [B,Cout,s(H-1)+2P-n+2,s(W-1)+2P-n+2])."""
-    return _general(lib().ukst_conv_transpose2d_strided, ukst_output_shape_strided, x, w, P, s, y, stream)
+    return _general(False, x, w, P, s, y, stream)
 
 
 def ukst_dilated_conv2d(x, w, P: int, d: int, y=None, stream=None):
     """Marshal torch device tensors into ukst_dilated_conv2d (dilation-d convolution; float32
     output [B,Cout,H+2P-d(n-1),W+2P-d(n-1)])."""
-    return _general(lib().ukst_dilated_conv2d, ukst_output_shape_dilated, x, w, P, d, y, stream)
+    return _general(True, x, w, P, d, y, stream)

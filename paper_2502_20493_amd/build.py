@@ -10,6 +10,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libukst.so")
+MARSHAL_LIB = os.path.join(HERE, "_ukst_marshal.so")  # native marshalling of the Python binding
+MARSHAL_SRC = os.path.join(CSRC, "binding", "ukst_marshal.cpp")
 BENCH_LIB = os.path.join(HERE, "libukst_bench.so")  # measurement helpers, not part of the product
 
 HIPCC_FLAGS = [
@@ -40,9 +42,22 @@ def _run(cmd, verbose):
         print(out)
 
 
+def _marshal_command():
+    """g++ line of the Python extension module that marshals tensors (CPython and torch headers, host code only)."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I" + os.path.join(root, "include"), "-I" + os.path.join(rocm, "include"),
+            "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", MARSHAL_LIB,
+            "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_library(verbose: bool = False, jobs: int | None = None) -> str:
     """Compile every csrc/*.hip to an object (in parallel) and link libukst.so; csrc/bench/*.hip
-    become libukst_bench.so (the benchmark's measured ceilings)."""
+    become libukst_bench.so (the benchmark's measured ceilings), csrc/binding/ukst_marshal.cpp the binding's extension module."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJDIR, exist_ok=True)
     srcs, bsrcs = sources(), bench_sources()
@@ -52,6 +67,7 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         futs = [pool.submit(_run, [hipcc] + HIPCC_FLAGS + ["-c", s, "-o", o], verbose)
                 for s, o in zip(srcs + bsrcs, objs + bobjs)]
+        futs.append(pool.submit(_run, _marshal_command(), verbose))
         for f in futs:
             f.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
@@ -60,10 +76,11 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(BENCH_LIB):
+    libs = (LIB, BENCH_LIB, MARSHAL_LIB)
+    if not all(os.path.exists(p) for p in libs):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(BENCH_LIB))
-    deps = sources() + bench_sources() + glob.glob(os.path.join(CSRC, "*.h")) + \
+    t = min(os.path.getmtime(p) for p in libs)
+    deps = sources() + bench_sources() + [MARSHAL_SRC] + glob.glob(os.path.join(CSRC, "*.h")) + \
         glob.glob(os.path.join(HERE, "..", "include", "*.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
