@@ -123,7 +123,12 @@ static bool prefer_small(const SmallProblem& q)
     if (q.K < 16 || q.M < 8 || q.n < 2 || q.n > 5) return false;
     if (q.op == SmallOp::strided && q.step != 3 && q.step != 4) return false;
     const long long tiles = small_blocks(q, q.op == SmallOp::strided ? 16 : 32);
-    return tiles > 0 && tiles <= (q.op == SmallOp::strided ? (q.dtype == 0 ? 512 : 256) : q.dtype == 0 ? 1200 : 512);
+    if (tiles > 0 && tiles <= (q.op == SmallOp::strided ? (q.dtype == 0 ? 512 : 256) : q.dtype == 0 ? 1200 : 512)) return true;
+    // dilated layers that do not fit that kernel's LDS (long rows under a wide dilation) have only the vector ALUs besides (us,
+    // dilation 4, n = 5: 64 -> 64 channels, 4 of 100 x 100 452 / 125; 160 -> 200, 8 of 96 x 96 4178 / 1267; 17 -> 40, 13 of 56 x 56
+    // 96 / 58; bf16, 16 -> 16, 6 of 128 x 128, dilation 8 82 / 57)
+    return q.op == SmallOp::dilated && tiles > 0 &&
+           !general_mfma_fits(1, q.B, q.K, q.M, q.XH, q.XW, q.n, q.P, q.step, q.OH, q.OW, q.dtype);
 }
 
 // k = stride (dilated == 0) or dilation (dilated == 1); shapes validated by the caller

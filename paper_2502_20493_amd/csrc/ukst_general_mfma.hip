@@ -435,10 +435,10 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
     }
 }
 
-// LDS bytes, XU and grid of a layer; false if the kernel cannot run it
+// LDS bytes, XU and grid of a layer on blocks of 32 * mt channels; false if the kernel cannot run it
 struct ConvPlan { ConvArgs a; int mt, xu; size_t lds; unsigned blocks; };
 
-bool make_plan(ConvArgs a, int es, ConvPlan& p)
+bool make_plan(ConvArgs a, int es, int mt, ConvPlan& p)
 {
     const size_t lim = 0x7FFFFFF0u;  // single buffer descriptors, 32-bit byte offsets
     const int NN = a.n * a.n, parts = es == 4 ? 3 : 1;
@@ -446,7 +446,7 @@ bool make_plan(ConvArgs a, int es, ConvPlan& p)
         (size_t)a.B * a.Cout * a.OH * a.OW * 4 > lim)
         return false;
     a.classes = a.dilated ? 1 : a.k * a.k;
-    p.mt = a.Cout > 32 ? 2 : 1;
+    p.mt = mt;
     a.nco = (a.Cout + 32 * p.mt - 1) / (32 * p.mt);
     long long slots = 0, units = 0, qmax = 0;
     for (int c = 0; c < a.classes; ++c) {
@@ -481,6 +481,19 @@ bool make_plan(ConvArgs a, int es, ConvPlan& p)
     return true;
 }
 
+// Blocks of 64 channels read less per product; of 32 where those do not fit LDS (14 images, 184 -> 152 channels, 45 x 10, n = 5,
+// dilation 4: 1122 us on the vector ALUs, 176 so), where there are no more than 32, and where even twice the blocks leave
+// every one a compute unit of its own (us, 64 / 32: 72 -> 128, 10 of 38 x 38, n = 5, dilation 2, 228 blocks of 32 120 / 87; 216 -> 144
+// bf16, 250 blocks 70 / 55; but 40 -> 184, 294 blocks 51 / 71, strided layers of 800 to 12000 blocks 0.7 to 1.2 times as fast)
+bool pick_plan(const ConvArgs& a, int es, ConvPlan& p)
+{
+    if (a.Cout <= 32) return make_plan(a, es, 1, p);
+    if (!make_plan(a, es, 2, p)) return make_plan(a, es, 1, p);
+    ConvPlan q;
+    if (p.blocks <= 256 && make_plan(a, es, 1, q) && q.blocks <= 256) p = q;
+    return true;
+}
+
 template <int MT, int XU, typename TIn>
 hipError_t launch_v(const ConvPlan& p, const void* x, const void* w, float* y, hipStream_t stream)
 {
@@ -494,12 +507,20 @@ hipError_t launch_v(const ConvPlan& p, const void* x, const void* w, float* y, h
 
 }  // namespace
 
+bool general_mfma_fits(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW, int dtype)
+{
+    ConvArgs a;
+    a.B = B; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.n = n; a.P = P; a.k = k; a.OH = OH; a.OW = OW;
+    a.dilated = dilated;
+    ConvPlan p;
+    return pick_plan(a, dtype == 0 ? 4 : 2, p);
+}
+
 bool launch_general_mfma(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW,
                          const void* x, const void* w, float* y, int dtype, hipStream_t stream, hipError_t* err)
 {
     // from 16 channels on the smallest layers gain too (16 -> 16 channels, 8 x 8 maps, stride 3: 9.3 -> 7.2 us;
-    // 16 x 16 maps, dilation 2: 30 -> 11.5); what does not fit LDS (long rows under a wide dilation, fp32:
-    // 96 columns, n = 5, d = 4) stays on the vector ALUs
+    // 16 x 16 maps, dilation 2: 30 -> 11.5); what does not fit LDS (long rows under a wide dilation) is for the small tiles
     if (Cin < 16 || Cout < 8) return false;
     // one stage of channels and many lattice pixels: writing y with a stride is all there is (16 -> 16 channels,
     // 8 x 48 x 48, stride 3, fp32: 17.2 against 17.7 us)
@@ -521,7 +542,7 @@ bool launch_general_mfma(int dilated, int B, int Cin, int Cout, int H, int W, in
     a.B = B; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.n = n; a.P = P; a.k = k; a.OH = OH; a.OW = OW;
     a.dilated = dilated;
     ConvPlan p;
-    if (!make_plan(a, dtype == 0 ? 4 : 2, p)) return false;
+    if (!pick_plan(a, dtype == 0 ? 4 : 2, p)) return false;
     if (dtype == 0) {
         if (p.mt == 2)
             *err = p.xu == 3 ? launch_v<2, 3, float>(p, x, w, y, stream)

@@ -197,6 +197,8 @@ hipError_t launch_general(int dilated, int B, int Cin, int Cout, int H, int W, i
                           int OH, int OW, const void* x, const void* w, float* y, int dtype,
                           hipStream_t stream);
 
+// false if the matrix-core kernel below does not fit the layer
+bool general_mfma_fits(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW, int dtype);
 // The same on the matrix cores: false if the layer is not for it (nothing launched), else *err is the launch
 bool launch_general_mfma(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW,
                          const void* x, const void* w, float* y, int dtype, hipStream_t stream, hipError_t* err);
