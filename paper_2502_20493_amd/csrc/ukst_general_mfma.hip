@@ -484,13 +484,19 @@ bool make_plan(ConvArgs a, int es, int mt, ConvPlan& p)
 // Blocks of 64 channels read less per product; of 32 where those do not fit LDS (14 images, 184 -> 152 channels, 45 x 10, n = 5,
 // dilation 4: 1122 us on the vector ALUs, 176 so), where there are no more than 32, and where even twice the blocks leave
 // every one a compute unit of its own (us, 64 / 32: 72 -> 128, 10 of 38 x 38, n = 5, dilation 2, 228 blocks of 32 120 / 87; 216 -> 144
-// bf16, 250 blocks 70 / 55; but 40 -> 184, 294 blocks 51 / 71, strided layers of 800 to 12000 blocks 0.7 to 1.2 times as fast)
+// bf16, 250 blocks 70 / 55; but 40 -> 184, 294 blocks 51 / 71, strided layers of 800 to 12000 blocks 0.7 to 1.2 times as fast).
+// fp32: also where all of them are resident at once, two to a compute unit, and cover each other's waits (dilation 2, 64 -> 64 at
+// 64 x 64, n = 3: 11 images, 352 blocks 46.3 / 41.3, 16 images, 512 blocks 44.0 / 40.4; 20, 640 blocks 61 / 65; n = 5, where LDS
+// holds one, 100 / 131; bf16, whose loop waits less, 27.0 / 27.2).  Classes of one tap have little to
+// share (stride 3, 64 -> 64, n = 3, one of 64 x 64 17.8 / 18.5, two of 40 x 40 17.5 / 16.5; n = 4 27.1 / 25.1, 26.8 / 22.5)
 bool pick_plan(const ConvArgs& a, int es, ConvPlan& p)
 {
     if (a.Cout <= 32) return make_plan(a, es, 1, p);
     if (!make_plan(a, es, 2, p)) return make_plan(a, es, 1, p);
     ConvPlan q;
-    if (p.blocks <= 256 && make_plan(a, es, 1, q) && q.blocks <= 256) p = q;
+    if (p.blocks <= 256 && (a.dilated || a.n > a.k) && make_plan(a, es, 1, q) &&
+        (q.blocks <= 256 || (es == 4 && q.blocks <= 512 && 2 * q.lds <= LDS_LIMIT)))
+        p = q;
     return true;
 }
 

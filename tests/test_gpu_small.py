@@ -153,11 +153,12 @@ GENERAL_SHAPES = [
 ]
 
 
-# the kernel for larger layers on blocks of 32 channels (no more of them than compute units; of 64, they do not fit LDS), the
+# the kernel for larger layers on blocks of 32 channels (no more of them than compute units, fp32 two to one; of 64, they do not fit LDS), the
 # small tiles where neither fits, and blocks of 64 on either side
 GENERAL_SHAPES += [
     ("dilated", 2, (10, 17, 125, 38, 38, 5, 4)), ("dilated", 2, (10, 17, 70, 38, 38, 5, 4)), ("dilated", 2, (10, 17, 170, 38, 38, 2, 1)),
     ("dilated", 4, (9, 16, 50, 60, 84, 3, 4)), ("dilated", 4, (13, 17, 40, 56, 56, 5, 8)), ("strided", 3, (1, 33, 61, 37, 39, 5, 2)),
+    ("dilated", 2, (11, 17, 61, 64, 64, 3, 2)),
 ]
 
 
