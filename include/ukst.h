@@ -258,9 +258,11 @@ size_t ukst_static_workspace_bytes(void);
  * i.e. kernel sides up to about 5;
  * "ukst_grad_input_mfma_kernel_parts": other fp32 layers with enough pixels, bf16 MFMA on three exact
  * bf16 parts of every operand;
- * "ukst_grad_input_mfma_kernel": fp32 MFMA for the rest, weights packed once per call into the
- * workspace, which also holds the copies of dx when the sum over output channels is split),
- * layers with Cin, Cout >= 32 run the kernel gradient there too
+ * "ukst_grad_input_mfma_kernel": fp32 MFMA for the rest, and for layers of few tiles from Cin >= 16 and
+ * Cout >= 8 on, which use no workspace; for the others weights are packed once per call into it, and it
+ * holds the copies of dx when the sum over output channels is split),
+ * layers with Cin, Cout >= 32 (16 for bf16 operands, and fp32 with n = 5, with enough pixels) run the
+ * kernel gradient there too
  * ("ukst_grad_weight_mfma_bf16_kernel": bf16 MFMA with the pixel axis as the contraction, for bf16
  * operands with kernel sides 2 to 4, W a multiple of 8 and at least 16;
  * "ukst_grad_weight_mfma_kernel_parts": bf16 MFMA on bf16 parts (three of an fp32 value, one of a

@@ -1,7 +1,7 @@
 """ukst: unified kernel-segregated stride-2 transpose convolution for MI355X (gfx950).
 
 The compute lives in the C-ABI library built from ``csrc/`` (declared in ``include/ukst.h``);
-``binding`` is a thin ctypes layer with the same names.  Importing this package never loads the
+``binding`` is a thin layer over it with the same names.  Importing this package never loads the
 library; the first call does, and raises if it has not been built.
 """
 from . import workloads  # noqa: F401
