@@ -29,6 +29,8 @@ struct ConvArgs {
     int B, Cin, Cout, H, W, n, P, k, OH, OW;
     int dilated;
     int classes;  // k*k or 1
+    int group;    // pixel tiles whose blocks lie together, the classes of most taps first
+    unsigned long long order;  // the classes by taps, four bits each
     int nco, nqt; // channel blocks, pixel tiles of the largest class
     int XPL;      // bytes of one part's activation stage
 };
@@ -108,8 +110,13 @@ void ukst_general_mfma_kernel(const TIn* __restrict__ x, const TIn* __restrict__
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, gk = lane >> 5;
     int bid = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int cls = bid % a.classes; bid /= a.classes;
-    const int cb = bid % a.nco, qt = bid / a.nco;
+    const int gs = a.group * a.classes * a.nco, grp = bid / gs;
+    bid -= grp * gs;
+    const int gt = a.nqt - grp * a.group < a.group ? a.nqt - grp * a.group : a.group;  // tiles of this group
+    const int cb = bid / (gt * a.classes);
+    bid -= cb * gt * a.classes;
+    const int rank = bid / gt, qt = grp * a.group + bid - rank * gt;
+    const int cls = a.group > 1 ? (int)(a.order >> (4 * rank)) & 15 : rank;
     const Class g = class_of(a, cls);
     const int IJ = g.NI * g.NJ, Q = a.B * IJ;
     const int co0 = cb * TM, q0 = qt * TN;
@@ -476,6 +483,24 @@ bool make_plan(ConvArgs a, int es, int mt, ConvPlan& p)
     a.nqt = (int)((qmax + TN - 1) / TN);
     const long long nb = (long long)a.nqt * a.nco * a.classes;
     if (nb > 0x3FFFFFFF) return false;
+    // Classes of unequal taps, an incomplete further round of 512 blocks and a long sum (fp32): within four pixel tiles the
+    // classes of most taps start first, so that the blocks that start last are the short ones.  Neighbouring classes
+    // write y later than one another, which few channels do not repay (us, class by class / by taps: 128 -> 64, 16 of 32 x 32,
+    // n = 5, stride 3, 576 blocks 80.2 / 70.5; 288 -> 232, 6 of 24 x 27, n = 4, 612 blocks 151 / 137; 280 -> 104, 26 of 16 x 16, n = 5,
+    // stride 4 174 / 152; 376 -> 200, 15 of 27 x 25, n = 5, 1332 blocks 379 / 350; but 369 blocks 49.5 / 52.4, equal taps,
+    // 168 -> 152, n = 4, stride 4 231 / 244, 24 -> 144, n = 5, stride 4 167 / 174)
+    a.group = !a.dilated && a.classes <= 16 && a.n > a.k && a.n % a.k != 0 && es == 4 && a.Cin >= 128 && nb > 512 &&
+              nb <= 2560 ? 4 : 1;
+    a.order = 0;
+    for (int c = 0; a.group > 1 && c < a.classes; ++c) {
+        const Class g = class_of(a, c);
+        int rank = 0;
+        for (int d = 0; d < a.classes; ++d) {
+            const Class h = class_of(a, d);
+            rank += h.Tr * h.Tc > g.Tr * g.Tc || (h.Tr * h.Tc == g.Tr * g.Tc && d < c) ? 1 : 0;
+        }
+        a.order |= (unsigned long long)c << (4 * rank);
+    }
     p.blocks = (unsigned)nb;
     p.a = a;
     return true;

@@ -159,6 +159,7 @@ GENERAL_SHAPES += [
     ("dilated", 2, (10, 17, 125, 38, 38, 5, 4)), ("dilated", 2, (10, 17, 70, 38, 38, 5, 4)), ("dilated", 2, (10, 17, 170, 38, 38, 2, 1)),
     ("dilated", 4, (9, 16, 50, 60, 84, 3, 4)), ("dilated", 4, (13, 17, 40, 56, 56, 5, 8)), ("strided", 3, (1, 33, 61, 37, 39, 5, 2)),
     ("dilated", 2, (11, 17, 61, 64, 64, 3, 2)),
+    ("strided", 3, (14, 130, 37, 31, 33, 5, 2)),  # classes in order of their taps, two tiles left over
 ]
 
 
