@@ -483,14 +483,14 @@ bool make_plan(ConvArgs a, int es, int mt, ConvPlan& p)
     a.nqt = (int)((qmax + TN - 1) / TN);
     const long long nb = (long long)a.nqt * a.nco * a.classes;
     if (nb > 0x3FFFFFFF) return false;
-    // Classes of unequal taps, an incomplete further round of 512 blocks and a long sum (fp32): within four pixel tiles the
+    // Classes of unequal taps, an incomplete second round of 512 blocks and a long sum (fp32): within four pixel tiles the
     // classes of most taps start first, so that the blocks that start last are the short ones.  Neighbouring classes
     // write y later than one another, which few channels do not repay (us, class by class / by taps: 128 -> 64, 16 of 32 x 32,
     // n = 5, stride 3, 576 blocks 80.2 / 70.5; 288 -> 232, 6 of 24 x 27, n = 4, 612 blocks 151 / 137; 280 -> 104, 26 of 16 x 16, n = 5,
-    // stride 4 174 / 152; 376 -> 200, 15 of 27 x 25, n = 5, 1332 blocks 379 / 350; but 369 blocks 49.5 / 52.4, equal taps,
+    // stride 4 174 / 152; but 336 -> 72, 13 of 34 x 34, n = 5, 1116 blocks 233 / 243, 369 blocks 49.5 / 52.4, equal taps,
     // 168 -> 152, n = 4, stride 4 231 / 244, 24 -> 144, n = 5, stride 4 167 / 174)
     a.group = !a.dilated && a.classes <= 16 && a.n > a.k && a.n % a.k != 0 && es == 4 && a.Cin >= 128 && nb > 512 &&
-              nb <= 2560 ? 4 : 1;
+              nb <= 1024 ? 4 : 1;
     a.order = 0;
     for (int c = 0; a.group > 1 && c < a.classes; ++c) {
         const Class g = class_of(a, c);
