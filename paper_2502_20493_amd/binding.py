@@ -266,7 +266,10 @@ def ukst_conv_transpose2d_bias_act(x, w, P: int, bias=None, act: int = UKST_ACT_
                                    path: int = UKST_PATH_AUTO, stream=None, out_bf16: bool = False,
                                    workspace=False):
     """Marshal torch device tensors into ukst_conv_transpose2d_bias_act:
-    y = act(conv_transpose(x, w) + bias[co]); bias: float32 device tensor [Cout] or None."""
+    y = act(conv_transpose(x, w) + bias[co]); bias: float32 device tensor [Cout] or None;
+    act=None is UKST_ACT_NONE."""
+    if act is None:
+        act = UKST_ACT_NONE
     if y is None and stream is None and path == UKST_PATH_AUTO and (workspace is None or workspace is False):
         out = (_native or _load_native()).forward(x, w, P, bias, act, out_bf16, workspace is None)
         if out is not None:
@@ -302,7 +305,7 @@ def ukst_conv_transpose2d(x, w, P: int, y=None, path: int = UKST_PATH_AUTO, stre
     out_bf16 (bf16 inputs only), or a bfloat16 y: the output is bfloat16 (UKST_BF16_BF16).
     The call is asynchronous on ``stream`` (default: torch's current stream).
     """
-    if (y is None and stream is None and path == UKST_PATH_AUTO and _act is None
+    if (y is None and stream is None and path == UKST_PATH_AUTO and _bias is None and _act is None
             and (workspace is None or workspace is False)):
         out = (_native or _load_native()).forward(x, w, P, None, None, out_bf16, workspace is None)
         if out is not None:
@@ -342,13 +345,13 @@ def ukst_conv_transpose2d(x, w, P: int, y=None, path: int = UKST_PATH_AUTO, stre
         _call(device, lib().ukst_conv_transpose2d_ws, x.data_ptr(), w.data_ptr(),
               None if _bias is None else _bias.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype,
               UKST_ACT_NONE if _act is None else int(_act), path, wp, wb, sp)
-    elif _act is None:
+    elif _bias is None and _act is None:
         _call(device, lib().ukst_conv_transpose2d_path, x.data_ptr(), w.data_ptr(), y.data_ptr(), B, Cin, Cout,
               H, W, n, P, dtype, path, sp)
     else:
         _call(device, lib().ukst_conv_transpose2d_bias_act, x.data_ptr(), w.data_ptr(),
               None if _bias is None else _bias.data_ptr(), y.data_ptr(), B, Cin, Cout, H, W, n, P, dtype,
-              int(_act), path, sp)
+              UKST_ACT_NONE if _act is None else int(_act), path, sp)
     return y
 
 

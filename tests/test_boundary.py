@@ -312,6 +312,29 @@ def test_backward_kernel_selection_is_host_arithmetic():
     assert name(0, 1, 1, 1, 1, 4, 3, 0, ukst.UKST_F32) == ""
 
 
+@pytest.mark.parametrize("call", [ukst.ukst_conv_transpose2d_ws, ukst.ukst_conv_transpose2d_bias_act])
+@pytest.mark.parametrize("workspace", [None, False])
+def test_a_bias_without_an_activation_is_never_left_out(call, workspace, monkeypatch):
+    """act=None is no activation, with the bias or without; a call that the native marshalling turns down does not come
+    back to it without its bias."""
+    import types
+    import torch
+    ukst.lib()
+    seen = []
+
+    class Native:
+        @staticmethod
+        def forward(x, w, P, bias, act, out_bf16, with_workspace):
+            seen.append((bias, act, with_workspace))  # (None: turned down)
+
+    monkeypatch.setattr(ukst, "_native", Native)
+    bias = types.SimpleNamespace(is_cuda=True, dtype=torch.float32, is_contiguous=lambda: True, shape=(5,))
+    x, w = torch.zeros(1, 2, 4, 4), torch.zeros(5, 2, 3, 3)
+    with pytest.raises(ValueError, match="device tensors"):  # (x is on the CPU: as far as it gets here)
+        call(x, w, 1, bias=bias, act=None, workspace=workspace)
+    assert seen == [(bias, ukst.UKST_ACT_NONE, workspace is None)]
+
+
 def test_generalised_operations_host_side():
     """Stride-s transpose convolution and dilated convolution: shapes, multiply-add counts and
     argument validation are host arithmetic (fake addresses: nothing may be launched)."""

@@ -15,6 +15,14 @@ def _calls(x, w, dy, bias, stream):
     for f in (ukst.ukst_conv_transpose2d_ws, ukst.ukst_conv_transpose2d_bias_act):
         for kw in (dict(), dict(bias=bias), dict(bias=bias, act=ukst.UKST_ACT_TANH)):
             yield lambda: f(x, w, P, **kw), lambda: f(x, w, P, stream=stream, **kw)
+    # act=None is no activation, with the bias or without
+    for f in (ukst.ukst_conv_transpose2d_ws, ukst.ukst_conv_transpose2d_bias_act):
+        for b in (None, bias):
+            for ws in (None, False):
+                yield (lambda: f(x, w, P, bias=b, act=None, workspace=ws),
+                       lambda: f(x, w, P, bias=b, act=ukst.UKST_ACT_NONE, workspace=ws, stream=stream))
+                yield (lambda: f(x, w, P, bias=b, act=None, workspace=ws, stream=stream),
+                       lambda: f(x, w, P, bias=b, act=ukst.UKST_ACT_NONE, workspace=ws))
     yield (lambda: ukst.ukst_conv_transpose2d_grad_input(dy, w, H, W, P),
            lambda: ukst.ukst_conv_transpose2d_grad_input(dy, w, H, W, P, stream=stream))
     yield (lambda: ukst.ukst_conv_transpose2d_grad_weight(x, dy, n, P),
