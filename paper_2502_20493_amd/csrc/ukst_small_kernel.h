@@ -174,6 +174,12 @@ __device__ __forceinline__ void small_tile(const TIn* __restrict__ x, const TIn*
         return (L::RPI == 1 ? wq + q < L::PPR : lane < L::RPI * L::PPR) && i / L::IPR * L::RPI + wrow < L::NROWS;
     };
     auto row_step = [&](int i) __attribute__((always_inline)) { return i / L::IPR * L::RPI; };
+    // rows past the last output channel are fetched from its row (they reach no output): the scalar offset stays inside w
+    const int m_last = a.M - 1 - m0;
+    auto row_in = [&](int i) __attribute__((always_inline)) {
+        const int r = row_step(i);
+        return TW || r < m_last ? r : m_last;
+    };
 
     unsigned xr[KC][L::JR], wr[L::NI][PD];
     // A last stage that reaches past channel K - 1 is moved down to end there; the channels it shares with the stage
@@ -191,7 +197,7 @@ __device__ __forceinline__ void small_tile(const TIn* __restrict__ x, const TIn*
     auto load_w = [&](int s, bool on, int i) __attribute__((always_inline)) {
         const int k0 = first_of(s);
         const unsigned voff = on && piece_on(i) ? wv + (unsigned)(i % L::IPR * 256 * ES) : kNone;
-        const unsigned soff = (unsigned)((TW ? (k0 + row_step(i)) * a.M * NN : (row_step(i) * a.K + k0) * NN) * ES);
+        const unsigned soff = (unsigned)((TW ? (k0 + row_in(i)) * a.M * NN : (row_in(i) * a.K + k0) * NN) * ES);
         if constexpr (B16) {
             const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_w, voff, soff, 0);
             wr[i][0] = v.x;
