@@ -1105,11 +1105,11 @@ struct GwMfmaArgs {
     int coTiles, ciTiles;
     int cols4;                 // four-column pieces per staged dy row
     int fast, npass;           // piecewise staging (rows of at least four elements), its passes per channel
-    int flush;                 // every stage is added to the copy of dw in memory
+    int flush;                 // stages after which the sums are added to the copy of dw in memory (0: at the end)
     FastDiv dC4, dRows, dLR;
 };
 
-// FLUSH: every stage is added to the block's copy of dw in memory (see gw_mfma_args)
+// FLUSH: every a.flush stages are added to the block's copy of dw in memory (see gw_mfma_args)
 template <int N, int NC, typename TIn, bool FLUSH>
 __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn* __restrict__ x,
                                                                       const TIn* __restrict__ dy,
@@ -1144,13 +1144,18 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
         const int ta = t / N, tc = t % N;
         tapoff[ts] = (N - 1 - ta) * a.cols + ((N - 1 - tc) & 1) * a.HC + ((N - 1 - tc) >> 1);
     }
-    f32x16 acc[TS][NC];
+    // FLUSH, n = 2: every other pixel pair on accumulators of its own, half the roundings in a chain
+    constexpr int PH = FLUSH && N == 2 ? 2 : 1;
+    f32x16 acc2[PH][TS][NC];
+    auto& acc = acc2[0];
 #pragma unroll
-    for (int ts = 0; ts < TS; ++ts)
+    for (int ph = 0; ph < PH; ++ph)
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc)
+        for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ts][nc][i] = 0.f;
+            for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc2[ph][ts][nc][i] = 0.f;
 
     const int npix = 1 << a.logPix, rowsPerCo = a.TB * a.LR;
     const int a_lane = l32 * a.DP + kk, b_lane = l32 * a.XP + kk;
@@ -1346,7 +1351,7 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
                 if (b0 + bl >= g.B || i0 + li >= g.H) continue;  // uniform
                 const float* ap = dys + a_lane + (bl * a.LR + 2 * li) * a.cols;
                 const float* bp = xs + b_lane + tr * a.TJ;
-                auto step = [&](int sp) {
+                auto step = [&](int sp, auto ph) {
                     float bv[NC], av[NTS > 0 ? NTS : 1];
 #pragma unroll
                     for (int nc = 0; nc < NC; ++nc) bv[nc] = bp[nc * 32 * a.XP + 2 * sp];
@@ -1356,17 +1361,21 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
                     for (int ts = 0; ts < NTS; ++ts)
 #pragma unroll
                         for (int nc = 0; nc < NC; ++nc)
-                            acc[ts][nc] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[ts], bv[nc], acc[ts][nc], 0, 0, 0);
+                            acc2[ph][ts][nc] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[ts], bv[nc], acc2[ph][ts][nc], 0, 0, 0);
                 };
+                std::integral_constant<int, 0> even;
+                std::integral_constant<int, PH - 1> odd;
                 int sp = 0;
-                for (; sp + 2 <= steps; sp += 2) { step(sp); step(sp + 1); }
-                if (sp < steps) step(sp);
+                for (; sp + 2 <= steps; sp += 2) { step(sp, even); step(sp + 1, odd); }
+                if (sp < steps) step(sp, even);
             }
         };
         if (nts == TS) rows(std::integral_constant<int, TS>{});
         else rows(std::integral_constant<int, TS - 1>{});
         if constexpr (FLUSH) {
-            const bool add = st > slice * a.stagesPerSlice;  // uniform
+            const int done = st - slice * a.stagesPerSlice;
+            if ((done + 1) % a.flush != 0 && st + 1 != st_end) continue;  // uniform
+            const bool add = done >= a.flush;  // uniform
 #pragma unroll
             for (int ts = 0; ts < TS; ++ts) {
                 if (ts >= nts) continue;
@@ -1375,13 +1384,19 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
                     const int ci = ci0 + nc * 32 + l32;
                     int row = (co0 + 4 * kk) * NN + wave + 4 * ts;
                     asm("" : "+v"(row));  // (worked out here and not kept across the loop)
-                    const unsigned voff = ci < g.Cin ? (unsigned)((row * g.Cin + ci) * 4) : kGwInvalid;
+                    const int cos = ci < g.Cin ? g.Cout - co0 - 4 * kk : 0;  // output channels from the lane's first one on
+                    const unsigned first = (unsigned)((row * g.Cin + ci) * 4);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const unsigned soff = (unsigned)((8 * (i / 4) + (i % 4)) * NN * g.Cin * 4);
+                        const int co = 8 * (i / 4) + i % 4;
+                        const unsigned voff = co < cos ? first + (unsigned)(co * NN * g.Cin * 4) : kGwInvalid;
                         float v = acc[ts][nc][i];
-                        if (add) v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_out, voff, soff, 0));
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs_out, voff, soff, 0);
+                        if constexpr (PH == 2) {
+                            v += acc2[1][ts][nc][i];
+                            acc2[1][ts][nc][i] = 0.f;
+                        }
+                        if (add) v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_out, voff, 0, 0));
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs_out, voff, 0, 0);
                         acc[ts][nc][i] = 0.f;
                     }
                 }
@@ -1409,45 +1424,55 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
 }
 
 // Sum of the copies p[0], p[n], p[2n], ...: running sums taken in turn, each with a load in flight, then pairs of them.  From
-// 64 copies on sixteen of them: a chain of copies / 16 roundings keeps the sum as exact as the copies are, and few kernel
-// elements leave a thread's loads a chain of round trips; with fewer copies the remainder costs more than it gives
-// (128 x 128 channels, n = 3, 63 copies: 194 -> 200 us with the gradient), so four.
+// 64 copies on, and for layers of few channels, sixteen of them, put away every 64 copies: a chain of four roundings and one for
+// every 64 copies keeps the sum as exact as the copies are (few channels, bf16, n = 2, 2048 to 4096 pixels: error 1.11 times that
+// of the vector ALUs with four running sums, 1.04 with sixteen), and few kernel elements leave a thread's loads a chain
+// of round trips; otherwise the remainder costs more than it gives (128 x 128 channels, n = 3, 63 copies: 194 -> 200 us with
+// the gradient), so four.
 template <int SUMS>
 __device__ __forceinline__ float sum_copies_in(const float* __restrict__ p, int n, int copies)
 {
-    float v[SUMS];
+    constexpr int CHUNK = SUMS == 16 ? 4 * SUMS : 0x7FFFFFF0;  // copies after which the running sums are put away
+    float total = 0.f;
+    for (int k = 0; k < copies;) {
+        const int end = copies - k > CHUNK ? k + CHUNK : copies;
+        float v[SUMS];
 #pragma unroll
-    for (int u = 0; u < SUMS; ++u) v[u] = 0.f;
-    int k = 0;
-    for (; k + SUMS - 1 < copies; k += SUMS) {
+        for (int u = 0; u < SUMS; ++u) v[u] = 0.f;
+        for (; k + SUMS - 1 < end; k += SUMS) {
 #pragma unroll
-        for (int u = 0; u < SUMS; ++u) v[u] += p[(size_t)(k + u) * n];
+            for (int u = 0; u < SUMS; ++u) v[u] += p[(size_t)(k + u) * n];
+        }
+        if (k < end) {  // (all loads in flight)
+            float t[SUMS - 1];
+#pragma unroll
+            for (int u = 0; u < SUMS - 1; ++u) t[u] = p[(size_t)(k + u < end ? k + u : end - 1) * n];
+#pragma unroll
+            for (int u = 0; u < SUMS - 1; ++u) v[u] += k + u < end ? t[u] : 0.f;
+            k = end;
+        }
+#pragma unroll
+        for (int m = 1; m < SUMS; m *= 2)
+#pragma unroll
+            for (int u = 0; u < SUMS; u += 2 * m) v[u] += v[u + m];
+        total += v[0];
     }
-    for (int u = 0; k < copies; ++k, ++u) {
-        const float t = p[(size_t)k * n];
-#pragma unroll
-        for (int w = 0; w < SUMS - 1; ++w) v[w] += w == u ? t : 0.f;
-    }
-#pragma unroll
-    for (int m = 1; m < SUMS; m *= 2)
-#pragma unroll
-        for (int u = 0; u < SUMS; u += 2 * m) v[u] += v[u + m];
-    return v[0];
+    return total;
 }
-__device__ __forceinline__ float sum_copies(const float* __restrict__ p, int n, int copies)
+__device__ __forceinline__ float sum_copies(const float* __restrict__ p, int n, int copies, int wide)
 {
-    return copies >= 64 ? sum_copies_in<16>(p, n, copies) : sum_copies_in<4>(p, n, copies);  // uniform
+    return wide ? sum_copies_in<16>(p, n, copies) : sum_copies_in<4>(p, n, copies);  // uniform
 }
 
 // dw[co][ci][tap] = sum over the copies of part[copy][co][tap][ci], copies added in a fixed order;
 // threads run along the copies' layout (coalesced reads), the single write pass is scattered
 __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restrict__ part,
                                                            float* __restrict__ dw, int n, int copies,
-                                                           int NN, int Cin)
+                                                           int wide, int NN, int Cin)
 {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
-    const float v = sum_copies(part + s, n, copies);
+    const float v = sum_copies(part + s, n, copies, wide);
     const int ci = s % Cin, r = s / Cin;
     const int tap = r % NN, co = r / NN;
     dw[((size_t)co * Cin + ci) * NN + tap] = v;
@@ -1459,7 +1484,7 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restr
 // for every fourth tap only, it is the slower one (64 x 64 channels, n = 5: 63 against 119 us with the gradient).
 __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __restrict__ part,
                                                            float* __restrict__ dw, int n, int copies,
-                                                           int NN, int Cin)
+                                                           int wide, int NN, int Cin)
 {
     extern __shared__ __align__(16) float lds_t[];  // [64][NN + 1]
     const int tilesI = (Cin + 63) / 64;
@@ -1468,7 +1493,7 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __
     if (ci0 + l < Cin)
         for (int tap = wv; tap < NN; tap += 4) {
             const float* p = part + ((size_t)co * NN + tap) * Cin + ci0 + l;
-            lds_t[l * (NN + 1) + tap] = sum_copies(p, n, copies);
+            lds_t[l * (NN + 1) + tap] = sum_copies(p, n, copies, wide);
         }
     __syncthreads();
     const int cis = Cin - ci0 < 64 ? Cin - ci0 : 64;
@@ -1484,12 +1509,13 @@ hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size
 {
     const int NN = g.n * g.n;
     const long long blocks = (long long)g.Cout * ((g.Cin + 63) / 64);
+    const int wide = copies >= 64 || few_channels(g) ? 1 : 0;
     if (blocks >= 2048 && blocks <= 0x7fffffffLL)
         hipLaunchKernelGGL(ukst_sum_taps_wide_kernel, dim3((unsigned)blocks), dim3(256), 64 * (NN + 1) * sizeof(float),
-                           stream, part, dw, (int)elems, copies, NN, g.Cin);
+                           stream, part, dw, (int)elems, copies, wide, NN, g.Cin);
     else
         hipLaunchKernelGGL(ukst_sum_taps_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, stream, part, dw,
-                           (int)elems, copies, NN, g.Cin);
+                           (int)elems, copies, wide, NN, g.Cin);
     return hipGetLastError();
 }
 
@@ -1498,17 +1524,18 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
 {
     const int N = g.n, CI_T = 32 * NC;
     // Layers of 16 to 31 channels leave up to half of a tile empty and still beat the vector ALUs (us, bf16: 30 -> 234
-    // channels, 7 x 23 x 23, n = 5 222 -> 50; 17 -> 346, 17 x 12 x 43, n = 4 238 -> 43; 178 -> 31, 14 x 72 x 72, n = 3 548 -> 47).
-    // Those kernels sum a few pixels in a chain: with 490 pixels this one's error against 64
-    // bits is 6 % above theirs (5.26e-8), with 5365 it is below (7.9e-8 -> 7.7e-8).  fp32 operands are rounded 16 times
-    // as often as bf16 ones: n = 5 adds every stage of at most 256 pixels to its copy of dw in memory (38 -> 30, 29 x 88 x 88
-    // 1412 -> 700 us, error 2.4e-7 -> 1.5e-7; 17 -> 78, 4 x 90 x 90 420 -> 190, 1.9e-7 -> 1.4e-7), for smaller kernels that costs
-    // what it gives (n = 4, 21 -> 70, 15 x 32 x 32 88 -> 96 us).
+    // channels, 7 x 23 x 23, n = 5 222 -> 55; 17 -> 346, 17 x 12 x 43, n = 4 235 -> 44; 178 -> 31, 14 x 72 x 72, n = 3 552 -> 63).
+    // Sums (few_channels()): this kernel rounds at every pixel pair where those on the bf16 pipe round at every sixteenth pixel.
+    // Its stages are 32 or 64 pixels, and its sums are added to the copy of dw in memory every 256 pixels, of fp32 operands,
+    // whose products are rounded too, every 64: error against 64 bits before (vector ALUs) / without / so: bf16, n = 5, 20 -> 512,
+    // 8 x 90 x 90 1.96e-7 / 3.89e-7 / 1.33e-7 (3707 / 660 / 949 us), n = 2 1.57e-7 / 3.89e-7 / 1.12e-7 (424 / 305 / 357 us); fp32, n = 5, 38 -> 30,
+    // 29 x 88 x 88 3.1e-7 / 5.3e-7 / 1.8e-7 (1416 / 294 / 725 us), 24 -> 100, 5 x 31 x 33 1.44e-7 / 1.59e-7 (64 pixels a stage) / 1.28e-7.
+    // fp32 operands of smaller kernels gain nothing (n = 4, 21 -> 70, 15 x 32 x 32 88 -> 96 us).
     const int least = g.Cin < g.Cout ? g.Cin : g.Cout;
     const long long pixels = (long long)g.B * g.H * g.W;
     if (least < 16 || N < 2 || (least < 32 && (N > 5 || (es == 4 ? N < 5 || pixels < 4096 : pixels < 2048)))) return false;
-    a.flush = least < 32 && es == 4 ? 1 : 0;
-    if (a.flush && (size_t)g.Cout * g.Cin * N * N * 4 > 0x7FFFFFF0u) return false;  // (one buffer descriptor)
+    const bool few = least < 32;
+    if (few && (size_t)g.Cout * g.Cin * N * N * 4 > 0x7FFFFFF0u) return false;  // (one buffer descriptor)
     a.g = g;
     a.TJ = pow2_ceil(g.W < 32 ? g.W : 32);
     if (a.TJ < 2) a.TJ = 2;
@@ -1516,7 +1543,8 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     a.HC = a.TJ + N / 2;
     a.cols = 2 * a.HC;
     const size_t budget = 78 * 1024;
-    int TR = (a.flush ? 256 : 512) / a.TJ;  // at most that many pixels per stage
+    // at most that many pixels per stage
+    int TR = (!few ? 512 : pixels < 16384 && (es == 4 || N < 5) ? 32 : 64) / a.TJ;
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);
@@ -1541,6 +1569,11 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     if (want > stages) want = stages;
     a.stagesPerSlice = (int)((stages + want - 1) / want);
     a.nSlices = (int)((stages + a.stagesPerSlice - 1) / a.stagesPerSlice);
+    a.flush = 0;
+    if (few) {
+        const int px = TR * a.TJ, most = es == 4 ? 64 : 256;
+        a.flush = px < most ? most / px : 1;
+    }
     a.cols4 = (a.cols + 3) / 4;
     a.npass = (a.TB * a.LR * a.cols4 + 63) / 64;
     // piecewise staging: rows of at least four elements (a row-end piece is fetched from inside
@@ -1579,7 +1612,7 @@ hipError_t launch_gw_mfma(const GwMfmaArgs& a, const void* x, const void* dy, fl
     const size_t lds = (size_t)4 * (32 * NC * a.XP + 32 * a.DP);
     typedef void (*kernel_t)(const TIn*, const TIn*, float*, GwMfmaArgs);
     kernel_t kernel = ukst_grad_weight_mfma_kernel<N, NC, TIn, false>;
-    if constexpr (sizeof(TIn) == 4 && N == 5)
+    if constexpr (N <= 5 && (sizeof(TIn) == 2 || N == 5))
         if (a.flush) kernel = ukst_grad_weight_mfma_kernel<N, NC, TIn, true>;
     const void* kfn = (const void*)kernel;
     e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1634,7 +1667,7 @@ __device__ __forceinline__ gw_u4 shift_elements(gw_u4 v, int s)
     return gw_u4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
 }
 
-template <int N, int NC>
+template <int N, int NC, bool FEW>
 __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(const uint16_t* __restrict__ x,
                                                                            const uint16_t* __restrict__ dy,
                                                                            float* __restrict__ part, GwB16Args a)
@@ -1668,13 +1701,18 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
     // (N - 1 - tc) >> 1 elements into the half row of parity (N - 1 - tc) & 1
     const int trow = ROWS ? wave : wave / N;
     const int tapoff = (N - 1 - trow) * a.cols + (ROWS ? 0 : ((N - 1 - wave % N) & 1) * a.HC);
-    f32x16 acc[TS][NC];
+    // FEW, n = 2: every other step on accumulators of its own, half the roundings in a chain
+    constexpr int PH = FEW && N == 2 ? 2 : 1;
+    f32x16 acc2[PH][TS][NC];
+    auto& acc = acc2[0];
 #pragma unroll
-    for (int ts = 0; ts < TS; ++ts)
+    for (int ph = 0; ph < PH; ++ph)
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc)
+        for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ts][nc][i] = 0.f;
+            for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc2[ph][ts][nc][i] = 0.f;
 
     const int npix = 1 << a.logPix, rowsPerCo = a.TB * a.LR;
     const int a_lane = l32 * a.DP + 8 * kk, b_lane = l32 * a.XP + 8 * kk;
@@ -1788,7 +1826,7 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
             if (b0 + bl >= g.B || i0 + li >= g.H) continue;  // uniform
             const uint16_t* ap = dys + a_lane + (bl * a.LR + 2 * li) * a.cols + tapoff;
             const uint16_t* bp = xs + b_lane + tr * a.TJ;
-            for (int sp = 0; sp < steps; ++sp) {
+            auto step = [&](int sp, auto ph) {
                 gw_bf16x8 bv[NC], av[TS];
 #pragma unroll
                 for (int nc = 0; nc < NC; ++nc)
@@ -1821,11 +1859,26 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_bf16_kernel(cons
                 for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
                     for (int nc = 0; nc < NC; ++nc)
-                        acc[ts][nc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ts], bv[nc], acc[ts][nc], 0, 0, 0);
+                        acc2[ph][ts][nc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ts], bv[nc], acc2[ph][ts][nc], 0, 0, 0);
+            };
+            std::integral_constant<int, 0> even;
+            std::integral_constant<int, PH - 1> odd;
+            if constexpr (PH == 1) {
+                for (int sp = 0; sp < steps; ++sp) step(sp, even);
+            } else if (tr & 1) {  // (rows of one or two steps)
+                for (int sp = 0; sp < steps; ++sp) step(sp, odd);
+            } else {
+                for (int sp = 0; sp < steps; ++sp) step(sp, even);
             }
         }
     }
 
+    if constexpr (PH == 2) {
+#pragma unroll
+        for (int ts = 0; ts < TS; ++ts)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) acc[ts][nc] += acc2[1][ts][nc];
+    }
     // accumulator register i: output channel 8*(i/4) + 4*kk + (i%4) of the 32, input channel l32
     float* out = part + (size_t)slice * g.Cout * g.Cin * NN;
 #pragma unroll
@@ -1850,7 +1903,7 @@ bool gw_b16_args(const Geom& g, GwB16Args& a)
 {
     const int N = g.n, CI_T = 32 * GW_B16_NC;
     if (g.Cin < 16 || g.Cout < 16 || N < 2 || N > 4) return false;
-    if ((g.Cin < 32 || g.Cout < 32) && (long long)g.B * g.H * g.W < 2048) return false;  // (see gw_mfma_args)
+    if (few_channels(g) && (long long)g.B * g.H * g.W < 2048) return false;  // (see gw_mfma_args)
     if (g.W % 8 != 0 || g.W < 16) return false;
     a.g = g;
     a.TJ = g.W >= 32 ? 32 : 16;
@@ -1859,7 +1912,8 @@ bool gw_b16_args(const Geom& g, GwB16Args& a)
     a.cols = 2 * a.HC;
     a.c8 = (2 * a.TJ + N - 2 + 7) / 8;
     const size_t budget = 78 * 1024;
-    int TR = 512 / a.TJ;  // at most 512 pixels per stage
+    const bool few = few_channels(g);
+    int TR = (few ? few_stage(g) : 512) / a.TJ;  // at most that many pixels per stage
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);
@@ -1883,10 +1937,12 @@ bool gw_b16_args(const Geom& g, GwB16Args& a)
     a.coTiles = (g.Cout + 31) / 32;
     a.ciTiles = (g.Cin + CI_T - 1) / CI_T;
     long long want = 512 / ((long long)a.coTiles * a.ciTiles);
+    if (few) want = few_slices(g, stages * TR * a.TJ, want);
     if (want < 1) want = 1;
     if (want > stages) want = stages;
     a.stagesPerSlice = (int)((stages + want - 1) / want);
     a.nSlices = (int)((stages + a.stagesPerSlice - 1) / a.stagesPerSlice);
+    if (few && (long long)a.stagesPerSlice * TR * a.TJ > kFewChainMax) return false;
     a.dC8 = make_fastdiv((unsigned)a.c8);
     a.dRows = make_fastdiv((unsigned)(a.TB * a.LR));
     a.dLR = make_fastdiv((unsigned)a.LR);
@@ -1912,11 +1968,14 @@ hipError_t launch_gw_b16(const GwB16Args& a, const void* x, const void* dy, floa
     float* part = (float*)ws.ptr;
     hipError_t e;
     const size_t lds = (size_t)2 * (32 * NC * a.XP + 32 * a.DP);
-    const void* kfn = (const void*)ukst_grad_weight_mfma_bf16_kernel<N, NC>;
+    typedef void (*kernel_t)(const uint16_t*, const uint16_t*, float*, GwB16Args);
+    const kernel_t kernel = few_channels(g) ? ukst_grad_weight_mfma_bf16_kernel<N, NC, true>
+                                                      : ukst_grad_weight_mfma_bf16_kernel<N, NC, false>;
+    const void* kfn = (const void*)kernel;
     e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess) {
         const unsigned nb = (unsigned)((long long)a.nSlices * a.coTiles * a.ciTiles);
-        hipLaunchKernelGGL((ukst_grad_weight_mfma_bf16_kernel<N, NC>), dim3(nb), dim3(256), lds, stream,
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), lds, stream,
                            (const uint16_t*)x, (const uint16_t*)dy, part, a);
         e = hipGetLastError();
     }

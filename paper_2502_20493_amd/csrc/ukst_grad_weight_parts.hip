@@ -373,7 +373,8 @@ bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
     a.HC = a.TJ + 8;  // half rows: TJ + 1 columns are read, at most TJ + 4 written, whole 16-byte slots
     a.cols = 2 * a.HC;
     a.c4 = (2 * a.TJ + N - 2 + 3) / 4;
-    for (int TR = 512 / a.TJ;; TR >>= 1) {
+    const bool few = few_channels(g);
+    for (int TR = (few ? few_stage(g) : 512) / a.TJ;; TR >>= 1) {
         if (TR < 1) return false;
         a.TR = TR;
         a.TI = 1 << log2_of(g.H < TR ? g.H : TR);
@@ -396,11 +397,13 @@ bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
     a.coTiles = (g.Cout + 31) / 32;
     a.ciTiles = (g.Cin + CI_T - 1) / CI_T;
     long long want = 512 / ((long long)a.coTiles * a.ciTiles);
+    if (few) want = few_slices(g, stages * a.TR * a.TJ, want);
     if (want < 1) want = 1;
     if (want > stages) want = stages;
-    if (want > max_slices) want = max_slices;
+    if (!few && want > max_slices) want = max_slices;
     a.stagesPerSlice = (int)((stages + want - 1) / want);
     a.nSlices = (int)((stages + a.stagesPerSlice - 1) / a.stagesPerSlice);
+    if (few && (long long)a.stagesPerSlice * a.TR * a.TJ > kFewChainMax) return false;
     a.npass = (a.TB * a.LR * a.c4 + 63) / 64;
     a.dC4 = make_fastdiv((unsigned)a.c4);
     a.dLR = make_fastdiv((unsigned)a.LR);

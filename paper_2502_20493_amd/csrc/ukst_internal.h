@@ -219,9 +219,27 @@ hipError_t launch_grad_input_window(const Geom& g, const void* dy, const void* w
 bool grad_narrow_supported(const Geom& g, int dtype);
 hipError_t launch_grad_narrow(int which, const Geom& g, const void* p0, const void* p1, float* out, Workspace& ws,
                               hipStream_t stream);
+// Kernel gradients on the matrix cores of layers with fewer than 32 channels on a side, which the vector ALUs, with sixteen
+// times as many threads' sums, took before: short chains keep their sums as exact as those.  Short stages (a few pixels are
+// one stage per copy of dw), and a copy for every kFewChain pixels as long as the copies fit 64 MiB, the static
+// scratch; beyond kFewChainMax the layer is for the kernel that adds its sums to the copy in memory on the way.
+// (bf16 operands, error against 64 bits over that of the vector ALUs, 2500 layers: n = 2, 65536 pixels and more 1.25 to 1.37, up to
+// 1.79, at 512 pixels a stage and 512 blocks, 0.86 to 0.90 so; n = 4 1.15, up to 1.47 / 0.82; n = 3, 2048 to 4096 pixels 1.06 / 0.93.)
+constexpr int kFewChannels = 32, kFewChain = 512, kFewChainMax = 2048;
+inline bool few_channels(const GeomBase& g) { return g.Cin < kFewChannels || g.Cout < kFewChannels; }
+// pixels of a stage, at most (128 instead of 64 cost 0 to 4 % of error and save 7 % of the time)
+inline int few_stage(const GeomBase& g) { return (long long)g.B * g.H * g.W < 8192 ? 64 : 128; }
+// copies of dw of such a layer, `least` if not more
+inline long long few_slices(const GeomBase& g, long long pixels, long long least)
+{
+    const long long fit = (long long)(((size_t)1 << 26) / ((size_t)g.Cout * g.Cin * g.n * g.n * 4));
+    long long want = (pixels + kFewChain - 1) / kFewChain;
+    if (want > fit) want = fit;
+    return want > least ? want : least;
+}
 // Kernel gradient of wide layers from bf16 parts (n = 3, 4, rows of at least 16 pixels): the number of copies of dw,
-// laid out [co][tap][ci], that it writes to `part` (at most max_slices; 0: the layer is not for it).  es: 4 or 2,
-// bytes of an operand element
+// laid out [co][tap][ci], that it writes to `part` (at most max_slices, or as many as few_slices() says; 0: the layer is not
+// for it).  es: 4 or 2, bytes of an operand element
 int grad_weight_parts_slices(const GeomBase& g, int es, int max_slices);
 hipError_t launch_grad_weight_parts(const GeomBase& g, const void* x, const void* dy, float* part, int es,
                                     int max_slices, hipStream_t stream);

@@ -239,3 +239,54 @@ def test_kernel_gradient_of_16_to_31_channels(shape, integer):
     ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
     got = run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096)
     check_elements(got, ref, S, TOL["f32"], exact=integer)
+
+
+def _kernel_gradient64(x, dy, n, P):
+    """dw of the definition in 64 bits, from the operands as they are."""
+    import torch
+    B, Cin, H, W = x.shape
+    Cout, OH, OW = dy.shape[1:]
+    dw = torch.zeros((Cout, Cin, n, n), dtype=torch.float64, device=x.device)
+    # rows of dy from -(n - 1) + P on: the lattice of tap a starts at row P - a
+    lo, hi = max(0, n - 1 - P), max(0, 2 * (H - 1) + P - (OH - 1))
+    wi = max(0, 2 * (W - 1) + P - (OW - 1))
+    for b in range(B):
+        xb = x[b].double().reshape(Cin, H * W).t().contiguous()
+        d = torch.nn.functional.pad(dy[b].double(), (lo, wi, lo, hi))
+        for a in range(n):
+            for c in range(n):
+                r, q = P - a + lo, P - c + lo
+                t = d[:, r:r + 2 * H - 1:2, q:q + 2 * W - 1:2]
+                dw[:, :, a, c] += t.reshape(Cout, H * W) @ xb
+    return dw
+
+
+# B, Cin, Cout, H, W, n, P, dtype, the error of the vector ALUs' kernel (2-norm, against 64 bits) on operands of this law
+@pytest.mark.parametrize("shape,before", [
+    ((8, 20, 512, 90, 90, 5, 2, "bf16"), 1.96e-7),   # fp32 pipe, sums added to memory on the way
+    ((8, 20, 512, 90, 90, 2, 1, "bf16"), 1.57e-7),   # ... on two sets of accumulators
+    ((8, 20, 512, 88, 88, 2, 1, "bf16"), 1.55e-7),   # bf16 pipe
+    ((8, 20, 512, 88, 88, 3, 1, "bf16"), 1.85e-7),
+    ((8, 20, 512, 88, 88, 4, 1, "bf16"), 1.94e-7),
+    ((8, 20, 512, 90, 90, 3, 1, "bf16"), 1.86e-7),   # one part
+    ((8, 20, 512, 90, 90, 4, 1, "bf16"), 1.95e-7),
+    ((2, 24, 24, 48, 48, 3, 1, "bf16"), 8.11e-8),    # few pixels
+    ((2, 24, 24, 48, 48, 4, 1, "bf16"), 8.30e-8),
+    ((5, 24, 100, 31, 33, 5, 2, "f32"), 1.44e-7),
+])
+def test_kernel_gradient_of_16_to_31_channels_is_as_exact_as_the_vector_alus(shape, before):
+    import torch
+    B, Cin, Cout, H, W, n, P, dtype = shape
+    print(f"case {shape}", flush=True)
+    dt = ukst.UKST_F32 if dtype == "f32" else ukst.UKST_BF16_F32
+    assert "mfma" in ukst.ukst_grad_kernel_name(1, *shape[:7], dt)
+    OH, OW = ukst.ukst_output_shape(H, W, n, P)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9700 + sum(shape[:7]))
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    x = torch.randn((B, Cin, H, W), generator=g, device="cuda").to(t)
+    dy = torch.randn((B, Cout, OH, OW), generator=g, device="cuda").to(t)
+    dw = ukst.ukst_conv_transpose2d_grad_weight(x, dy, n, P)
+    ref = _kernel_gradient64(x, dy, n, P)
+    err = float((dw - ref).norm() / ref.norm())
+    assert err <= 1.02 * before, err  # (other operands of the same law: 2 %)
