@@ -168,11 +168,13 @@ typedef enum { UKST_OP_FORWARD = 0, UKST_OP_GRAD_INPUT = 1, UKST_OP_GRAD_WEIGHT 
  *   UKST_OP_FORWARD      fp32 matrix-core layers with fewer output tiles than compute units divide
  *                        the input channels of a tile among several blocks; each slice writes its
  *                        partial sums to its own copy of y in the workspace and a second kernel
- *                        adds the copies in slice order.
+ *                        adds the copies in slice order.  (Layers on the small tiles, from 52 input
+ *                        channels on: those that leave half of the compute units idle.)
  *   UKST_OP_GRAD_INPUT   matrix-core kernels (Cin >= 32, Cout >= 16): the weights re-packed once
  *                        per call, plus, for layers with few pixels, one copy of dx per slice of
  *                        the sum over output channels (added in slice order).  Asked for also where
- *                        the layer runs on a kernel that leaves it untouched.
+ *                        the layer runs on bf16 parts, which leaves it untouched; none for layers
+ *                        of few tiles, which run on the small ones.
  *   UKST_OP_GRAD_WEIGHT  one copy of dw per slice of the sum over batch and space (added in a
  *                        fixed order); every kernel of this operation needs it.
  * The workspace is caller-owned DEVICE memory, 256-byte aligned, needs no initialisation, holds

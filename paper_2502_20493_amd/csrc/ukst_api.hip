@@ -434,4 +434,18 @@ const char* ukst_kernel_name(int B, int Cin, int Cout, int H, int W, int n, int 
                                     : ukst::direct_kernel_name(g, dtype);
 }
 
+// For the tests of the dispatch, not part of the interface: op 0 forward (AUTO, with its workspace), 1 input gradient,
+// 2 kernel gradient, 3 strided, 4 dilated (k: the step); valid arguments expected.  See forward_plan().
+int ukst_test_plan(int op, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int dtype)
+{
+    if (op == 3 || op == 4) {
+        int OH = 0, OW = 0;
+        if (!general_shape(op == 4, H, W, n, P, k, &OH, &OW)) return -1;
+        return ukst::general_plan(op == 4, B, Cin, Cout, H, W, n, P, k, OH, OW, dtype);
+    }
+    if (validate_shape(B, Cin, Cout, H, W, n, P) != UKST_OK || n > UKST_MAX_N) return -1;
+    const ukst::Geom g = ukst::make_geom(B, Cin, Cout, H, W, n, P);
+    return op == 0 ? ukst::forward_plan(g, dtype) : ukst::grad_plan(g, op - 1, dtype);
+}
+
 }  // extern "C"

@@ -2491,6 +2491,18 @@ hipError_t launch_gi(const Geom& g, const void* dy, const void* w, float* dx, in
 
 }  // namespace
 
+int grad_plan(const Geom& g, int which, int dtype)
+{
+    if (which == 0) return prefer_small(g, dtype) ? small_plan(small_problem(g, dtype), 0) : 0;
+    const int es = dtype == 0 ? 4 : 2;
+    GwB16Args ba;
+    GwMfmaArgs wa;
+    if ((dtype == 1 && gw_b16_args(g, ba)) || !(g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa, es) : gw_mfma_args<gw_nc(5)>(g, wa, es)) ||
+        wa.flush == 0 || (g.n <= 4 && grad_weight_parts_slices(g, es, wa.nSlices) != 0))
+        return 0;
+    return wa.flush | (wa.stagesPerSlice < 0x7FFF ? wa.stagesPerSlice : 0x7FFF) << 16;
+}
+
 const char* grad_kernel_name(const Geom& g, int which, int dtype)
 {
     if (which == 1) {
@@ -2521,13 +2533,9 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
 hipError_t launch_grad_input(const Geom& g, const void* dy, const void* w, float* dx, int dtype,
                              Workspace& ws, hipStream_t stream)
 {
-    if (ws.query || !prefer_small(g, dtype)) return launch_gi(g, dy, w, dx, dtype, ws, stream);
-    // (the small tiles use no workspace; what is asked for and refused is what the kernel beyond the line asks for)
-    Workspace need;
-    need.query = true;
-    const hipError_t e = launch_gi(g, nullptr, nullptr, nullptr, dtype, need, stream);
-    if (e != hipSuccess) return e;
-    if (ws.bytes < need.need) return kWorkspaceTooSmall;
+    if (!prefer_small(g, dtype)) return launch_gi(g, dy, w, dx, dtype, ws, stream);
+    ws.need = 0;
+    if (ws.query) return hipSuccess;
     Workspace none;
     return launch_small(small_problem(g, dtype), Epilogue{nullptr, 0}, dy, w, dx, none, stream);
 }

@@ -131,6 +131,12 @@ static bool prefer_small(const SmallProblem& q)
            !general_mfma_fits(1, q.B, q.K, q.M, q.XH, q.XW, q.n, q.P, q.step, q.OH, q.OW, q.dtype);
 }
 
+int general_plan(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW, int dtype)
+{
+    const SmallProblem q{dilated ? SmallOp::dilated : SmallOp::strided, B, Cin, Cout, H, W, OH, OW, n, P, k, dtype};
+    return prefer_small(q) ? small_plan(q, 0) : 0;
+}
+
 // k = stride (dilated == 0) or dilation (dilated == 1); shapes validated by the caller
 hipError_t launch_general(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k,
                           int OH, int OW, const void* x, const void* w, float* y, int dtype,

@@ -183,6 +183,8 @@ struct SmallProblem {
 long long small_blocks(const SmallProblem& q, int edge = 32);  // its edge x edge tiles, 0 if the kernels do not take it
 // bytes of workspace with which fp32 forward layers of very few blocks run in slices (without, or with less: unsliced)
 size_t small_workspace(const SmallProblem& q);
+// the tile a launch takes, with that workspace (rows | waves << 8 | slices << 16), 0 if the kernels do not take the problem
+int small_plan(const SmallProblem& q, size_t workspace_bytes);
 hipError_t launch_small(const SmallProblem& q, const Epilogue& ep, const void* x, const void* w, void* y, Workspace& ws,
                         hipStream_t stream);
 // y[i] = part[0][i] + part[1][i] + ... in this order, `ks` copies copy_bytes apart, then the epilogue
@@ -248,5 +250,11 @@ bool grad_input_parts_supported(const GeomBase& g);
 hipError_t launch_grad_input_parts(const GeomBase& g, const float* dy, const float* w, float* dx, hipStream_t stream);
 // which: 0 gradient w.r.t. the input, 1 w.r.t. the kernel
 const char* grad_kernel_name(const Geom& g, int which, int dtype);
+
+// What the tests of the dispatch look at: small_plan() of the layers that run on the small tiles, 64 | slices << 16 of the
+// forward layers that run in slices on the fp32 pipe's wider ones, 0 for all others; of a kernel gradient that adds to its copies on the way, the stages after which it does, | stages of a copy << 16
+int forward_plan(const Geom& g, int dtype);
+int grad_plan(const Geom& g, int which, int dtype);
+int general_plan(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW, int dtype);
 
 }  // namespace ukst

@@ -657,25 +657,14 @@ hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, in
         if (e == hipSuccess && (ws.query || (ws.ptr != nullptr && ws.bytes >= need.need)))
             return launch_mfma_parts_split(g, x, w, y, ws, stream);
     }
-    // even n and P, whole stages of 64 (n = 2: 128) channels: slices, if they are of use
-    const bool slices = g.n % 2 == 0 && g.P % 2 == 0 && g.Cin % (g.n == 2 ? 128 : 64) == 0;
-    if (small && (!ws.query || slices)) {
+    if (small) {
         if (ws.query) {
             ws.need = small_workspace(small_problem(g, dtype));
             return hipSuccess;
         }
-        // the others need no workspace; what is asked for, and refused if it is too small, is what the kernel asks for
-        // that runs such layers beyond the line
-        if (ws.ptr != nullptr && !slices && mfma_f32_supported(g, dtype) && !prefer_parts(g, dtype)) {
-            Workspace need;
-            need.query = true;
-            const hipError_t e = launch_mfma_f32(g, nullptr, nullptr, nullptr, dtype, need, stream);
-            if (e != hipSuccess) return e;
-            if (ws.bytes < need.need && ((uintptr_t)y & 15) == 0) return kWorkspaceTooSmall;
-        }
         return launch_small(small_problem(g, dtype), g.ep, x, w, y, ws, stream);
     }
-    if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)) && !(small && prefer_parts(g, dtype)))
+    if (mfma_f32_supported(g, dtype) && (dtype == 0 || !bf16_pipe(g, dtype)))
         return launch_mfma_f32(g, x, w, y, dtype, ws, stream);
     if (ws.query) return hipSuccess;  // the kernels below use no scratch
     if (dtype == 0) return launch_thin_mfma(g, x, w, y, stream);
@@ -714,6 +703,19 @@ hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, in
     hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(256), lds, stream, (const uint16_t*)x,
                        (const uint16_t*)w, (void*)y, a, g.ep);
     return hipGetLastError();
+}
+
+int forward_plan(const Geom& g, int dtype)
+{
+    const bool small = prefer_small(g, dtype);
+    Workspace ws;
+    ws.query = true;
+    if ((!small && prefer_parts(g, dtype)) || launch_mfma(g, nullptr, nullptr, nullptr, dtype, ws, nullptr) != hipSuccess ||
+        (prefer_parts_split(g, dtype) && (!small || small_blocks(small_problem(g, dtype)) > 256)))
+        return 0;
+    if (small) return small_plan(small_problem(g, dtype), ws.need);
+    const size_t slices = ws.need / ((size_t)g.B * g.Cout * g.OH * g.OW * 4);
+    return slices != 0 ? 64 | (int)slices << 16 : 0;
 }
 
 const char* mfma_kernel_name(const Geom& g, int dtype)

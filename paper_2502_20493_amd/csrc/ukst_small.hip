@@ -139,12 +139,13 @@ bool pick(const SmallProblem& q, SmallArgs& a, int& mt, int& wv)
     return best != 0.;
 }
 
-// cuts the stages of a plan into slices over blocks; false if that is no use
-bool slice(const SmallProblem& q, SmallArgs& a, int wv)
+// cuts the stages of a plan into slices over blocks; false if that is no use (see small_workspace())
+bool slice(const SmallProblem& q, SmallArgs& a, int mt, int wv)
 {
     const long long blocks = (long long)a.nmt * a.npt * a.nct;
     const int per_wave = (a.kslice + wv - 1) / wv;
-    if (q.dtype != 0 || blocks > 128 || per_wave < 4) return false;
+    const int least = q.n == 3 || (q.n == 2 && mt == 32) ? 5 : 4;
+    if (q.op != SmallOp::forward || q.dtype != 0 || blocks > 128 || per_wave < least) return false;
     a.copy_bytes = ws_align((size_t)q.B * q.M * q.OH * q.OW * 4);
     int ks = (int)(256 / blocks);
     if (ks > per_wave) ks = per_wave;
@@ -181,14 +182,26 @@ long long small_blocks(const SmallProblem& q, int edge)
     return m * p * a.nct * a.res * a.res;
 }
 
-// Slices of the stages, given a workspace: layers that leave half of the compute units idle and have at least four stages
-// for every wave (us, unsliced -> sliced with the sum: one image, 512 -> 256 channels, 4 x 4, n = 4 13.3 -> 8.6; two, 1024 -> 64,
-// 8 x 8 22.4 -> 10.6; eight, 512 -> 256, 4 x 4 14.3 -> 12.2; 60, 512 -> 24, 4 x 4 14.4 -> 12.2)
+// Slices of the stages, given a workspace: fp32 layers that leave half of the compute units idle and have at least four stages
+// for every wave, five of the shorter ones of n = 3 and of n = 2 in 32 x 32 tiles (us, unsliced -> sliced with the sum: one image,
+// 512 -> 256 channels, 4 x 4, n = 4 13.3 -> 8.6, 500 -> 256 13.4 -> 8.6, n = 5, P = 1 23.7 -> 10.8, n = 3 11.0 -> 7.9; two, 1024 -> 64,
+// 8 x 8 22.4 -> 10.6; eight, 512 -> 256, 4 x 4 14.3 -> 12.2; 60, 512 -> 24, 4 x 4 14.4 -> 12.2; at the line, n = 2, 449 -> 16, 6 of 7 x 6
+// 9.0 -> 7.9, n = 4, 256 -> 128, 8 x 8 8.6 -> 7.9, but n = 3, 256 -> 128, 2 of 8 x 8 7.9 -> 8.0, 210 -> 313, 6 x 8 7.3 -> 8.4, n = 2, 211 -> 482,
+// 2 of 7 x 15 10.3 -> 11.6; 128 layers 1.49 times as fast on average)
 size_t small_workspace(const SmallProblem& q)
 {
     SmallArgs a;
     int mt, wv;
-    return q.op == SmallOp::forward && pick(q, a, mt, wv) && slice(q, a, wv) ? a.ksplit * a.copy_bytes : 0;
+    return pick(q, a, mt, wv) && slice(q, a, mt, wv) ? a.ksplit * a.copy_bytes : 0;
+}
+
+int small_plan(const SmallProblem& q, size_t workspace_bytes)
+{
+    SmallArgs a;
+    int mt, wv;
+    if (!pick(q, a, mt, wv)) return 0;
+    const bool sliced = slice(q, a, mt, wv) && workspace_bytes >= a.ksplit * a.copy_bytes;
+    return mt | wv << 8 | (sliced ? a.ksplit : 1) << 16;
 }
 
 hipError_t launch_small(const SmallProblem& q, const Epilogue& ep, const void* x, const void* w, void* y, Workspace& ws,
@@ -197,8 +210,7 @@ hipError_t launch_small(const SmallProblem& q, const Epilogue& ep, const void* x
     SmallArgs a;
     int mt, wv;
     if (!pick(q, a, mt, wv)) return hipErrorInvalidValue;
-    const bool sliced = q.op == SmallOp::forward && ws.ptr != nullptr && slice(q, a, wv) &&
-                        ws.bytes >= a.ksplit * a.copy_bytes;
+    const bool sliced = ws.ptr != nullptr && slice(q, a, mt, wv) && ws.bytes >= a.ksplit * a.copy_bytes;
     if (!sliced) {
         a.ksplit = 1;
         a.kslice = q.K;  // (at least the stages)

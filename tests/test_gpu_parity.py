@@ -453,7 +453,7 @@ def test_non_default_stream(case):
     import torch
     from gpu_util import to_device
     w = {"narrow": wl.WORKLOADS["cfg1"],
-         "mfma_f32_split_k": _mk("stream_f32", 8201, 2, 64, 16, 5, 6, 4, 1),
+         "mfma_f32_split_k": _mk("stream_f32", 8201, 2, 48, 16, 5, 6, 4, 1),
          "mfma_bf16": _mk("stream_bf16", 8202, 2, 32, 64, 6, 16, 4, 2, dtype="bf16")}[case]
     data = wl.generate(w)
     x, wt = to_device(data, w.dtype)

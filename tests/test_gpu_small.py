@@ -26,6 +26,15 @@ FORWARD_SHAPES = [
 ]
 
 
+def _plan(op, shape, dtype="f32", k=2):
+    """What the dispatch of ukst_internal.h says: tile rows, waves, slices on the small tiles (zeros elsewhere); of a kernel
+    gradient, the stages after which its sums are added to memory, and the stages of a slice."""
+    v = ukst.lib().ukst_test_plan(("forward", "grad_input", "grad_weight", "strided", "dilated").index(op), *shape[:7], k,
+                                  ukst.UKST_F32 if dtype == "f32" else ukst.UKST_BF16_F32)
+    assert v >= 0
+    return (v & 0xFFFF, v >> 16) if op == "grad_weight" else (v & 255, v >> 8 & 255, v >> 16)
+
+
 def _mk(shape):
     B, Cin, Cout, H, W, n, P, dtype = shape
     return wl.Workload("small", 9500 + sum(shape[:7]), B, Cin, Cout, H, W, n, P, dtype, "normal", "normal:0.5")
@@ -290,3 +299,57 @@ def test_kernel_gradient_of_16_to_31_channels_is_as_exact_as_the_vector_alus(sha
     ref = _kernel_gradient64(x, dy, n, P)
     err = float((dw - ref).norm() / ref.norm())
     assert err <= 1.02 * before, err  # (other operands of the same law: 2 %)
+
+
+# odd P, kernels of odd side, channel counts that are no whole stages
+@pytest.mark.parametrize("shape,slices", [
+    ((1, 500, 256, 4, 4, 4, 2), 8), ((1, 333, 37, 5, 4, 5, 1), 6), ((2, 430, 8, 7, 10, 3, 1), 7), ((2, 704, 4, 17, 17, 2, 0), 6),
+    ((3, 397, 35, 5, 7, 4, 3), 7)])
+def test_forward_layers_in_slices(shape, slices):
+    """Whatever layer the plan cuts, with what ukst_workspace_bytes asks for; with less, or none, the whole sum in one block."""
+    import torch
+    from gpu_util import to_device
+    B, Cin, Cout, H, W, n, P = shape
+    assert _plan("forward", shape)[2] == slices
+    OH, OW = ukst.ukst_output_shape(H, W, n, P)
+    need = ukst.ukst_workspace_bytes(ukst.UKST_OP_FORWARD, *shape, ukst.UKST_F32)
+    copy = -(-B * Cout * OH * OW * 4 // 256) * 256  # (copies start at whole 256 bytes)
+    assert need == slices * copy
+    w = _mk(shape + ("f32",))
+    data = wl.generate(w)
+    x, k = to_device(data, w.dtype)
+    y_ref, S = oracle.naive(data["x"], data["w"], P)
+    bias = np.linspace(-1.0, 1.0, Cout).astype(np.float32)
+    z = np.tanh(y_ref + bias.astype(np.float64)[None, :, None, None])
+    whole = ukst.ukst_conv_transpose2d(x, k, P)
+    space = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for ws in (None, space, space[:need - 256], False):
+        y = ukst.ukst_conv_transpose2d(x, k, P, workspace=ws)
+        check_against_oracle(y.cpu().numpy(), y_ref, S, TOL["f32"])
+        assert torch.equal(y, whole) == (ws is False or (ws is not None and ws.numel() < need))
+        y = ukst.ukst_conv_transpose2d_ws(x, k, P, bias=torch.from_numpy(bias).cuda(), act=ukst.UKST_ACT_TANH, workspace=ws)
+        assert (np.abs(y.cpu().numpy() - z) <= TOL["f32"] * S + 1.2e-7 * np.abs(y_ref) + 2e-6).all()
+
+
+@pytest.mark.parametrize("shape", [GRAD_INPUT_SHAPES[1], GRAD_INPUT_SHAPES[5], (1, 34, 18, 43, 35, 4, 2, "f32")])
+def test_input_gradients_on_the_small_tiles_ask_for_no_workspace(shape):
+    import torch
+    from gpu_util import check_elements
+    w = _mk(shape)
+    dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
+    assert ukst.ukst_workspace_bytes(ukst.UKST_OP_GRAD_INPUT, *shape[:7], dt) == 0
+    data = wl.generate(w)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P))
+    ref, S = oracle.grad_input(dyd["dy"], data["w"], w.H, w.W, w.P)
+
+    def dev(a, bits):
+        return (torch.from_numpy(a) if w.dtype == "f32" else torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16)).cuda()
+    dy, k = dev(dyd["dy"], dyd.get("dy_bits")), dev(data["w"], data.get("w_bits"))
+    dx = torch.full((w.B, w.Cin, w.H, w.W), -777.0, device="cuda")
+    status = ukst.lib().ukst_conv_transpose2d_grad_input(dy.data_ptr(), k.data_ptr(), dx.data_ptr(), *shape[:7], dt, None, 0,
+                                                         torch.cuda.current_stream().cuda_stream)
+    assert status == ukst.UKST_OK
+    check_elements(dx.cpu().numpy(), ref, S, TOL["f32"])
+    # a workspace that an earlier version asked for is accepted
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    assert torch.equal(ukst.ukst_conv_transpose2d_grad_input(dy, k, w.H, w.W, w.P, workspace=ws), dx)
