@@ -255,11 +255,11 @@ MFMA_F32_SHAPES = [
     (1, 16, 128, 33, 31, 3, 0),   # several row tiles of one image, two channel blocks
     (1, 8, 64, 1, 9, 4, 2),       # single input row
     (2, 32, 64, 63, 63, 3, 0),    # cfg4b spatial shape: wide tiles (NW = 4)
-    (2, 64, 16, 5, 6, 4, 2),      # few tiles, even n and P: 32 x 32 tiles, K pairs dealt to the four waves
-    (2, 64, 16, 5, 6, 4, 1),      # few tiles, odd P: the K loop is split over 4 blocks (workspace)
-    (1, 96, 8, 3, 5, 3, 1),       # 6 stages of 16: split in 2
+    (2, 64, 16, 5, 6, 4, 2),      # few tiles, even n and P: on the small tiles (ukst_small_kernel.h)
+    (2, 64, 16, 5, 6, 4, 1),      # ... and odd P
+    (1, 96, 8, 3, 5, 3, 1),
     (3, 128, 40, 4, 4, 4, 2),     # 4x4 maps, ragged channel block and ragged last quad tile, 4 stages
-    (3, 48, 40, 4, 4, 4, 2),      # same maps, a channel count the small tiles do not take
+    (3, 48, 40, 4, 4, 4, 2),      # same maps, a channel count the small tiles do not take: split in 2 (workspace)
     (2, 128, 32, 3, 7, 2, 0),     # n = 2 on small tiles (64 input channels per stage: 8 K pairs per wave)
     (5, 64, 72, 2, 3, 4, 4),      # P > n - 1 on tiny maps
 ]
@@ -296,6 +296,45 @@ def test_bf16_layers_with_other_kernel_sides_run_on_the_fp32_matrix_pipe(shape):
     _parity(w, PATHS["mfma"], integer=False)
     if ukst.ukst_workspace_bytes(ukst.UKST_OP_FORWARD, B, Cin, Cout, H, W, n, P, ukst.UKST_BF16_F32):
         _parity(w, PATHS["mfma"], integer=False, workspace=None)
+
+
+# the K loop split over blocks of the wide tiles, partial sums in the workspace: B, Cin, Cout, H, W, n, P, dtype, slices
+SPLIT_K_SHAPES = [
+    (3, 48, 40, 4, 4, 4, 2, "f32", 2), (3, 48, 40, 4, 4, 4, 2, "bf16", 2),   # output-aligned quads
+    (2, 48, 16, 5, 6, 4, 1, "f32", 2), (2, 48, 16, 5, 6, 4, 1, "bf16", 2),   # shifted quads
+    (4, 32, 24, 5, 3, 5, 0, "f32", 2), (4, 32, 24, 5, 3, 5, 0, "bf16", 2),
+    (13, 128, 80, 15, 28, 3, 1, "f32", 4), (15, 64, 40, 9, 34, 3, 0, "bf16", 2),
+    (13, 64, 112, 11, 40, 2, 4, "f32", 2), (20, 64, 104, 39, 3, 2, 4, "bf16", 2),
+]
+
+
+def _slices_on_the_wide_tiles(shape, dtype):
+    v = ukst.lib().ukst_test_plan(0, *shape, 2, ukst.UKST_F32 if dtype == "f32" else ukst.UKST_BF16_F32)
+    return v >> 16 if v & 255 == 64 else 0
+
+
+@pytest.mark.parametrize("case", SPLIT_K_SHAPES)
+def test_mfma_f32_split_k_every_element(case):
+    """With bias and activation in the sum of the slices, and on a stream of its own."""
+    import torch
+    from gpu_util import to_device
+    shape, dtype, slices = case[:7], case[7], case[8]
+    assert _slices_on_the_wide_tiles(shape, dtype) == slices
+    w = _mk("split_k", 8600 + sum(shape), *shape, dtype=dtype)
+    for integer in (True, False):
+        _parity(w, PATHS["auto"], integer=integer, workspace=None)
+    data = wl.generate(w)
+    x, k = to_device(data, dtype)
+    bias = np.linspace(-1.0, 1.0, w.Cout).astype(np.float32)
+    y_ref, S = oracle.naive(data["x"], data["w"], w.P)
+    z = np.maximum(y_ref + bias.astype(np.float64)[None, :, None, None], 0.0)
+    b = torch.from_numpy(bias).cuda()
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        y = ukst.ukst_conv_transpose2d_ws(x, k, w.P, bias=b, act=ukst.UKST_ACT_RELU)
+    s.synchronize()
+    assert (np.abs(y.cpu().numpy() - z) <= TOL["f32"] * S + 1.2e-7 * np.abs(y_ref)).all()
 
 
 THIN_MFMA_SHAPES = [
@@ -551,7 +590,7 @@ EPILOGUE_CASES = [
     ("general_bf16", (2, 8, 8, 9, 11, 4, 2), "bf16", "auto", "ukst_direct_kernel"),
     ("thin_mfma", (2, 32, 3, 9, 12, 4, 2), "f32", "auto", "ukst_thin_mfma_kernel"),
     ("mfma_f32", (2, 16, 40, 23, 31, 3, 0), "f32", "mfma", "ukst_mfma_f32_kernel"),
-    ("mfma_f32_split_k", (2, 64, 16, 5, 6, 4, 1), "f32", "mfma", "ukst_mfma_f32_kernel"),
+    ("mfma_f32_split_k", (2, 48, 16, 5, 6, 4, 1), "f32", "mfma", "ukst_mfma_f32_kernel"),
     ("mfma_f32_small_tiles", (2, 64, 24, 5, 6, 4, 2), "f32", "mfma", "ukst_mfma_f32_kernel"),
     ("mfma_bf16", (2, 32, 128, 9, 16, 4, 1), "bf16", "auto", "ukst_mfma_bf16_kernel"),
     ("mfma_bf16_aligned", (2, 32, 128, 9, 16, 4, 2), "bf16", "auto", "ukst_mfma_bf16_aligned_kernel"),
@@ -571,6 +610,7 @@ def test_fused_bias_activation(case, act):
     w = _mk("epi_" + name, 9300 + sum(shape), B, Cin, Cout, H, W, n, P, dtype=dtype)
     dt = ukst.UKST_F32 if dtype == "f32" else ukst.UKST_BF16_F32
     assert ukst.ukst_kernel_name(B, Cin, Cout, H, W, n, P, dt, PATHS[pname]) == kernel
+    assert (_slices_on_the_wide_tiles(shape, dtype) > 1) == (name == "mfma_f32_split_k")
     data = wl.generate(w)
     rng = np.random.default_rng(9300 + sum(shape))
     bias = rng.normal(0.0, 1.0, Cout).astype(np.float32)

@@ -10,7 +10,7 @@ from gpu_util import TOL, check_against_oracle, run_gpu
 
 pytestmark = pytest.mark.gpu
 
-# B, Cin, Cout, H, W, n, P, dtype
+# B, Cin, Cout, H, W, n, P, dtype; in tiles of 16 x 16 but for one
 FORWARD_SHAPES = [
     (1, 52, 8, 4, 4, 4, 2, "f32"),       # one tile of 16 x 16, half of it empty
     (3, 53, 33, 5, 7, 4, 2, "f32"),      # a last stage of one new channel, a second channel tile of one
@@ -18,12 +18,24 @@ FORWARD_SHAPES = [
     (2, 70, 65, 9, 17, 2, 0, "f32"),     # columns in three tiles of six
     (2, 66, 17, 6, 9, 2, 3, "f32"),      # P beyond the kernel
     (1, 101, 35, 33, 11, 5, 4, "f32"),   # n = 5, seven and a half windows of P
-    (64, 128, 64, 6, 6, 4, 2, "f32"),    # blocks of four waves
+    (64, 128, 64, 6, 6, 4, 2, "f32"),    # 32 x 32, blocks of eight waves
     (3, 97, 4, 8, 8, 5, 1, "f32"),       # a thin output
     (3, 60, 33, 5, 7, 4, 1, "bf16"),
     (2, 77, 35, 7, 5, 5, 3, "bf16"),
     (9, 64, 40, 3, 3, 3, 2, "bf16"),
 ]
+
+# ... on every instance of 32 x 32 tiles: output-aligned and shifted quads, every kernel side, eight and four waves
+FORWARD_SHAPES_32 = [(s, 8) for s in [
+    (15, 73, 33, 4, 16, 2, 2, "f32"), (9, 63, 37, 4, 3, 4, 0, "f32"),
+    (5, 61, 34, 7, 40, 2, 1, "f32"), (15, 53, 55, 3, 13, 3, 3, "f32"), (14, 53, 49, 16, 4, 4, 3, "f32"), (11, 56, 48, 3, 6, 5, 0, "f32"),
+    (11, 55, 34, 8, 12, 2, 2, "bf16"), (13, 82, 35, 3, 3, 4, 0, "bf16"),
+    (4, 53, 37, 9, 37, 2, 1, "bf16"), (7, 53, 49, 11, 9, 3, 3, "bf16"), (13, 59, 65, 17, 3, 4, 3, "bf16"), (4, 78, 52, 6, 3, 5, 0, "bf16"),
+]] + [(s, 4) for s in [
+    (14, 56, 34, 7, 35, 2, 2, "f32"), (14, 59, 34, 55, 4, 4, 4, "f32"),
+    (4, 64, 36, 39, 26, 2, 1, "f32"), (10, 66, 34, 13, 7, 3, 3, "f32"), (9, 55, 34, 8, 49, 4, 3, "f32"), (14, 53, 34, 51, 3, 5, 5, "f32"),
+    (6, 57, 71, 22, 19, 4, 2, "bf16"), (9, 66, 34, 24, 4, 3, 3, "bf16"), (8, 78, 37, 22, 17, 5, 5, "bf16"),
+]]
 
 
 def _plan(op, shape, dtype="f32", k=2):
@@ -40,11 +52,13 @@ def _mk(shape):
     return wl.Workload("small", 9500 + sum(shape[:7]), B, Cin, Cout, H, W, n, P, dtype, "normal", "normal:0.5")
 
 
-@pytest.mark.parametrize("shape", FORWARD_SHAPES)
-def test_forward_every_element(shape):
+@pytest.mark.parametrize("shape,tile", [(s, (32, 8) if s[0] == 64 else (16, 8)) for s in FORWARD_SHAPES] +
+                         [(s, (32, waves)) for s, waves in FORWARD_SHAPES_32])
+def test_forward_every_element(shape, tile):
     w = _mk(shape)
     dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
     assert ukst.ukst_kernel_name(*shape[:7], dt) == "ukst_mfma_f32_kernel"
+    assert _plan("forward", shape, w.dtype) == tile + (1,)
     for integer in (True, False):
         print(f"case {shape} integer={integer}", flush=True)
         data = wl.generate(w, integer=integer)
@@ -73,7 +87,8 @@ def test_epilogue_and_bf16_output(act, out_bf16):
 
 
 @pytest.mark.parametrize("what", ["weight_inf", "inf", "nan", "huge"])
-@pytest.mark.parametrize("shape", [FORWARD_SHAPES[1], FORWARD_SHAPES[2], FORWARD_SHAPES[9]])
+@pytest.mark.parametrize("shape", [FORWARD_SHAPES[1], FORWARD_SHAPES[2], FORWARD_SHAPES[9], FORWARD_SHAPES_32[1][0],
+                                   FORWARD_SHAPES_32[15][0], FORWARD_SHAPES_32[11][0]])
 def test_forward_operands_that_are_not_finite(shape, what):
     """They reach the outputs whose sums hold them: the halo is left out, not multiplied by zero, and neither are the
     channels that a last stage repeats."""
@@ -84,10 +99,10 @@ def test_forward_operands_that_are_not_finite(shape, what):
     if what == "weight_inf":
         k[3, 2, 0, 1], k[4, w.Cin - 3, w.n - 1, w.n - 1] = np.inf, -np.inf
     elif what == "huge":
-        x[0, 5, 2, 3] = 3e38
+        x[0, 5, 2, w.W // 2] = 3e38
         k[:, 5] *= 100.0
     else:
-        x[0, 3, 2, 4], x[w.B - 1, w.Cin - 4, 0, 0] = (np.inf, -np.inf) if what == "inf" else (np.nan, np.nan)
+        x[0, 3, 2, w.W - 1], x[w.B - 1, w.Cin - 4, 0, 0] = (np.inf, -np.inf) if what == "inf" else (np.nan, np.nan)
     dt = torch.float32 if w.dtype == "f32" else torch.bfloat16
     x, k = torch.from_numpy(x).to(dt), torch.from_numpy(k).to(dt)
     y = ukst.ukst_conv_transpose2d(x.cuda(), k.cuda(), w.P).cpu().numpy()
@@ -134,16 +149,26 @@ GRAD_INPUT_SHAPES = [
     (2, 24, 37, 9, 10, 3, 2, "bf16"),
     (2, 19, 16, 6, 5, 5, 0, "bf16"),     # an odd number of channels of 25 taps
 ]
+# in 32 x 32 tiles: every kernel side, eight and four waves
+GRAD_INPUT_SHAPES_32 = [(s, 8) for s in [
+    (9, 35, 17, 18, 9, 2, 1, "f32"), (3, 33, 19, 39, 11, 3, 2, "f32"), (1, 34, 18, 43, 35, 4, 2, "f32"), (16, 66, 17, 3, 17, 5, 1, "f32"),
+    (6, 50, 74, 18, 9, 2, 1, "bf16"), (10, 34, 83, 14, 9, 3, 1, "bf16"), (6, 33, 75, 20, 12, 4, 0, "bf16"), (13, 178, 19, 7, 4, 5, 0, "bf16"),
+]] + [(s, 4) for s in [
+    (5, 40, 17, 35, 22, 2, 1, "f32"), (5, 39, 19, 41, 19, 3, 1, "f32"), (12, 34, 34, 11, 11, 4, 4, "f32"), (1, 34, 34, 50, 27, 5, 4, "f32"),
+    (12, 34, 72, 16, 23, 2, 1, "bf16"), (15, 38, 80, 24, 11, 3, 0, "bf16"), (15, 37, 75, 23, 11, 4, 1, "bf16"), (15, 134, 35, 4, 7, 5, 4, "bf16"),
+]]
 
 
 @pytest.mark.parametrize("integer", [True, False])
-@pytest.mark.parametrize("shape", GRAD_INPUT_SHAPES)
-def test_input_gradient_every_element(shape, integer):
+@pytest.mark.parametrize("shape,tile", [(s, (16, 8)) for s in GRAD_INPUT_SHAPES] +
+                         [(s, (32, waves)) for s, waves in GRAD_INPUT_SHAPES_32])
+def test_input_gradient_every_element(shape, tile, integer):
     from gpu_util import check_elements, run_gpu_grad_input
     w = _mk(shape)
     dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
     if shape[:2] != (2, 19):  # (the vector ALUs keep that one)
         assert ukst.ukst_grad_kernel_name(0, *shape[:7], dt) == "ukst_grad_input_mfma_kernel"
+        assert _plan("grad_input", shape, w.dtype) == tile + (1,)
     print(f"case {shape} integer={integer}", flush=True)
     data = wl.generate(w, integer=integer)
     dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
@@ -171,6 +196,26 @@ GENERAL_SHAPES += [
     ("strided", 3, (14, 130, 37, 31, 33, 5, 2)),  # classes in order of their taps, two tiles left over
 ]
 
+# dilated layers in 32 x 32 tiles: every kernel side, both operand types, eight and four waves (strided ones take 16 x 16)
+DILATED_SHAPES_32 = [
+    (2, (10, 18, 78, 11, 3, 2, 2), "f32", 8), (3, (5, 45, 41, 11, 3, 3, 2), "f32", 8), (2, (7, 22, 38, 7, 4, 4, 2), "f32", 8),
+    (2, (8, 28, 23, 5, 16, 5, 2), "f32", 8), (3, (15, 20, 57, 3, 13, 2, 2), "bf16", 8), (2, (10, 55, 21, 6, 5, 3, 0), "bf16", 8),
+    (3, (8, 28, 32, 9, 3, 4, 4), "bf16", 8), (2, (5, 17, 19, 11, 27, 5, 5), "bf16", 8),
+    (2, (6, 17, 35, 12, 43, 2, 2), "f32", 4), (2, (8, 19, 33, 3, 13, 3, 1), "f32", 4), (4, (7, 35, 19, 5, 25, 4, 4), "f32", 4),
+    (3, (7, 34, 24, 11, 5, 5, 5), "f32", 4), (2, (11, 19, 34, 21, 13, 2, 2), "bf16", 4), (3, (10, 25, 20, 5, 8, 3, 1), "bf16", 4),
+    (2, (12, 48, 41, 3, 7, 4, 2), "bf16", 4), (2, (8, 47, 33, 4, 5, 5, 3), "bf16", 4),
+]
+
+
+@pytest.mark.parametrize("case", DILATED_SHAPES_32)
+def test_dilated_32_x_32_every_element(case):
+    from test_gpu_general import _run
+    k, shape, dtype, waves = case
+    assert _plan("dilated", shape, dtype, k) == (32, waves, 1)
+    w = wl.Workload("small_dilated", 9800 + sum(shape) + k, *shape, dtype, "normal", "normal:0.5")
+    _run("dilated", w, k, integer=True)
+    _run("dilated", w, k, integer=False)
+
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("case", GENERAL_SHAPES)
@@ -183,11 +228,18 @@ def test_strided_and_dilated_every_element(case, dtype):
 
 
 @pytest.mark.parametrize("what", ["inf", "nan", "weight_inf"])
-@pytest.mark.parametrize("op", ["grad_input", "strided", "dilated"])
-def test_other_operations_with_operands_that_are_not_finite(op, what):
+@pytest.mark.parametrize("op,shape,tile", [  # images, summed channels, channels of the result, H, W, n, P, step
+    ("grad_input", (2, 53, 20, 6, 7, 3, 1, 3), (16, 8)), ("grad_input", (3, 19, 33, 39, 11, 3, 2, 2), (32, 8)),
+    ("strided", (2, 53, 20, 6, 7, 3, 1, 3), (16, 8)),
+    ("dilated", (2, 53, 20, 6, 7, 3, 1, 3), (16, 8)), ("dilated", (7, 22, 38, 7, 4, 4, 2, 2), (32, 8)),
+    ("dilated", (10, 25, 20, 5, 8, 3, 1, 3), (32, 4)),
+])
+def test_other_operations_with_operands_that_are_not_finite(op, shape, tile, what):
     """As for the forward layers; against the definitions in 64 bits, products with the padding left out."""
     import torch
-    B, K, M, H, W, n, P, k = 2, 53, 20, 6, 7, 3, 1, 3
+    B, K, M, H, W, n, P, k = shape
+    cin, cout = (M, K) if op == "grad_input" else (K, M)
+    assert _plan(op, (B, cin, cout, H, W, n, P), "f32", k) == tile + (1,)
     rng = np.random.default_rng(7)
     wshape = (K, M, n, n) if op == "grad_input" else (M, K, n, n)
     OH, OW = ukst.ukst_output_shape(H, W, n, P) if op == "grad_input" else (0, 0)
@@ -234,7 +286,7 @@ def test_other_operations_with_operands_that_are_not_finite(op, what):
     (3, 40, 19, 26, 32, 3, 1, "bf16"),   # bf16 pipe, a channel tile of 8
     (2, 21, 18, 65, 63, 4, 0, "bf16"),   # one part
     (5, 16, 33, 30, 31, 2, 1, "bf16"),
-    (4, 18, 37, 33, 35, 5, 2, "f32"),    # every stage added to the copy in memory
+    (4, 18, 37, 33, 35, 5, 2, "f32"),
     (9, 70, 16, 20, 25, 5, 4, "f32"),
 ])
 @pytest.mark.parametrize("integer", [True, False])
@@ -243,6 +295,29 @@ def test_kernel_gradient_of_16_to_31_channels(shape, integer):
     w = _mk(shape)
     dt = ukst.UKST_F32 if w.dtype == "f32" else ukst.UKST_BF16_F32
     assert "mfma" in ukst.ukst_grad_kernel_name(1, *shape[:7], dt)
+    data = wl.generate(w, integer=integer)
+    dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
+    ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
+    got = run_gpu_grad_weight(data, dyd, w.dtype, w.n, w.P, guard=4096)
+    check_elements(got, ref, S, TOL["f32"], exact=integer)
+
+
+# B, Cin, Cout, H, W, n, P, dtype: stages after which the sums go to memory, stages of a slice
+@pytest.mark.parametrize("shape,plan", [
+    ((3, 17, 300, 35, 45, 5, 2, "f32"), (2, 5)),     # twice, and a remainder of one
+    ((4, 17, 78, 90, 90, 5, 4, "f32"), (1, 4)),      # after every stage
+    ((3, 17, 590, 35, 45, 5, 2, "bf16"), (4, 5)),
+    ((3, 17, 590, 35, 45, 2, 1, "bf16"), (8, 9)),    # two sets of accumulators
+    ((6, 590, 17, 35, 45, 2, 0, "bf16"), (8, 9)),
+    ((3, 30, 590, 35, 45, 3, 0, "bf16"), (8, 9)),
+    ((3, 17, 590, 35, 45, 4, 3, "bf16"), (8, 9)),
+])
+@pytest.mark.parametrize("integer", [True, False])
+def test_kernel_gradient_sums_added_to_memory_on_the_way(shape, plan, integer):
+    from gpu_util import check_elements, run_gpu_grad_weight
+    w = _mk(shape)
+    assert _plan("grad_weight", shape, w.dtype) == plan
+    print(f"case {shape} integer={integer}", flush=True)
     data = wl.generate(w, integer=integer)
     dyd = wl.generate_dy(w, oracle.out_shape(w.H, w.W, w.n, w.P), integer=integer)
     ref, S = oracle.grad_weight(data["x"], dyd["dy"], w.n, w.P)
@@ -331,7 +406,7 @@ def test_forward_layers_in_slices(shape, slices):
         assert (np.abs(y.cpu().numpy() - z) <= TOL["f32"] * S + 1.2e-7 * np.abs(y_ref) + 2e-6).all()
 
 
-@pytest.mark.parametrize("shape", [GRAD_INPUT_SHAPES[1], GRAD_INPUT_SHAPES[5], (1, 34, 18, 43, 35, 4, 2, "f32")])
+@pytest.mark.parametrize("shape", [GRAD_INPUT_SHAPES[1], GRAD_INPUT_SHAPES[5], GRAD_INPUT_SHAPES_32[2][0]])
 def test_input_gradients_on_the_small_tiles_ask_for_no_workspace(shape):
     import torch
     from gpu_util import check_elements
