@@ -1443,13 +1443,21 @@ __device__ __forceinline__ float sum_copies_in(const float* __restrict__ p, int 
 #pragma unroll
             for (int u = 0; u < SUMS; ++u) v[u] += p[(size_t)(k + u) * n];
         }
-        if (k < end) {  // (all loads in flight)
-            float t[SUMS - 1];
+        if constexpr (SUMS == 16) {
+            if (k < end) {  // (all loads in flight)
+                float t[SUMS - 1];
 #pragma unroll
-            for (int u = 0; u < SUMS - 1; ++u) t[u] = p[(size_t)(k + u < end ? k + u : end - 1) * n];
+                for (int u = 0; u < SUMS - 1; ++u) t[u] = p[(size_t)(k + u < end ? k + u : end - 1) * n];
 #pragma unroll
-            for (int u = 0; u < SUMS - 1; ++u) v[u] += k + u < end ? t[u] : 0.f;
-            k = end;
+                for (int u = 0; u < SUMS - 1; ++u) v[u] += k + u < end ? t[u] : 0.f;
+                k = end;
+            }
+        } else {
+            for (int u = 0; k < end; ++k, ++u) {
+                const float t = p[(size_t)k * n];
+#pragma unroll
+                for (int w = 0; w < SUMS - 1; ++w) v[w] += w == u ? t : 0.f;
+            }
         }
 #pragma unroll
         for (int m = 1; m < SUMS; m *= 2)
