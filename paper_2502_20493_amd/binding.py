@@ -1,7 +1,8 @@
 """Thin binding of libukst: same names as include/ukst.h, argument marshalling only.
 
 Ordinary calls (tensors on the current device, the result and the workspace allocated for the call, torch's current stream)
-are marshalled natively by _ukst_marshal.so, everything else and every refusal here with ctypes.
+are marshalled natively by _ukst_marshal.so, everything else and every refusal here with ctypes; all of them if that
+extension is not there or was built for another torch.
 
 Every step of the computation runs in the HIP kernels behind the C ABI.  There is no CPU
 fallback: if the library has not been built, loading raises.
@@ -11,6 +12,7 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libukst.so")
@@ -40,7 +42,7 @@ BENCH_EXPORTS = ["ukst_bench_mfma_ceiling", "ukst_bench_stream_ceiling"]
 
 _lib = None
 _bench_lib = None
-_native = None  # the extension module, from the time the library is loaded on
+_native = None  # the extension module (or _Ctypes), from the first call with tensors on
 _torch = None  # the module, from the time the library is loaded on
 
 
@@ -53,13 +55,12 @@ class UkstError(RuntimeError):
 def lib():
     """Load libukst.so (once).  Raises if it is missing: build it with
     ``python -m paper_2502_20493_amd.build`` (or ``__graft_entry__.build()``)."""
-    global _lib, _torch, _native
+    global _lib, _torch
     if _lib is None:
-        for path in (LIB_PATH, MARSHAL_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError(
-                    f"{path} is missing: the HIP library has not been built "
-                    "(python -m paper_2502_20493_amd.build). There is no fallback path.")
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError(
+                f"{LIB_PATH} is missing: the HIP library has not been built "
+                "(python -m paper_2502_20493_amd.build). There is no fallback path.")
         # PyTorch bundles its own HIP runtime.  It has to be in the process before this library
         # is loaded, otherwise the two ends see different runtimes and the first HIP call made
         # from here reports that there is no device.
@@ -98,19 +99,38 @@ def lib():
             f.argtypes, f.restype = [i] * 9, ctypes.c_ulonglong
         L.ukst_static_workspace_bytes.argtypes = []
         L.ukst_static_workspace_bytes.restype = ctypes.c_size_t
+        _lib = L
+    return _lib
+
+
+class _Ctypes:
+    """In the place of the extension module: turns every call down, so that it is marshalled here."""
+
+    @staticmethod
+    def forward(*args):
+        return None
+
+    input_gradient = kernel_gradient = general = forward
+
+
+def _load_native():
+    global _native
+    L, vp = lib(), ctypes.c_void_p
+    try:
         spec = importlib.util.spec_from_file_location("_ukst_marshal", MARSHAL_PATH)
         native = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(native)
+        if native.built_for != _torch.__version__:
+            raise ImportError(f"built for torch {native.built_for}, this is {_torch.__version__}")
         native.bind(*(ctypes.cast(f, vp).value for f in (
             L.ukst_workspace_bytes, L.ukst_conv_transpose2d_path, L.ukst_conv_transpose2d_bias_act,
             L.ukst_conv_transpose2d_ws, L.ukst_conv_transpose2d_grad_input, L.ukst_conv_transpose2d_grad_weight,
             L.ukst_conv_transpose2d_strided, L.ukst_dilated_conv2d)))
-        _lib, _native = L, native
-    return _lib
-
-
-def _load_native():
-    lib()
+    except (ImportError, OSError) as e:
+        warnings.warn(f"{MARSHAL_PATH} cannot be used ({e}): calls are marshalled with ctypes, 4 to 5 us slower each; "
+                      "python -m paper_2502_20493_amd.build", RuntimeWarning, stacklevel=3)
+        native = _Ctypes
+    _native = native
     return _native
 
 

@@ -12,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libukst.so")
 MARSHAL_LIB = os.path.join(HERE, "_ukst_marshal.so")  # native marshalling of the Python binding
 MARSHAL_SRC = os.path.join(CSRC, "binding", "ukst_marshal.cpp")
+MARSHAL_STAMP = os.path.join(HERE, "_build", "marshal_built_for.txt")
 BENCH_LIB = os.path.join(HERE, "libukst_bench.so")  # measurement helpers, not part of the product
 
 HIPCC_FLAGS = [
@@ -37,7 +38,7 @@ def _run(cmd, verbose):
     # hipcc's host pass warns that it does not know the packed-fp32 feature: harmless
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + out)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed: " + " ".join(cmd) + "\n" + out)
     if verbose and out.strip():
         print(out)
 
@@ -49,10 +50,16 @@ def _marshal_command():
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DUKST_BUILT_FOR="{torch.__version__}"',
             "-I" + os.path.join(root, "include"), "-I" + os.path.join(rocm, "include"),
             "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", MARSHAL_LIB,
             "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def _marshal_versions():
+    """What the extension module fits: this Python and this torch."""
+    import torch
+    return f"{sys.implementation.cache_tag} {torch.__version__}"
 
 
 def build_library(verbose: bool = False, jobs: int | None = None) -> str:
@@ -70,6 +77,8 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
         futs.append(pool.submit(_run, _marshal_command(), verbose))
         for f in futs:
             f.result()
+    with open(MARSHAL_STAMP, "w") as f:
+        f.write(_marshal_versions())
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + bobjs + ["-o", BENCH_LIB], verbose)
     return LIB
@@ -77,8 +86,11 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
 
 def is_stale() -> bool:
     libs = (LIB, BENCH_LIB, MARSHAL_LIB)
-    if not all(os.path.exists(p) for p in libs):
+    if not all(os.path.exists(p) for p in libs + (MARSHAL_STAMP,)):
         return True
+    with open(MARSHAL_STAMP) as f:
+        if f.read() != _marshal_versions():
+            return True
     t = min(os.path.getmtime(p) for p in libs)
     deps = sources() + bench_sources() + [MARSHAL_SRC] + glob.glob(os.path.join(CSRC, "*.h")) + \
         glob.glob(os.path.join(HERE, "..", "include", "*.h"))

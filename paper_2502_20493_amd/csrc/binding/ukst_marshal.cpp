@@ -255,4 +255,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ukst_marshal", nullptr, -1, metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ukst_marshal(void) { return PyModule_Create(&module); }
+// built_for: the version of torch whose headers this was compiled with
+PyMODINIT_FUNC PyInit__ukst_marshal(void)
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", UKST_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -312,6 +312,41 @@ def test_backward_kernel_selection_is_host_arithmetic():
     assert name(0, 1, 1, 1, 1, 4, 3, 0, ukst.UKST_F32) == ""
 
 
+@pytest.mark.parametrize("what", ["missing", "not a library", "another torch"])
+def test_an_extension_that_cannot_be_used_leaves_the_calls_to_ctypes(what, monkeypatch, tmp_path):
+    """Queries and raw calls never need it; calls with tensors warn once and are marshalled in Python."""
+    import torch
+    if what == "another torch":
+        import types
+        other = types.SimpleNamespace(built_for="1.0", bind=lambda *a: pytest.fail("bound"))
+        monkeypatch.setattr(ukst.importlib.util, "module_from_spec", lambda spec: other)
+        monkeypatch.setattr(ukst.importlib.util, "spec_from_file_location", lambda *a: types.SimpleNamespace(
+            loader=types.SimpleNamespace(exec_module=lambda m: None)))
+    else:
+        path = tmp_path / "_ukst_marshal.so"
+        if what == "not a library":
+            path.write_bytes(b"nothing")
+        monkeypatch.setattr(ukst, "MARSHAL_PATH", str(path))
+    monkeypatch.setattr(ukst, "_native", None)
+    monkeypatch.setattr(ukst, "_lib", None)
+    assert ukst.ukst_workspace_bytes(ukst.UKST_OP_GRAD_WEIGHT, 1, 3, 3, 8, 8, 3, 0, ukst.UKST_F32) > 0
+    assert ukst._native is None
+    x, w = torch.zeros(1, 2, 4, 4), torch.zeros(5, 2, 3, 3)
+    with pytest.warns(RuntimeWarning, match="marshalled with ctypes"):
+        with pytest.raises(ValueError, match="device tensors"):  # (x is on the CPU: as far as it gets here)
+            ukst.ukst_conv_transpose2d(x, w, 1)
+    assert ukst._native is ukst._Ctypes
+    for call in (lambda: ukst.ukst_conv_transpose2d_grad_input(x, w, 4, 4, 1), lambda: ukst.ukst_dilated_conv2d(x, w, 1, 1),
+                 lambda: ukst.ukst_conv_transpose2d_grad_weight(x, x, 3, 1)):
+        with pytest.raises(ValueError):
+            call()
+
+
+def test_the_extension_is_built_for_this_torch():
+    import torch
+    assert ukst._load_native().built_for == torch.__version__
+
+
 @pytest.mark.parametrize("call", [ukst.ukst_conv_transpose2d_ws, ukst.ukst_conv_transpose2d_bias_act])
 @pytest.mark.parametrize("workspace", [None, False])
 def test_a_bias_without_an_activation_is_never_left_out(call, workspace, monkeypatch):

@@ -21,9 +21,9 @@ class _Spy:
 
 @pytest.fixture
 def native(monkeypatch):
-    ukst.lib()
-    assert ukst._native is not None
-    spy = _Spy(ukst._native)
+    module = ukst._load_native()
+    assert module is not ukst._Ctypes
+    spy = _Spy(module)
     monkeypatch.setattr(ukst, "_native", spy)
     return spy
 
