@@ -483,14 +483,19 @@ bool make_plan(ConvArgs a, int es, int mt, ConvPlan& p)
     a.nqt = (int)((qmax + TN - 1) / TN);
     const long long nb = (long long)a.nqt * a.nco * a.classes;
     if (nb > 0x3FFFFFFF) return false;
-    // Classes of unequal taps, an incomplete second round of 512 blocks and a long sum (fp32): within four pixel tiles the
-    // classes of most taps start first, so that the blocks that start last are the short ones.  Neighbouring classes
-    // write y later than one another, which few channels do not repay (us, class by class / by taps: 128 -> 64, 16 of 32 x 32,
-    // n = 5, stride 3, 576 blocks 80.2 / 70.5; 288 -> 232, 6 of 24 x 27, n = 4, 612 blocks 151 / 137; 280 -> 104, 26 of 16 x 16, n = 5,
-    // stride 4 174 / 152; but 336 -> 72, 13 of 34 x 34, n = 5, 1116 blocks 233 / 243, 369 blocks 49.5 / 52.4, equal taps,
-    // 168 -> 152, n = 4, stride 4 231 / 244, 24 -> 144, n = 5, stride 4 167 / 174)
-    a.group = !a.dilated && a.classes <= 16 && a.n > a.k && a.n % a.k != 0 && es == 4 && a.Cin >= 128 && nb > 512 &&
-              nb <= 1024 ? 4 : 1;
+    // Classes of unequal taps, an incomplete second round of blocks and a sum of some length (fp32): within four pixel tiles
+    // the classes of most taps start first, so that the blocks that start last are the short ones.  Neighbouring classes
+    // write y later than one another, which few channels do not repay.  Time class by class over time by taps, geometric means
+    // of 18000 layers, from 64 channels on (48 to 63: stride 3 1.07 at 513 to 576 blocks, 1.00 beyond): stride 2 1.21 to 1.25 at 513 to
+    // 576 blocks, 1.09 to 1.18 up to 1024; stride 3, two blocks to a compute unit 1.07 to 1.12 and 1.01 to 1.02, but where LDS
+    // holds one, whose rounds are of 256, 0.98 to 1.04 and 0.99; stride 4, n = 5, 6 1.03 to 1.12 from 577 blocks on, below (a second
+    // round of a few blocks, most of them of one tap) 0.95 to 1.00, n = 7, one class in four short, 0.93 to 1.00.
+    // 128 -> 64 channels, 16 of 32 x 32, n = 5, stride 3, 576 blocks 80.2 / 70.5 us; beyond 1024 blocks 336 -> 72, 13 of 34 x 34,
+    // n = 5, 1116 blocks 233 / 243, below 513 49.5 / 52.4, equal taps, 168 -> 152, n = 4, stride 4 231 / 244.
+    const bool unequal = !a.dilated && a.classes <= 16 && a.n > a.k && a.n % a.k != 0;
+    const bool second_round = nb > (a.k == 4 ? 576 : 512) && nb <= 1024;
+    a.group = unequal && second_round && es == 4 && a.Cin >= 64 && (a.k != 3 || 2 * p.lds <= LDS_LIMIT) &&
+              (a.k != 4 || a.n < 7) ? 4 : 1;
     a.order = 0;
     for (int c = 0; a.group > 1 && c < a.classes; ++c) {
         const Class g = class_of(a, c);

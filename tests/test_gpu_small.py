@@ -194,6 +194,7 @@ GENERAL_SHAPES += [
     ("dilated", 4, (9, 16, 50, 60, 84, 3, 4)), ("dilated", 4, (13, 17, 40, 56, 56, 5, 8)), ("strided", 3, (1, 33, 61, 37, 39, 5, 2)),
     ("dilated", 2, (11, 17, 61, 64, 64, 3, 2)),
     ("strided", 3, (14, 130, 37, 31, 33, 5, 2)),  # classes in order of their taps, two tiles left over
+    ("strided", 2, (9, 66, 37, 63, 65, 3, 1)), ("strided", 4, (9, 65, 50, 33, 31, 5, 3)),  # ... of four and of sixteen classes
 ]
 
 # dilated layers in 32 x 32 tiles: every kernel side, both operand types, eight and four waves (strided ones take 16 x 16)
