@@ -106,12 +106,16 @@ void add_divisors(SmallArgs& a)
 }
 
 // Time of a plan in us, fitted to 900 layers of every operation (17 % off on average; the choice it makes costs 1 % against the
-// best plan of each): rounds of blocks, each with a fixed part and its waves' MFMAs, two waves per SIMD
+// best plan of each): rounds of blocks, each with a fixed part and its waves' MFMAs, two waves per SIMD.  Input gradients
+// of small kernels stage more than they multiply (four cells of dy and n * n weights for n * n products): with their MFMAs alone the
+// 16 x 16 tiles looked three times as fast as they are for n = 2, and were taken where the 32 x 32 ones are up to 1.7 times as fast
+// (398 <- 344 channels, 16 x 16 24.1 / 15.0 us; 1 % of 1700 layers by more than 1.5 for n = 2, 1.2 for n = 3; now 1.07 and 1.08)
 double estimate(const SmallProblem& q, const SmallArgs& a, int mt, int wv)
 {
     const int kind = q.op == SmallOp::grad_input ? kInputGrad : q.op == SmallOp::dilated ? kDilated : kShifted;
     const int kc = kc_of(kind, q.n, mt), per_wave = ((q.K + kc - 1) / kc + wv - 1) / wv;
-    const double mfma = (mt == 32 ? 64. * kc / 2 : 32. * kc / 4) * q.n * q.n / 2400. * per_wave;
+    const double staging = kind != kInputGrad || q.n > 3 ? 1. : q.n == 2 ? (mt == 32 ? 1.9 : 3.4) : (mt == 32 ? 1.35 : 1.75);
+    const double mfma = staging * (mt == 32 ? 64. * kc / 2 : 32. * kc / 4) * q.n * q.n / 2400. * per_wave;
     const long long blocks = (long long)a.nmt * a.npt * a.nct * a.res * a.res;
     const double rounds = (double)((blocks + 255) / 256);
     if (mt == 16) return rounds * (2.6 + 1.95 * 2. * mfma);

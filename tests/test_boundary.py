@@ -370,6 +370,19 @@ def test_a_bias_without_an_activation_is_never_left_out(call, workspace, monkeyp
     assert seen == [(bias, ukst.UKST_ACT_NONE, workspace is None)]
 
 
+def _small_tile(op, shape, dtype=ukst.UKST_F32):
+    """(rows, waves) of the small tile a layer runs on, (0, 0) of layers that run elsewhere; op 0 forward, 1 input gradient."""
+    v = ukst.lib().ukst_test_plan(op, *shape, 2, dtype)
+    return v & 255, v >> 8 & 255
+
+
+def test_input_gradients_of_small_kernels_count_their_staging():
+    """Two and three taps a side: 16 x 16 tiles stage more for each product than 32 x 32 ones, and are only for fewer tiles."""
+    for n in (2, 3):
+        assert _small_tile(1, (1, 398, 344, 16, 16, n, 1)) == (32, 8), n   # n = 2: 15.0 us, in 16 x 16 tiles 24.1
+        assert _small_tile(1, (1, 398, 344, 4, 5, n, 1)) == (16, 8), n
+
+
 def test_generalised_operations_host_side():
     """Stride-s transpose convolution and dilated convolution: shapes, multiply-add counts and
     argument validation are host arithmetic (fake addresses: nothing may be launched)."""
