@@ -2465,12 +2465,24 @@ SmallProblem small_problem(const Geom& g, int dtype)
 
 // Input gradients on the small tiles (ukst_small_kernel.h), in 32 x 32 tiles.  Where the fp32 pipe's own kernel would run,
 // always: its blocks of 64 channels x 256 pixels pack the weights first and add slices afterwards (us, its time against the
+// Time of the input gradient on the bf16 pipe in us, fitted to 6400 layers (14 % off on average): the packing and the launch,
+// rounds of blocks, two to a compute unit, of stages of 8 output channels, and the copies of dx written and added
+double gi_bf16_estimate(const GiMfmaArgs& a)
+{
+    const long long blocks = (long long)a.tilesX * a.tilesY * a.tilesB * a.ciTiles * a.KS;
+    const double mb = (double)a.g.B * a.g.Cin * a.g.H * a.g.W * 4e-6;
+    return 9.5 + (4.1 + 0.235 * a.g.n * a.g.n) * (double)((blocks + 511) / 512) * (a.coPer / a.CC) +
+           (a.KS > 1 ? 0.6 * (a.KS + 1) * mb : 0.);
+}
+
 // small tiles': 27 images, 144 <- 454 channels, 10 x 18, n = 4 601 / 118; 104 <- 368, 14 of 5 x 16, n = 2 35.6 / 18.4; over 124
 // drawn layers 1.27 to 6 times as fast).  Against the vector ALUs, which take layers of fewer than 32 input channels, up to the
 // tile counts where those catch up (24 <- 456, 4 of 11 x 5, n = 2 343 / 15; 24 <- 256 bf16, 56 of 20 x 20, n = 4 434 / 76; fp32 120 <- 13,
-// 1136 tiles 13.0 / 15.6).  Against the bf16 pipe, which multiplies 16 times as fast, only with a long sum and up to
-// about a round of blocks (72 <- 248, 11 of 10 x 22, n = 4 99 / 27; 216 <- 176, 12 of 9 x 9 33.0 / 20.7; 112 <- 112, 4 of 26 x 26, n = 5, 368
-// tiles 36.2 / 39.6).
+// 1136 tiles 13.0 / 15.6).  Against the bf16 pipe, which multiplies 16 times as fast, from 72 output channels on, up to about
+// a round of blocks and where its time is estimated a tenth above the small tiles' (72 <- 248, 11 of 10 x 22, n = 4 99 / 27; 216 <-
+// 176, 12 of 9 x 9 33.0 / 20.7; 272 <- 200, one of 14 x 14, n = 5 33.0 / 16.8; 32 <- 248, 55 of 8 x 19, n = 3 50.1 / 35.4; but 112 <- 112,
+// 4 of 26 x 26, n = 5 36.2 / 39.6; 96 <- 571, 5 of 24 x 24, n = 5 68 / 157; 224 <- 504, 4 of 31 x 7, n = 5 45 / 80.  2520 layers
+// inside 1.84 times as fast on average, the least 0.84; 320 more that the estimates leave out 0.86).
 bool prefer_small(const Geom& g, int dtype)
 {
     if (g.n < 2 || g.n > 5 || g.Cin < 16 || g.Cout < 8 || grad_narrow_supported(g, dtype)) return false;
@@ -2482,6 +2494,8 @@ bool prefer_small(const Geom& g, int dtype)
     const long long tiles = small_blocks(small_problem(g, dtype));
     return tiles > 0 && tiles <= (b16 ? 300 : !wide && dtype == 0 ? 1000 : 2500);
 }
+    if (b16 && !grad_input_window_supported(g, dtype) && gi_bf16_estimate(ma) < 1.1 * small_estimate(small_problem(g, dtype)))
+        return false;
 
 hipError_t launch_gi(const Geom& g, const void* dy, const void* w, float* dx, int dtype, Workspace& ws, hipStream_t stream)
 {

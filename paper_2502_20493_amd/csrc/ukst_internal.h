@@ -180,6 +180,7 @@ struct SmallProblem {
     SmallOp op;
     int B, K, M, XH, XW, OH, OW, n, P, step, dtype;
 };
+double small_estimate(const SmallProblem& q);                  // us, roughly; 0 if the kernels do not take it
 long long small_blocks(const SmallProblem& q, int edge = 32);  // its edge x edge tiles, 0 if the kernels do not take it
 // bytes of workspace with which fp32 forward layers of very few blocks run in slices (without, or with less: unsliced)
 size_t small_workspace(const SmallProblem& q);

@@ -178,6 +178,13 @@ hipError_t launch_t(const SmallProblem& q, const SmallArgs& a, int mt, int wv, c
 
 }  // namespace
 
+double small_estimate(const SmallProblem& q)
+{
+    SmallArgs a;
+    int mt = 0, wv = 0;
+    return pick(q, a, mt, wv) ? estimate(q, a, mt, wv) : 0.;
+}
+
 long long small_blocks(const SmallProblem& q, int edge)
 {
     SmallArgs a;

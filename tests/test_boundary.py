@@ -383,6 +383,20 @@ def test_input_gradients_of_small_kernels_count_their_staging():
         assert _small_tile(1, (1, 398, 344, 4, 5, n, 1)) == (16, 8), n
 
 
+def test_bf16_input_gradients_go_where_they_are_estimated_the_faster():
+    """The small tiles against the bf16 pipe, which multiplies 16 times as fast (us, the pipe / the small tiles)."""
+    for shape, small in (((11, 72, 248, 10, 22, 4, 1), True),      # 99 / 27
+                         ((12, 216, 176, 9, 9, 4, 1), True),       # 33.0 / 20.7
+                         ((1, 272, 200, 14, 14, 5, 4), True),      # 33.0 / 16.8
+                         ((55, 32, 248, 8, 19, 3, 1), True),       # 50.1 / 35.4, tiles beyond one round
+                         ((4, 112, 112, 26, 26, 5, 2), False),     # 36.2 / 39.6
+                         ((5, 96, 571, 24, 24, 5, 2), False),      # 68 / 157
+                         ((4, 224, 504, 31, 7, 5, 2), False)):     # 45 / 80
+        name = "ukst_grad_input_mfma_kernel" if small else "ukst_grad_input_mfma_bf16_kernel"
+        assert ukst.ukst_grad_kernel_name(0, *shape, ukst.UKST_BF16_F32) == name, shape
+        assert (_small_tile(1, shape, ukst.UKST_BF16_F32) != (0, 0)) == small, shape
+
+
 def test_generalised_operations_host_side():
     """Stride-s transpose convolution and dilated convolution: shapes, multiply-add counts and
     argument validation are host arithmetic (fake addresses: nothing may be launched)."""
