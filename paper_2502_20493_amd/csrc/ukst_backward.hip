@@ -1551,8 +1551,10 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     a.HC = a.TJ + N / 2;
     a.cols = 2 * a.HC;
     const size_t budget = 78 * 1024;
-    // at most that many pixels per stage
-    int TR = (!few ? 512 : pixels < 16384 && (es == 4 || N < 5) ? 32 : 64) / a.TJ;
+    // At most that many pixels per stage.  Few channels: 64 are the faster ones (bf16, n = 5 1.05 to 1.16 times on 1100 layers,
+    // others from 8192 pixels on 1.03 times), 32 the more exact ones of fewer pixels (error above the vector ALUs', n = 4, 2048 to 4096
+    // pixels: 176 of 907 layers, with 64 303; on average 0.87 and 0.90 of theirs) and of fp32 operands
+    int TR = (!few ? 512 : (es == 4 ? pixels < 16384 : N < 5 && pixels < 8192) ? 32 : 64) / a.TJ;
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);
@@ -2463,8 +2465,6 @@ SmallProblem small_problem(const Geom& g, int dtype)
     return SmallProblem{SmallOp::grad_input, g.B, g.Cout, g.Cin, g.OH, g.OW, g.H, g.W, g.n, g.P, 2, dtype};
 }
 
-// Input gradients on the small tiles (ukst_small_kernel.h), in 32 x 32 tiles.  Where the fp32 pipe's own kernel would run,
-// always: its blocks of 64 channels x 256 pixels pack the weights first and add slices afterwards (us, its time against the
 // Time of the input gradient on the bf16 pipe in us, fitted to 6400 layers (14 % off on average): the packing and the launch,
 // rounds of blocks, two to a compute unit, of stages of 8 output channels, and the copies of dx written and added
 double gi_bf16_estimate(const GiMfmaArgs& a)
@@ -2475,6 +2475,8 @@ double gi_bf16_estimate(const GiMfmaArgs& a)
            (a.KS > 1 ? 0.6 * (a.KS + 1) * mb : 0.);
 }
 
+// Input gradients on the small tiles (ukst_small_kernel.h), in 32 x 32 tiles.  Where the fp32 pipe's own kernel would run,
+// always: its blocks of 64 channels x 256 pixels pack the weights first and add slices afterwards (us, its time against the
 // small tiles': 27 images, 144 <- 454 channels, 10 x 18, n = 4 601 / 118; 104 <- 368, 14 of 5 x 16, n = 2 35.6 / 18.4; over 124
 // drawn layers 1.27 to 6 times as fast).  Against the vector ALUs, which take layers of fewer than 32 input channels, up to the
 // tile counts where those catch up (24 <- 456, 4 of 11 x 5, n = 2 343 / 15; 24 <- 256 bf16, 56 of 20 x 20, n = 4 434 / 76; fp32 120 <- 13,
@@ -2492,10 +2494,10 @@ bool prefer_small(const Geom& g, int dtype)
     if (!b16 && wide && dtype == 0 && grad_input_parts_supported(g)) return false;
     if (b16 && g.Cout < 72) return false;
     const long long tiles = small_blocks(small_problem(g, dtype));
-    return tiles > 0 && tiles <= (b16 ? 300 : !wide && dtype == 0 ? 1000 : 2500);
-}
     if (b16 && !grad_input_window_supported(g, dtype) && gi_bf16_estimate(ma) < 1.1 * small_estimate(small_problem(g, dtype)))
         return false;
+    return tiles > 0 && tiles <= (b16 ? 300 : !wide && dtype == 0 ? 1000 : 2500);
+}
 
 hipError_t launch_gi(const Geom& g, const void* dy, const void* w, float* dx, int dtype, Workspace& ws, hipStream_t stream)
 {
