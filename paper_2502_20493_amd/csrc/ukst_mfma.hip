@@ -618,7 +618,18 @@ static bool prefer_small(const Geom& g, int dtype)
     if (g.Cin < (g.Cout <= 4 ? 96 : 52) || g.n > 5 || (double)g.B * g.KH * g.KW * g.Cout > 1024. * 1024. * 2.) return false;
     const long long tiles = small_blocks(small_problem(g, dtype));
     if (dtype != 0) return tiles > 0 && tiles <= 256 && !bf16_pipe(g, dtype);
-    if (g.Cout <= 4) return tiles > 0 && tiles <= 256;
+    if (g.Cout <= 4) {
+        // the kernels of such layers take sixteen classes or pixels of all output channels at once: against them up to one round of
+        // 16 x 16 tiles, of a longer sum against the matrix-core one (336 -> 3 channels, 45 of 4 x 4, n = 4 14.4 / 10.4 us, 800 layers
+        // inside 1.4 times as fast; 160 -> 2, 2 of 48 x 48, n = 4, 576 tiles 8.5 / 15.1, 112 -> 2, 22 of 24 x 4, n = 4 0.89), beyond
+        // it against the vector ALUs' from three channels on (152 -> 3, 3 of 45 x 32 10.1 / 9.5,
+        // but 112 -> 1, 2 of 40 x 40, n = 5, 258 tiles 11.8 / 18.8, 113 -> 2, 3 of 37 x 37, n = 2 7.1 / 8.8)
+        const bool matrix = thin_mfma_supported(g, dtype);
+        if (matrix && g.Cin < 128) return false;
+        if ((matrix || (thin_supported(g, dtype) && (g.Cout < 3 || g.Cin < 128))) && small_blocks(small_problem(g, dtype), 16) > 256)
+            return false;
+        return tiles > 0 && tiles <= 256;
+    }
     // output-aligned quads: 64 images, 128 -> 64 channels, 16 x 16, n = 4, 1024 tiles, 49.5 -> 42.6 (parts 42.4)
     const bool aligned = g.P % 2 == 0 && (g.n == 4 || (g.n == 2 && g.Cin % 128 == 0));
     return tiles > 0 && tiles <= (aligned ? 1024 : g.n <= 3 ? 512 : 700);

@@ -397,6 +397,18 @@ def test_bf16_input_gradients_go_where_they_are_estimated_the_faster():
         assert (_small_tile(1, shape, ukst.UKST_BF16_F32) != (0, 0)) == small, shape
 
 
+def test_few_output_channels_go_to_the_small_tiles_for_one_round():
+    """Up to four output channels: the kernels made for them against the small tiles (us, the former / the latter)."""
+    for shape, kernel in (((45, 336, 3, 4, 4, 4, 3), "ukst_mfma_f32_kernel"),       # 14.4 / 10.4
+                          ((2, 160, 2, 48, 48, 4, 1), "ukst_thin_mfma_kernel"),     # 8.5 / 15.1, more than a round
+                          ((22, 112, 2, 24, 4, 4, 4), "ukst_thin_mfma_kernel"),     # 6.2 / 7.0, a short sum
+                          ((3, 152, 3, 45, 32, 2, 0), "ukst_mfma_f32_kernel"),      # 10.1 / 9.5
+                          ((2, 112, 1, 40, 40, 5, 5), "ukst_thin_kernel"),          # 11.8 / 18.8
+                          ((3, 113, 2, 37, 37, 2, 0), "ukst_thin_kernel")):         # 7.1 / 8.8
+        assert ukst.ukst_kernel_name(*shape, ukst.UKST_F32) == kernel, shape
+        assert (_small_tile(0, shape) != (0, 0)) == (kernel == "ukst_mfma_f32_kernel"), shape
+
+
 def test_generalised_operations_host_side():
     """Stride-s transpose convolution and dilated convolution: shapes, multiply-add counts and
     argument validation are host arithmetic (fake addresses: nothing may be launched)."""
