@@ -169,7 +169,7 @@ double mfma_parts_tiles(const Geom& g, int dtype);
 hipError_t launch_mfma_parts(const Geom& g, const void* x, const void* w, void* y, int dtype, Workspace& ws,
                              hipStream_t stream);
 // fp32 layers of few tiles, given a workspace: slices of the input channels and a sum over them
-bool mfma_parts_split_supported(const Geom& g, int dtype);
+int mfma_parts_split_slices(const Geom& g, int dtype);  // one or none: no
 hipError_t launch_mfma_parts_split(const Geom& g, const void* x, const void* w, float* y, Workspace& ws,
                                    hipStream_t stream);
 // Layers of few tiles: 32 x 32 or 16 x 16 output tiles on the fp32 matrix pipe, the sum dealt to the block's waves

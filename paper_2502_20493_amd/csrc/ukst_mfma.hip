@@ -595,7 +595,7 @@ static bool prefer_parts_split(const Geom& g, int dtype)
     if (dtype != 0 || g.Cin < 16 || g.Cout <= 4 || !mfma_f32_supported(g, dtype) || prefer_parts(g, dtype)) return false;
     const double macs = (double)g.B * g.Cin * g.Cout * g.H * g.W * g.n * g.n;
     return (macs >= 3e9 || mfma_f32_blocks(g, dtype) < 192) && mfma_parts_tiles(g, dtype) >= 12. &&
-           mfma_parts_split_supported(g, dtype);
+           mfma_parts_split_slices(g, dtype) >= 2;
 }
 
 // Layers of few tiles and a long sum: small tiles whose waves split the sum (ukst_small_kernel.h).  In 32 x 32 tiles: fp32
@@ -635,6 +635,17 @@ static bool prefer_small(const Geom& g, int dtype)
     return tiles > 0 && tiles <= (aligned ? 1024 : g.n <= 3 ? 512 : 700);
 }
 
+// ... and of them, given a workspace, those that the slices of the kernel on parts still are the faster ones of: beyond
+// one round, and a long sum in many slices (us, small tiles in slices / parts: 920 -> 336 channels, 6 of 5 x 16, n = 5 103 / 77,
+// 896 -> 40, 20 of 8 x 34, n = 4 66 / 50, 608 -> 112, 12 of 11 x 11, n = 4 45.7 / 40.6; but 832 -> 32, 10 of 12 x 12, n = 4, 0.6e9
+// multiply-adds 38.9 / 47.5, 432 -> 360, 18 of 4 x 4, n = 5 51 / 57, 800 -> 312, 2 of 9 x 28, n = 5, four slices 87 / 111)
+static bool parts_split_over_small(const Geom& g, int dtype)
+{
+    const double macs = (double)g.B * g.Cin * g.Cout * g.H * g.W * g.n * g.n;
+    return small_blocks(small_problem(g, dtype)) > 256 ||
+           (g.Cin >= 560 && macs >= 1.25e9 && mfma_parts_split_slices(g, dtype) >= 6);
+}
+
 bool mfma_auto_extra(const Geom& g, int dtype)
 {
     return prefer_small(g, dtype) || (!mfma_supported(g, dtype) && prefer_parts(g, dtype));
@@ -660,8 +671,7 @@ hipError_t launch_mfma(const Geom& g, const void* x, const void* w, float* y, in
 {
     const bool small = prefer_small(g, dtype);
     if (!small && prefer_parts(g, dtype)) return launch_mfma_parts(g, x, w, y, dtype, ws, stream);
-    // (of the layers for the small tiles only those that are long on them too)
-    if (prefer_parts_split(g, dtype) && (!small || small_blocks(small_problem(g, dtype)) > 256)) {
+    if (prefer_parts_split(g, dtype) && (!small || parts_split_over_small(g, dtype))) {
         Workspace need;
         need.query = true;
         const hipError_t e = launch_mfma_parts_split(g, nullptr, nullptr, nullptr, need, stream);
@@ -722,7 +732,7 @@ int forward_plan(const Geom& g, int dtype)
     Workspace ws;
     ws.query = true;
     if ((!small && prefer_parts(g, dtype)) || launch_mfma(g, nullptr, nullptr, nullptr, dtype, ws, nullptr) != hipSuccess ||
-        (prefer_parts_split(g, dtype) && (!small || small_blocks(small_problem(g, dtype)) > 256)))
+        (prefer_parts_split(g, dtype) && (!small || parts_split_over_small(g, dtype))))
         return 0;
     if (small) return small_plan(small_problem(g, dtype), ws.need);
     const size_t slices = ws.need / ((size_t)g.B * g.Cout * g.OH * g.OW * 4);

@@ -144,11 +144,11 @@ static int pick_split(const Geom& g, int dtype, PartsArgs& a, Config& c)
     return a.ksplit;
 }
 
-bool mfma_parts_split_supported(const Geom& g, int dtype)
+int mfma_parts_split_slices(const Geom& g, int dtype)
 {
     PartsArgs a;
     Config c;
-    return dtype == 0 && pick_split(g, dtype, a, c) >= 2;
+    return dtype == 0 ? pick_split(g, dtype, a, c) : 0;
 }
 
 static hipError_t launch_sides(const PartsArgs& a, const Config& c, const Epilogue& ep, const void* x, const void* w,

@@ -409,6 +409,19 @@ def test_few_output_channels_go_to_the_small_tiles_for_one_round():
         assert (_small_tile(0, shape) != (0, 0)) == (kernel == "ukst_mfma_f32_kernel"), shape
 
 
+def test_long_sums_with_a_workspace_keep_the_slices_of_the_kernel_on_parts():
+    """Given a workspace, slices on bf16 parts against the small tiles in slices (us, the latter / the former)."""
+    for shape, small in (((6, 920, 336, 5, 16, 5, 2), False),      # 103 / 77
+                         ((20, 896, 40, 8, 34, 4, 0), False),      # 66 / 50
+                         ((12, 608, 112, 11, 11, 4, 2), False),    # 45.7 / 40.6
+                         ((10, 832, 32, 12, 12, 4, 4), True),      # 38.9 / 47.5, few products
+                         ((18, 432, 360, 4, 4, 5, 4), True),       # 51 / 57, fewer channels
+                         ((2, 800, 312, 9, 28, 5, 2), True)):      # 87 / 111, four slices
+        assert (_small_tile(0, shape) != (0, 0)) == small, shape
+        assert ukst.ukst_kernel_name(*shape, ukst.UKST_F32) == "ukst_mfma_f32_kernel"  # (the choice without one)
+        assert small or ukst.ukst_workspace_bytes(ukst.UKST_OP_FORWARD, *shape, ukst.UKST_F32) > 0
+
+
 def test_generalised_operations_host_side():
     """Stride-s transpose convolution and dilated convolution: shapes, multiply-add counts and
     argument validation are host arithmetic (fake addresses: nothing may be launched)."""
