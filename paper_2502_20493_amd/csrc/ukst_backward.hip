@@ -1423,64 +1423,70 @@ __global__ __launch_bounds__(256, 2) void ukst_grad_weight_mfma_kernel(const TIn
     }
 }
 
-// Sum of the copies p[0], p[n], p[2n], ...: running sums taken in turn, each with a load in flight, then pairs of them.  From
-// 64 copies on, and for layers of few channels, sixteen of them, put away every 64 copies: a chain of four roundings and one for
-// every 64 copies keeps the sum as exact as the copies are (few channels, bf16, n = 2, 2048 to 4096 pixels: error 1.11 times that
-// of the vector ALUs with four running sums, 1.04 with sixteen), and few kernel elements leave a thread's loads a chain
-// of round trips; otherwise the remainder costs more than it gives (128 x 128 channels, n = 3, 63 copies: 194 -> 200 us with
-// the gradient), so four.
-template <int SUMS>
-__device__ __forceinline__ float sum_copies_in(const float* __restrict__ p, int n, int copies)
+// Sum of the copies p[0], p[n], p[2n], ...: four running sums taken in turn, each with a load in flight, then pairs of them.
+// From 64 copies on, and for layers of few channels, in sixteens, as below: the remainder costs more than it gives otherwise
+// (128 x 128 channels, n = 3, 63 copies: 194 -> 200 us with the gradient)
+__device__ __forceinline__ float sum_copies_in_fours(const float* __restrict__ p, int n, int copies)
 {
-    constexpr int CHUNK = SUMS == 16 ? 4 * SUMS : 0x7FFFFFF0;  // copies after which the running sums are put away
-    float total = 0.f;
-    for (int k = 0; k < copies;) {
-        const int end = copies - k > CHUNK ? k + CHUNK : copies;
-        float v[SUMS];
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    const size_t m = (size_t)n;
+    int k = 0;
+    for (; k + 3 < copies; k += 4, p += 4 * m) {
 #pragma unroll
-        for (int u = 0; u < SUMS; ++u) v[u] = 0.f;
-        for (; k + SUMS - 1 < end; k += SUMS) {
-#pragma unroll
-            for (int u = 0; u < SUMS; ++u) v[u] += p[(size_t)(k + u) * n];
-        }
-        if constexpr (SUMS == 16) {
-            if (k < end) {  // (all loads in flight)
-                float t[SUMS - 1];
-#pragma unroll
-                for (int u = 0; u < SUMS - 1; ++u) t[u] = p[(size_t)(k + u < end ? k + u : end - 1) * n];
-#pragma unroll
-                for (int u = 0; u < SUMS - 1; ++u) v[u] += k + u < end ? t[u] : 0.f;
-                k = end;
-            }
-        } else {
-            for (int u = 0; k < end; ++k, ++u) {
-                const float t = p[(size_t)k * n];
-#pragma unroll
-                for (int w = 0; w < SUMS - 1; ++w) v[w] += w == u ? t : 0.f;
-            }
-        }
-#pragma unroll
-        for (int m = 1; m < SUMS; m *= 2)
-#pragma unroll
-            for (int u = 0; u < SUMS; u += 2 * m) v[u] += v[u + m];
-        total += v[0];
+        for (int u = 0; u < 4; ++u) v[u] += p[u * m];
     }
-    return total;
+    if (copies - k == 3) {  // (uniform; the loads of the remainder in flight together)
+        const float t0 = p[0], t1 = p[m], t2 = p[2 * m];
+        v[0] += t0;
+        v[1] += t1;
+        v[2] += t2;
+    } else if (copies - k == 2) {
+        const float t0 = p[0], t1 = p[m];
+        v[0] += t0;
+        v[1] += t1;
+    } else if (copies - k == 1) {
+        v[0] += p[0];
+    }
+    return (v[0] + v[1]) + (v[2] + v[3]);
 }
-__device__ __forceinline__ float sum_copies(const float* __restrict__ p, int n, int copies, int wide)
+// Sixteen loads in flight, as few kernel elements leave a thread's loads a chain of round trips, and the sums in 64 bits, so
+// that a slice may be short without a rounding for every copy
+__device__ __forceinline__ float sum_copies_in_sixteens(const float* __restrict__ p, int n, int copies)
 {
-    return wide ? sum_copies_in<16>(p, n, copies) : sum_copies_in<4>(p, n, copies);  // uniform
+    double v[4] = {0., 0., 0., 0.};
+    for (int k = 0; k < copies; k += 16) {
+        float t[16];
+        if (k + 16 <= copies) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t[u] = p[(size_t)(k + u) * n];
+        } else {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const float q = p[(size_t)(k + u < copies ? k + u : copies - 1) * n];
+                t[u] = k + u < copies ? q : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u % 4] += (double)t[u];
+    }
+    return (float)((v[0] + v[1]) + (v[2] + v[3]));
+}
+template <bool WIDE>
+__device__ __forceinline__ float sum_copies(const float* __restrict__ p, int n, int copies)
+{
+    return WIDE ? sum_copies_in_sixteens(p, n, copies) : sum_copies_in_fours(p, n, copies);
 }
 
 // dw[co][ci][tap] = sum over the copies of part[copy][co][tap][ci], copies added in a fixed order;
 // threads run along the copies' layout (coalesced reads), the single write pass is scattered
+template <bool WIDE>
 __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restrict__ part,
                                                            float* __restrict__ dw, int n, int copies,
-                                                           int wide, int NN, int Cin)
+                                                           int NN, int Cin)
 {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
-    const float v = sum_copies(part + s, n, copies, wide);
+    const float v = sum_copies<WIDE>(part + s, n, copies);
     const int ci = s % Cin, r = s / Cin;
     const int tap = r % NN, co = r / NN;
     dw[((size_t)co * Cin + ci) * NN + tap] = v;
@@ -1490,9 +1496,10 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_kernel(const float* __restr
 // along the input channels, turns the (tap, channel) square in LDS and writes one contiguous run of dw, where
 // the kernel above stores 4 bytes every n*n floats.  From 2048 blocks on: with fewer, many copies and a thread
 // for every fourth tap only, it is the slower one (64 x 64 channels, n = 5: 63 against 119 us with the gradient).
+template <bool WIDE>
 __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __restrict__ part,
                                                            float* __restrict__ dw, int n, int copies,
-                                                           int wide, int NN, int Cin)
+                                                           int NN, int Cin)
 {
     extern __shared__ __align__(16) float lds_t[];  // [64][NN + 1]
     const int tilesI = (Cin + 63) / 64;
@@ -1501,7 +1508,7 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __
     if (ci0 + l < Cin)
         for (int tap = wv; tap < NN; tap += 4) {
             const float* p = part + ((size_t)co * NN + tap) * Cin + ci0 + l;
-            lds_t[l * (NN + 1) + tap] = sum_copies(p, n, copies, wide);
+            lds_t[l * (NN + 1) + tap] = sum_copies<WIDE>(p, n, copies);
         }
     __syncthreads();
     const int cis = Cin - ci0 < 64 ? Cin - ci0 : 64;
@@ -1517,13 +1524,13 @@ hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size
 {
     const int NN = g.n * g.n;
     const long long blocks = (long long)g.Cout * ((g.Cin + 63) / 64);
-    const int wide = copies >= 64 || few_channels(g) ? 1 : 0;
+    const bool wide = copies >= 64 || few_channels(g);  // (a kernel each: the second's registers cost the first 1 %)
     if (blocks >= 2048 && blocks <= 0x7fffffffLL)
-        hipLaunchKernelGGL(ukst_sum_taps_wide_kernel, dim3((unsigned)blocks), dim3(256), 64 * (NN + 1) * sizeof(float),
-                           stream, part, dw, (int)elems, copies, wide, NN, g.Cin);
+        hipLaunchKernelGGL(wide ? ukst_sum_taps_wide_kernel<true> : ukst_sum_taps_wide_kernel<false>, dim3((unsigned)blocks),
+                           dim3(256), 64 * (NN + 1) * sizeof(float), stream, part, dw, (int)elems, copies, NN, g.Cin);
     else
-        hipLaunchKernelGGL(ukst_sum_taps_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, stream, part, dw,
-                           (int)elems, copies, wide, NN, g.Cin);
+        hipLaunchKernelGGL(wide ? ukst_sum_taps_kernel<true> : ukst_sum_taps_kernel<false>, dim3((unsigned)((elems + 255) / 256)),
+                           dim3(256), 0, stream, part, dw, (int)elems, copies, NN, g.Cin);
     return hipGetLastError();
 }
 
@@ -1534,10 +1541,10 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     // Layers of 16 to 31 channels leave up to half of a tile empty and still beat the vector ALUs (us, bf16: 30 -> 234
     // channels, 7 x 23 x 23, n = 5 222 -> 55; 17 -> 346, 17 x 12 x 43, n = 4 235 -> 44; 178 -> 31, 14 x 72 x 72, n = 3 552 -> 63).
     // Sums (few_channels()): this kernel rounds at every pixel pair where those on the bf16 pipe round at every sixteenth pixel.
-    // Its stages are 32 or 64 pixels, and its sums are added to the copy of dw in memory every 256 pixels, of fp32 operands,
-    // whose products are rounded too, every 64: error against 64 bits before (vector ALUs) / without / so: bf16, n = 5, 20 -> 512,
-    // 8 x 90 x 90 1.96e-7 / 3.89e-7 / 1.33e-7 (3707 / 660 / 949 us), n = 2 1.57e-7 / 3.89e-7 / 1.12e-7 (424 / 305 / 357 us); fp32, n = 5, 38 -> 30,
-    // 29 x 88 x 88 3.1e-7 / 5.3e-7 / 1.8e-7 (1416 / 294 / 725 us), 24 -> 100, 5 x 31 x 33 1.44e-7 / 1.59e-7 (64 pixels a stage) / 1.28e-7.
+    // Its stages are 32 or 64 pixels, and its sums are added to the copy of dw in memory every 512 pixels, of fp32 operands,
+    // whose products are rounded too, every 64: error against 64 bits of the vector ALUs / without / so: bf16, n = 5, 20 -> 512,
+    // 8 x 90 x 90 1.96e-7 / 3.90e-7 / 1.60e-7 (3699 / 681 / 824 us), n = 2 1.58e-7 / 3.95e-7 / 1.18e-7 (431 / 317 / 338 us); fp32, n = 5,
+    // 38 -> 30, 29 x 88 x 88 3.13e-7 / 5.3e-7 / 1.62e-7 (1430 / 294 / 725 us), 24 -> 100, 5 x 31 x 33 1.44e-7 / 1.58e-7 / 1.09e-7.
     // fp32 operands of smaller kernels gain nothing (n = 4, 21 -> 70, 15 x 32 x 32 88 -> 96 us).
     const int least = g.Cin < g.Cout ? g.Cin : g.Cout;
     const long long pixels = (long long)g.B * g.H * g.W;
@@ -1551,10 +1558,10 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     a.HC = a.TJ + N / 2;
     a.cols = 2 * a.HC;
     const size_t budget = 78 * 1024;
-    // At most that many pixels per stage.  Few channels: 64 are the faster ones (bf16, n = 5 1.05 to 1.16 times on 1100 layers,
-    // others from 8192 pixels on 1.03 times), 32 the more exact ones of fewer pixels (error above the vector ALUs', n = 4, 2048 to 4096
-    // pixels: 176 of 907 layers, with 64 303; on average 0.87 and 0.90 of theirs) and of fp32 operands
-    int TR = (!few ? 512 : (es == 4 ? pixels < 16384 : N < 5 && pixels < 8192) ? 32 : 64) / a.TJ;
+    // At most that many pixels per stage.  Few channels: 64 are the faster ones (n = 5 1.05 to 1.15 times on 1850 layers, n = 2 to 4 on
+    // average 1.02); with fp32 operands and up to 16384 pixels 32, the more exact ones (error above the vector ALUs', n = 5, 4096 to
+    // 8192 pixels: 3 of 399 layers, by 4 % at most, with 64 74, up to 26 %)
+    int TR = (!few ? 512 : es == 4 && pixels < 16384 ? 32 : 64) / a.TJ;
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);
@@ -1581,7 +1588,7 @@ bool gw_mfma_args(const Geom& g, GwMfmaArgs& a, int es)
     a.nSlices = (int)((stages + a.stagesPerSlice - 1) / a.stagesPerSlice);
     a.flush = 0;
     if (few) {
-        const int px = TR * a.TJ, most = es == 4 ? 64 : 256;
+        const int px = TR * a.TJ, most = es == 4 ? 64 : 512;
         a.flush = px < most ? most / px : 1;
     }
     a.cols4 = (a.cols + 3) / 4;
@@ -1923,7 +1930,7 @@ bool gw_b16_args(const Geom& g, GwB16Args& a)
     a.c8 = (2 * a.TJ + N - 2 + 7) / 8;
     const size_t budget = 78 * 1024;
     const bool few = few_channels(g);
-    int TR = (few ? few_stage(g) : 512) / a.TJ;  // at most that many pixels per stage
+    int TR = (few ? kFewStage : 512) / a.TJ;  // at most that many pixels per stage
     for (;; TR >>= 1) {
         if (TR < 1) return false;
         a.TI = pow2_ceil(g.H < TR ? g.H : TR);

@@ -374,7 +374,7 @@ bool make_args(const GeomBase& g, int es, int max_slices, GwPartsArgs& a)
     a.cols = 2 * a.HC;
     a.c4 = (2 * a.TJ + N - 2 + 3) / 4;
     const bool few = few_channels(g);
-    for (int TR = (few ? few_stage(g) : 512) / a.TJ;; TR >>= 1) {
+    for (int TR = (few ? kFewStage : 512) / a.TJ;; TR >>= 1) {
         if (TR < 1) return false;
         a.TR = TR;
         a.TI = 1 << log2_of(g.H < TR ? g.H : TR);

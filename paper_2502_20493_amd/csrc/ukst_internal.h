@@ -226,12 +226,12 @@ hipError_t launch_grad_narrow(int which, const Geom& g, const void* p0, const vo
 // times as many threads' sums, took before: short chains keep their sums as exact as those.  Short stages (a few pixels are
 // one stage per copy of dw), and a copy for every kFewChain pixels as long as the copies fit 64 MiB, the static
 // scratch; beyond kFewChainMax the layer is for the kernel that adds its sums to the copy in memory on the way.
-// (bf16 operands, error against 64 bits over that of the vector ALUs, 2500 layers: n = 2, 65536 pixels and more 1.25 to 1.37, up to
-// 1.79, at 512 pixels a stage and 512 blocks, 0.86 to 0.90 so; n = 4 1.15, up to 1.47 / 0.82; n = 3, 2048 to 4096 pixels 1.06 / 0.93.)
-constexpr int kFewChannels = 32, kFewChain = 512, kFewChainMax = 2048;
+// (bf16 operands, error against 64 bits over that of the vector ALUs, 700 layers: stages of 512 pixels, 512 blocks and the
+// copies added in fp32 0.93 on average and up to 1.91, so, with the copies added in 64 bits, 0.57 and up to 0.98, at 0.98
+// times the speed; stages of 64 instead of 128 pixels save a sixth of the error and cost up to 9 % of the time, chains of 1024 take
+// n = 3 to 1.05.)
+constexpr int kFewChannels = 32, kFewStage = 128, kFewChain = 768, kFewChainMax = 2048;  // kFewStage: pixels of a stage, at most
 inline bool few_channels(const GeomBase& g) { return g.Cin < kFewChannels || g.Cout < kFewChannels; }
-// pixels of a stage, at most (128 instead of 64 cost 0 to 4 % of error and save 7 % of the time)
-inline int few_stage(const GeomBase& g) { return (long long)g.B * g.H * g.W < 8192 ? 64 : 128; }
 // copies of dw of such a layer, `least` if not more
 inline long long few_slices(const GeomBase& g, long long pixels, long long least)
 {

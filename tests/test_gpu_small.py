@@ -308,11 +308,11 @@ def test_kernel_gradient_of_16_to_31_channels(shape, integer):
 @pytest.mark.parametrize("shape,plan", [
     ((3, 17, 300, 35, 45, 5, 2, "f32"), (2, 5)),     # twice, and a remainder of one
     ((4, 17, 78, 90, 90, 5, 4, "f32"), (1, 4)),      # after every stage
-    ((3, 17, 590, 35, 45, 5, 2, "bf16"), (4, 5)),
-    ((3, 17, 590, 35, 45, 2, 1, "bf16"), (8, 9)),    # two sets of accumulators
-    ((6, 590, 17, 35, 45, 2, 0, "bf16"), (4, 5)),
-    ((3, 30, 590, 35, 45, 3, 0, "bf16"), (8, 9)),
-    ((3, 17, 590, 35, 45, 4, 3, "bf16"), (8, 9)),
+    ((6, 17, 590, 35, 45, 5, 2, "bf16"), (8, 9)),
+    ((6, 17, 1200, 35, 45, 2, 1, "bf16"), (8, 17)),  # two sets of accumulators
+    ((12, 590, 17, 35, 45, 2, 0, "bf16"), (8, 9)),
+    ((3, 17, 1200, 35, 45, 3, 0, "bf16"), (8, 9)),
+    ((3, 17, 1200, 35, 45, 4, 3, "bf16"), (8, 9)),
 ])
 @pytest.mark.parametrize("integer", [True, False])
 def test_kernel_gradient_sums_added_to_memory_on_the_way(shape, plan, integer):
@@ -357,6 +357,8 @@ def _kernel_gradient64(x, dy, n, P):
     ((8, 20, 512, 90, 90, 3, 1, "bf16"), 1.86e-7),   # one part
     ((8, 20, 512, 90, 90, 4, 1, "bf16"), 1.95e-7),
     ((2, 24, 24, 48, 48, 3, 1, "bf16"), 8.11e-8),    # few pixels
+    ((7, 20, 24, 34, 34, 2, 1, "bf16"), 8.01e-8),
+    ((4, 16, 25, 33, 33, 3, 2, "bf16"), 7.71e-8),
     ((2, 24, 24, 48, 48, 4, 1, "bf16"), 8.30e-8),
     ((5, 24, 100, 31, 33, 5, 2, "f32"), 1.44e-7),
 ])
