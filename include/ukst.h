@@ -261,8 +261,9 @@ size_t ukst_static_workspace_bytes(void);
  * "ukst_grad_input_mfma_kernel_parts": other fp32 layers with enough pixels, bf16 MFMA on three exact
  * bf16 parts of every operand;
  * "ukst_grad_input_mfma_kernel": fp32 MFMA for the rest, and for layers of few tiles from Cin >= 16 and
- * Cout >= 8 on, which use no workspace; for the others weights are packed once per call into it, and it
- * holds the copies of dx when the sum over output channels is split),
+ * Cout >= 8 on, which use no workspace and appear in the trace as "ukst_grad_input_mfma_kernel_small";
+ * for the others weights are packed once per call into it, and it holds the copies of dx when the sum
+ * over output channels is split),
  * layers with Cin, Cout >= 32 (16 for bf16 operands, and fp32 with n = 5, with enough pixels) run the
  * kernel gradient there too
  * ("ukst_grad_weight_mfma_bf16_kernel": bf16 MFMA with the pixel axis as the contraction, for bf16
@@ -283,8 +284,10 @@ const char* ukst_grad_kernel_name(int which, int B, int Cin, int Cout, int H, in
  * The two generalisations the paper's discussion (Sec. 5) points to.  Both use the computation
  * pattern of Algorithm 2 -- every output pixel selects, from its own coordinates, the taps that
  * can meet data, and no inserted zero is ever multiplied -- in one general vector-ALU kernel, and on
- * the matrix cores ("ukst_general_mfma_kernel") for layers of at least 16 input and 8 output channels
- * (all but a few with hardly anything to multiply).
+ * the matrix cores for layers of at least 16 input and 8 output channels (all but a few with hardly
+ * anything to multiply): "ukst_general_mfma_kernel", or "ukst_mfma_f32_kernel_small" for few tiles
+ * (strided up to 512 of 16 x 16 outputs of a class, bf16 256; dilated up to 1200 of 32 x 32, bf16 512)
+ * and for dilated layers whose window does not fit the former's LDS.
  *
  * ukst_conv_transpose2d_strided: transpose convolution with stride s (Algorithm 1 with s-1 zeros
  * between neighbouring pixels; s = 2 is ukst_conv_transpose2d).  s*s parity classes: output row oy
