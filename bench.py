@@ -255,7 +255,8 @@ def measure_backward(w, which, steps, rotate_bytes=LLC_BYTES + (64 << 20)):
     exact = 2 * ukst.ukst_mac_count(*shape, 0)
     bound = BOUND.get(w.name, "hbm")
     if bound in ("mfma_f32", "mfma_f32_parts"):  # the pipe the gradient runs on, whatever the forward layer does
-        bound = "mfma_f32_parts" if kernel.endswith("_parts") else "mfma_f32"
+        on_parts = kernel.endswith("_parts") or (which == "grad_weight" and ukst.lib().ukst_test_plan(2, *shape, 2, dt) >> 30 & 1)
+        bound = "mfma_f32_parts" if on_parts else "mfma_f32"
     roof = _roof(bound, exact, nbytes, med, kernel, measured_traffic(f"{w.name} {which}"))
     if bound != "hbm" and "mfma" not in kernel:
         roof["bound"] = "alu"  # fp32 vector peak = fp32 MFMA peak on this chip (157.3 TFLOP/s)

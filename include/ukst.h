@@ -270,7 +270,9 @@ size_t ukst_static_workspace_bytes(void);
  * operands with kernel sides 2 to 4, W a multiple of 8 and at least 16;
  * "ukst_grad_weight_mfma_kernel_parts": bf16 MFMA on bf16 parts (three of an fp32 value, one of a
  * bf16 value), for n = 3, 4 and rows of at least 16 pixels on layers with enough of them;
- * "ukst_grad_weight_mfma_kernel": fp32 MFMA for everything else of that width, either dtype).
+ * "ukst_grad_weight_mfma_kernel": fp32 MFMA for everything else of that width, either dtype).  Wide layers with enough
+ * rows to walk down, n = 2..5, run on bf16 parts whatever their rows, as "ukst_grad_weight_mfma_kernel_parts_rows" or
+ * "ukst_grad_weight_mfma_bf16_kernel_rows" in the trace.
  * Layers with at most 4 output channels, Cout * n * n <= 64 and Cin >= 16 run the kernel gradient
  * as "ukst_grad_weight_thin_mfma_kernel" (fp32 MFMA whose rows are (channel, tap) pairs).
  * Narrow fp32 layers (Cin, Cout <= 4, 2 <= n <= 5, W >= 32) run both gradients as

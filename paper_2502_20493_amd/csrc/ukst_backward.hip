@@ -1520,11 +1520,12 @@ __global__ __launch_bounds__(256) void ukst_sum_taps_wide_kernel(const float* __
 }
 
 // dw from the copies of a kernel gradient
-hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size_t elems, int copies, hipStream_t stream)
+hipError_t launch_sum_taps(const GeomBase& g, const float* part, float* dw, size_t elems, int copies, hipStream_t stream,
+                           bool in64 = false)
 {
     const int NN = g.n * g.n;
     const long long blocks = (long long)g.Cout * ((g.Cin + 63) / 64);
-    const bool wide = copies >= 64 || few_channels(g);  // (a kernel each: the second's registers cost the first 1 %)
+    const bool wide = copies >= 64 || few_channels(g) || in64;  // (a kernel each: the second's registers cost the first 1 %)
     if (blocks >= 2048 && blocks <= 0x7fffffffLL)
         hipLaunchKernelGGL(wide ? ukst_sum_taps_wide_kernel<true> : ukst_sum_taps_wide_kernel<false>, dim3((unsigned)blocks),
                            dim3(256), 64 * (NN + 1) * sizeof(float), stream, part, dw, (int)elems, copies, NN, g.Cin);
@@ -2419,6 +2420,31 @@ hipError_t launch_gw(const Geom& g, const void* x, const void* dy, float* dw, Wo
     return e;
 }
 
+// Kernel gradients on the kernel of ukst_grad_weight_rows.hip: in no more copies of dw than the kernels before it take (`most`),
+// and in chains of at most `chain` pixels, short enough that the error against 64 bits is no larger.  The matrix pipe rounds
+// a sum of bf16 products more than once: on equal chains the error of three parts was 1.2 to 1.4 times that of the fp32 pipe (32 x 128 -> 128 channels, 64 x 64, n = 5 1.49e-6 / 1.10e-6,
+// with two chains 1.06e-6), that of one part 0.8 to 1.0 times, also on chains half as long again
+// (twice as long 1.09 to 1.19).
+// (Copies that were added in 64 bits, 64 and more, are so here where they are fewer: in fp32 the error doubled.)
+struct GwRowsPlan { int copies, most, chain; bool bf16_pipe; };
+GwRowsPlan gw_rows_plan(const Geom& g, int es)
+{
+    const int N = g.n;
+    const GwRowsPlan none = {0, 0, 0, false};
+    if (few_channels(g) || N < 2 || N > 5) return none;
+    GwB16Args ba;
+    GwMfmaArgs ma;
+    const bool b16 = es == 2 && N <= 4 && gw_b16_args(g, ba);
+    if (!b16 && !(N <= 4 ? gw_mfma_args<gw_nc(4)>(g, ma, es) : gw_mfma_args<gw_nc(5)>(g, ma, es))) return none;
+    const int most = b16 ? ba.nSlices : ma.nSlices;
+    const int parts = !b16 && N <= 4 ? grad_weight_parts_slices(g, es, most) : 0;
+    double chain = (double)g.B * g.H * g.W / (parts ? parts : most);  // of the kernel before
+    const bool pipe = b16 || (es == 2 && parts);
+    if (parts ? N == 3 : es == 4) chain /= 2;  // (n = 3 on parts: two chains there)
+    else if (es == 2 && !pipe) chain *= 1.5;
+    return {grad_weight_rows_slices(g, es, most, (int)chain + 1, pipe), most, (int)chain + 1, pipe};
+}
+
 // register block: CO_R x CI_R channel pairs x n*n taps per thread; layers with at most four
 // channels on a side take one channel per thread there, which leaves the block's threads to the
 // pixels and keeps the closing shuffle reduction short
@@ -2426,6 +2452,17 @@ template <int N, typename TIn>
 hipError_t launch_gw_n(const Geom& g, const void* x, const void* dy, float* dw, Workspace& ws,
                        hipStream_t stream)
 {
+    if constexpr (N >= 2 && N <= 5) {
+        const GwRowsPlan r = gw_rows_plan(g, (int)sizeof(TIn));
+        if (r.copies) {
+            const size_t elems = (size_t)g.Cout * g.Cin * N * N;
+            const size_t need = elems * r.copies * sizeof(float);  // one copy of dw per slice
+            if (ws.query) { ws.need = need; return hipSuccess; }
+            if (ws.bytes < need) return kWorkspaceTooSmall;
+            const hipError_t e = launch_grad_weight_rows(g, x, dy, (float*)ws.ptr, (int)sizeof(TIn), r.most, r.chain, r.bf16_pipe, stream);
+            return e != hipSuccess ? e : launch_sum_taps(g, (const float*)ws.ptr, dw, elems, r.copies, stream, r.most >= 64);
+        }
+    }
     if constexpr (N >= 2 && N <= 4 && sizeof(TIn) == 2) {
         GwB16Args ba;  // bf16 layers: the bf16 matrix pipe where the kernel takes the shape
         if (gw_b16_args(g, ba)) return launch_gw_b16<N>(ba, x, dy, dw, ws, stream);
@@ -2526,6 +2563,12 @@ int grad_plan(const Geom& g, int which, int dtype)
 {
     if (which == 0) return prefer_small(g, dtype) ? small_plan(small_problem(g, dtype), 0) : 0;
     const int es = dtype == 0 ? 4 : 2;
+    const GwRowsPlan rp = gw_rows_plan(g, es);
+    if (rp.copies) {
+        int runs = 0;
+        grad_weight_rows_slices(g, es, rp.most, rp.chain, rp.bf16_pipe, &runs);
+        return 1 << 30 | runs;
+    }
     GwB16Args ba;
     GwMfmaArgs wa;
     if ((dtype == 1 && gw_b16_args(g, ba)) || !(g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa, es) : gw_mfma_args<gw_nc(5)>(g, wa, es)) ||
@@ -2539,7 +2582,8 @@ const char* grad_kernel_name(const Geom& g, int which, int dtype)
     if (which == 1) {
         if (grad_narrow_supported(g, dtype)) return "ukst_grad_weight_narrow_kernel";
         GwB16Args ba;
-        if (dtype == 1 && gw_b16_args(g, ba)) return "ukst_grad_weight_mfma_bf16_kernel";
+        if (dtype == 1 && (gw_b16_args(g, ba) || (g.n <= 4 && g.W % 8 == 0 && gw_rows_plan(g, 2).copies != 0)))
+            return "ukst_grad_weight_mfma_bf16_kernel";
         GwMfmaArgs wa;
         const int es = dtype == 0 ? 4 : 2;
         const bool m = g.n <= 4 ? gw_mfma_args<gw_nc(4)>(g, wa, es) : gw_mfma_args<gw_nc(5)>(g, wa, es);

@@ -246,6 +246,12 @@ inline long long few_slices(const GeomBase& g, long long pixels, long long least
 int grad_weight_parts_slices(const GeomBase& g, int es, int max_slices);
 hipError_t launch_grad_weight_parts(const GeomBase& g, const void* x, const void* dy, float* part, int es,
                                     int max_slices, hipStream_t stream);
+// The same for n = 2..5, rows of any length, at least 32 channels on a side, from either operand type; chains of sums of
+// at most `chain` pixels, a block adds a chain's sums to its copy (runs: chains of a copy).  bf16_pipe: the kernel that takes
+// the layer otherwise multiplies on the bf16 pipe too
+int grad_weight_rows_slices(const GeomBase& g, int es, int max_slices, int chain, bool bf16_pipe, int* runs = nullptr);
+hipError_t launch_grad_weight_rows(const GeomBase& g, const void* x, const void* dy, float* part, int es, int max_slices,
+                                   int chain, bool bf16_pipe, hipStream_t stream);
 // Input gradient of wide fp32 layers with enough pixels from bf16 parts; no scratch
 bool grad_input_parts_supported(const GeomBase& g);
 hipError_t launch_grad_input_parts(const GeomBase& g, const float* dy, const float* w, float* dx, hipStream_t stream);
@@ -253,7 +259,8 @@ hipError_t launch_grad_input_parts(const GeomBase& g, const float* dy, const flo
 const char* grad_kernel_name(const Geom& g, int which, int dtype);
 
 // What the tests of the dispatch look at: small_plan() of the layers that run on the small tiles, 64 | slices << 16 of the
-// forward layers that run in slices on the fp32 pipe's wider ones, 0 for all others; of a kernel gradient that adds to its copies on the way, the stages after which it does, | stages of a copy << 16
+// forward layers that run in slices on the fp32 pipe's wider ones, 0 for all others; of a kernel gradient that adds to its copies on the way, the stages after which it does, | stages of a copy << 16;
+// of one that walks down rows (ukst_grad_weight_rows.hip) 1 << 30 | chains of a copy
 int forward_plan(const Geom& g, int dtype);
 int grad_plan(const Geom& g, int which, int dtype);
 int general_plan(int dilated, int B, int Cin, int Cout, int H, int W, int n, int P, int k, int OH, int OW, int dtype);
