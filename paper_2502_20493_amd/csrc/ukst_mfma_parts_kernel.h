@@ -70,6 +70,36 @@ constexpr int w_half_slots(int n, int parts, int tm)
     return used + 1 + (want + 31 - used % 16) % 16;
 }
 
+// One part: the taps in the order of their window positions, so that the activations of a position are read once
+// (n = 5: 43 fragments of 50 MFMAs instead of 55); the i-th tap of that order, and the number of taps before position (pa, pb)
+template <int N, bool AL>
+constexpr int tap_in_order(int i)
+{
+    for (int p = 0; p < 64; ++p)
+        for (int tap = 0; tap < N * N; ++tap)
+            if (pos_of<AL>(tap / N) * 8 + pos_of<AL>(tap % N) == p && i-- == 0) return tap;
+    return 0;
+}
+
+template <int N, bool AL>
+constexpr int pos_in_order(int i) { return pos_of<AL>(tap_in_order<N, AL>(i) / N) * 8 + pos_of<AL>(tap_in_order<N, AL>(i) % N); }
+template <int N, bool AL>
+constexpr int positions_until(int i)  // changes of position up to the i-th tap
+{
+    int k = 0;
+    for (int j = 1; j <= i; ++j) k += pos_in_order<N, AL>(j) != pos_in_order<N, AL>(j - 1);
+    return k;
+}
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>): constants before the loops are unrolled
+template <int N, class F>
+__device__ __forceinline__ void in_turn(F&& f)
+{
+    if constexpr (N > 0) {
+        in_turn<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
 // CW x QW waves: block tile = 32*CW channels x 32*NT*QW quads; a wave owns 32 channels x 32*NT quads x 4 classes.
 // XU: staging units of activations per thread.  EPI / OUT16 as in the other kernels.
 template <int N, int CW, int QW, int NT, int XU, bool AL, bool EPI, typename TIn, bool OUT16>
@@ -308,9 +338,8 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     // One weight stage (sub is a constant once unrolled), with the staging of the next ones dealt out
     // between its MFMAs: two waves that share a SIMD get through their MFMAs side by side, so whatever is
     // left for the end is left for both and finds the matrix pipe idle.
-    //   weights: three parts: the next stage's registers go to the other buffer under taps 1 and 2 and are
-    //     refilled at once for the stage after it; one part: fetched before the first tap, written under
-    //     the second half of them
+    //   weights: the next stage's registers go to the other buffer under taps 1 and 2 and are refilled at once for
+    //     the stage after it (one part: fetched before the first tap, written under the second half of them)
     //   activations of the next 16 channels: fetched before, split under the last tap of their last stage
     const int s0 = ks * a.kstages;
     const int nstages = (g.Cin + KC - 1) / KC;
@@ -321,13 +350,11 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     };
     auto compute = [&](int buf, int s, int sub) {
         const unsigned char* const wb = lds + buf * WBUF + a_lds;
-        constexpr bool W3 = PARTS == 3;
         const int taps = sub_taps(N, PARTS, sub);
         const int s_w = stage_after(s, sub, 1), sub_w = (sub + 1) % NSUB;
         bf16x8_t bf[NT][PARTS];
         int have = -1;
         if (sub + 1 == NSUB) load_x(stage_after(s, sub, 1));
-        if (!W3) load_w(s_w, sub_w);
 #pragma unroll
         for (int t = 0; t < taps; ++t) {
             const int tap = sub_first(N, PARTS, sub) + t, tr = tap / N, tc = tap % N;
@@ -345,7 +372,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
                         bf[nt][i] = *reinterpret_cast<const bf16x8_t*>(lds + b_lds[nt] + i * a.XPL + pa * a.LWX * 16 +
                                                                        pb * 16);
             }
-            if (t == (W3 ? 1 : taps / 2)) trim_w(s_w, sub_w);
+            if (t == 1) trim_w(s_w, sub_w);
             if (t + 1 == taps && sub + 1 == NSUB) trim_x(stage_after(s, sub, 1));
 #pragma unroll
             for (int m = 0; m < PP::count; ++m) {
@@ -353,30 +380,64 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
                 for (int nt = 0; nt < NT; ++nt)
                     acc[nt][tr & 1][tc & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         af[PP::a[m]], bf[nt][PP::b[m]], acc[nt][tr & 1][tc & 1], 0, 0, 0);
-                if constexpr (W3) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    if ((t == 1 || t == 2) && (m == 1 || m == 3)) store_w_tap(sub_w, buf ^ 1, 2 * (t - 1) + m / 2);
-                    if (t == 2 && m == 4) load_w(stage_after(s, sub, 2), (sub + 2) % NSUB);
-                    if (t + 1 == taps && sub + 1 == NSUB) {
+                __builtin_amdgcn_sched_barrier(0);
+                if ((t == 1 || t == 2) && (m == 1 || m == 3)) store_w_tap(sub_w, buf ^ 1, 2 * (t - 1) + m / 2);
+                if (t == 2 && m == 4) load_w(stage_after(s, sub, 2), (sub + 2) % NSUB);
+                if (t + 1 == taps && sub + 1 == NSUB) {
 #pragma unroll
-                        for (int i = m * 4 * XU / 6; i < (m + 1) * 4 * XU / 6; ++i) pack_x(i);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                } else {
-                    // tap i of the pieces under tap taps/2 + i*(taps - taps/2)/4
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (t == taps / 2 + i * (taps - taps / 2) / 4) store_w_tap(sub_w, buf ^ 1, i);
-                    if (t + 1 == taps && sub + 1 == NSUB) {
-#pragma unroll
-                        for (int i = 0; i < 4 * XU; ++i) pack_x(i);
-                    }
+                    for (int i = m * 4 * XU / 6; i < (m + 1) * 4 * XU / 6; ++i) pack_x(i);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
 
+    // One part: a tap is only NT MFMAs, and a wave issues in order, so reading a tap's fragments right before them
+    // left the matrix pipe waiting for LDS at every tap.  Here a tap's fragments are read while the tap before it is
+    // multiplied, and the taps go by window position, so that the activations are read once per position.
+    // [16,200->72,93x61] n=5 ragged bf16 152 -> 143 us; [26,388->72,21x54] n=4 68 -> 58; [64,128->64,33x33] n=4
+    // 50 -> 45; [32,256->128,128x128] n=5 1287 -> 1180.
+    auto compute1 = [&](int buf, int s) {
+        const unsigned char* const wb = lds + buf * WBUF + a_lds;
+        const int s_w = stage_after(s, 0, 1);
+        bf16x8_t af[2], bf[2][NT];
+        auto fetch = [&](auto ic) {
+            constexpr int i = decltype(ic)::value, tap = tap_in_order<N, AL>(i), pos = pos_in_order<N, AL>(i);
+            constexpr int p = positions_until<N, AL>(i) & 1, before = pos_in_order<N, AL>(i > 0 ? i - 1 : 0);
+            af[i & 1] = *reinterpret_cast<const bf16x8_t*>(wb + tap * WTS);
+            if constexpr (i == 0 || pos != before) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    bf[p][nt] =
+                        *reinterpret_cast<const bf16x8_t*>(lds + b_lds[nt] + (pos >> 3) * a.LWX * 16 + (pos & 7) * 16);
+            }
+        };
+        fetch(std::integral_constant<int, 0>{});
+        load_x(s_w);
+        load_w(s_w, 0);
+        in_turn<NN>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, tap = tap_in_order<N, AL>(i), tr = tap / N, tc = tap % N;
+            constexpr int p = positions_until<N, AL>(i) & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i + 1 < NN) fetch(std::integral_constant<int, i + 1>{});
+            if (i == NN / 2) trim_w(s_w, 0);
+            if (i + 1 == NN) trim_x(s_w);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                acc[nt][tr & 1][tc & 1] =
+                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i & 1], bf[p][nt], acc[nt][tr & 1][tc & 1], 0, 0, 0);
+            // weights: tap k of the pieces under tap NN/2 + k*(NN - NN/2)/4; activations under the last one
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i == NN / 2 + k * (NN - NN / 2) / 4) store_w_tap(0, buf ^ 1, k);
+            if (i + 1 == NN) {
+#pragma unroll
+                for (int k = 0; k < 4 * XU; ++k) pack_x(k);
+            }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
     load_w(s0, 0);
     load_x(s0);
     __syncthreads();  // zero fill done before the first activation writes
@@ -397,7 +458,8 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             // window row, tap run), they would push the accumulators out of the register file
             #pragma unroll
             for (int nt = 0; nt < NT; ++nt) asm("" : "+v"(b_lds[nt]));
-            compute(buf, s, sub);
+            if constexpr (PARTS == 3) compute(buf, s, sub);
+            else compute1(buf, s);
             __syncthreads();
             buf ^= 1;
         }
