@@ -41,6 +41,8 @@ struct PartsArgs {
     FastDiv dKHW, dKW, dEH, dRW, dW;
 };
 
+typedef unsigned u3v_t __attribute__((ext_vector_type(3)));
+
 // tap of class c = 2r + s at window position (pa, pb) lies at tap row a = r + 2u, pa = u (+ r if aligned)
 template <bool AL>
 constexpr int pos_of(int a) { return AL ? (a >> 1) + (a & 1) : a >> 1; }
@@ -57,6 +59,17 @@ constexpr int sub_first(int n, int parts, int sub)  // first tap of a stage; sub
 constexpr int sub_taps(int n, int parts, int sub) { return sub_first(n, parts, sub + 1) - sub_first(n, parts, sub); }
 constexpr int sub_pieces(int n, int parts, int sub) { return (sub_taps(n, parts, sub) + 3) / 4; }
 constexpr int piece_at(int taps, int piece) { return 4 * piece + 4 <= taps ? 4 * piece : taps - 4; }  // within the stage
+// One part, odd n: a channel's taps start in the middle of a dword half the time, and such loads keep the address unit
+// busy for a multiple of the time that whole dwords take (it was busy 73% of the kernel's time, the matrix pipe 31%).
+// Whole dwords are read and shifted, and a load is 16 bytes long so that there are half as many of them.  Pieces are of
+// seven taps, the least that such a load holds.  (even n: taps start at whole dwords; pieces of 8 at n = 4 measured slower,
+// 58 -> 65 us on [26,388->72,21x54].)
+constexpr int long_piece(int n) { return n % 2 ? 7 : 4; }
+constexpr int long_pieces(int n) { return (n * n + long_piece(n) - 1) / long_piece(n); }
+constexpr int long_piece_at(int n, int piece)
+{
+    return long_piece(n) * (piece + 1) <= n * n ? long_piece(n) * piece : n * n - long_piece(n);
+}
 constexpr int max_taps(int n, int parts) { return parts == 1 ? n * n : 4 + n * n % 4; }
 constexpr int max_pieces(int n, int parts) { return (max_taps(n, parts) + 3) / 4; }
 // LDS image of one part of a weight stage: 16-byte slots [channel half][tap][output channel], with strides
@@ -119,7 +132,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     constexpr int UK = PARTS == 3 ? 2 : 8;      // input channels of a weight unit
     constexpr int UPC = KC / UK;                // weight units per (output channel, piece)
     constexpr int WCG = PARTS == 3 ? (TM * UPC + T - 1) / T : 1;  // (groups of output channels per thread)
-    constexpr int WU = PARTS == 3 ? WCG * max_pieces(N, PARTS) : (TM * UPC * max_pieces(N, PARTS) + T - 1) / T;
+    constexpr int WU = PARTS == 3 ? WCG * max_pieces(N, PARTS) : (TM * UPC * long_pieces(N) + T - 1) / T;
     // (WU: weight units per thread)
     constexpr int PX = PARTS == 3 ? 1 : 4;      // pixels of an activation unit
     constexpr int XS_OFF = 2 * WBUF;
@@ -148,10 +161,23 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     for (int i = tid; i < PARTS * a.XPL / 16; i += T)
         *reinterpret_cast<u4v_t*>(lds + XS_OFF + i * 16) = u4v_t{0u, 0u, 0u, 0u};
 
+    // (FUNNEL_X: activations of odd images are read in whole dwords too, and shifted.  Not where a thread has two units:
+    // there are no registers for it; nor at n = 2, whose few MFMAs per unit wait for memory: 62 us without, 64 with it
+    // on [1,649->208,34x34].  Neither shifted, weights only, both, at n = 5: [16,200->72,93x61]
+    // 143, 123, 119 us; [12,256->56,80x80] 106, 94, 89; [32,256->128,128x128] 1180, 1077, 1030)
+    constexpr bool FUNNEL_X = PARTS == 1 && XU == 1 && N > 2;
+    const int x_low = FUNNEL_X ? (int)((uintptr_t)x & 2) : 0;
+    const size_t x_bytes = (size_t)g.B * g.Cin * g.H * g.W * ES;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)x, 0, (int)((size_t)g.B * g.Cin * g.H * g.W * ES), kRawBuffer);
+        (void*)((const char*)x - x_low), 0, (int)(FUNNEL_X ? (x_low + x_bytes + 3) & ~(size_t)3 : x_bytes), kRawBuffer);
+    const int x_odd = FUNNEL_X && g.H * g.W % 2 ? 2 : 0;  // bytes by which an odd channel starts past a dword
+    // (FUNNEL: w is read in whole dwords; the first and the last of them may hold two bytes of something else)
+    constexpr bool FUNNEL = PARTS == 1 && N % 2;
+    constexpr int PT = PARTS == 3 ? 4 : long_piece(N);  // taps of a weight unit
+    const int w_low = FUNNEL ? (int)((uintptr_t)w & 2) : 0;
+    const size_t w_bytes = (size_t)g.Cout * g.Cin * NN * ES;
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)w, 0, (int)((size_t)g.Cout * g.Cin * NN * ES), kRawBuffer);
+        (void*)((const char*)w - w_low), 0, (int)(FUNNEL ? (w_low + w_bytes + 3) & ~(size_t)3 : w_bytes), kRawBuffer);
     const unsigned x_cstride = (unsigned)(g.H * g.W * ES);
 
     // ---- staging units.  Activations: (channel half, row, PX columns), columns fastest; the last unit of a
@@ -171,7 +197,7 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             const int er = e_first + row;
             const int b = fdiv(er, a.dEH), i = er - b * a.EH - (g.P >> 1);
             if (b < g.B && i >= 0 && i < g.H)
-                x_goff[j] = (unsigned)((((b * g.Cin + 8 * h) * g.H + i) * g.W + col) * ES);
+                x_goff[j] = (unsigned)((((b * g.Cin + 8 * h) * g.H + i) * g.W + col) * ES) + x_low;
             x_loff[j] = XS_OFF + ((h * a.ROWS + row) * a.LWX + a.SH + col) * 16;
         }
     }
@@ -188,17 +214,17 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     } else {
 #pragma unroll
         for (int j = 0; j < WU; ++j) {
-            constexpr int pieces = sub_pieces(N, 1, 0);
+            constexpr int pieces = long_pieces(N);
             const int e = tid + T * j;
-            const int t = e / pieces, tap = piece_at(NN, e - t * pieces);
+            const int t = e / pieces, tap = long_piece_at(N, e - t * pieces);
             const int cg = t % UPC, co = t / UPC;
-            w_goff[j] = co < TM && co0 + co < g.Cout ? (((co0 + co) * g.Cin + UK * cg) * NN + tap) * ES : (int)kNoByte;
+            w_goff[j] = co < TM && co0 + co < g.Cout ? (((co0 + co) * g.Cin + UK * cg) * NN + tap) * ES + w_low : (int)kNoByte;
             w_loff[j] = co < TM ? cg * WHS + tap * WTS + co * 16 : -1;
         }
     }
     const int w_gstep = T / UPC * g.Cin * NN * ES;
-    // raw registers of the stage being fetched: UK (8) values of four taps (PX pixels) per unit
-    constexpr int WD = PARTS == 3 ? 4 : 2, XD = PARTS == 3 ? 1 : 2;  // dwords per load
+    // raw registers of the stage being fetched: UK (8) values of PT taps (PX pixels) per unit
+    constexpr int WD = PARTS == 1 && N % 2 == 0 ? 2 : 4, XD = PARTS == 3 ? 1 : FUNNEL_X ? 3 : 2;  // dwords per load
     unsigned xr[XU][8][XD], wr[WU][UK][WD];
     auto load_x = [&](int s) {
 #pragma unroll
@@ -206,7 +232,12 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const unsigned soff = (unsigned)(s * KC + k) * x_cstride;
-                if constexpr (XD == 1) {
+                if constexpr (FUNNEL_X) {
+                    const int odd = k & 1 ? x_odd : 0;
+                    const u3v_t v = __builtin_amdgcn_raw_buffer_load_b96(rs_x, (x_goff[j] + odd) & ~3u, soff - odd, 0);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) xr[j][k][i] = v[i];
+                } else if constexpr (XD == 1) {
                     xr[j][k][0] = __builtin_amdgcn_raw_buffer_load_b32(rs_x, x_goff[j], soff, 0);
                 } else {
                     const u2v_t v = __builtin_amdgcn_raw_buffer_load_b64(rs_x, x_goff[j], soff, 0);
@@ -220,10 +251,16 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
 #pragma unroll
         for (int j = 0; j < w_units(sub); ++j) {
             const int tap0 = PARTS == 3 ? sub_first(N, PARTS, sub) + piece_at(sub_taps(N, PARTS, sub), j / WCG) : 0;
-            const unsigned voff = (unsigned)(PARTS == 3 ? w_goff[0] + (j % WCG) * w_gstep : w_goff[j]);
 #pragma unroll
             for (int k = 0; k < UK; ++k) {
-                const unsigned soff = (unsigned)(((s * KC + k) * NN + tap0) * ES);
+                unsigned voff = (unsigned)(PARTS == 3 ? w_goff[0] + (j % WCG) * w_gstep : w_goff[j]);
+                unsigned soff = (unsigned)(((s * KC + k) * NN + tap0) * ES);
+                if constexpr (FUNNEL) {
+                    // an odd channel starts two bytes past a dword of its own where an even one does not, and the
+                    // other way round: the dwords that hold the taps are read, and align_w shifts them
+                    voff = (voff + 2 * (k & 1)) & ~3u;
+                    soff -= 2 * (k & 1);
+                }
                 if constexpr (WD == 4) {
                     const u4v_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_w, voff, soff, 0);
 #pragma unroll
@@ -246,11 +283,24 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             for (int k = 0; k < UK; ++k) {
                 int e = tid + (PARTS == 3 ? 0 : T * j);
                 asm("" : "+v"(e));
-                const int cg = PARTS == 3 ? e % UPC : e / sub_pieces(N, 1, 0) % UPC;
+                const int cg = PARTS == 3 ? e % UPC : e / long_pieces(N) % UPC;
                 const bool in = s * KC + UK * cg + k < g.Cin;
 #pragma unroll
                 for (int i = 0; i < WD; ++i) wr[j][k][i] = in ? wr[j][k][i] : 0u;
             }
+    };
+    auto align_w = [&]() {  // odd n: the taps of a unit from the start of its registers on
+        if constexpr (FUNNEL) {
+#pragma unroll
+            for (int j = 0; j < WU; ++j)
+#pragma unroll
+                for (int k = 0; k < UK; ++k) {
+                    const unsigned sh = (unsigned)((w_goff[j] + 2 * (k & 1)) & 2) * 8;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) wr[j][k][i] = __builtin_amdgcn_alignbit(wr[j][k][i + 1], wr[j][k][i], sh);
+                    wr[j][k][3] >>= sh;
+                }
+        }
     };
     auto store_w_tap = [&](int sub, int buf, int t) {  // tap t of every unit's piece
 #pragma unroll
@@ -286,6 +336,16 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
                 const bool in = s * KC + 8 * h + k < g.Cin;
 #pragma unroll
                 for (int i = 0; i < XD; ++i) xr[j][k][i] = in ? xr[j][k][i] : 0u;
+            }
+        }
+    };
+    auto align_x = [&]() {
+        if constexpr (FUNNEL_X) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const unsigned sh = ((x_goff[0] + (k & 1 ? x_odd : 0)) & 2) * 8;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) xr[0][k][i] = __builtin_amdgcn_alignbit(xr[0][k][i + 1], xr[0][k][i], sh);
             }
         }
     };
@@ -421,16 +481,22 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
             constexpr int p = positions_until<N, AL>(i) & 1;
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (i + 1 < NN) fetch(std::integral_constant<int, i + 1>{});
-            if (i == NN / 2) trim_w(s_w, 0);
-            if (i + 1 == NN) trim_x(s_w);
+            if (i == NN / 2) {
+                trim_w(s_w, 0);
+                align_w();
+            }
+            if (i + 1 == NN) {
+                trim_x(s_w);
+                align_x();
+            }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
                 acc[nt][tr & 1][tc & 1] =
                     __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i & 1], bf[p][nt], acc[nt][tr & 1][tc & 1], 0, 0, 0);
-            // weights: tap k of the pieces under tap NN/2 + k*(NN - NN/2)/4; activations under the last one
+            // weights: tap k of the pieces under tap NN/2 + k*(NN - NN/2)/PT; activations under the last one
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (i == NN / 2 + k * (NN - NN / 2) / 4) store_w_tap(0, buf ^ 1, k);
+            for (int k = 0; k < PT; ++k)
+                if (i == NN / 2 + k * (NN - NN / 2) / PT) store_w_tap(0, buf ^ 1, k);
             if (i + 1 == NN) {
 #pragma unroll
                 for (int k = 0; k < 4 * XU; ++k) pack_x(k);
@@ -442,9 +508,11 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
     load_x(s0);
     __syncthreads();  // zero fill done before the first activation writes
     trim_w(s0, 0);
+    align_w();
 #pragma unroll
-    for (int t = 0; t < 4; ++t) store_w_tap(0, 0, t);
+    for (int t = 0; t < PT; ++t) store_w_tap(0, 0, t);
     trim_x(s0);
+    align_x();
 #pragma unroll
     for (int i = 0; i < 4 * XU; ++i) pack_x(i);
     store_x();
