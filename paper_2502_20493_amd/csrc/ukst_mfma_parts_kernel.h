@@ -162,7 +162,8 @@ void ukst_mfma_f32_kernel_parts(const TIn* __restrict__ x, const TIn* __restrict
         *reinterpret_cast<u4v_t*>(lds + XS_OFF + i * 16) = u4v_t{0u, 0u, 0u, 0u};
 
     // (FUNNEL_X: activations of odd images are read in whole dwords too, and shifted.  Not where a thread has two units:
-    // there are no registers for it; nor at n = 2, whose few MFMAs per unit wait for memory: 62 us without, 64 with it
+    // there are no registers for it (weights fetched eight taps later to make room: 119 -> 132 us on [16,200->72,93x61]); nor
+    // at n = 2, whose few MFMAs per unit wait for memory: 62 us without, 64 with it
     // on [1,649->208,34x34].  Neither shifted, weights only, both, at n = 5: [16,200->72,93x61]
     // 143, 123, 119 us; [12,256->56,80x80] 106, 94, 89; [32,256->128,128x128] 1180, 1077, 1030)
     constexpr bool FUNNEL_X = PARTS == 1 && XU == 1 && N > 2;
